@@ -429,11 +429,12 @@ hipError_t launch_quantize_small(const void *x, egeria_dtype dt, int nimg, int c
 // Every workgroup finds its tensor in the launch's table (kernel argument) and
 // works on a fixed share of it: first the maximum of its share of the values,
 // then its share of the 16-byte output units [o][hw][cp / 16].
+// (one load per lane and a ballot; walking the table is a chain of scalar loads, up to 32 long)
 __device__ __forceinline__ int find_job(const WeightBatch &b, int blk)
 {
-    int j = 0;
-    while (j + 1 < b.n && blk >= b.job[j + 1].first_block) ++j;
-    return j;
+    const int lane = threadIdx.x & 63;
+    const int first = b.job[lane < kWeightBatch ? lane : kWeightBatch - 1].first_block;
+    return __popcll(__ballot(lane < b.n && blk >= first)) - 1;     // first_block ascends, job 0 starts at 0
 }
 
 __device__ __forceinline__ uint32_t job_share_absmax(const WeightJob &jb, int lb, uint32_t *sm)
@@ -602,48 +603,187 @@ __global__ __launch_bounds__(256) void quantize_weights_kernel(const WeightBatch
     job_share_quantize(jb, lb, inv);
 }
 
-// One scale per output channel: a wave owns channel oc of its tensor, takes the
-// maximum of the channel's c * hw values, publishes the scale and writes the
+// One scale per output channel: a wave owns channel oc of its tensor, reads the channel's c * hw values once
+// with 16-byte loads into registers, takes the maximum, publishes the scale and maps the registers to the
 // channel's codes [hw][cp].  No barrier, one launch.
-__global__ __launch_bounds__(256) void quantize_weights_pc_kernel(const WeightBatch b, uint32_t *__restrict__ flag)
+// Bound by HBM (4 or 2 bytes read, 1 written per value).  All of a row's loads are in flight together: NV units
+// of EPU values per lane (3 for rows of up to 768 floats, 12 up to 3072; what is longer is read a second time,
+// from cache).  A linear layer's codes leave as one 4- or 8-byte store per unit, lanes side by side; where the
+// codes of a unit are not neighbours (3x3 kernels, odd row lengths) they are put in place in LDS first and
+// leave as 16-byte stores.  Reading 16 neighbouring values per lane with scalar loads (64 cache lines per
+// instruction) took 119 us for 28.3 M fp32 values; this form 34 us (4.2 TB/s read + written).
+constexpr int kPcRowLds = 8192;          // bytes of codes of one channel that LDS holds (per wave)
+
+template <bool BF16, int EPU, int NV>
+__device__ __forceinline__ void quantize_channel(const WeightJob &jb, int oc, uint8_t *ldsrow, uint32_t *flag, bool first_wave)
 {
-    const int j = find_job(b, (int)blockIdx.x);
-    const WeightJob &jb = b.job[j];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int oc = ((int)blockIdx.x - jb.first_block) * 4 + wave;
-    if (oc >= jb.o) return;
+    using Unit = std::conditional_t<EPU == 1, float, uint4>;
+    const int lane = threadIdx.x & 63;
+    const int n_row = jb.c * jb.hw, nu = n_row / EPU;             // EPU divides n_row
+    const char *row = (const char *)jb.x + (int64_t)oc * n_row * (BF16 ? 2 : 4);
+    auto load = [&](int u) -> Unit {
+        if constexpr (EPU == 1) return BF16 ? bf16_to_f32(((const uint16_t *)row)[u]) : ((const float *)row)[u];
+        else return ((const uint4 *)row)[u];
+    };
+    auto value = [&](const Unit &v, int e) -> float {
+        if constexpr (EPU == 1) return v;
+        else {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            if (!BF16) return __uint_as_float(w[e]);
+            return __uint_as_float((e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+        }
+    };
+    auto unit_max = [&](const Unit &v) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int e = 0; e < EPU; ++e) {
+            const uint32_t a = abs_bits(value(v, e));
+            m = m > a ? m : a;
+        }
+        return m;
+    };
+    Unit v[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = load(lane + 64 * i < nu ? lane + 64 * i : nu - 1);   // (a repeated unit changes no maximum)
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const uint32_t a = unit_max(v[i]);
+        m = m > a ? m : a;
+    }
+    for (int u = lane + 64 * NV; u < nu; u += 64) {
+        const uint32_t a = unit_max(load(u));
+        m = m > a ? m : a;
+    }
+    float scale;
+    bool bad;
+    const float inv = scale_from_bits(wave_max_u32(m), nullptr, &scale, &bad);
+    if (lane == 0) {
+        if (bad || first_wave) publish_shared(scale, bad, jb.scale + oc, flag);
+        else jb.scale[oc] = scale;
+    }
+    int8_t *q = jb.q + (int64_t)oc * jb.hw * jb.cp;
+    const bool direct = EPU > 1 && jb.hw == 1;                    // a row of whole units: its codes are neighbours
+    const uint32_t magic = (uint32_t)(0x100000000ull / (uint32_t)jb.hw) + 1u;   // k / hw = mulhi(k, magic) for k * hw < 2^32
+    if (!direct && jb.cp != jb.c) {
+        for (int o = lane * 16; o < jb.hw * jb.cp; o += 1024) *(uint4 *)(ldsrow + o) = make_uint4(0, 0, 0, 0);
+        __builtin_amdgcn_wave_barrier();
+    }
+    auto emit = [&](const Unit &x, int u) {
+        if (direct) {
+            uint32_t w[(EPU + 3) / 4];
+#pragma unroll
+            for (int k = 0; k < (EPU + 3) / 4; ++k) {
+                w[k] = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * k + e < EPU) w[k] |= quant1(value(x, 4 * k + e), inv) << (8 * e);
+            }
+            if constexpr (EPU == 8) *(uint2 *)(q + 8 * u) = make_uint2(w[0], w[1]);
+            else *(uint32_t *)(q + 4 * u) = w[0];
+        } else {
+#pragma unroll
+            for (int e = 0; e < EPU; ++e) {
+                const uint32_t k = (uint32_t)(u * EPU + e);
+                const uint32_t ch = jb.hw == 1 ? k : __umulhi(k, magic);
+                ldsrow[(k - ch * (uint32_t)jb.hw) * (uint32_t)jb.cp + ch] = (uint8_t)quant1(value(x, e), inv);
+            }
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+        if (lane + 64 * i < nu) emit(v[i], lane + 64 * i);
+    for (int u = lane + 64 * NV; u < nu; u += 64) emit(load(u), u);
+    if (direct) {
+        for (int c = jb.c + 4 * lane; c < jb.cp; c += 256) *(uint32_t *)(q + c) = 0u;   // pad bytes (jb.c is a multiple of 4)
+    } else {
+        __builtin_amdgcn_wave_barrier();                          // the wave's own LDS traffic is in order
+        for (int o = lane * 16; o < jb.hw * jb.cp; o += 1024) *(uint4 *)(q + o) = *(const uint4 *)(ldsrow + o);
+    }
+}
+
+// channels whose codes exceed the LDS row and are not neighbours in memory either: 16 gathered values per lane
+template <bool BF16>
+__device__ __forceinline__ void quantize_channel_gather(const WeightJob &jb, int oc, uint32_t *flag, bool first_wave)
+{
+    const int lane = threadIdx.x & 63;
     const int64_t n_row = (int64_t)jb.c * jb.hw, base = (int64_t)oc * n_row;
     uint32_t m = 0;
     for (int64_t k = lane; k < n_row; k += 64) {
-        const float v = jb.bf16 ? bf16_to_f32(((const uint16_t *)jb.x)[base + k]) : ((const float *)jb.x)[base + k];
-        const uint32_t a = abs_bits(v);
+        const uint32_t a = abs_bits(load_elem<BF16>(jb.x, base + k));
         m = m > a ? m : a;
     }
-    m = wave_max_u32(m);
     float scale;
     bool bad;
-    const float inv = scale_from_bits(m, nullptr, &scale, &bad);
-    if (lane == 0) publish_shared(scale, bad, jb.scale + oc, flag);
+    const float inv = scale_from_bits(wave_max_u32(m), nullptr, &scale, &bad);
+    if (lane == 0) {
+        if (bad || first_wave) publish_shared(scale, bad, jb.scale + oc, flag);
+        else jb.scale[oc] = scale;
+    }
     const int cpu = jb.cp >> 4;
-    const int units = jb.hw * cpu;
-    for (int u = lane; u < units; u += 64) {
-        const int pix = u / cpu, c0 = (u - pix * cpu) << 4;
+    const int64_t units = (int64_t)jb.hw * cpu;
+    for (int64_t u = lane; u < units; u += 64) {
+        const int pix = (int)(u / cpu), c0 = (int)(u - (int64_t)pix * cpu) << 4;
         uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            if (c0 + e < jb.c) {
-                const int64_t idx = base + (int64_t)(c0 + e) * jb.hw + pix;
-                const float v = jb.bf16 ? bf16_to_f32(((const uint16_t *)jb.x)[idx]) : ((const float *)jb.x)[idx];
-                w[e >> 2] |= quant1(v, inv) << ((e & 3) * 8);
-            }
+            if (c0 + e < jb.c) w[e >> 2] |= quant1(load_elem<BF16>(jb.x, base + (int64_t)(c0 + e) * jb.hw + pix), inv) << ((e & 3) * 8);
         *(uint4 *)(jb.q + ((int64_t)oc * units + u) * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// lds_row: bytes of LDS per wave
+__global__ __launch_bounds__(256) void quantize_weights_pc_kernel(const WeightBatch b, uint32_t *__restrict__ flag, int lds_row)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t rows[];
+    const int j = find_job(b, (int)blockIdx.x);
+    const WeightJob &jb = b.job[j];
+    const int wave = threadIdx.x >> 6;
+    const int oc = ((int)blockIdx.x - jb.first_block) * 4 + wave;
+    if (oc >= jb.o) return;
+    const bool first_wave = blockIdx.x == 0 && wave == 0;          // leaves the flag word initialised
+    uint8_t *mine = rows + wave * lds_row;
+    const int64_t n_row = (int64_t)jb.c * jb.hw;
+    if (n_row == 0) {
+        if ((threadIdx.x & 63) == 0) publish_shared(1.0f, false, jb.scale + oc, flag);
+        return;
+    }
+    const bool bf = jb.bf16 != 0;
+    const int epu = bf ? 8 : 4;
+    const bool whole = n_row % epu == 0 && n_row < (1 << 24);      // rows of whole 16-byte units, 16-byte aligned
+    if (whole && jb.hw == 1) {
+        if (bf) {
+            if (n_row <= 3 * 64 * 8) quantize_channel<true, 8, 3>(jb, oc, mine, flag, first_wave);
+            else quantize_channel<true, 8, 12>(jb, oc, mine, flag, first_wave);
+        } else {
+            if (n_row <= 3 * 64 * 4) quantize_channel<false, 4, 3>(jb, oc, mine, flag, first_wave);
+            else quantize_channel<false, 4, 12>(jb, oc, mine, flag, first_wave);
+        }
+    } else if ((int64_t)jb.hw * jb.cp <= lds_row) {
+        if (whole) {
+            if (bf) quantize_channel<true, 8, 6>(jb, oc, mine, flag, first_wave);
+            else quantize_channel<false, 4, 10>(jb, oc, mine, flag, first_wave);
+        } else {
+            if (bf) quantize_channel<true, 1, 12>(jb, oc, mine, flag, first_wave);
+            else quantize_channel<false, 1, 12>(jb, oc, mine, flag, first_wave);
+        }
+    } else {
+        if (bf) quantize_channel_gather<true>(jb, oc, flag, first_wave);
+        else quantize_channel_gather<false>(jb, oc, flag, first_wave);
     }
 }
 
 hipError_t launch_quantize_weights_pc(const WeightBatch &b, int total_blocks, uint32_t *flag, hipStream_t st)
 {
-    return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_weights_pc_kernel, dim3((unsigned)total_blocks), dim3(256), 0, st, b,
-                    flag);
+    // LDS for the tensors that need it (the largest row of codes among those that fit), none for plain matrices
+    int lds_row = 0;
+    for (int i = 0; i < b.n; ++i) {
+        const WeightJob &jb = b.job[i];
+        const int64_t row = (int64_t)jb.hw * jb.cp;
+        if ((jb.hw > 1 || jb.c % (jb.bf16 ? 8 : 4) != 0) && row <= kPcRowLds && row > lds_row) lds_row = (int)row;
+    }
+    return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_weights_pc_kernel, dim3((unsigned)total_blocks), dim3(256),
+                    (size_t)4 * lds_row, st, b, flag, lds_row);
 }
 
 hipError_t launch_quantize_weights(const WeightBatch &b, int total_blocks, bool one_launch, uint32_t *partials,
