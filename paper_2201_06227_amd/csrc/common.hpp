@@ -332,6 +332,23 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
 
 // ---- device helpers ------------------------------------------------------------
 #ifdef __HIPCC__
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint8_t lds_byte;
+
+// 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes
+// LDS bytes [lds_base + 16 l, lds_base + 16 l + 16) with what it reads at byte
+// offset voff of the buffer (zeros if voff is out of range).  Written as an
+// assembly statement so that the request stays outstanding across later LDS
+// reads of other stages: completion is awaited with an explicit vmcnt wait,
+// and ordering against other waves' reads with workgroup barriers.
+__device__ __forceinline__ void load_to_lds_b128(v4i rsrc, uint32_t lds_base, uint32_t voff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(rsrc)
+                 : "memory", "m0");
+}
+
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

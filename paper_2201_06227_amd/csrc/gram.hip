@@ -6,38 +6,52 @@
 // P is a squared *difference* of two nearly equal matrices, so forming both
 // Gram matrices in fp32 and subtracting loses most of the digits once the
 // layer has converged.  The kernels therefore contract
-//   M = (T - R)(T + R)^T     and     B = R R^T
-// (T, R the two activations): the Gram difference is exactly (M + M^T)/2, it is
+//   W = (T - R)(T + R)^T + (T + R)(T - R)^T     and     B = R R^T
+// (T, R the two activations): the Gram difference is exactly W / 2, it is
 // obtained to fp32 *relative* accuracy, and G_T's Gram is recovered as
-// B + (M + M^T)/2 in fp64 in the finaliser.  Same bytes and the same number of
-// matrix-core operations as two plain Gram products.
+// B + W / 2 in fp64 in the finaliser.
 //
-// Kernel 1 (gram_partial): split-K over D.  A workgroup owns one chunk of D and
-//   one macro tile of both products: 64x64 (four 32x32 blocks, one per wave) for
-//   b > 32, or the single 32x32 block for b <= 32 with the four waves splitting
-//   each K tile.  Every fp32 product of the two contractions is formed exactly
-//   on the bf16 matrix cores: an fp32 value is the sum of three bf16 values
-//   (8 + 8 + 8 significant bits, obtained by truncation and exact subtraction),
-//   so x * y = sum of nine bf16 x bf16 products, each exact in fp32; the six
-//   largest are issued (v_mfma_f32_32x32x16_bf16, fp32 accumulation), the three
-//   dropped ones sum to less than 2^-21 of the product.  Six bf16 MFMAs cost 0.375 of the
-//   eight fp32 MFMAs they replace.  Sample rows are fetched with coalesced loads
-//   one K tile ahead into registers, split once per element, and written to LDS
-//   as bf16 planes (hi / mid / lo of T-R, T+R and R) in 16-byte units whose
-//   position is xor-rotated by the row so that writes and the 128-bit operand
-//   reads are bank-conflict free.  Lane l supplies row l % 32 and the 8 values of
-//   unit l / 32 of a 16-deep slab, A and B operand alike, so the order of k
-//   inside the sum never matters.
-//   Each workgroup stores its M block twice, as is and transposed, so that
-//   the next kernel reads rows only.
-// Kernel 2 (sp_finalize): one workgroup per row i of the b x b matrices.  It
-//   sums row i of M, M^T and B over the chunks in fp64 (fixed assignment of
-//   chunks to thread groups, fixed order), forms row i of both Gram matrices,
-//   their norms and the row's share of the squared difference; the last
-//   workgroup to finish adds the b shares in index order and writes P.
+// Kernel 1 (gram_kernel): split-K over D.  Samples come in blocks of 32.  A
+//   workgroup owns one chunk of D and one pair (p, q) of blocks - both diagonal
+//   blocks of W and B and the off-diagonal ones for b <= 64, else one of the
+//   3 or 6 pairs with at most one diagonal block - or the single block of b <= 32.
+//   Both matrices are symmetric: only blocks p <= q are contracted (7 block
+//   products instead of 8 for b = 64, 26 instead of 32 for b = 128).
+//   Every fp32 product is formed exactly on the bf16 matrix cores: an fp32
+//   value is the sum of three bf16 values (8 + 8 + 8 significant bits, obtained
+//   by truncation and exact subtraction), so x * y = sum of nine bf16 x bf16
+//   products, each exact in fp32; the six largest are issued
+//   (v_mfma_f32_32x32x16_bf16, fp32 accumulation), the three dropped ones sum
+//   to less than 2^-21 of the product.  Six bf16 MFMAs cost 0.375 of the eight
+//   fp32 MFMAs they replace.
+//   Eight waves split the chunk by slabs of 16 features, each with all of the
+//   pair's products in its accumulators: a wave streams its own slabs, no
+//   barrier until the end.  The raw values go from global memory straight into
+//   the wave's stage in LDS (rows of 64 bytes, 16-byte units xor-rotated
+//   by the row: conflict-free) and are read back once, in the lane layout of
+//   the matrix instruction (row l % 32, eight features of half l / 32), which
+//   is the same for both operands; T - R, T + R and the three-way splits are
+//   formed in registers, once per value and pair, and never return to LDS.
+//   What bounds it: HBM for large D - the stream of 103 MB at b = 64, D = 200704 takes 16 us by itself (5.6 TB/s), the
+//   matrix and vector work 12 us beside it, filling and draining six slabs per wave, the final sum over the waves (3 us)
+//   and the launch the rest of 27 us - and the L2 -> LDS path for b > 64, where a block of samples is read by up to three
+//   pairs.  Before (one 64x64 tile of both products, four waves, operands passed through LDS as nine bf16 planes: 18
+//   bytes of LDS writes and 48 of reads per value pair, and one wave per SIMD, which issues a vector instruction
+//   every 5 clocks where two waves issue one every 2.9): per score, both launches, us: b = 64, D = 200704 47 -> 38;
+//   b = 100, D = 62720 (bf16 T) 52 -> 32; b = 128, D = 16384 26 -> 21; b = 32, D = 98304 (bf16 T) 17.6 -> 13.3.
+//   The eight waves' accumulators are added through
+//   LDS at the end; the diagonal blocks of W are symmetrised there.
+//   Partials are [nsplit][2][b][b] fp32 (W and B, whole rows).
+// Kernel 2 (sp_finalize): workgroups own parts of the rows of the b x b
+//   matrices.  They sum W and B over the chunks in fp64 and reduce their columns
+//   to the sums from which a row's norms and its share of the squared difference
+//   follow; the last workgroup to finish adds the shares in index order and writes P.
+// A problem of one chunk (b <= 64, D <= 1024) is finished by kernel 1 itself,
+// whose one workgroup has both matrices in LDS: one launch less.
 //   Results are bit-reproducible from call to call.
 #include "common.hpp"
 #include <mutex>
+#include <type_traits>
 
 namespace egeria {
 
@@ -45,80 +59,50 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
+constexpr int kSlab = 16;                // features of one matrix instruction
+constexpr int kGramWaves = 8;
+constexpr int kGramLds = 144 * 1024;     // one workgroup per CU
+constexpr int kFusedSlabs = 64;          // slabs (of 16 features) up to which one workgroup does the whole score
+
 struct GramPlan {
-    int mt;          // blocks of 32 per macro-tile side: 1 (b <= 32) or 2
-    int nm;          // macro tiles per side
-    int nmacro;      // nm * nm
-    int kt;          // features per K tile: 64 (mt = 1) or 32 (mt = 2)
+    int nb;          // blocks of 32 samples
+    int npair;       // workgroups (pairs of blocks) per chunk
+    int nslab;       // slabs of 16 features in D
     int nsplit;      // chunks of D
-    int nsplit_pad;  // rounded up to a multiple of 8 (chunks are dealt to XCDs)
-    int64_t kc;      // chunk length, multiple of kt
+    int spc;         // slabs per chunk
+    int fused;       // one chunk, finished by its workgroup
+    int direct;      // whole slabs are loaded straight into LDS (else element by element)
 };
 
 static GramPlan plan_gram(int32_t b, int64_t D)
 {
-    GramPlan p;
-    p.mt = b <= 32 ? 1 : 2;
-    p.nm = p.mt == 1 ? 1 : (b + 63) / 64;
-    p.nmacro = p.nm * p.nm;
-    p.kt = p.mt == 1 ? 64 : 32;
-    // about one workgroup per CU: measured per score (partials + finaliser, us) for targets of 128 / 256 /
-    // 512 / 1024 workgroups: b = 32, D = 98304: 19.6 / 17.6 / 20.6 / 24.6; b = 64, D = 200704: 57.7 / 43.5 /
-    // 43.8 / 55.9 (more chunks mean more partials for the finaliser to add)
-    int64_t want = (compute_units() + p.nmacro - 1) / p.nmacro;
-    int64_t cap = D / ((p.mt == 1 ? 4 : 2) * (int64_t)b);  // bound the partials by a fraction of the input bytes
-    if (cap < 1) cap = 1;
+    GramPlan p{};
+    p.nb = (b + 31) / 32;
+    p.npair = p.nb <= 2 ? 1 : (p.nb == 3 ? 3 : 6);
+    const int64_t nslab = (D + kSlab - 1) / kSlab;
+    p.nslab = (int)nslab;
+    p.fused = p.nb <= 2 && nslab <= kFusedSlabs;
+    // about one workgroup per CU (its LDS fills one), and at least one slab for every wave
+    // (the pairs of a chunk share an XCD, so the CUs of an XCD bound the chunks dealt to it)
+    int64_t want = p.fused ? 1 : 8 * (compute_units() / 8 / p.npair);
+    const int64_t cap = (nslab + kGramWaves - 1) / kGramWaves;
     if (want > cap) want = cap;
-    int64_t kc = (D + want - 1) / want;
-    kc = (kc + p.kt - 1) / p.kt * p.kt;
-    p.kc = kc;
-    p.nsplit = (int)((D + kc - 1) / kc);
-    p.nsplit_pad = (p.nsplit + 7) / 8 * 8;
+    if (want < 1) want = 1;
+    p.spc = (int)((nslab + want - 1) / want);
+    p.nsplit = (int)((nslab + p.spc - 1) / p.spc);
     return p;
 }
 
-// workspace of the metric: [counter | row shares (b doubles) | partials [nsplit][3][b][b] (M, M^T, B)]
-static size_t off_rowsum() { return 256; }
-static size_t off_partials(int32_t b) { return 256 + align_up((size_t)b * sizeof(double), 256); }
+// workspace of the metric: [counter | four sums per workgroup of the finaliser | partials [nsplit][2][b][b] (W, B)]
+static int fin_parts(int b);
+constexpr int kFinSums = 4;
+static size_t off_sums() { return 256; }
+static size_t off_partials(int32_t b) { return 256 + align_up((size_t)b * fin_parts(b) * kFinSums * sizeof(double), 256); }
 
 size_t plasticity_partial_bytes(int32_t b, int64_t D)
 {
     GramPlan p = plan_gram(b, D);
-    return off_partials(b) + align_up((size_t)p.nsplit * 3 * (size_t)b * b * sizeof(float), 256);
-}
-
-// ---- four consecutive features of one sample row, as fp32 -------------------------------
-// FAST: rows are 16-byte aligned and every K tile is whole, so the load is
-// unconditional (the caller clamps row and tile to valid ones; what a clamped
-// load returns only reaches outputs that are never stored).  Unconditional
-// loads also let the compiler count outstanding requests exactly, which the
-// two-tile-deep prefetch depends on.  Otherwise: zeros for a row beyond b or
-// features beyond the chunk's end, scalar loads.
-template <int DT, bool FAST>
-__device__ __forceinline__ float4 load4(const void *__restrict__ base, int64_t row, bool row_ok,
-                                        int64_t D, int64_t k, int64_t kend)
-{
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (FAST) {
-        if (DT == 0) {
-            v = *(const float4 *)((const float *)base + row * D + k);
-        } else {
-            const uint2 q = *(const uint2 *)((const uint16_t *)base + row * D + k);
-            v.x = __uint_as_float(q.x << 16);
-            v.y = __uint_as_float(q.x & 0xffff0000u);
-            v.z = __uint_as_float(q.y << 16);
-            v.w = __uint_as_float(q.y & 0xffff0000u);
-        }
-        return v;
-    }
-    if (!row_ok || k >= kend) return v;
-    float e[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (k + i < kend)
-            e[i] = DT == 0 ? ((const float *)base)[row * D + k + i]
-                           : bf16_to_f32(((const uint16_t *)base)[row * D + k + i]);
-    return make_float4(e[0], e[1], e[2], e[3]);
+    return off_partials(b) + align_up((size_t)p.nsplit * 2 * (size_t)b * b * sizeof(float), 256);
 }
 
 // The three bf16 parts of eight fp32 values, packed as the 16-byte operand unit
@@ -126,382 +110,547 @@ __device__ __forceinline__ float4 load4(const void *__restrict__ base, int64_t r
 // truncated, lo = what is left; both subtractions are exact and lo has at most
 // eight significant bits, so hi + mid + lo == x exactly.
 struct Split8 {
-    v4u h, m, l;
+    v4u part[3];     // hi, mid, lo
 };
 __device__ __forceinline__ uint32_t pack_hi16(float x1, float x0)
 {
     return __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
 }
-__device__ __forceinline__ Split8 split8(const float (&x)[8])
+// values 2 e and 2 e + 1 of the eight
+__device__ __forceinline__ void split_pair(float x0, float x1, int e, Split8 &o)
 {
-    Split8 o;
+    const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & 0xffff0000u);
+    const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & 0xffff0000u);
+    const float l0 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
+    const float l1 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+    o.part[0][e] = pack_hi16(x1, x0);
+    o.part[1][e] = pack_hi16(r1, r0);
+    o.part[2][e] = pack_hi16(l1, l0);
+}
+// acc += a b^T with a in NA parts and b in NB parts (three for fp32, one for a value that is a bf16 value): every
+// partial product whose share of the result can exceed 2^-24, smallest first.  `after` runs behind every instruction.
+template <int NA, int NB, typename F>
+__device__ __forceinline__ void mma_parts(const Split8 &a, const Split8 &b, v16f &acc, F after)
+{
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float x0 = x[2 * e], x1 = x[2 * e + 1];
-        const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & 0xffff0000u);
-        const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & 0xffff0000u);
-        const float l0 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
-        const float l1 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-        o.h[e] = pack_hi16(x1, x0);
-        o.m[e] = pack_hi16(r1, r0);
-        o.l[e] = pack_hi16(l1, l0);
-    }
-    return o;
+    for (int order = 2; order >= 0; --order)
+#pragma unroll
+        for (int i = order; i >= 0; --i)
+            if (i < NA && order - i < NB) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a.part[i]), __builtin_bit_cast(v8bf, b.part[order - i]), acc, 0, 0, 0);
+                after();
+            }
 }
 
-template <int MT, bool OFFD, int TDT, int RDT, bool FAST>
-__global__ __launch_bounds__(256) void gram_partial_kernel(const void *__restrict__ at,
-                                                           const void *__restrict__ ar, int b,
-                                                           int64_t D, GramPlan p,
-                                                           float *__restrict__ part,
-                                                           uint32_t *__restrict__ counter)
-{
-    constexpr int ROWS = MT * 32;                 // rows per side of the macro tile
-    constexpr int KT = MT == 1 ? 64 : 32;         // features per K tile
-    constexpr int UPR = KT / 8;                   // 16-byte units (8 bf16) per row of a plane
-    constexpr int SWR = 16 / UPR;                 // rows that share a rotation of the units
-    constexpr int PLANE = ROWS * KT * 2;          // bytes of one bf16 plane
-    constexpr int STAGE = (OFFD ? 12 : 9) * PLANE;
-    static_assert(MT == 2 || !OFFD, "a macro tile of one block has no off-diagonal neighbours");
-    static_assert(ROWS * UPR == 256, "one unit per thread and plane");
-    // planes: 0-2 hi/mid/lo of T-R (rows i), 3-5 of R (rows i), 6-8 of T+R (rows j),
-    // 9-11 of R (rows j; off-diagonal macro tiles only, else planes 3-5 serve)
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];     // [2 stages][planes][ROWS][KT] bf16
+// One tensor's share of a stage: a block of 32 samples x 16 features, as read from memory.
+template <int DT>
+struct Tile {
+    static constexpr int kRow = kSlab * (DT == 0 ? 4 : 2);       // bytes per row
+    static constexpr int kBytes = 32 * kRow;
+    static constexpr int kUnits = kRow / 16;                     // 16-byte units per row: 4 or 2
+    static constexpr int kLoads = kBytes / 1024;                 // load instructions of a wave
+    static constexpr int kRowsPerLoad = 64 / kUnits;
+    // unit u of row r lies at slot u ^ ((r / (16 / kUnits)) % kUnits) of its row
+    static __device__ __forceinline__ int slot(int r, int u) { return u ^ ((r / (16 / kUnits)) % kUnits); }
+};
 
-    // consecutive workgroup ids land on different XCDs: all macro tiles of one
-    // chunk go to the same XCD so that its L2 serves the re-reads of that chunk
-    const int id = blockIdx.x;
-    const int xcd = id & 7, slot = id >> 3;
-    const int chunk = (slot / p.nmacro) * 8 + xcd;
-    const int mtile = slot % p.nmacro;
+// || g / max(|g|, 1e-12) - a / max(|a|, 1e-12) ||^2 for g = a + e from aa = |a|^2, gg = |g|^2, ae = a.e, ee = |e|^2
+__device__ __forceinline__ double row_share(double aa, double gg, double ae, double ee)
+{
+    const double nr = sqrt(aa), nt = sqrt(gg);
+    if (nr < 1e-12 || nt < 1e-12) {
+        const double r = nr < 1e-12 ? 1e-12 : nr, t = nt < 1e-12 ? 1e-12 : nt;
+        return fmax(gg / (t * t) + aa / (r * r) - 2.0 * (aa + ae) / (t * r), 0.0);
+    }
+    const double c = (aa + ae) / (nr * nt), s2 = fmax(aa * ee - ae * ae, 0.0) / (aa * gg);
+    return c > 0.0 ? 2.0 * s2 / (1.0 + c) : 2.0 - 2.0 * c;
+}
+
+// KIND 0: one block (b <= 32); 1: two blocks and all three block products of W and B (b <= 64); 2: two of three
+// or four blocks, the off-diagonal products and those of the first block's diagonal if the pair's turn says so.
+template <int KIND, int TDT, int RDT>
+__global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__restrict__ at, const void *__restrict__ ar,
+                                                                  int b, int64_t D, GramPlan p, float *__restrict__ part,
+                                                                  uint32_t *__restrict__ counter, float *__restrict__ p_out)
+{
+    constexpr int NBLK = KIND == 0 ? 1 : 2;                      // blocks of samples
+    constexpr int NACC = KIND == 0 ? 1 : (KIND == 1 ? 3 : 2);    // accumulator blocks per matrix: [diag p][off][diag q]
+    using TT = Tile<TDT>;
+    using TR = Tile<RDT>;
+    constexpr int kStage = NBLK * (TT::kBytes + TR::kBytes);
+    constexpr int NLD = NBLK * (TT::kLoads + TR::kLoads);        // load instructions of a slab
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    // consecutive workgroup ids land on different XCDs: all pairs of one chunk go to the same XCD so that its L2
+    // serves the re-reads of that chunk
+    const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
+    const int chunk = (turn / p.npair) * 8 + xcd, pair = turn % p.npair;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;      // ticket of the finaliser
     if (chunk >= p.nsplit) return;
-    const int mi = mtile / p.nm, mj = mtile % p.nm;
-    const bool diag = !OFFD || mi == mj;
-    const int64_t k0 = (int64_t)chunk * p.kc;
-    const int64_t k1 = k0 + p.kc < D ? k0 + p.kc : D;
-    const int ntiles = (int)((k1 - k0 + KT - 1) / KT);
+    // pairs of four blocks: (0,1) (1,2) (2,3) (3,0) with the first one's diagonal, (0,2) (1,3) without;
+    // of three: (0,1) (1,2) (2,0), each with a diagonal
+    const int bp = KIND == 2 ? (pair < p.nb ? pair : pair - p.nb) : 0;
+    const int bq = KIND == 2 ? (pair < p.nb ? (pair + 1 == p.nb ? 0 : pair + 1) : bp + 2) : 1;
+    const bool diag_p = KIND != 2 || pair < p.nb;
+    const int slab0 = chunk * p.spc;
+    const int slab1 = slab0 + p.spc < p.nslab ? slab0 + p.spc : p.nslab;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, h = lane >> 5;
+    uint8_t *stage = lds + wave * kStage;
+    const uint32_t stage0 = (uint32_t)(uintptr_t)(lds_byte *)stage;
 
-    // Staging: thread tid owns unit tid % UPR of row tid / UPR.  Its eight values
-    // are features 4u .. 4u+3 and KT/2 + 4u .. KT/2 + 4u+3 of the tile (two 16-byte
-    // loads, each contiguous over the threads of a row); which features share a
-    // unit is free as long as every plane uses the same assignment.
-    const int srow = tid / UPR, su = tid % UPR;
-    int64_t row_i = (int64_t)mi * ROWS + srow, row_j = (int64_t)mj * ROWS + srow;
-    const bool ok_i = row_i < b, ok_j = row_j < b;
-    row_i = ok_i ? row_i : 0;                     // rows beyond b: a valid address for the unconditional loads
-    row_j = ok_j ? row_j : 0;
-    const uint32_t soff = (uint32_t)(srow * (UPR * 16) + ((su ^ ((srow / SWR) % UPR)) * 16));
-    struct Staged {
-        float4 t[2], r[2], tj[2], rj[2];
+    // ---- a slab into the wave's stage: [T block p][T block q][R block p][R block q].  One load instruction of the wave
+    // fills 1 KiB; which 16 bytes a lane fetches for its slot is free, hence the rotation of the units.  Samples
+    // beyond b are given an offset outside the buffer and arrive as zeros.
+    constexpr uint32_t kOob = 0x80000000u;
+    auto descriptor = [&](const void *base, int64_t row, int es) {
+        const uint64_t a = (uint64_t)base + (uint64_t)(row * D * es);
+        v4i d;
+        d[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+        d[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xffff);
+        d[2] = 0x7fffffff;                                       // (rows and features are checked here, not by the extent)
+        d[3] = 0x00020000;
+        return d;
     };
-    auto fetch = [&](int t, Staged &s) {
-        // past the chunk's end: the last tile again (FAST; such a tile is never contracted) or zeros
-        const int tt = FAST ? (t < ntiles ? t : ntiles - 1) : t;
-        const int64_t kb = k0 + (int64_t)tt * KT + 4 * su;
+    v4i rt[NBLK], rr[NBLK];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int64_t k = kb + q * (KT / 2);
-            s.t[q] = load4<TDT, FAST>(at, row_i, ok_i, D, k, k1);
-            s.r[q] = load4<RDT, FAST>(ar, row_i, ok_i, D, k, k1);
-            if (OFFD && !diag) {
-                s.tj[q] = load4<TDT, FAST>(at, row_j, ok_j, D, k, k1);
-                s.rj[q] = load4<RDT, FAST>(ar, row_j, ok_j, D, k, k1);
-            }
-        }
-    };
-    auto put = [&](int stage, int plane, const float (&x)[8]) {
-        const Split8 sp = split8(x);
-        uint8_t *base = lds + stage * STAGE + plane * PLANE + soff;
-        *(v4u *)(base) = sp.h;
-        *(v4u *)(base + PLANE) = sp.m;
-        *(v4u *)(base + 2 * PLANE) = sp.l;
-    };
-    auto stash = [&](int stage, const Staged &s) {
-        const float t8[8] = {s.t[0].x, s.t[0].y, s.t[0].z, s.t[0].w, s.t[1].x, s.t[1].y, s.t[1].z, s.t[1].w};
-        const float r8[8] = {s.r[0].x, s.r[0].y, s.r[0].z, s.r[0].w, s.r[1].x, s.r[1].y, s.r[1].z, s.r[1].w};
-        float d8[8], s8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) d8[e] = t8[e] - r8[e];
-        put(stage, 0, d8);
-        put(stage, 3, r8);
-        if (OFFD && !diag) {
-            const float tj8[8] = {s.tj[0].x, s.tj[0].y, s.tj[0].z, s.tj[0].w, s.tj[1].x, s.tj[1].y, s.tj[1].z, s.tj[1].w};
-            const float rj8[8] = {s.rj[0].x, s.rj[0].y, s.rj[0].z, s.rj[0].w, s.rj[1].x, s.rj[1].y, s.rj[1].z, s.rj[1].w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s8[e] = tj8[e] + rj8[e];
-            put(stage, 6, s8);
-            put(stage, 9, rj8);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s8[e] = t8[e] + r8[e];
-            put(stage, 6, s8);
-        }
-    };
-
-    v16f accM, accB;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { accM[i] = 0.0f; accB[i] = 0.0f; }
-
-    // operand rows of this wave inside the macro tile
-    const int bi = MT == 1 ? 0 : (wave >> 1), bj = MT == 1 ? 0 : (wave & 1);
-    const int rowA = bi * 32 + r, rowB = bj * 32 + r;
-    const uint32_t offA = (uint32_t)(rowA * (UPR * 16)), swA = (uint32_t)((rowA / SWR) % UPR);
-    const uint32_t offB = (uint32_t)(rowB * (UPR * 16)), swB = (uint32_t)((rowB / SWR) % UPR);
-    const int planeRj = diag ? 3 : 9;
-
-    // One 16-deep slab: unit 2 * slab + h of the operand rows, six partial
-    // products per fp32 product, smallest first.
-    auto slab = [&](int stage, int sl) {
-        const uint32_t u = (uint32_t)(2 * sl + h);
-        const uint8_t *pa = lds + stage * STAGE + offA + ((u ^ swA) * 16);
-        const uint8_t *pb = lds + stage * STAGE + offB + ((u ^ swB) * 16);
-        v8bf dA[3], rA[3], sB[3], rB[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            dA[c] = __builtin_bit_cast(v8bf, *(const v4u *)(pa + (0 + c) * PLANE));
-            rA[c] = __builtin_bit_cast(v8bf, *(const v4u *)(pa + (3 + c) * PLANE));
-            sB[c] = __builtin_bit_cast(v8bf, *(const v4u *)(pb + (6 + c) * PLANE));
-            rB[c] = __builtin_bit_cast(v8bf, *(const v4u *)(pb + (planeRj + c) * PLANE));
-        }
-        constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};   // (lo,hi) (hi,lo) (mid,mid) (mid,hi) (hi,mid) (hi,hi)
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            accM = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dA[ia[q]], sB[ib[q]], accM, 0, 0, 0);
-            accB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rA[ia[q]], rB[ib[q]], accB, 0, 0, 0);
-        }
-    };
-
-    // Software pipeline: during step t the matrix cores contract tile t from LDS
-    // stage t & 1 while tile t + 1, already in registers, is split into the other
-    // stage; tile t + 2 is in flight (requested one step ago) and tile t + 3 is
-    // requested into the registers that tile t + 1 has just left.  One barrier
-    // per tile.
-    auto contract = [&](int stage) {
-        if (MT == 1) {
-            slab(stage, wave);
-        } else {
-            slab(stage, 0);
-            slab(stage, 1);
-        }
-    };
-    Staged st0, st1;
-    fetch(0, st0);
-    fetch(1, st1);
-    stash(0, st0);
-    fetch(2, st0);
-    __syncthreads();
-    auto step = [&](int t, Staged &next) {
-        contract(t & 1);
-        stash((t + 1) & 1, next);
-        fetch(t + 3, next);
-        // issue order: the splitting arithmetic of the next tile and its LDS writes between the
-        // MFMAs of this one (an MFMA occupies the matrix pipe for 8 passes, the vector ALU is free
-        // meanwhile; the nine 16-byte LDS writes, spread out, do not queue up at the tile's end)
-        constexpr int NMF = MT == 1 ? 12 : 24;
-#pragma unroll
-        for (int i = 0; i < NMF; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, MT == 1 ? 12 : 6, 0);     // vector ALU
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                    // one LDS write
-        }
-        __syncthreads();
-    };
-    for (int t = 0; t < ntiles; t += 2) {
-        step(t, st1);
-        if (t + 1 < ntiles) step(t + 1, st0);
+    for (int k = 0; k < NBLK; ++k) {
+        rt[k] = descriptor(at, 32 * (k == 0 ? bp : bq), TDT == 0 ? 4 : 2);
+        rr[k] = descriptor(ar, 32 * (k == 0 ? bp : bq), RDT == 0 ? 4 : 2);
     }
-
-    // lane l of a 32x32 block holds column l % 32, rows 8 * (i / 4) + 4 * (l / 32) + i % 4
-    const size_t nelem = (size_t)b * b;
-    float *dst = part + (size_t)chunk * 3 * nelem;               // M | M^T | B of this chunk
-    if (id == 0 && tid == 0) *counter = 0u;                       // ticket of the finaliser
-    if (MT == 1) {
-        // the four waves hold partial sums over disjoint k: add them through LDS
-        float *red = (float *)lds;                // [4][2][1024], the stage memory is free now
+    auto load_tile = [&](auto dt_c, const v4i &rsrc, int blk, int slab, bool ok, uint32_t dst, int i) {
+        constexpr int DT = decltype(dt_c)::value;
+        using T = Tile<DT>;
+        const int row = lane / T::kUnits, unit = (lane % T::kUnits) ^ ((row / (16 / T::kUnits)) % T::kUnits);
+        const int rl = i * T::kRowsPerLoad + row;
+        const uint32_t off = ok && 32 * blk + rl < b ? (uint32_t)rl * (uint32_t)(D * (DT == 0 ? 4 : 2)) + (uint32_t)(slab * T::kRow + unit * 16) : kOob;
+        load_to_lds_b128(rsrc, dst + i * 1024, off);
+    };
+    // element by element, with zeros beyond b and D (the last slab of a ragged D; rows that 4-byte accesses cannot address)
+    auto fill_tile = [&](auto dt_c, const void *base, int blk, int slab, uint8_t *dst) {
+        constexpr int DT = decltype(dt_c)::value;
+        using T = Tile<DT>;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            red[(wave * 2 + 0) * 1024 + i * 64 + lane] = accM[i];
-            red[(wave * 2 + 1) * 1024 + i * 64 + lane] = accB[i];
+        for (int i = 0; i < 8; ++i) {
+            const int rl = i * 4 + (lane >> 4), f = lane & 15;
+            const int64_t row = 32 * blk + rl, k = (int64_t)slab * kSlab + f;
+            const bool ok = row < b && k < D;
+            const int64_t idx = ok ? row * D + k : 0;
+            if (DT == 0) {
+                const float v = ((const float *)base)[idx];
+                *(float *)(dst + rl * T::kRow + T::slot(rl, f >> 2) * 16 + (f & 3) * 4) = ok ? v : 0.0f;
+            } else {
+                const uint16_t v = ((const uint16_t *)base)[idx];
+                *(uint16_t *)(dst + rl * T::kRow + T::slot(rl, f >> 3) * 16 + (f & 7) * 2) = ok ? v : (uint16_t)0;
+            }
+        }
+    };
+    using ct = std::integral_constant<int, TDT>;
+    using cr = std::integral_constant<int, RDT>;
+    const int last_direct = p.direct ? (int)(D / kSlab) : 0;     // slabs below this one are loaded straight into LDS
+    // request q of the NLD of a slab (a slab past the end: no traffic, zeros)
+    auto request_one = [&](int slab, int end, int q) {
+        constexpr int nt = NBLK * TT::kLoads;
+        if (q < nt) {
+            const int k = q / TT::kLoads;
+            load_tile(ct{}, rt[k], k == 0 ? bp : bq, slab, slab < end, stage0 + k * TT::kBytes, q % TT::kLoads);
+        } else {
+            const int k = (q - nt) / TR::kLoads;
+            load_tile(cr{}, rr[k], k == 0 ? bp : bq, slab, slab < end, stage0 + NBLK * TT::kBytes + k * TR::kBytes, (q - nt) % TR::kLoads);
+        }
+    };
+    auto request = [&](int slab, int end) {
+#pragma unroll
+        for (int q = 0; q < NLD; ++q) request_one(slab, end, q);
+    };
+    auto fill = [&](int slab) {
+        uint8_t *dst = stage;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the slab before has been read
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k, dst += TT::kBytes) fill_tile(ct{}, at, k == 0 ? bp : bq, slab, dst);
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k, dst += TR::kBytes) fill_tile(cr{}, ar, k == 0 ? bp : bq, slab, dst);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    auto read8 = [&](auto dt_c, const uint8_t *tile, float (&x)[8], v4u &bits) {
+        constexpr int DT = decltype(dt_c)::value;
+        using T = Tile<DT>;
+        const uint8_t *row = tile + r * T::kRow;
+        if (DT == 0) {
+            const float4 a = *(const float4 *)(row + T::slot(r, 2 * h) * 16), c = *(const float4 *)(row + T::slot(r, 2 * h + 1) * 16);
+            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+            x[4] = c.x; x[5] = c.y; x[6] = c.z; x[7] = c.w;
+        } else {
+            const v4u a = *(const v4u *)(row + T::slot(r, h) * 16);
+            bits = a;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[2 * e] = __uint_as_float(a[e] << 16);
+                x[2 * e + 1] = __uint_as_float(a[e] & 0xffff0000u);
+            }
+        }
+    };
+
+    v16f accW[NACC], accB[NACC];
+#pragma unroll
+    for (int k = 0; k < NACC; ++k)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { accW[k][i] = 0.0f; accB[k][i] = 0.0f; }
+
+    // One slab of this wave.  Its raw values and the parts of R are in registers; T's parts are the raw bits where T is
+    // bf16 (then W / 2 = D T^T + R D^T is what is summed: D T^T takes three exact partial products and S is not needed).
+    constexpr bool TF = TDT == 1;
+    constexpr int NR = RDT == 1 ? 1 : 3, NX = TF ? 1 : 3, NY = TF ? NR : 3;
+    struct Raw {
+        float t[NBLK][8], r[NBLK][8];
+        v4u tbits[NBLK];
+    };
+    auto read_raw = [&](Raw &x) {
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) {
+            read8(ct{}, stage + k * TT::kBytes, x.t[k], x.tbits[k]);
+            v4u unused;
+            read8(cr{}, stage + NBLK * TT::kBytes + k * TR::kBytes, x.r[k], unused);
+        }
+    };
+    // The splits come in pieces of one pair of values: piece 4 k + e of block k.
+    constexpr int kPieces = 4 * NBLK;
+    auto split_r = [&](const Raw &x, int piece, Split8 (&rp)[NBLK]) {
+        const int k = piece >> 2, e = piece & 3;
+        split_pair(x.r[k][2 * e], x.r[k][2 * e + 1], e, rp[k]);
+    };
+    // D, and the factor that D multiplies: S = T + R, or T itself
+    auto split_d = [&](const Raw &x, int piece, Split8 (&d)[NBLK]) {
+        const int k = piece >> 2, e = piece & 3;
+        split_pair(x.t[k][2 * e] - x.r[k][2 * e], x.t[k][2 * e + 1] - x.r[k][2 * e + 1], e, d[k]);
+    };
+    auto split_x = [&](const Raw &x, int piece, Split8 (&o)[NBLK]) {
+        const int k = piece >> 2, e = piece & 3;
+        if constexpr (TF) o[k].part[0][e] = x.tbits[k][e];
+        else split_pair(x.t[k][2 * e] + x.r[k][2 * e], x.t[k][2 * e + 1] + x.r[k][2 * e + 1], e, o[k]);
+    };
+    auto nothing = [] {};
+    auto run = [&](auto diag_c) {
+        constexpr bool DG = decltype(diag_c)::value;             // the first block's diagonal products belong to this pair
+        constexpr int nRR = NR == 3 ? 6 : 1, nDX = NX == 3 ? 6 : 3, nYD = NY == 3 ? 6 : 3;   // partial products of each kind
+        constexpr int kDiag = (DG ? 1 : 0) + (NACC == 3 ? 1 : 0);
+        constexpr int mfB = nRR * ((NBLK - 1) + kDiag), mfW = (nDX + nYD) * (NBLK - 1) + kDiag * (nDX + (TF ? nYD : 0));
+        auto products_b = [&](const Split8 (&rp)[NBLK], auto after) {
+            if constexpr (NBLK == 2) mma_parts<NR, NR>(rp[0], rp[1], accB[1], after);
+            if constexpr (DG) mma_parts<NR, NR>(rp[0], rp[0], accB[0], after);
+            if constexpr (NACC == 3) mma_parts<NR, NR>(rp[1], rp[1], accB[2], after);
+        };
+        auto products_w = [&](const Split8 (&rp)[NBLK], const Split8 (&d)[NBLK], const Split8 (&x)[NBLK], auto after) {
+            if constexpr (NBLK == 2) mma_parts<3, NX>(d[0], x[1], accW[1], after);
+            if constexpr (DG) {
+                mma_parts<3, NX>(d[0], x[0], accW[0], after);
+                if constexpr (TF) mma_parts<NR, 3>(rp[0], d[0], accW[0], after);
+            }
+            if constexpr (NBLK == 2) {
+                if constexpr (TF) mma_parts<NR, 3>(rp[0], d[1], accW[1], after);
+                else mma_parts<3, 3>(x[0], d[1], accW[1], after);
+            }
+            if constexpr (NACC == 3) {
+                mma_parts<3, NX>(d[1], x[1], accW[2], after);
+                if constexpr (TF) mma_parts<NR, 3>(rp[1], d[1], accW[2], after);
+            }
+        };
+        // slabs first, first + 8, ... of the chunk: neighbouring waves take neighbouring slabs, i.e. the two halves
+        // of a cache line at about the same time
+        const int first = slab0 + wave;
+        const int end = slab1 < last_direct ? slab1 : last_direct;
+        const int n = first < end ? (end - first + kGramWaves - 1) / kGramWaves : 0;
+        if (n > 0) {
+            // the stage is free again as soon as its raw values are in registers: one slab in registers, the next landing
+            // (two stages per wave, i.e. 128 KB in flight per CU instead of 64, made no difference)
+            request(first, end);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            Raw cur;
+            Split8 rp[NBLK];
+            read_raw(cur);
+#pragma unroll
+            for (int k = 0; k < kPieces; ++k) split_r(cur, k, rp);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            int ahead = first + kGramWaves;
+            request(ahead, end);
+            // Two steps per slab: the products of B beside the splits of D and S, the products of W beside the split of the
+            // next slab's R and the requests for the slab after.  The pieces and the requests are placed between the
+            // matrix instructions one by one: left to itself the compiler puts all of one kind first, and the two waves
+            // of a SIMD, which start together, wait for the same pipe; a burst of requests holds the wave up.
+            for (int i = 0; i < n; ++i) {
+                Split8 d[NBLK], x[NBLK], rn[NBLK];
+                int m = 0;                                       // (a constant everywhere: the code is straight-line)
+                constexpr int perB = (2 * kPieces + mfB - 1) / mfB;
+                products_b(rp, [&] {
+#pragma unroll
+                    for (int q = m * perB; q < (m + 1) * perB && q < 2 * kPieces; ++q) {
+                        if (q & 1) split_x(cur, q >> 1, x); else split_d(cur, q >> 1, d);
+                    }
+                    ++m;
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                // the next slab has landed (past the last one: zeros, which nothing uses)
+                ahead += kGramWaves;
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                read_raw(cur);
+                m = 0;
+                constexpr int lead = mfW > 8 ? 3 : 0, room = mfW - lead;     // the first instructions cover the LDS reads
+                constexpr int perW = (kPieces + room - 1) / room, perL = (NLD + room - 1) / room;
+                products_w(rp, d, x, [&] {
+                    if (m == lead) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
+                    if (m >= lead) {
+                        const int j = m - lead;
+#pragma unroll
+                        for (int q = j * perL; q < (j + 1) * perL && q < NLD; ++q) request_one(ahead, end, q);
+#pragma unroll
+                        for (int q = j * perW; q < (j + 1) * perW && q < kPieces; ++q) split_r(cur, q, rn);
+                    }
+                    ++m;
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+#pragma unroll
+                for (int k = 0; k < NBLK; ++k) rp[k] = rn[k];
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        // slabs that are filled element by element
+        for (int slab = first + n * kGramWaves; slab < slab1; slab += kGramWaves) {
+            fill(slab);
+            Raw cur;
+            Split8 rp[NBLK], d[NBLK], x[NBLK];
+            read_raw(cur);
+#pragma unroll
+            for (int k = 0; k < kPieces; ++k) { split_r(cur, k, rp); split_d(cur, k, d); split_x(cur, k, x); }
+            products_b(rp, nothing);
+            products_w(rp, d, x, nothing);
+        }
+    };
+    if (diag_p) run(std::true_type{});
+    else if constexpr (KIND == 2) run(std::false_type{});
+
+    // ---- the eight waves' sums: first W, then B through LDS (the stages are free).  Register i of lane l of a
+    // 32x32 block is row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.
+    constexpr int kBlockF = 32 * 33;                             // floats of a block with padded rows
+    float *red = (float *)lds;                                   // [waves][NACC][16][64]
+    float *sum = red + kGramWaves * NACC * 1024;                 // [NACC][32][33]
+    float *fin = sum + NACC * kBlockF;                           // fused: W and B, [2][64][65]
+    static_assert((kGramWaves * 3 * 1024 + 3 * kBlockF + 2 * 64 * 65) * 4 <= kGramLds, "the reduction must fit the LDS");
+    const size_t nelem = (size_t)b * b;
+    float *dst = part + (size_t)chunk * 2 * nelem;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        __syncthreads();                                         // the stages, or the matrix before, have been read
+#pragma unroll
+        for (int k = 0; k < NACC; ++k)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[(wave * NACC + k) * 1024 + i * 64 + lane] = m == 0 ? accW[k][i] : accB[k][i];
+        __syncthreads();
+#pragma unroll
+        for (int e0 = 0; e0 < NACC * 1024; e0 += 64 * kGramWaves) {
+            const int e = e0 + tid, k = e >> 10, i = (e >> 6) & 15;
+            float v[kGramWaves];
+#pragma unroll
+            for (int w = 0; w < kGramWaves; ++w) v[w] = red[w * NACC * 1024 + e];
+            float t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            if (TF && m == 0) t *= 2.0f;                         // (exact)
+            sum[k * kBlockF + (8 * (i >> 2) + 4 * h + (i & 3)) * 33 + r] = t;
         }
         __syncthreads();
-        for (int e = tid; e < 2048; e += 256) {
-            const int prod = e >> 10, w = e & 1023;
-            const int i = w >> 6, l = w & 63;
-            const float s = (red[(0 * 2 + prod) * 1024 + w] + red[(1 * 2 + prod) * 1024 + w]) +
-                            (red[(2 * 2 + prod) * 1024 + w] + red[(3 * 2 + prod) * 1024 + w]);
-            const int row = (i >> 2) * 8 + (l >> 5) * 4 + (i & 3), col = l & 31;
-            if (row < b && col < b) {
-                if (prod == 0) {
-                    dst[(size_t)row * b + col] = s;
-                    dst[nelem + (size_t)col * b + row] = s;
-                } else {
-                    dst[2 * nelem + (size_t)row * b + col] = s;
-                }
-            }
-        }
-    } else {
-        const int col = mj * ROWS + bj * 32 + r;
-        const bool quad_ok = (b & 3) == 0;        // four consecutive rows of a column: one 16-byte store of M^T
+        // whole rows out: block (p, p), (p, q) and its transpose (q, p), (q, q)
+        auto store = [&](int k, int rowb, int colb, bool transposed, bool add_transposed) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = mi * ROWS + bi * 32 + (i >> 2) * 8 + h * 4 + (i & 3);
-            if (row < b && col < b) {
-                dst[(size_t)row * b + col] = accM[i];
-                dst[2 * nelem + (size_t)row * b + col] = accB[i];
-                if (!quad_ok) dst[nelem + (size_t)col * b + row] = accM[i];
+            for (int e0 = 0; e0 < 1024; e0 += 64 * kGramWaves) {
+                const int e = e0 + tid, row = e >> 5, col = e & 31;
+                const float a = sum[k * kBlockF + row * 33 + col], c = sum[k * kBlockF + col * 33 + row];
+                const float v = add_transposed ? a + c : (transposed ? c : a);
+                const int gr = 32 * rowb + row, gc = 32 * colb + col;
+                if (p.fused) fin[(m * 64 + gr) * 65 + gc] = v;
+                else if (gr < b && gc < b) dst[(size_t)m * nelem + (size_t)gr * b + gc] = v;
             }
+        };
+        if (diag_p) store(0, bp, bp, false, !TF && m == 0);
+        if constexpr (NBLK == 2) {
+            store(1, bp, bq, false, false);
+            store(1, bq, bp, true, false);
         }
-        if (quad_ok && col < b) {
+        if constexpr (NACC == 3) store(2, bq, bq, false, !TF && m == 0);
+    }
+    if constexpr (KIND < 2) {
+        if (!p.fused) return;
+        // the whole score: a wave per row, the row's columns in its lanes, shares added in index order
+        __syncthreads();
+        double *share = (double *)lds;                           // [64][4]
+        constexpr int RW = 32 * NBLK / kGramWaves;               // rows of a wave, side by side: their sums are chains of exchanges
+        double q[4][RW];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int row = mi * ROWS + bi * 32 + q * 8 + h * 4;
-                if (row < b)
-                    *(float4 *)&dst[nelem + (size_t)col * b + row] =
-                        make_float4(accM[4 * q], accM[4 * q + 1], accM[4 * q + 2], accM[4 * q + 3]);
-            }
+        for (int k = 0; k < RW; ++k) {
+            const int i = wave + kGramWaves * k;
+            const bool in = i < b && lane < b;
+            const double a = in ? (double)fin[(64 + i) * 65 + (lane < b ? lane : 0)] : 0.0;
+            const double e = in ? 0.5 * (double)fin[i * 65 + (lane < b ? lane : 0)] : 0.0, g = a + e;
+            q[0][k] = a * a;
+            q[1][k] = g * g;
+            q[2][k] = a * e;
+            q[3][k] = e * e;
+        }
+        // (a block of 32 columns needs no exchange between the halves of the wave)
+#pragma unroll
+        for (int off = NBLK == 1 ? 16 : 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int k = 0; k < RW; ++k)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) q[m][k] += __shfl_xor(q[m][k], off, kWave);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < RW; ++k)
+                if (wave + kGramWaves * k < b)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) share[4 * (wave + kGramWaves * k) + m] = q[m][k];
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const double tot = wave_sum(lane < b ? row_share(share[4 * lane], share[4 * lane + 1], share[4 * lane + 2], share[4 * lane + 3]) : 0.0);
+            if (lane == 0) *p_out = (float)(tot / ((double)b * (double)b));
         }
     }
 }
 
-// One workgroup per row i (b <= 128).  The 256 threads form G = 256 / W groups of
-// W >= b lanes (W = 32, 64 or 128); group g adds chunks g, g + G, ... of row i
-// of M, M^T and B in fp64, lane j taking column j (coalesced 4 W-byte reads),
-// and the G sums are added in group order.
-__global__ __launch_bounds__(256) void sp_finalize_kernel(const float *__restrict__ part, int nsplit, int b,
-                                                          double *__restrict__ rowsum,
-                                                          uint32_t *__restrict__ counter,
-                                                          float *__restrict__ p_out)
+// Workgroup (row i, part): columns part * CS .. + CS - 1 of row i.  Its threads form groups of CS lanes, a chunk of the
+// partials each, lane j taking column j; W and B are summed over the chunks in fp64 (fixed assignment, fixed order).
+// With a = row i of R R^T and e = half of row i of W (so a + e = row i of T T^T) the row's share of P,
+// || (a + e) / |a + e| - a / |a| ||^2, follows from four sums over the columns: |a|^2, |a + e|^2, a.e and |e|^2, since
+// it is 2 sin^2 / (1 + cos) of the angle between the two rows and sin^2 = (|a|^2 |e|^2 - (a.e)^2) / (|a|^2 |a + e|^2)
+// without cancellation where e is small.  The last workgroup to finish adds the parts and the rows in index order.
+// Bound by latency: launch, one round trip for the partials (which other XCDs wrote), one for the ticket.  One
+// workgroup per row reading 256 chunks of 2 x 256 bytes took 8.5 us for b = 64 (64 of 256 CUs at work, three dependent
+// row sums, a fence that writes the L2 back); this form takes 6.
+constexpr int kFinThreads = 1024;
+static int fin_columns(int b) { return b <= 32 ? 16 : 64; }      // CS
+static int fin_parts(int b) { return (b + fin_columns(b) - 1) / fin_columns(b); }
+
+template <int CS>
+__global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *__restrict__ part, int nsplit, int b, int parts,
+                                                                  double *__restrict__ sums, uint32_t *__restrict__ counter,
+                                                                  float *__restrict__ p_out)
 {
-    __shared__ double sm[3][256];
-    __shared__ double wsum[4];
-    const int i = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int W = b <= 32 ? 32 : (b <= 64 ? 64 : 128), G = 256 / W;
-    const int j = t & (W - 1), grp = t / W;
-    const size_t nelem = (size_t)b * b, cstride = 3 * nelem;
-    constexpr int U = 8;                                          // chunks in flight per thread (3 loads each)
-    double am = 0.0, at = 0.0, ab = 0.0;
-    if (j < b) {
-        const float *p = part + (size_t)i * b + j;
-        int c = grp;
-        for (; c + (U - 1) * G < nsplit; c += U * G) {
-            float vm[U], vt[U], vb[U];
+    constexpr int NW = kFinThreads / 64, G = kFinThreads / CS;
+    __shared__ double sm[2][NW][CS];
+    __shared__ uint32_t ticket_s;
+    const int i = blockIdx.x / parts, pt = blockIdx.x % parts, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int j = pt * CS + t % CS, grp = t / CS;
+    const size_t nelem = (size_t)b * b, cstride = 2 * nelem;
+    constexpr int U = CS == 16 ? 4 : 8;                           // chunks in flight per thread (2 loads each)
+    double aw = 0.0, ab = 0.0;
+    const float *p = part + (size_t)i * b + (j < b ? j : b - 1);
+    for (int c = grp; c < nsplit; c += U * G) {
+        float vw[U], vb[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float *pc = p + (size_t)(c + u * G) * cstride;
-                vm[u] = pc[0];
-                vt[u] = pc[nelem];
-                vb[u] = pc[2 * nelem];
-            }
+        for (int u = 0; u < U; ++u) {                             // (unconditional: a chunk past the end reads the last one)
+            const float *pc = p + (size_t)(c + u * G < nsplit ? c + u * G : nsplit - 1) * cstride;
+            vw[u] = pc[0];
+            vb[u] = pc[nelem];
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                am += (double)vm[u];
-                at += (double)vt[u];
+        for (int u = 0; u < U; ++u)
+            if (c + u * G < nsplit) {
+                aw += (double)vw[u];
                 ab += (double)vb[u];
             }
-        }
-        for (; c < nsplit; c += G) {
-            const float *pc = p + (size_t)c * cstride;
-            am += (double)pc[0];
-            at += (double)pc[nelem];
-            ab += (double)pc[2 * nelem];
-        }
     }
-    sm[0][t] = am;
-    sm[1][t] = at;
-    sm[2][t] = ab;
+#pragma unroll
+    for (int off = CS; off < 64; off <<= 1) { aw += __shfl_xor(aw, off, kWave); ab += __shfl_xor(ab, off, kWave); }
+    if (lane < CS) { sm[0][wave][lane] = aw; sm[1][wave][lane] = ab; }
     __syncthreads();
-    double gt = 0.0, gr = 0.0;
-    if (t < W && t < b) {
-        double m = 0.0, mt = 0.0, bb = 0.0;
-        for (int g = 0; g < G; ++g) {
-            m += sm[0][g * W + t];
-            mt += sm[1][g * W + t];
-            bb += sm[2][g * W + t];
+    if (wave == 0) {
+        double q[kFinSums] = {0.0, 0.0, 0.0, 0.0};
+        if (lane < CS && j < b) {
+            double w = 0.0, a = 0.0;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) { w += sm[0][k][lane]; a += sm[1][k][lane]; }
+            const double e = 0.5 * w, g = a + e;                  // rows of R R^T: a, of T T^T: g
+            q[0] = a * a;
+            q[1] = g * g;
+            q[2] = a * e;
+            q[3] = e * e;
         }
-        gr = bb;                                   // row i of R R^T
-        gt = bb + 0.5 * (m + mt);                  // row i of T T^T
-    }
-    // sums over the row: waves 0 and 1 hold the (at most 128) columns
-    auto row_sum = [&](double v) {
-        v = wave_sum(v);
-        __syncthreads();
-        if (lane == 0) wsum[wave] = v;
-        __syncthreads();
-        return wsum[0] + wsum[1];
-    };
-    double nt = sqrt(row_sum(gt * gt)), nr = sqrt(row_sum(gr * gr));
-    nt = nt < 1e-12 ? 1e-12 : nt;
-    nr = nr < 1e-12 ? 1e-12 : nr;
-    const double d = (t < W && t < b) ? gt / nt - gr / nr : 0.0;
-    const double share = row_sum(d * d);
-    __shared__ uint32_t ticket_s;
-    if (t == 0) {
-        rowsum[i] = share;
-        __threadfence();                                   // publish the share, then take a ticket
-        ticket_s = atomicAdd(counter, 1u);
+#pragma unroll
+        for (int off = CS / 2; off > 0; off >>= 1)
+#pragma unroll
+            for (int k = 0; k < kFinSums; ++k) q[k] += __shfl_xor(q[k], off, kWave);
+        if (lane == 0) {
+            // device-scope stores (they bypass the XCD's L2), waited for before the ticket is taken: no cache write-back
+#pragma unroll
+            for (int k = 0; k < kFinSums; ++k)
+                __hip_atomic_store(&sums[(size_t)blockIdx.x * kFinSums + k], q[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            ticket_s = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
-    if (ticket_s != (uint32_t)(b - 1) || wave != 0) return;
-    __threadfence();                                       // see every other workgroup's share
-    const double v0 = lane < b ? __hip_atomic_load(&rowsum[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-    const double v1 = lane + 64 < b ? __hip_atomic_load(&rowsum[lane + 64], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-    const double tot = wave_sum(v0 + v1);
-    if (lane == 0) *p_out = (float)(tot / ((double)b * (double)b));
+    if (ticket_s != gridDim.x - 1) return;
+    double share = 0.0;
+    if (t < b) {
+        double q[kFinSums] = {0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < parts; ++k)
+#pragma unroll
+            for (int m = 0; m < kFinSums; ++m)
+                q[m] += __hip_atomic_load(&sums[((size_t)t * parts + k) * kFinSums + m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        share = row_share(q[0], q[1], q[2], q[3]);
+    }
+    __syncthreads();                                              // sm is free
+    share = wave_sum(share);
+    if (lane == 0) sm[0][wave][0] = share;
+    __syncthreads();
+    if (t == 0) *p_out = (float)((sm[0][0][0] + sm[0][1][0]) / ((double)b * (double)b));   // waves 0 and 1 hold the rows
 }
 
 hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r, egeria_dtype r_dt,
                              int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st)
 {
-    const GramPlan p = plan_gram(b, D);
+    if (D > (int64_t)0x7fffffff * kSlab / 2) return hipErrorInvalidValue;        // 32-bit slab numbers
+    GramPlan p = plan_gram(b, D);
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     uint32_t *counter = (uint32_t *)ws_part;
-    double *rowsum = (double *)((char *)ws_part + off_rowsum());
+    double *sums = (double *)((char *)ws_part + off_sums());
     float *part = (float *)((char *)ws_part + off_partials(b));
-    // whole K tiles and 16-byte aligned rows: the unconditional-load variant
-    const bool vec = D % p.kt == 0;
-    const dim3 grid((unsigned)(p.nsplit_pad * p.nmacro)), block(256);
     const int tcode = t_dt == EGERIA_BF16 ? 1 : 0, rcode = r_dt == EGERIA_BF16 ? 1 : 0;
+    // straight into LDS: rows that start at 4-byte boundaries (what buffer loads need) and 32-bit byte offsets within
+    // a block of samples
+    p.direct = D * (tcode ? 2 : 4) % 4 == 0 && D * (rcode ? 2 : 4) % 4 == 0 && D < (1LL << 24) - 4096;
+    const dim3 grid((unsigned)((p.nsplit + 7) / 8 * 8 * p.npair)), block(64 * kGramWaves);
     hipError_t e = hipSuccess;
-#define EGERIA_GRAM(MTV, OFF, T, R, V)                                                                 \
+#define EGERIA_GRAM(K, T, R)                                                                           \
     do {                                                                                               \
-        /* two stages of nine bf16 planes of 4 KiB, twelve when off-diagonal macro tiles exist */      \
-        constexpr size_t smem = (size_t)2 * (OFF ? 12 : 9) * 4096;                                     \
         static bool attr_set[kMaxDevices] = {};                                                        \
         if (!attr_set[dev]) {                                                                          \
-            e = hipFuncSetAttribute((const void *)gram_partial_kernel<MTV, OFF, T, R, V>,              \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);            \
+            e = hipFuncSetAttribute((const void *)gram_kernel<K, T, R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGramLds); \
             if (e != hipSuccess) return e;                                                             \
             attr_set[dev] = true;                                                                      \
         }                                                                                              \
-        e = launch_k(EGERIA_KERNEL_GRAM, gram_partial_kernel<MTV, OFF, T, R, V>, grid, block, smem,    \
-                     st, a_t, a_r, (int)b, D, p, part, counter);                                       \
+        e = launch_k(EGERIA_KERNEL_GRAM, gram_kernel<K, T, R>, grid, block, kGramLds, st, a_t, a_r, (int)b, D, p, part, counter, p_out); \
     } while (0)
-#define EGERIA_GRAM_DT(MTV, OFF)                                                                       \
+#define EGERIA_GRAM_DT(K)                                                                              \
     do {                                                                                               \
-        if (vec) {                                                                                     \
-            if (!tcode && !rcode) EGERIA_GRAM(MTV, OFF, 0, 0, true);                                   \
-            else if (tcode && !rcode) EGERIA_GRAM(MTV, OFF, 1, 0, true);                               \
-            else if (!tcode && rcode) EGERIA_GRAM(MTV, OFF, 0, 1, true);                               \
-            else EGERIA_GRAM(MTV, OFF, 1, 1, true);                                                    \
-        } else {                                                                                       \
-            if (!tcode && !rcode) EGERIA_GRAM(MTV, OFF, 0, 0, false);                                  \
-            else if (tcode && !rcode) EGERIA_GRAM(MTV, OFF, 1, 0, false);                              \
-            else if (!tcode && rcode) EGERIA_GRAM(MTV, OFF, 0, 1, false);                              \
-            else EGERIA_GRAM(MTV, OFF, 1, 1, false);                                                   \
-        }                                                                                              \
+        if (!tcode && !rcode) EGERIA_GRAM(K, 0, 0);                                                    \
+        else if (tcode && !rcode) EGERIA_GRAM(K, 1, 0);                                                \
+        else if (!tcode && rcode) EGERIA_GRAM(K, 0, 1);                                                \
+        else EGERIA_GRAM(K, 1, 1);                                                                     \
     } while (0)
-    if (p.mt == 1) EGERIA_GRAM_DT(1, false);
-    else if (p.nm == 1) EGERIA_GRAM_DT(2, false);
-    else EGERIA_GRAM_DT(2, true);
+    if (p.nb == 1) EGERIA_GRAM_DT(0);
+    else if (p.nb == 2) EGERIA_GRAM_DT(1);
+    else EGERIA_GRAM_DT(2);
 #undef EGERIA_GRAM_DT
 #undef EGERIA_GRAM
-    if (e != hipSuccess) return e;
-    return launch_k(EGERIA_KERNEL_NONE, sp_finalize_kernel, dim3((unsigned)b), dim3(256), 0, st, (const float *)part,
-                    p.nsplit, (int)b, rowsum, counter, p_out);
+    if (e != hipSuccess || p.fused) return e;
+    const int parts = fin_parts(b);
+    auto finish = [&](auto kernel) {
+        return launch_k(EGERIA_KERNEL_NONE, kernel, dim3((unsigned)(b * parts)), dim3(kFinThreads), 0, st, (const float *)part,
+                        p.nsplit, (int)b, parts, sums, counter, p_out);
+    };
+    return fin_columns(b) == 16 ? finish(sp_finalize_kernel<16>) : finish(sp_finalize_kernel<64>);
 }
 
 }  // namespace egeria
