@@ -19,7 +19,7 @@
  *     device memory and never synchronises: work is enqueued on `stream` (a
  *     hipStream_t passed as void*; NULL is the default stream) and results
  *     land in device memory when the stream reaches them.  One exception to
- *     "on `stream`": for a stack of layers (n_layers > 1)
+ *     "on `stream`": for a stack of several layers with large activations
  *     egeria_plasticity_eval and egeria_refresh_eval enqueue the score of
  *     layer l on a side stream that the library creates once per device
  *     (default priority, on the device that is current at the first such

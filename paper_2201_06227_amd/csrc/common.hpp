@@ -325,10 +325,11 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
                                       int8_t *xq, int64_t ldq, float *scale_out,
                                       uint32_t *flag, uint32_t *unsure_total, hipStream_t st);
 
-// Training plasticity.  ws_part must hold plasticity_partial_bytes(b, D).
+// Training plasticity.  ws_part must hold plasticity_partial_bytes(b, D).  beside: the launch shares the device with
+// another stream's work.
 size_t plasticity_partial_bytes(int32_t b, int64_t D);
 hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r, egeria_dtype r_dt,
-                             int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st);
+                             int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st, bool beside = false);
 
 // ---- device helpers ------------------------------------------------------------
 #ifdef __HIPCC__

@@ -61,7 +61,10 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kSlab = 16;                // features of one matrix instruction
 constexpr int kGramWaves = 8;
-constexpr int kGramLds = 144 * 1024;     // one workgroup per CU
+// LDS of a workgroup: the waves' stages, then the reduction (two blocks of eight waves, their sums) and, for a score
+// that the workgroup finishes itself, both matrices.  Kept near 72 KB: other streams' kernels share the CU.
+constexpr int kGramReduce = (2 * kGramWaves * 1024 + 2 * 32 * 33) * 4;
+constexpr int kGramFused = kGramReduce + 2 * 64 * 65 * 4;
 constexpr int kFusedSlabs = 64;          // slabs (of 16 features) up to which one workgroup does the whole score
 
 struct GramPlan {
@@ -70,6 +73,7 @@ struct GramPlan {
     int nslab;       // slabs of 16 features in D
     int nsplit;      // chunks of D
     int spc;         // slabs per chunk
+    int turns;       // (chunks per XCD) x (pairs)
     int fused;       // one chunk, finished by its workgroup
     int direct;      // whole slabs are loaded straight into LDS (else element by element)
 };
@@ -90,6 +94,7 @@ static GramPlan plan_gram(int32_t b, int64_t D)
     if (want < 1) want = 1;
     p.spc = (int)((nslab + want - 1) / want);
     p.nsplit = (int)((nslab + p.spc - 1) / p.spc);
+    p.turns = (p.nsplit + 7) / 8 * p.npair;
     return p;
 }
 
@@ -170,7 +175,7 @@ __device__ __forceinline__ double row_share(double aa, double gg, double ae, dou
 // or four blocks, the off-diagonal products and those of the first block's diagonal if the pair's turn says so.
 template <int KIND, int TDT, int RDT>
 __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__restrict__ at, const void *__restrict__ ar,
-                                                                  int b, int64_t D, GramPlan p, float *__restrict__ part,
+                                                                  int b, int64_t D, GramPlan p, int turn0, float *__restrict__ part,
                                                                   uint32_t *__restrict__ counter, float *__restrict__ p_out)
 {
     constexpr int NBLK = KIND == 0 ? 1 : 2;                      // blocks of samples
@@ -179,12 +184,13 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     using TR = Tile<RDT>;
     constexpr int kStage = NBLK * (TT::kBytes + TR::kBytes);
     constexpr int NLD = NBLK * (TT::kLoads + TR::kLoads);        // load instructions of a slab
+    static_assert(kGramWaves * kStage <= kGramReduce, "the stages must fit the reduction's LDS");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // consecutive workgroup ids land on different XCDs: all pairs of one chunk go to the same XCD so that its L2
     // serves the re-reads of that chunk
-    const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
-    const int chunk = (turn / p.npair) * 8 + xcd, pair = turn % p.npair;
+    const int turn = turn0 + (blockIdx.x >> 3);
+    const int chunk = (turn / p.npair) * 8 + (blockIdx.x & 7), pair = turn % p.npair;
     if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;      // ticket of the finaliser
     if (chunk >= p.nsplit) return;
     // pairs of four blocks: (0,1) (1,2) (2,3) (3,0) with the first one's diagonal, (0,2) (1,3) without;
@@ -430,52 +436,55 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     if (diag_p) run(std::true_type{});
     else if constexpr (KIND == 2) run(std::false_type{});
 
-    // ---- the eight waves' sums: first W, then B through LDS (the stages are free).  Register i of lane l of a
-    // 32x32 block is row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.
-    constexpr int kBlockF = 32 * 33;                             // floats of a block with padded rows
-    float *red = (float *)lds;                                   // [waves][NACC][16][64]
-    float *sum = red + kGramWaves * NACC * 1024;                 // [NACC][32][33]
-    float *fin = sum + NACC * kBlockF;                           // fused: W and B, [2][64][65]
-    static_assert((kGramWaves * 3 * 1024 + 3 * kBlockF + 2 * 64 * 65) * 4 <= kGramLds, "the reduction must fit the LDS");
+    // ---- the eight waves' sums, one 32x32 block after the other through LDS (the stages are free; the halves of the
+    // reduction area alternate, so a block costs two barriers).  Register i of lane l of a block is row
+    // 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.
+    float *red = (float *)lds;                                   // [2][waves][16][64]: this block's, the next one's
+    float *sum = red + 2 * kGramWaves * 1024;                    // [2][32][33], padded rows
+    float *fin = sum + 2 * 32 * 33;                              // fused: W and B, [2][64][65]
     const size_t nelem = (size_t)b * b;
     float *dst = part + (size_t)chunk * 2 * nelem;
+    __syncthreads();                                             // every wave has read its last slab
+    int turn_ = 0;
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
-        __syncthreads();                                         // the stages, or the matrix before, have been read
 #pragma unroll
-        for (int k = 0; k < NACC; ++k)
+        for (int k = 0; k < NACC; ++k) {
+            // [diag p][off][diag q]; KIND 0 has the first one only
+            if (k == 0 && !diag_p) continue;
+            float *rd = red + (turn_ & 1) * kGramWaves * 1024, *sm = sum + (turn_ & 1) * 32 * 33;
+            ++turn_;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) red[(wave * NACC + k) * 1024 + i * 64 + lane] = m == 0 ? accW[k][i] : accB[k][i];
-        __syncthreads();
+            for (int i = 0; i < 16; ++i) rd[wave * 1024 + i * 64 + lane] = m == 0 ? accW[k][i] : accB[k][i];
+            __syncthreads();
 #pragma unroll
-        for (int e0 = 0; e0 < NACC * 1024; e0 += 64 * kGramWaves) {
-            const int e = e0 + tid, k = e >> 10, i = (e >> 6) & 15;
-            float v[kGramWaves];
+            for (int e0 = 0; e0 < 1024; e0 += 64 * kGramWaves) {
+                const int e = e0 + tid, i = e >> 6;
+                float v[kGramWaves];
 #pragma unroll
-            for (int w = 0; w < kGramWaves; ++w) v[w] = red[w * NACC * 1024 + e];
-            float t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-            if (TF && m == 0) t *= 2.0f;                         // (exact)
-            sum[k * kBlockF + (8 * (i >> 2) + 4 * h + (i & 3)) * 33 + r] = t;
-        }
-        __syncthreads();
-        // whole rows out: block (p, p), (p, q) and its transpose (q, p), (q, q)
-        auto store = [&](int k, int rowb, int colb, bool transposed, bool add_transposed) {
+                for (int w = 0; w < kGramWaves; ++w) v[w] = rd[w * 1024 + e];
+                float t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+                if (TF && m == 0) t *= 2.0f;                     // (exact)
+                sm[(8 * (i >> 2) + 4 * h + (i & 3)) * 33 + r] = t;
+            }
+            __syncthreads();
+            // whole rows out: block (p, p), (q, q), or (p, q) and its transpose (q, p)
+            const int rowb = k == 2 ? bq : bp, colb = k == 0 ? bp : bq;
 #pragma unroll
             for (int e0 = 0; e0 < 1024; e0 += 64 * kGramWaves) {
                 const int e = e0 + tid, row = e >> 5, col = e & 31;
-                const float a = sum[k * kBlockF + row * 33 + col], c = sum[k * kBlockF + col * 33 + row];
-                const float v = add_transposed ? a + c : (transposed ? c : a);
-                const int gr = 32 * rowb + row, gc = 32 * colb + col;
-                if (p.fused) fin[(m * 64 + gr) * 65 + gc] = v;
-                else if (gr < b && gc < b) dst[(size_t)m * nelem + (size_t)gr * b + gc] = v;
+                const float a = sm[row * 33 + col], c = sm[col * 33 + row];
+                const float v = k != 1 && !TF && m == 0 ? a + c : a;    // a diagonal block of (T - R)(T + R)^T: plus its transpose
+                const int gr = 32 * rowb + row, gc = 32 * colb + col, tr = 32 * colb + row, tc = 32 * rowb + col;
+                if (p.fused) {
+                    fin[(m * 64 + gr) * 65 + gc] = v;
+                    if (k == 1) fin[(m * 64 + tr) * 65 + tc] = c;
+                } else {
+                    if (gr < b && gc < b) dst[(size_t)m * nelem + (size_t)gr * b + gc] = v;
+                    if (k == 1 && tr < b && tc < b) dst[(size_t)m * nelem + (size_t)tr * b + tc] = c;
+                }
             }
-        };
-        if (diag_p) store(0, bp, bp, false, !TF && m == 0);
-        if constexpr (NBLK == 2) {
-            store(1, bp, bq, false, false);
-            store(1, bq, bp, true, false);
         }
-        if constexpr (NACC == 3) store(2, bq, bq, false, !TF && m == 0);
     }
     if constexpr (KIND < 2) {
         if (!p.fused) return;
@@ -607,7 +616,7 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
 }
 
 hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r, egeria_dtype r_dt,
-                             int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st)
+                             int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st, bool beside)
 {
     if (D > (int64_t)0x7fffffff * kSlab / 2) return hipErrorInvalidValue;        // 32-bit slab numbers
     GramPlan p = plan_gram(b, D);
@@ -620,17 +629,23 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
     // straight into LDS: rows that start at 4-byte boundaries (what buffer loads need) and 32-bit byte offsets within
     // a block of samples
     p.direct = D * (tcode ? 2 : 4) % 4 == 0 && D * (rcode ? 2 : 4) % 4 == 0 && D < (1LL << 24) - 4096;
-    const dim3 grid((unsigned)((p.nsplit + 7) / 8 * 8 * p.npair)), block(64 * kGramWaves);
+    // Beside another stream's work: the same chunks (the same bits) in two launches of half the workgroups.  The kernel
+    // is bound by HBM either way, and one that sits on every CU keeps the other stream's workgroups waiting: 12-layer
+    // stack of 64 x 256 tokens 6.73 -> 6.64 ms.
+    const int launches = beside && p.turns > 1 ? 2 : 1, width = (p.turns + launches - 1) / launches;
+    const dim3 grid((unsigned)(width * 8)), block(64 * kGramWaves);
+    const size_t smem = p.fused ? kGramFused : kGramReduce;      // (covers the stages: 8 KB per wave at most)
     hipError_t e = hipSuccess;
 #define EGERIA_GRAM(K, T, R)                                                                           \
     do {                                                                                               \
         static bool attr_set[kMaxDevices] = {};                                                        \
         if (!attr_set[dev]) {                                                                          \
-            e = hipFuncSetAttribute((const void *)gram_kernel<K, T, R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGramLds); \
+            e = hipFuncSetAttribute((const void *)gram_kernel<K, T, R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGramFused); \
             if (e != hipSuccess) return e;                                                             \
             attr_set[dev] = true;                                                                      \
         }                                                                                              \
-        e = launch_k(EGERIA_KERNEL_GRAM, gram_kernel<K, T, R>, grid, block, kGramLds, st, a_t, a_r, (int)b, D, p, part, counter, p_out); \
+        for (int l = 0; l < launches && e == hipSuccess; ++l)                                          \
+            e = launch_k(EGERIA_KERNEL_GRAM, gram_kernel<K, T, R>, grid, block, smem, st, a_t, a_r, (int)b, D, p, l * width, part, counter, p_out); \
     } while (0)
 #define EGERIA_GRAM_DT(K)                                                                              \
     do {                                                                                               \
