@@ -347,124 +347,12 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the zero-filled K steps past the end
 
-    // The int8 residual of the tile goes through LDS (the stage memory is free
-    // now): one coalesced pass of 16-byte loads instead of one byte load per
-    // output element issued from inside the epilogue, whose round trips would add up.
-    constexpr bool RES_LDS = ET == 0;
-    static_assert(!RES_LDS || (size_t)NST * STAGE >= (size_t)BM * BN, "the residual tile must fit the stage memory");
-    if (RES_LDS && g.res_q) {
-        constexpr int RU = BN / 16, RIT = (BM * RU + NT - 1) / NT;     // 16-byte units per row, units per thread
-        v4i rv[RIT];
-        __syncthreads();                                              // every wave has read its last operands
-#pragma unroll
-        for (int it = 0; it < RIT; ++it) {
-            const int u = tid + it * NT, rr = u / RU, cu = u % RU;
-            const int64_t m = m0 + rr;
-            const int64_t col = n0 + cu * 16;
-            rv[it] = v4i{0, 0, 0, 0};
-            if (u < BM * RU && m < g.M && col < g.res_ld) rv[it] = *(const v4i *)(g.res_q + m * g.res_ld + col);
-        }
-#pragma unroll
-        for (int it = 0; it < RIT; ++it) {
-            const int u = tid + it * NT;
-            if (u < BM * RU) *(v4i *)&lds[(u / RU) * BN + (u % RU) * 16] = rv[it];
-        }
-        __syncthreads();
-    }
-
-    // ---- epilogue, straight from the accumulators.  Lane l of a 32x32 block
-    // holds column l % 32 and rows 8 * (r / 4) + 4 * (l / 32) + r % 4 (r = 0..15),
-    // so for a fixed r each half of the wave owns 32 consecutive columns of one
-    // row: every store instruction writes two full 128-byte row segments, and the
-    // row part of the address is uniform (scalar arithmetic only).
     const int lcol = lane & 31, lrow = (lane >> 5) * 4;
     const int wm_u = __builtin_amdgcn_readfirstlane(wm), wn_u = __builtin_amdgcn_readfirstlane(wn);
     // Running maximum for the next quantiser, kept as a bit pattern so that a
     // NaN or an infinity stays visible.  Non-negative values (after ReLU, or
     // when only positive values are wanted) order like signed integers.
-    const bool pos = g.amax_pos != 0;
     int32_t amax = 0;
-    const bool interior = m0 + BM <= g.M && n0 + BN <= g.N && (g.y || g.q_out) && !g.acc_out && !g.zp_in && !g.zp_res;
-    const uint32_t qoff = g.q_out ? (uint32_t)(lrow * g.q_ld + lcol) : 0u;
-    const uint32_t yoff = (uint32_t)(lrow * g.ldy + lcol);
-    const uint32_t roff = g.res_q ? (uint32_t)(lrow * g.res_ld + lcol) : 0u;
-    const uint32_t aoff = (uint32_t)(lrow * g.N + lcol);
-    // EDGE false: interior tile, no bounds tests, no observation outputs.
-    // EDGE true : edge tiles and observed runs, every element tested.
-    // QOUT (interior tiles): the tile also, or only, goes out as int8 codes.
-    auto emit = [&](auto edge_c, auto res_c, auto relu_c, auto pos_c, auto qout_c) {
-        constexpr bool EDGE = decltype(edge_c)::value, RES = decltype(res_c)::value, RELU = decltype(relu_c)::value;
-        constexpr bool POS = decltype(pos_c)::value, QOUT = decltype(qout_c)::value;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col0 = n0 + (wn_u * TN + j) * 32;
-            const bool col_ok = !EDGE || col0 + lcol < g.N;
-            const float bj = (g.bias && col_ok) ? g.bias[col0 + lcol] : 0.0f;
-            const float sj = g.sw_per_n ? (col_ok ? sxv * g.sw[col0 + lcol] : 0.0f) : s;   // one fp32 multiply
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int64_t row0 = m0 + (wm_u * TM + i) * 32;
-                float *yb = g.y + row0 * g.ldy + col0;
-                const res_t *rb = (const res_t *)g.res_q + row0 * g.res_ld + col0;
-                int32_t *ab = g.acc_out + row0 * g.N + col0;
-                int8_t *qb = g.q_out + row0 * g.q_ld + col0;
-                const int rows_left = EDGE ? (int)(g.M - row0 < 32 ? g.M - row0 : 32) - lrow : 32;
-                // the block stays in the accumulation registers until its turn
-                asm volatile("" : "+a"(acc[i][j]));
-                // float residuals of an interior block: all sixteen requested before the first is used
-                // (interleaved with the stores of y the compiler keeps each load behind the store before it)
-                float rpre[16];
-                if constexpr (!RES_LDS && !EDGE && RES) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        rpre[r] = (float)rb[(size_t)(8 * (r >> 2) + (r & 3)) * g.res_ld + roff];
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int rr = 8 * (r >> 2) + (r & 3);
-                    if (EDGE && !(col_ok && rr < rows_left)) {
-                        // pad columns of the int8 output are zero
-                        if (g.q_out && !col_ok && col0 + lcol < g.q_ld && rr < rows_left) qb[(size_t)rr * g.q_ld + qoff] = 0;
-                        continue;
-                    }
-                    auto a = acc[i][j][r];
-                    if constexpr (EDGE && ET == 0) {
-                        if (g.zp_in) {
-                            // the sum of the centred codes: the weight codes of this output channel, over the
-                            // window positions inside the image for this pixel, times 128 - zero point
-                            int cls = 0;
-                            if (CONV) {
-                                const uint32_t m = (uint32_t)(row0 + lrow + rr);
-                                const uint32_t mrow = m / (uint32_t)g.W;
-                                const int ow = (int)(m - mrow * (uint32_t)g.W), oh = (int)(mrow % (uint32_t)g.H);
-                                cls = (oh == 0 ? 1 : 0) | (oh == g.H - 1 ? 2 : 0) | (ow == 0 ? 4 : 0) | (ow == g.W - 1 ? 8 : 0);
-                            }
-                            a += zmul * g.colsum[(size_t)cls * g.N + col0 + lcol];
-                        }
-                    }
-                    float v = fmaf((float)a, sj, bj);
-                    if (EDGE ? g.res_q != nullptr : RES) {
-                        if constexpr (RES_LDS)
-                            v = v + (float)((int)(int8_t)lds[((wm_u * TM + i) * 32 + lrow + rr) * BN + (wn_u * TN + j) * 32 + lcol] + rmul) * rs;
-                        else if constexpr (!EDGE && RES)
-                            v = v + rpre[r] * rs;
-                        else
-                            v = v + (float)rb[(size_t)rr * g.res_ld + roff] * rs;
-                    }
-                    if (EDGE ? g.act == 1 : RELU) v = v > 0.0f ? v : 0.0f;
-                    if (EDGE ? g.y != nullptr : (!QOUT || g.y != nullptr)) yb[(size_t)rr * g.ldy + yoff] = v;
-                    if (EDGE ? g.q_out != nullptr : QOUT) qb[(size_t)rr * g.q_ld + qoff] = (int8_t)quant1(v, q_inv);
-                    if (EDGE && g.acc_out) ab[(size_t)rr * g.N + aoff] = acc_bits(a);
-                    int32_t bits = (int32_t)__float_as_uint(v);
-                    if (EDGE ? !(g.act == 1 || pos) : !(RELU || POS)) bits &= 0x7fffffff;
-                    amax = amax > bits ? amax : bits;
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-    using T = std::true_type;
-    using F = std::false_type;
     if constexpr (LNF) {
         // The layer norm of the rows in the same launch: the workgroup owns whole rows (one tile across N).
         // A 32-row block of the fp32 output goes to LDS (the stage memory is free now), then each wave
@@ -536,15 +424,231 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         }
         amax = (int32_t)amax_u;
-    } else
-    if (!interior || (g.q_out && (g.res_q || g.act != 1))) emit(T{}, F{}, F{}, F{}, F{});
-    else if (g.q_out) emit(F{}, F{}, T{}, F{}, T{});
-    else if (g.res_q) {
-        if (g.act == 1) emit(F{}, T{}, T{}, F{}, F{}); else emit(F{}, T{}, F{}, F{}, F{});
     } else {
-        if (g.act == 1) emit(F{}, F{}, T{}, F{}, F{});
-        else if (pos) emit(F{}, F{}, F{}, T{}, F{});
-        else emit(F{}, F{}, F{}, F{}, F{});
+        // ---- epilogue.  A wave's sums go through LDS (its own part of the stage memory, no barriers), a 32-row block at
+        // a time, and come back as four neighbouring columns of one row per lane: one 16-byte store of y, four packed
+        // codes, four residual codes in one load, the columns' scale and bias in registers.  Stores of y are raw buffer
+        // stores: what must not be written (rows beyond M, columns beyond N) lies outside the buffer, so edge tiles
+        // run the same straight code as interior ones.
+        // (Stores straight from the accumulators, two 128-byte row segments each, needed a specialised copy of the epilogue
+        // per combination of residual, activation and output; the general copy, for tiles at an edge and for affine
+        // codes, tested every element: 4728 x 2304 x 768 took 35.7 us where 4096 rows took 20.5.)
+        constexpr int WC = TN * 32, WS = WC + 8;        // columns of a wave's block; words per row (pad: the two rows a
+                                                        // write instruction touches fall into different banks)
+        constexpr int LPR = WC / 4, RPI = 64 / LPR;     // lanes per row, rows per instruction (TN = 3: 48 lanes at work)
+        constexpr int NP = 32 / RPI;
+        static_assert(32 % RPI == 0 && (size_t)NST * STAGE >= (size_t)NW * 32 * WS * 4, "the waves' blocks must fit the stage memory");
+        int32_t *yt = (int32_t *)lds + wave_u * 32 * WS;
+        const bool zp = ET == 0 && g.zp_in != nullptr, relu = g.act == 1, has_res = g.res_q != nullptr;
+        const int row_l = lane / LPR, unit = lane % LPR;
+        const bool active = row_l < RPI;
+        const int wcol = wn_u * WC + 4 * unit, col = n0 + wcol;
+        // the four columns' scale, bias and residual multiplier (zero beyond N: what is computed there is zero)
+        float sj[4], bj[4], rj[4];
+        int zlin[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool ok = col + e < g.N;
+            const int ce = ok ? col + e : g.N - 1;
+            bj[e] = g.bias ? g.bias[ce] : 0.0f;
+            sj[e] = g.sw_per_n ? sxv * g.sw[ce] : s;    // one fp32 multiply
+            if (zp && !CONV) zlin[e] = zmul * g.colsum[ce];
+            if (!ok) { bj[e] = 0.0f; sj[e] = 0.0f; zlin[e] = 0; }
+            rj[e] = ok ? rs : 0.0f;
+        }
+        const int rows = (int)(g.M - m0 < BM ? g.M - m0 : BM);                    // valid rows of the tile
+        // 16-byte stores through a buffer of the tile's rows (32-bit offsets)
+        const bool vec = (g.N & 3) == 0 && (g.ldy & 3) == 0 && ((uintptr_t)g.y & 15) == 0 && g.ldy < (1 << 20) && g.res_ld < (1 << 20);
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)(g.y + m0 * g.ldy), 0, vec && g.y ? (int)(rows * g.ldy * 4) : 0, 0x00020000);
+        const uint32_t ycol = active && col < g.N ? (uint32_t)col * 4u : kOob, ystep = (uint32_t)g.ldy * 4u;
+        const int32_t keep = relu || g.amax_pos ? -1 : 0x7fffffff;
+        __syncthreads();                                // every wave has read its last operands
+        // lane l of a 32x32 block holds column l % 32 and rows 8 * (r / 4) + 4 * (l / 32) + r % 4
+        auto put = [&](int i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) yt[(lrow + 8 * (r >> 2) + (r & 3)) * WS + j * 32 + lcol] = acc_bits(acc[i][j][r]);
+        };
+        auto get = [&](int p) { return *(const v4i *)&yt[(p * RPI + (active ? row_l : 0)) * WS + 4 * unit]; };
+        int32_t *zp_sum = (int32_t *)lds + NW * 32 * WS;         // affine codes: [16][BN], then a class per row (a launch
+        uint8_t *zp_class = (uint8_t *)(zp_sum + 16 * BN);       // that has them brings the LDS for it)
+        if (zp && CONV) {
+            // the sums of the weight codes of the tile's columns per border class, and the class of every row's pixel
+            for (int e = tid; e < 16 * BN; e += NT) {
+                const int cls = e / BN, c = n0 + e % BN;
+                zp_sum[e] = c < g.N ? zmul * g.colsum[(size_t)cls * g.N + c] : 0;
+            }
+            for (int e = tid; e < BM; e += NT) {
+                const uint32_t m = (uint32_t)(m0 + e), mrow = m / (uint32_t)g.W;
+                const int ow = (int)(m - mrow * (uint32_t)g.W), oh = (int)(mrow % (uint32_t)g.H);
+                zp_class[e] = (uint8_t)((oh == 0 ? 1 : 0) | (oh == g.H - 1 ? 2 : 0) | (ow == 0 ? 4 : 0) | (ow == g.W - 1 ? 8 : 0));
+            }
+            __syncthreads();
+        }
+        // the combinations that forward passes ask for, straight-line
+        auto fixed = [&](auto relu_c, auto track_c, auto res_c, auto qout_c, auto zp_c) {
+            constexpr bool RELU = decltype(relu_c)::value, TRACK = decltype(track_c)::value, RES = decltype(res_c)::value;
+            constexpr bool QOUT = decltype(qout_c)::value, ZP = decltype(zp_c)::value;
+            const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)(g.q_out + m0 * g.q_ld), 0, QOUT ? (int)(rows * g.q_ld) : 0, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)((const res_t *)g.res_q + m0 * g.res_ld), 0,
+                                                                                 RES ? (int)(rows * g.res_ld * (int)sizeof(res_t)) : 0, 0x00020000);
+            const uint32_t qcol = active && col < g.q_ld ? (uint32_t)col : kOob;
+            const uint32_t rcol = active && col < g.res_ld ? (uint32_t)col * (uint32_t)sizeof(res_t) : kOob;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row0 = (wm_u * TM + i) * 32 + row_l;   // the lane's first row within the tile
+                const int left = rows - row0;                    // valid rows from it on
+                // four residual values per lane and row, requested before anything is awaited
+                v4u rv[RES ? NP : 1];
+                if constexpr (RES) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) {
+                        const int off = (int)(rcol + (uint32_t)(row0 + p * RPI) * (uint32_t)(g.res_ld * (int)sizeof(res_t)));
+                        if constexpr (ET == 0) rv[p][0] = __builtin_amdgcn_raw_buffer_load_b32(rr, off, 0, 0);
+                        else if constexpr (ET == 1) {
+                            const auto t = __builtin_amdgcn_raw_buffer_load_b64(rr, off, 0, 0);
+                            rv[p][0] = t[0];
+                            rv[p][1] = t[1];
+                        } else rv[p] = __builtin_amdgcn_raw_buffer_load_b128(rr, off, 0, 0);
+                    }
+                }
+                put(i);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    v4i a = get(p);
+                    if constexpr (ZP) {
+                        if constexpr (CONV) {
+                            const v4i z = *(const v4i *)&zp_sum[zp_class[row0 + p * RPI] * BN + wcol];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) a[e] += z[e];
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) a[e] += zlin[e];
+                        }
+                    }
+                    v4u w;
+                    uint32_t codes = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float v = fmaf(ET == 0 ? (float)a[e] : __int_as_float(a[e]), sj[e], bj[e]);
+                        if constexpr (RES) {
+                            float x;
+                            if constexpr (ET == 0) x = (float)((int)(int8_t)(rv[p][0] >> (8 * e)) + (ZP ? rmul : 0));
+                            else if constexpr (ET == 1) x = (float)__builtin_bit_cast(_Float16, (uint16_t)(rv[p][e >> 1] >> (16 * (e & 1))));
+                            else x = __uint_as_float(rv[p][e]);
+                            v = v + x * rj[e];
+                        }
+                        if (RELU) v = v > 0.0f ? v : 0.0f;
+                        w[e] = __float_as_uint(v);
+                        if (QOUT) codes |= (col + e < g.N ? quant1(v, q_inv) : 0u) << (8 * e);   // pad columns are zero
+                        if (TRACK) {
+                            int32_t bits = (int32_t)w[e];
+                            if (!RELU) bits &= keep;
+                            bits = p * RPI < left ? bits : 0;
+                            amax = amax > bits ? amax : bits;
+                        }
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(w, ry, (int)(ycol + (uint32_t)(row0 + p * RPI) * ystep), 0, 0);
+                    if (QOUT) __builtin_amdgcn_raw_buffer_store_b32(codes, rq, (int)(qcol + (uint32_t)(row0 + p * RPI) * (uint32_t)g.q_ld), 0, 0);
+                }
+            }
+        };
+        // everything else: observed runs, rows that 16-byte stores cannot address, rare combinations
+        auto general = [&]() {
+            const bool acc16 = (g.N & 3) == 0 && ((uintptr_t)g.acc_out & 15) == 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row0 = (wm_u * TM + i) * 32 + row_l;   // the lane's first row within the tile
+                // the residual of the block's rows, requested before anything is awaited
+                int32_t rcode[ET == 0 ? NP : 1];
+                if constexpr (ET == 0) {
+                    if (has_res) {
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) {
+                            const bool ok = active && row0 + p * RPI < rows && col < g.res_ld;
+                            rcode[p] = *(const int32_t *)(g.res_q + (ok ? (m0 + row0 + p * RPI) * g.res_ld + col : 0));
+                        }
+                    }
+                }
+                put(i);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const int tr = row0 + p * RPI;
+                    const int64_t m = m0 + tr;
+                    const v4i a4 = get(p);
+                    int a[4] = {a4[0], a4[1], a4[2], a4[3]};
+                    if constexpr (ET == 0) {
+                        if (zp) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) a[e] += CONV ? zp_sum[zp_class[tr] * BN + wcol + e] : zlin[e];
+                        }
+                    }
+                    const bool in = active && tr < rows;
+                    if (g.acc_out && in) {              // observed runs: the raw sums
+                        int32_t *dst = g.acc_out + m * g.N + col;
+                        if (acc16 && col < g.N) *(v4i *)dst = v4i{a[0], a[1], a[2], a[3]};
+                        else
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (col + e < g.N) dst[e] = a[e];
+                    }
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaf(ET == 0 ? (float)a[e] : __int_as_float(a[e]), sj[e], bj[e]);
+                    if (has_res) {
+                        if constexpr (ET == 0) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = v[e] + (float)((int)(int8_t)(rcode[p] >> (8 * e)) + rmul) * rj[e];
+                        } else {
+                            const res_t *res = (const res_t *)g.res_q + (in && col < g.res_ld ? m * g.res_ld + col : 0);   // (rows are padded to whole units)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = v[e] + (float)res[e] * rj[e];
+                        }
+                    }
+                    v4u w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float vp = v[e] > 0.0f ? v[e] : 0.0f;
+                        v[e] = relu ? vp : v[e];
+                        w[e] = __float_as_uint(v[e]);
+                        const int32_t bits = in ? (int32_t)w[e] & keep : 0;
+                        amax = amax > bits ? amax : bits;
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(w, ry, (int)(ycol + (uint32_t)tr * ystep), 0, 0);   // (no extent unless vec)
+                    if (g.y && !vec && in) {
+                        float *dst = g.y + m * g.ldy + col;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col + e < g.N) dst[e] = v[e];
+                    }
+                    if (g.q_out && in && col < g.q_ld) {         // pad columns of the int8 output are zero
+                        uint32_t c4 = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) c4 |= (col + e < g.N ? quant1(v[e], q_inv) : 0u) << (8 * e);
+                        *(uint32_t *)(g.q_out + m * g.q_ld + col) = c4;
+                    }
+                }
+            }
+        };
+        using T = std::true_type;
+        using F = std::false_type;
+        const bool track = g.absmax_out != nullptr, q = g.q_out != nullptr;
+        const bool rare = !vec || g.acc_out || (track && (has_res || zp || q)) || (q && (!relu || has_res || zp)) || (has_res && !relu);
+        if (rare) general();
+        else if (zp) {
+            if constexpr (ET == 0) {
+                if (has_res) fixed(T{}, F{}, T{}, F{}, T{});
+                else if (relu) fixed(T{}, F{}, F{}, F{}, T{});
+                else fixed(F{}, F{}, F{}, F{}, T{});
+            }
+        } else if (has_res) fixed(T{}, F{}, T{}, F{}, F{});
+        else if (q) { if constexpr (ET == 0) fixed(T{}, F{}, F{}, T{}, F{}); }
+        else if (relu) {
+            if (track) fixed(T{}, T{}, F{}, F{}, F{}); else fixed(T{}, F{}, F{}, F{}, F{});
+        } else {
+            if (track) fixed(F{}, T{}, F{}, F{}, F{}); else fixed(F{}, F{}, F{}, F{}, F{});
+        }
     }
     if (g.absmax_out) {
         __shared__ uint32_t smw[NW];
@@ -578,15 +682,18 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     if (tiles > 0x3fffffffLL) return hipErrorInvalidValue;
     const int tpx = (int)((tiles + 7) / 8);
     const dim3 grid((unsigned)(tpx * 8)), block(64 * WM * WN);
-    constexpr size_t smem = (size_t)stages_for(BM, BN, BK) * (BM + BN) * BK;
+    constexpr size_t stages = (size_t)stages_for(BM, BN, BK) * (BM + BN) * BK;
+    // affine codes: weight-code sums and row classes behind the epilogue's block
+    constexpr size_t affine = ((size_t)WM * 32 * (BN + 8 * WN) + 16 * BN) * 4 + BM, largest = stages > affine ? stages : affine;
+    const size_t smem = g.zp_in ? largest : stages;
     hipError_t e;
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
-    if (g.conv3x3) {
+    if constexpr (!LNF && WM * WN == 4) if (g.conv3x3) {
         static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
         if (!set[dev]) {
             e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
             if (e != hipSuccess) return e;
             set[dev] = true;
         }
@@ -596,7 +703,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     static bool set[kMaxDevices] = {};
     if (!set[dev]) {
         e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
         if (e != hipSuccess) return e;
         set[dev] = true;
     }
@@ -973,27 +1080,23 @@ struct TileShape {
     int bm, bn, bk, resident, waves;
     double penalty;
 };
-constexpr int kNumShapes = 11;
+constexpr int kNumShapes = 8;
 static const TileShape kShapes[kNumShapes] = {
-    {256, 256, 64, 1, 4, 1.00},  {256, 192, 128, 1, 4, 1.03}, {256, 128, 64, 2, 4, 1.06}, {128, 192, 64, 2, 4, 1.10},
-    {128, 128, 64, 3, 4, 1.20},  {128, 128, 128, 2, 4, 1.22}, {128, 64, 64, 4, 4, 1.40},  {128, 64, 128, 3, 4, 1.38},
-    {256, 128, 128, 1, 4, 1.05}, {256, 256, 128, 1, 8, 1.00}, {256, 192, 128, 1, 8, 1.02},
+    {256, 128, 64, 2, 4, 1.06},  {128, 192, 64, 2, 4, 1.10}, {128, 128, 64, 3, 4, 1.20},  {128, 128, 128, 2, 4, 1.22},
+    {128, 64, 64, 4, 4, 1.40},   {128, 64, 128, 3, 4, 1.38}, {256, 256, 128, 1, 8, 1.00}, {256, 192, 128, 1, 8, 1.02},
 };
 
 static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 {
     switch (i) {
-    case 0: return launch_variant<256, 256, 2, 2, 64>(g, st);
-    case 1: return launch_variant<256, 192, 2, 2, 128>(g, st);
-    case 2: return launch_variant<256, 128, 2, 2, 64>(g, st);
-    case 3: return launch_variant<128, 192, 2, 2, 64>(g, st);
-    case 4: return launch_variant<128, 128, 2, 2, 64>(g, st);
-    case 5: return launch_variant<128, 128, 2, 2, 128>(g, st);
-    case 6: return launch_variant<128, 64, 2, 2, 64>(g, st);
-    case 7: return launch_variant<128, 64, 2, 2, 128>(g, st);
-    case 8: return launch_variant<256, 128, 2, 2, 128>(g, st);
-    case 9: return launch_variant<256, 256, 2, 4, 128>(g, st);
-    case 10: return launch_variant<256, 192, 4, 2, 128>(g, st);
+    case 0: return launch_variant<256, 128, 2, 2, 64>(g, st);
+    case 1: return launch_variant<128, 192, 2, 2, 64>(g, st);
+    case 2: return launch_variant<128, 128, 2, 2, 64>(g, st);
+    case 3: return launch_variant<128, 128, 2, 2, 128>(g, st);
+    case 4: return launch_variant<128, 64, 2, 2, 64>(g, st);
+    case 5: return launch_variant<128, 64, 2, 2, 128>(g, st);
+    case 6: return launch_variant<256, 256, 2, 4, 128>(g, st);
+    case 7: return launch_variant<256, 192, 4, 2, 128>(g, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1052,9 +1155,7 @@ hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
             // compute unit.  (With K = 768 they win by 5-10 % when timed alone, where the fp32 output stays in the
             // last-level cache, and lose as much inside an encoder layer, where it goes to HBM and the shapes
             // with two workgroups per compute unit hide more of the store behind the other workgroup's K loop.)
-            if (g.conv3x3 || g.kp < 2048 || tiles < compute_units()) continue;
-        } else if (sh.resident == 1 && g.kp < 2048) {
-            continue;
+            if (g.conv3x3 || g.kp < 2048 || tiles < compute_units() / 2) continue;
         }
         if (sh.bm * sh.bn > 128 * 128 && g.kp < 512) continue;     // store bound: many small workgroups in flight
         const int64_t slots = compute_units() * (int64_t)sh.resident;

@@ -54,3 +54,27 @@ def test_metric_block_and_slab_edges(eg, orc, b, types):
         want = orc.sp_loss(a_t.float().numpy(), a_r.float().numpy())
         got = eg.plasticity(a_t.cuda(), a_r.cuda()).item()
         assert abs(got - want) <= 1e-4 * abs(want) + 1e-12 * 4.0 / b, (b, D, types, got, want)
+
+
+# GEMM epilogue: rows and columns that end inside, at and just past a tile or a group of four columns, with and without a
+# residual, for the dynamic, static and affine paths (the parity tests hold the values to the oracle; here the observed
+# run, whose epilogue handles every element on its own, is the reference for the straight-line one).
+@pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "per_channel"])
+@pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 11, 12), (5, 68, 16, 13), (4, 130, 16, 16), (9, 64, 15, 17)])
+def test_conv_epilogue_edges(eg, orc, b, c, h, w, mode):
+    import gpu_common as gc
+    import synth_inputs as si
+    for wl in (si.make_basic_block(b=b, c=c, h=h, w=w, seed=5), si.make_bottleneck(b=b, c_in=2 * c, c_mid=c, h=h, w=w, seed=6)):
+        W = [gc.to_dev(t) for t in wl.weights]
+        B = [gc.to_dev(t) for t in wl.biases]
+        scales = torch.full((len(W),), 0.03, device="cuda") if mode == "static" else None
+        ref = eg.make_reference(wl.kind, wl.dims, W, B, scales, per_channel=mode == "per_channel",
+                                act_scheme=eg.ACT_AFFINE if mode == "affine" else eg.ACT_SYMMETRIC)
+        x = gc.to_dev(wl.x)
+        ws = eg.workspace(eg.workspace_bytes(ref.desc))
+        plain, seen = (torch.full((gc.a_ref_numel(wl) + 64,), 7.0, device="cuda") for _ in range(2))
+        taps, _bufs, _keep = eg.make_taps(ref, gc.tap_shapes(wl))
+        eg.ref_forward(ref, x, seen, ws, taps)
+        eg.ref_forward(ref, x, plain, ws)
+        assert torch.equal(plain, seen), (wl.name, mode)
+        assert bool((plain[-64:] == 7.0).all()), "written past the end"
