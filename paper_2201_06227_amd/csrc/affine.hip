@@ -31,15 +31,21 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
     if (!BF16 && ((uintptr_t)x & 15) == 0) {
         const float4 *x4 = (const float4 *)x;
         const int64_t n4 = n >> 2;
-        for (int64_t i = first; i < n4; i += stride) {
-            const float4 v = x4[i];
-            const float e[4] = {v.x, v.y, v.z, v.w};
+        // four loads in flight per thread (indices clamped: a value seen twice changes no extremum)
+        for (int64_t i = first; i < n4; i += 4 * stride) {
+            float4 v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                hi = fmaxf(hi, e[k]);
-                nlo = fmaxf(nlo, -e[k]);
-                const uint32_t a = abs_bits(e[k]);
-                worst = worst > a ? worst : a;
+            for (int j = 0; j < 4; ++j) v[j] = x4[i + j * stride < n4 ? i + j * stride : i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    hi = fmaxf(hi, e[k]);
+                    nlo = fmaxf(nlo, -e[k]);
+                    const uint32_t a = abs_bits(e[k]);
+                    worst = worst > a ? worst : a;
+                }
             }
         }
         for (int64_t i = (n4 << 2) + first; i < n; i += stride) {
@@ -77,8 +83,16 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
     }
 }
 
-// [n, c, hw] (channel planes; hw = 1: rows of a matrix) -> codes [n, hw, cp], 16 per thread and store
-template <bool BF16>
+// [n, c, hw] (channel planes; hw = 1: rows of a matrix) -> codes [n, hw, cp], 16 per store.  HBM-bound; what counts
+// is the bytes in flight per thread.  Three forms:
+//   kRows    fp32 rows of whole 16-byte units: four 16-byte loads make the 16 codes of a unit
+//            (12544 x 256: 12.9 us with a load per value, 5.4 now);
+//   kPlanes  fp32 planes of whole 16-byte units: sixteen 16-byte loads (4 pixels x 16 channels) make four units
+//            (64 x 1024 x 196: 23.3 -> 16.5 us);
+//   kAny     everything else: one load per value (lanes along the pixels, or along the units of a row).
+enum AffineForm { kAny = 0, kRows = 1, kPlanes = 2 };
+
+template <bool BF16, int FORM>
 __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__restrict__ x, int64_t n, int64_t c, int64_t hw,
                                                               int64_t cp, const uint32_t *__restrict__ partials, int nb,
                                                               int store_offset, uint8_t *__restrict__ q,
@@ -86,10 +100,19 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
                                                               uint32_t *__restrict__ flag)
 {
     uint32_t hb = 0, lb = 0;
-    for (int i = threadIdx.x; i < nb; i += 256) {
-        const uint32_t a = partials[2 * i], b = partials[2 * i + 1];
-        hb = hb > a ? hb : a;
-        lb = lb > b ? lb : b;
+    {
+        // all candidates requested together (repeats of the last one change nothing)
+        uint2 cand[kMinMaxBlocks / 256];
+#pragma unroll
+        for (int k = 0; k < kMinMaxBlocks / 256; ++k) {
+            const int i = (int)threadIdx.x + 256 * k;
+            cand[k] = ((const uint2 *)partials)[i < nb ? i : nb - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < kMinMaxBlocks / 256; ++k) {
+            hb = hb > cand[k].x ? hb : cand[k].x;
+            lb = lb > cand[k].y ? lb : cand[k].y;
+        }
     }
     hb = wave_max_u32(hb);
     lb = wave_max_u32(lb);
@@ -114,37 +137,79 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
         publish(scale, bad, scale_out, nullptr, flag);
         *zp_out = zp;
     }
+    auto code_of = [&](float v) {
+        int code = (int)rintf(__fmul_rn(v, inv)) + zp;
+        code = code < 0 ? 0 : (code > 255 ? 255 : code);
+        return (uint32_t)(code - store_offset) & 0xffu;
+    };
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t upr = cp >> 4;
+    if constexpr (FORM == kRows) {
+        const int64_t total = n * upr;
+        const bool narrow = total < (1LL << 32);
+        for (int64_t u = first; u < total; u += stride) {
+            const int64_t row = narrow ? (int64_t)((uint32_t)u / (uint32_t)upr) : u / upr, c0 = (u - row * upr) * 16;
+            const float4 *src = (const float4 *)((const float *)x + row * c);
+            float4 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = src[c0 + 4 * j < c ? (c0 >> 2) + j : 0];
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)                    // pad channels: the stored byte is zero
+                w[j] = c0 + 4 * j < c ? code_of(v[j].x) | code_of(v[j].y) << 8 | code_of(v[j].z) << 16 | code_of(v[j].w) << 24 : 0u;
+            *(uint4 *)(q + row * cp + c0) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        return;
+    } else if constexpr (FORM == kPlanes) {
+        const int64_t pg = hw >> 2, total = n * upr * pg;   // groups of four pixels
+        const bool narrow = total < (1LL << 32);
+        for (int64_t u = first; u < total; u += stride) {
+            const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)pg) : u / pg, p = (u - rest * pg) * 4;
+            const int64_t img = narrow ? (int64_t)((uint32_t)rest / (uint32_t)upr) : rest / upr, ch0 = (rest - img * upr) * 16;
+            const float *src = (const float *)x + (img * c + ch0) * hw + p;
+            float4 v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = *(const float4 *)(src + (ch0 + e < c ? e * hw : 0));
+            uint32_t w[4][4] = {};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const bool in = ch0 + e < c;               // pad channels: the stored byte is zero
+                const float f[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[k][e >> 2] |= (in ? code_of(f[k]) : 0u) << (8 * (e & 3));
+            }
+            uint8_t *dst = q + (img * hw + p) * cp + ch0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) *(uint4 *)(dst + k * cp) = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+        }
+        return;
+    }
     const int64_t total = n * hw * upr;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < total; u += (int64_t)gridDim.x * blockDim.x) {
+    const bool narrow = total < (1LL << 32);
+    for (int64_t u = first; u < total; u += stride) {
+        const int64_t per = hw == 1 ? upr : hw;
+        const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)per) : u / per, at = u - rest * per;
         int64_t img, p, unit;
         if (hw == 1) {
-            img = u / upr;
-            unit = u - img * upr;
+            img = rest;
+            unit = at;
             p = 0;
         } else {
-            p = u % hw;
-            const int64_t rest = u / hw;
-            unit = rest % upr;
-            img = rest / upr;
+            p = at;
+            img = narrow ? (int64_t)((uint32_t)rest / (uint32_t)upr) : rest / upr;
+            unit = rest - img * upr;
         }
-        union {
-            uint8_t b[16];
-            uint4 v;
-        } pk;
+        // unconditional loads (channel clamped, the surplus discarded): loads under a condition are awaited one by one
+        float v[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int64_t ch = unit * 16 + e;
-            int code = store_offset;                       // pad channels: the stored byte is zero
-            if (ch < c) {
-                const int64_t i = (img * c + ch) * hw + p;
-                const float v = BF16 ? bf16_to_f32(((const uint16_t *)x)[i]) : ((const float *)x)[i];
-                code = (int)rintf(__fmul_rn(v, inv)) + zp;
-                code = code < 0 ? 0 : (code > 255 ? 255 : code);
-            }
-            pk.b[e] = (uint8_t)(code - store_offset);
+            const int64_t ch = unit * 16 + e, i = (img * c + (ch < c ? ch : c - 1)) * hw + p;
+            v[e] = BF16 ? bf16_to_f32(((const uint16_t *)x)[i]) : ((const float *)x)[i];
         }
-        *(uint4 *)(q + ((img * hw + p) * cp + unit * 16)) = pk.v;
+        uint32_t w[4] = {};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e >> 2] |= (unit * 16 + e < c ? code_of(v[e]) : 0u) << (8 * (e & 3));
+        *(uint4 *)(q + ((img * hw + p) * cp + unit * 16)) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
@@ -207,15 +272,21 @@ hipError_t launch_quantize_affine(const void *x, egeria_dtype dt, int64_t n, int
                                   const uint32_t *partials, int nb, int store_offset, void *q, float *scale_out,
                                   int32_t *zp_out, uint32_t *flag, hipStream_t st)
 {
-    int64_t blocks = (n * hw * (cp >> 4) + 255) / 256;
+    // whole 16-byte units of fp32 take the wide forms; bf16, odd rows and planes, and other addresses the general one
+    const bool wide = dt == EGERIA_F32 && ((uintptr_t)x & 15) == 0;
+    const int form = wide && hw == 1 && (c & 3) == 0 ? kRows : (wide && hw > 1 && (hw & 3) == 0 ? kPlanes : kAny);
+    int64_t blocks = (n * hw * (cp >> 4) / (form == kPlanes ? 4 : 1) + 255) / 256;
     if (blocks < 1) blocks = 1;                            // scale and zero point are still written
     if (blocks > 8192) blocks = 8192;
     const dim3 grid((unsigned)blocks), block(256);
-    if (dt == EGERIA_BF16)
-        return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_affine_kernel<true>, grid, block, 0, st, x, n, c, hw, cp, partials, nb,
-                        store_offset, (uint8_t *)q, scale_out, zp_out, flag);
-    return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_affine_kernel<false>, grid, block, 0, st, x, n, c, hw, cp, partials, nb,
-                    store_offset, (uint8_t *)q, scale_out, zp_out, flag);
+    auto go = [&](auto kernel) {
+        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cp, partials, nb, store_offset,
+                        (uint8_t *)q, scale_out, zp_out, flag);
+    };
+    if (dt == EGERIA_BF16) return go(quantize_affine_kernel<true, kAny>);
+    if (form == kRows) return go(quantize_affine_kernel<false, kRows>);
+    if (form == kPlanes) return go(quantize_affine_kernel<false, kPlanes>);
+    return go(quantize_affine_kernel<false, kAny>);
 }
 
 hipError_t launch_colsum(const int8_t *w_q, int32_t out, int32_t taps, int32_t cp, int32_t *colsum, hipStream_t st)

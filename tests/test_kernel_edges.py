@@ -78,3 +78,23 @@ def test_conv_epilogue_edges(eg, orc, b, c, h, w, mode):
         eg.ref_forward(ref, x, plain, ws)
         assert torch.equal(plain, seen), (wl.name, mode)
         assert bool((plain[-64:] == 7.0).all()), "written past the end"
+
+
+# Operands made of whole 16-byte units (rows of 4 k values, planes of 4 k pixels) and of everything else; channel counts
+# with and without pad channels.
+@pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 4, 3), (2, 17, 7, 7), (5, 68, 2, 2), (300, 20, 1, 1)])
+def test_operand_layouts(eg, b, c, h, w):
+    import gpu_common as gc
+    import synth_inputs as si
+    from oracle import affine_oracle as ao
+    from test_affine import _gpu_affine
+    from test_float_ref import _gpu_float_forward
+    wl = si.make_basic_block(b=b, c=c, h=h, w=w, seed=12)
+    q, s, zp = ao.quantize(wl.x)
+    _, taps, _, _ = _gpu_affine(wl)
+    got = taps[0]["x_q"].astype(np.int16) + 128
+    assert taps[0]["x_scale"][0] == s and taps[0]["x_zp"][0] == zp
+    assert np.array_equal(got[:, :c], gc.nhwc(q).reshape(-1, c)) and not taps[0]["x_q"][:, c:].any()
+    for precision, kind in (("f16", np.float16), ("f32", np.float32)):
+        _, taps, _, _ = _gpu_float_forward(wl, precision)
+        assert np.array_equal(taps[0]["x"], gc.nhwc(wl.x.astype(kind).astype(np.float32)).reshape(-1, c)), precision
