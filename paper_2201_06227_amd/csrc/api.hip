@@ -598,7 +598,7 @@ egeria_status forward_float_bert_layer(const Fwd &f, int l, const float *cur, fl
     float *one = f.scale(0);
     int8_t *xq = f.qbuf(0);
     auto linear = [&](int li, const float *src, int32_t k, int32_t kb, int32_t n, float *y, bool tap_y) -> egeria_status {
-        EG_HIP(launch_cast_chlast(src, EGERIA_F32, M, k, 1, kb / es, et, xq, one, f.st));
+        if (src) EG_HIP(launch_cast_chlast(src, EGERIA_F32, M, k, 1, kb / es, et, xq, one, f.st));
         const egeria_tap *t = f.tap(li);
         if (t && t->x_q) EG_HIP(hipMemcpyAsync(t->x_q, xq, (size_t)(M * kb), hipMemcpyDeviceToDevice, f.st));
         return run_gemm(f, li, xq, kb, M, n, kb, false, 0, 0, 0, one, 0, nullptr, nullptr, 0, y, nullptr, false, tap_y);
@@ -609,9 +609,19 @@ egeria_status forward_float_bert_layer(const Fwd &f, int l, const float *cur, fl
     EG_HIP(launch_layernorm(cur, proj, M, Hd, nm ? nm[0].gamma : nullptr, nm ? nm[0].beta : nullptr, d->ln_eps, y1,
                             nullptr, f.st));
     EG_OK(linear(s0 + 2, y1, Hd, hb, F, ff, false));
-    EG_HIP(launch_gelu_exact(ff, M * (int64_t)F, ff, f.st));
-    EG_OK(f.copy_tap_y(s0 + 2, ff, (size_t)M * F * 4));
-    EG_OK(linear(s0 + 3, ff, F, fb, Hd, proj, true));
+    // unobserved runs need the GELU's output only as the next operand: written as such (float32 rows without pad
+    // columns are the operand itself)
+    if (!f.taps && et == EGERIA_REF_F16) {
+        EG_HIP(launch_gelu_f16_rows(ff, M, F, fb / es, xq, f.st));
+        EG_OK(linear(s0 + 3, nullptr, F, fb, Hd, proj, true));
+    } else if (!f.taps && fb == 4 * F) {
+        EG_HIP(launch_gelu_exact(ff, M * (int64_t)F, (float *)xq, f.st));
+        EG_OK(linear(s0 + 3, nullptr, F, fb, Hd, proj, true));
+    } else {
+        EG_HIP(launch_gelu_exact(ff, M * (int64_t)F, ff, f.st));
+        EG_OK(f.copy_tap_y(s0 + 2, ff, (size_t)M * F * 4));
+        EG_OK(linear(s0 + 3, ff, F, fb, Hd, proj, true));
+    }
     EG_HIP(launch_layernorm(y1, proj, M, Hd, nm ? nm[1].gamma : nullptr, nm ? nm[1].beta : nullptr, d->ln_eps, out,
                             nullptr, f.st));
     return EGERIA_OK;

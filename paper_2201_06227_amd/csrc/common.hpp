@@ -130,6 +130,9 @@ hipError_t launch_quantize_gelu_rows(const float *v, int64_t rows, int64_t cols,
                                      float *scale_out, uint32_t *flag, hipStream_t st);
 // y = gelu(v) evaluated in fp64, rounded once (observation points only).
 hipError_t launch_gelu_exact(const float *v, int64_t n, float *y, hipStream_t st);
+// float16(fp32(gelu(v))) of [rows, cols] into rows of ldh float16 values (a multiple of 8, zero pad columns); v and out
+// on 16-byte boundaries
+hipError_t launch_gelu_f16_rows(const float *v, int64_t rows, int64_t cols, int64_t ldh, void *out, hipStream_t st);
 
 // One-launch quantisation of a small tensor [nimg, c, hw] -> int8 [nimg, hw, cp]
 // (at most kSmallTensor values, dynamic scale only).

@@ -98,3 +98,27 @@ def test_operand_layouts(eg, b, c, h, w):
     for precision, kind in (("f16", np.float16), ("f32", np.float32)):
         _, taps, _, _ = _gpu_float_forward(wl, precision)
         assert np.array_equal(taps[0]["x"], gc.nhwc(wl.x.astype(kind).astype(np.float32)).reshape(-1, c)), precision
+
+
+# The operand of the second feed-forward layer written by the GELU's own pass (unobserved runs) against the plain
+# sequence (observed runs): rows of whole and of ragged units, pre-activations from the table's lower end to beyond its
+# upper one and many near zero, where most values take the fp64 form.
+@pytest.mark.parametrize("precision", ["f16", "f32"])
+@pytest.mark.parametrize("ffn,spread", [(64, 1.0), (68, 12.0), (97, 3.0), (328, 0.01), (1, 1.0)])
+def test_gelu_operand(eg, precision, ffn, spread):
+    import gpu_common as gc
+    import synth_inputs as si
+    wl = si.make_bert(b=3, s=19, hidden=64, heads=2, ffn=ffn, n_layers=2, seed=21, train_act_dtype="f32")
+    W = [gc.to_dev(w * (spread if i % 4 == 2 else 1.0)) for i, w in enumerate(wl.weights)]
+    B = [None if t is None else gc.to_dev(t) for t in wl.biases]
+    ref = eg.make_float_reference(wl.kind, wl.dims, W, B, {"f16": eg.REF_F16, "f32": eg.REF_F32}[precision])
+    ws = eg.workspace(eg.workspace_bytes(ref.desc))
+    x = gc.to_dev(wl.x)
+    plain, seen = (torch.full((gc.a_ref_numel(wl),), 7.0, device="cuda") for _ in range(2))
+    shapes = gc.tap_shapes(wl)
+    for t in shapes:
+        t["kp"] = t["kp"] * 4                              # room for rows of either precision
+    taps, _bufs, _keep = eg.make_taps(ref, shapes)
+    eg.ref_forward(ref, x, seen, ws, taps)
+    eg.ref_forward(ref, x, plain, ws)
+    assert torch.equal(plain, seen)
