@@ -307,9 +307,8 @@ def weight_table(weights: Sequence[torch.Tensor], w_q: Sequence[torch.Tensor], s
     rows, pc = [], 1 if per_channel else 0
     for i, (w, q, s) in enumerate(zip(weights, w_q, scales)):
         _dev(w)
-        shape = w.shape
-        kh, kw = (shape[2], shape[3]) if len(shape) == 4 else (1, 1)
-        rows.append((w.data_ptr(), _dt(w), shape[0], shape[1], kh, kw, q.data_ptr(), s.data_ptr(), pc, REF_INT8,
+        o, c, kh, kw = w.shape if w.dim() == 4 else (*w.shape, 1, 1)      # (any other rank does not unpack)
+        rows.append((w.data_ptr(), _dt(w), o, c, kh, kw, q.data_ptr(), s.data_ptr(), pc, REF_INT8,
                      None if colsums is None else colsums[i].data_ptr()))
     return (Weight * len(rows))(*rows)
 

@@ -172,3 +172,14 @@ def test_gelu_table_is_what_its_generator_writes():
     text, worst_abs, worst_rel = mod.table_text()
     assert text == open(os.path.join(ROOT, "paper_2201_06227_amd", "csrc", "gelu_table.inc")).read()
     assert worst_abs < 5e-8 and worst_rel < 2e-7
+
+
+@pytest.mark.parametrize("shape", [(8,), (2, 3, 4), (2, 3, 4, 5, 6)])
+def test_weight_table_refuses_other_ranks(eg, monkeypatch, shape):
+    import torch
+    monkeypatch.setattr(eg, "_dev", lambda t: t)
+    q, s = torch.zeros(16, dtype=torch.int8), torch.zeros(1)
+    tab = eg.weight_table([torch.zeros(4, 5), torch.zeros(6, 7, 3, 2)], [q, q], [s, s])
+    assert [(t.out, t.in_, t.kh, t.kw) for t in tab] == [(4, 5, 1, 1), (6, 7, 3, 2)]
+    with pytest.raises(ValueError):
+        eg.weight_table([torch.zeros(shape)], [q], [s])
