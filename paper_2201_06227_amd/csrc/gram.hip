@@ -159,15 +159,18 @@ struct Tile {
     static __device__ __forceinline__ int slot(int r, int u) { return u ^ ((r / (16 / kUnits)) % kUnits); }
 };
 
+// (fmax would turn the NaN of a non-finite activation into 0)
+__device__ __forceinline__ double not_below_zero(double v) { return v < 0.0 ? 0.0 : v; }
+
 // || g / max(|g|, 1e-12) - a / max(|a|, 1e-12) ||^2 for g = a + e from aa = |a|^2, gg = |g|^2, ae = a.e, ee = |e|^2
 __device__ __forceinline__ double row_share(double aa, double gg, double ae, double ee)
 {
     const double nr = sqrt(aa), nt = sqrt(gg);
     if (nr < 1e-12 || nt < 1e-12) {
         const double r = nr < 1e-12 ? 1e-12 : nr, t = nt < 1e-12 ? 1e-12 : nt;
-        return fmax(gg / (t * t) + aa / (r * r) - 2.0 * (aa + ae) / (t * r), 0.0);
+        return not_below_zero(gg / (t * t) + aa / (r * r) - 2.0 * (aa + ae) / (t * r));
     }
-    const double c = (aa + ae) / (nr * nt), s2 = fmax(aa * ee - ae * ae, 0.0) / (aa * gg);
+    const double c = (aa + ae) / (nr * nt), s2 = not_below_zero(aa * ee - ae * ae) / (aa * gg);
     return c > 0.0 ? 2.0 * s2 / (1.0 + c) : 2.0 - 2.0 * c;
 }
 

@@ -56,6 +56,20 @@ def test_metric_block_and_slab_edges(eg, orc, b, types):
         assert abs(got - want) <= 1e-4 * abs(want) + 1e-12 * 4.0 / b, (b, D, types, got, want)
 
 
+# A non-finite activation makes the score NaN, also where the other activation's rows are all zeros (their Gram rows have
+# no norm, which takes the other branch of a row's share).
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("b,D", [(5, 40), (32, 4096), (64, 3001), (100, 640)])
+def test_metric_non_finite(eg, b, D, value):
+    for which in (0, 1):
+        for kind in (torch.float32, torch.bfloat16):
+            for other in (0.0, 1.0):
+                pair = [torch.full((b, D), other, dtype=kind, device="cuda") for _ in range(2)]
+                pair[which] = torch.randn(b, D, device="cuda").to(kind)
+                pair[which][b // 2, D // 3] = value
+                assert np.isnan(eg.plasticity(*pair).item()), (which, kind, other)
+
+
 # GEMM epilogue: rows and columns that end inside, at and just past a tile or a group of four columns, with and without a
 # residual, for the dynamic, static and affine paths (the parity tests hold the values to the oracle; here the observed
 # run, whose epilogue handles every element on its own, is the reference for the straight-line one).
