@@ -68,8 +68,12 @@ def algorithmic_work(wl, cls, eg):
             D = d["height"] * d["width"] * d["c_out"]
         else:
             D = d["seq"] * d["hidden"]
-        for _ in range(d.get("n_layers", 1)):
-            out.append((2 * 2.0 * b * b * D, b * D * (tsz + 4.0)))       # two b x b x D Gram products
+        layers = d.get("n_layers", 1)
+        # beside the next layer's forward (the library's rule for deep stacks of large scores) a score is two launches
+        # of half the workgroups each
+        halves = 2 if layers >= 4 and b * D * (tsz + 4.0) >= 64.0e6 else 1
+        for _ in range(layers * halves):
+            out.append((2 * 2.0 * b * b * D / halves, b * D * (tsz + 4.0) / halves))   # two b x b x D Gram products
     elif cls == eg.KERNEL_GEMM:
         if wl.kind == si.KIND_FC_RELU:
             shapes = [(b, d["c_out"], d["c_in"], d["c_in"], 0)]
@@ -140,7 +144,7 @@ def hbm_class_bytes(wl, cls, eg):
     return 0.0
 
 
-KERNEL_SOURCES = {"gram_partial_kernel": "gram.hip", "gemm_i8_kernel": "gemm_i8.hip", "conv3x3_c16_fused_kernel": "gemm_i8.hip",
+KERNEL_SOURCES = {"gram_kernel": "gram.hip", "gemm_i8_kernel": "gemm_i8.hip", "conv3x3_c16_fused_kernel": "gemm_i8.hip",
                   "attention_fast_kernel": "bert.hip", "attention_split_kernel": "bert.hip", "attention_kernel": "bert.hip",
                   "layernorm_vec_kernel": "bert.hip"}
 
@@ -191,7 +195,7 @@ def roofline_for(wl, cls, durations_ms, eg, steps, cfg=None, force_mfma=False):
     work = algorithmic_work(wl, cls, eg)
     import synth_inputs as si
     small_conv = wl.kind == si.KIND_BASIC_BLOCK and wl.dims["c_in"] <= 16 and wl.dims["c_out"] <= 32
-    names = {eg.KERNEL_GRAM: "gram_partial_kernel",
+    names = {eg.KERNEL_GRAM: "gram_kernel",
              eg.KERNEL_GEMM: "conv3x3_c16_fused_kernel" if small_conv else "gemm_i8_kernel",
              eg.KERNEL_ATTENTION: "attention_split_kernel", eg.KERNEL_LAYERNORM: "layernorm_vec_kernel"}
     att_peak = PEAK_GRAM_TFLOPS
