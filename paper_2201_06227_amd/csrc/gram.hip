@@ -162,15 +162,18 @@ struct Tile {
 // (fmax would turn the NaN of a non-finite activation into 0)
 __device__ __forceinline__ double not_below_zero(double v) { return v < 0.0 ? 0.0 : v; }
 
-// || g / max(|g|, 1e-12) - a / max(|a|, 1e-12) ||^2 for g = a + e from aa = |a|^2, gg = |g|^2, ae = a.e, ee = |e|^2
-__device__ __forceinline__ double row_share(double aa, double gg, double ae, double ee)
+// || g / max(|g|, 1e-12) - a / max(|a|, 1e-12) ||^2 for g = a + e from aa = |a|^2, gg = |g|^2, ae = a.e, ee = |e|^2.
+// single: rows of one entry (b = 1), which are parallel or opposite; each of the four sums is rounded, so sin^2 of
+// the angle would come out as some 1e-16 instead of 0.
+__device__ __forceinline__ double row_share(double aa, double gg, double ae, double ee, bool single)
 {
     const double nr = sqrt(aa), nt = sqrt(gg);
     if (nr < 1e-12 || nt < 1e-12) {
         const double r = nr < 1e-12 ? 1e-12 : nr, t = nt < 1e-12 ? 1e-12 : nt;
         return not_below_zero(gg / (t * t) + aa / (r * r) - 2.0 * (aa + ae) / (t * r));
     }
-    const double c = (aa + ae) / (nr * nt), s2 = not_below_zero(aa * ee - ae * ae) / (aa * gg);
+    const double c = (aa + ae) / (nr * nt);
+    const double s2 = single ? 0.0 * c : not_below_zero(aa * ee - ae * ae) / (aa * gg);      // (0 * NaN stays NaN)
     return c > 0.0 ? 2.0 * s2 / (1.0 + c) : 2.0 - 2.0 * c;
 }
 
@@ -523,7 +526,7 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
         }
         __syncthreads();
         if (wave == 0) {
-            const double tot = wave_sum(lane < b ? row_share(share[4 * lane], share[4 * lane + 1], share[4 * lane + 2], share[4 * lane + 3]) : 0.0);
+            const double tot = wave_sum(lane < b ? row_share(share[4 * lane], share[4 * lane + 1], share[4 * lane + 2], share[4 * lane + 3], b == 1) : 0.0);
             if (lane == 0) *p_out = (float)(tot / ((double)b * (double)b));
         }
     }
@@ -609,7 +612,7 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
 #pragma unroll
             for (int m = 0; m < kFinSums; ++m)
                 q[m] += __hip_atomic_load(&sums[((size_t)t * parts + k) * kFinSums + m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        share = row_share(q[0], q[1], q[2], q[3]);
+        share = row_share(q[0], q[1], q[2], q[3], b == 1);
     }
     __syncthreads();                                              // sm is free
     share = wave_sum(share);

@@ -70,6 +70,18 @@ def test_metric_non_finite(eg, b, D, value):
                 assert np.isnan(eg.plasticity(*pair).item()), (which, kind, other)
 
 
+# A batch of one: both rows normalise to the same single entry, so the score is 0 exactly, whatever the sums round to.
+@pytest.mark.parametrize("types", ["f32 f32", "bf16 f32", "bf16 bf16"])
+@pytest.mark.parametrize("D", [1, 7, 100, 1000, 5003, 100000])
+def test_metric_batch_of_one(eg, D, types):
+    kinds = [torch.bfloat16 if k == "bf16" else torch.float32 for k in types.split()]
+    for seed in range(8):
+        g = torch.Generator().manual_seed(seed)
+        r = torch.randn(1, D, generator=g)
+        t = r * (1.0 + 0.1 * seed) + 0.01 * torch.randn(1, D, generator=g)
+        assert eg.plasticity(t.to(kinds[0]).cuda(), r.to(kinds[1]).cuda()).item() == 0.0, seed
+
+
 # GEMM epilogue: rows and columns that end inside, at and just past a tile or a group of four columns, with and without a
 # residual, for the dynamic, static and affine paths (the parity tests hold the values to the oracle; here the observed
 # run, whose epilogue handles every element on its own, is the reference for the straight-line one).
