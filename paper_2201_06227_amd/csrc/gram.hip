@@ -170,7 +170,9 @@ __device__ __forceinline__ double row_share(double aa, double gg, double ae, dou
     const double nr = sqrt(aa), nt = sqrt(gg);
     if (nr < 1e-12 || nt < 1e-12) {
         const double r = nr < 1e-12 ? 1e-12 : nr, t = nt < 1e-12 ? 1e-12 : nt;
-        return not_below_zero(gg / (t * t) + aa / (r * r) - 2.0 * (aa + ae) / (t * r));
+        // |a u + e / t|^2: the large parts of the two rows leave each other in u (0 where both norms are clamped)
+        const double u = (r - t) / (t * r);
+        return not_below_zero(aa * u * u + 2.0 * (ae * u) / t + ee / (t * t));
     }
     const double c = (aa + ae) / (nr * nt);
     const double s2 = single ? 0.0 * c : not_below_zero(aa * ee - ae * ae) / (aa * gg);      // (0 * NaN stays NaN)

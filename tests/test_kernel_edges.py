@@ -70,6 +70,19 @@ def test_metric_non_finite(eg, b, D, value):
                 assert np.isnan(eg.plasticity(*pair).item()), (which, kind, other)
 
 
+# Activations whose Gram rows have norms below the 1e-12 at which a norm is clamped: the score is the squared difference of
+# the rows over 1e-24, and must not be lost among the rows' own squares.  fp32 sums of at most 4099 terms: 1e-4 relative.
+@pytest.mark.parametrize("b,D", [(1, 16), (4, 16), (32, 100), (33, 64), (64, 4099), (100, 300)])
+def test_metric_tiny_activations(eg, orc, b, D):
+    rng = np.random.default_rng(b + D)
+    size = 2e-7 / np.sqrt(D * b)                                   # row norms of about 5e-14
+    a_r = (size * rng.uniform(0.5, 1.0, (b, D))).astype(np.float32)
+    a_t = (a_r * (1.0 + 1e-6 * rng.standard_normal((b, D)))).astype(np.float32)
+    want = orc.sp_loss(a_t, a_r)
+    got = eg.plasticity(torch.from_numpy(a_t).cuda(), torch.from_numpy(a_r).cuda()).item()
+    assert want > 0.0 and abs(got - want) <= 1e-4 * want, (got, want)
+
+
 # A batch of one: both rows normalise to the same single entry, so the score is 0 exactly, whatever the sums round to.
 @pytest.mark.parametrize("types", ["f32 f32", "bf16 f32", "bf16 bf16"])
 @pytest.mark.parametrize("D", [1, 7, 100, 1000, 5003, 100000])
