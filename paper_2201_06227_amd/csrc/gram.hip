@@ -46,7 +46,7 @@
 //   matrices.  They sum W and B over the chunks in fp64 and reduce their columns
 //   to the sums from which a row's norms and its share of the squared difference
 //   follow; the last workgroup to finish adds the shares in index order and writes P.
-// A problem of one chunk (b <= 64, D <= 1024) is finished by kernel 1 itself,
+// A small problem of one block (b <= 32, D <= 512) is finished by kernel 1 itself,
 // whose one workgroup has both matrices in LDS: one launch less.
 //   Results are bit-reproducible from call to call.
 #include "common.hpp"
@@ -64,8 +64,14 @@ constexpr int kGramWaves = 8;
 // LDS of a workgroup: the waves' stages, then the reduction (two blocks of eight waves, their sums) and, for a score
 // that the workgroup finishes itself, both matrices.  Kept near 72 KB: other streams' kernels share the CU.
 constexpr int kGramReduce = (2 * kGramWaves * 1024 + 2 * 32 * 33) * 4;
-constexpr int kGramFused = kGramReduce + 2 * 64 * 65 * 4;
-constexpr int kFusedSlabs = 64;          // slabs (of 16 features) up to which one workgroup does the whole score
+constexpr int kGramFused = kGramReduce + 2 * 32 * 33 * 4;
+// Slabs (of 16 features) up to which one workgroup does the whole score of at most 32 samples, where slabs are loaded
+// straight into LDS and where they are filled element by element (one per wave: every further one is a round trip of
+// its own).  Its waves take the slabs one after the other, which soon costs more than the finaliser's launch, us with /
+// without: b = 32, D = 256 9.4 / 11, 512 10.4 / 11, 770 12.3 / 11, 1024 12.8 / 11; bf16 T with odd D, D = 65 9.5 /
+// 11.5, 129 11.1 / 11.6, 257 12.9 / 11.5, 1001 23 / 11.5.  Two blocks of samples never pay (three products and their
+// sums over the waves in one workgroup): b = 33, D = 8 16.0 / 12.5; b = 64, D = 1024 28.7 / 13.6.
+constexpr int kFusedSlabs = 32, kFusedFillSlabs = 8;
 
 struct GramPlan {
     int nb;          // blocks of 32 samples
@@ -85,10 +91,9 @@ static GramPlan plan_gram(int32_t b, int64_t D)
     p.npair = p.nb <= 2 ? 1 : (p.nb == 3 ? 3 : 6);
     const int64_t nslab = (D + kSlab - 1) / kSlab;
     p.nslab = (int)nslab;
-    p.fused = p.nb <= 2 && nslab <= kFusedSlabs;
     // about one workgroup per CU (its LDS fills one), and at least one slab for every wave
     // (the pairs of a chunk share an XCD, so the CUs of an XCD bound the chunks dealt to it)
-    int64_t want = p.fused ? 1 : 8 * (compute_units() / 8 / p.npair);
+    int64_t want = 8 * (compute_units() / 8 / p.npair);
     const int64_t cap = (nslab + kGramWaves - 1) / kGramWaves;
     if (want > cap) want = cap;
     if (want < 1) want = 1;
@@ -449,7 +454,7 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     // 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.
     float *red = (float *)lds;                                   // [2][waves][16][64]: this block's, the next one's
     float *sum = red + 2 * kGramWaves * 1024;                    // [2][32][33], padded rows
-    float *fin = sum + 2 * 32 * 33;                              // fused: W and B, [2][64][65]
+    float *fin = sum + 2 * 32 * 33;                              // fused: W and B, [2][32][33]
     const size_t nelem = (size_t)b * b;
     float *dst = part + (size_t)chunk * 2 * nelem;
     __syncthreads();                                             // every wave has read its last slab
@@ -484,9 +489,8 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
                 const float a = sm[row * 33 + col], c = sm[col * 33 + row];
                 const float v = k != 1 && !TF && m == 0 ? a + c : a;    // a diagonal block of (T - R)(T + R)^T: plus its transpose
                 const int gr = 32 * rowb + row, gc = 32 * colb + col, tr = 32 * colb + row, tc = 32 * rowb + col;
-                if (p.fused) {
-                    fin[(m * 64 + gr) * 65 + gc] = v;
-                    if (k == 1) fin[(m * 64 + tr) * 65 + tc] = c;
+                if (KIND == 0 && p.fused) {
+                    fin[(m * 32 + row) * 33 + col] = v;
                 } else {
                     if (gr < b && gc < b) dst[(size_t)m * nelem + (size_t)gr * b + gc] = v;
                     if (k == 1 && tr < b && tc < b) dst[(size_t)m * nelem + (size_t)tr * b + tc] = c;
@@ -494,27 +498,26 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
             }
         }
     }
-    if constexpr (KIND < 2) {
+    if constexpr (KIND == 0) {
         if (!p.fused) return;
         // the whole score: a wave per row, the row's columns in its lanes, shares added in index order
         __syncthreads();
-        double *share = (double *)lds;                           // [64][4]
-        constexpr int RW = 32 * NBLK / kGramWaves;               // rows of a wave, side by side: their sums are chains of exchanges
+        double *share = (double *)lds;                           // [32][4]
+        constexpr int RW = 32 / kGramWaves;                      // rows of a wave, side by side: their sums are chains of exchanges
         double q[4][RW];
 #pragma unroll
         for (int k = 0; k < RW; ++k) {
             const int i = wave + kGramWaves * k;
             const bool in = i < b && lane < b;
-            const double a = in ? (double)fin[(64 + i) * 65 + (lane < b ? lane : 0)] : 0.0;
-            const double e = in ? 0.5 * (double)fin[i * 65 + (lane < b ? lane : 0)] : 0.0, g = a + e;
+            const double a = in ? (double)fin[(32 + i) * 33 + (lane < b ? lane : 0)] : 0.0;
+            const double e = in ? 0.5 * (double)fin[i * 33 + (lane < b ? lane : 0)] : 0.0, g = a + e;
             q[0][k] = a * a;
             q[1][k] = g * g;
             q[2][k] = a * e;
             q[3][k] = e * e;
         }
-        // (a block of 32 columns needs no exchange between the halves of the wave)
 #pragma unroll
-        for (int off = NBLK == 1 ? 16 : 32; off > 0; off >>= 1)
+        for (int off = 16; off > 0; off >>= 1)                   // (32 columns: no exchange between the halves of the wave)
 #pragma unroll
             for (int k = 0; k < RW; ++k)
 #pragma unroll
@@ -637,6 +640,11 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
     // straight into LDS: rows that start at 4-byte boundaries (what buffer loads need) and 32-bit byte offsets within
     // a block of samples
     p.direct = D * (tcode ? 2 : 4) % 4 == 0 && D * (rcode ? 2 : 4) % 4 == 0 && D < (1LL << 24) - 4096;
+    p.fused = p.nb == 1 && p.nslab <= (p.direct ? kFusedSlabs : kFusedFillSlabs);
+    if (p.fused) {
+        p.spc = p.nslab;
+        p.nsplit = p.turns = 1;
+    }
     // Beside another stream's work: the same chunks (the same bits) in two launches of half the workgroups.  The kernel
     // is bound by HBM either way, and one that sits on every CU keeps the other stream's workgroups waiting: 12-layer
     // stack of 64 x 256 tokens 6.73 -> 6.64 ms.

@@ -42,14 +42,14 @@ def test_per_channel_snapshot_row_lengths(eg, orc, dtype):
 
 
 # The metric: one block of samples, two, three, four (with ragged last ones), one workgroup doing the whole score (up to
-# 1024 features) and its first neighbour, whole slabs of 16 features and ragged ones, rows at 16-, 4- and 2-byte
-# boundaries.  Bar as in the parity tests: fp32 products and sums, quadratic in the difference.
+# 512 features, up to 128 where the rows are filled element by element) and its first neighbour, whole slabs of 16 features
+# and ragged ones, rows at 16-, 4- and 2-byte boundaries.  Bar as in the parity tests: fp32 products and sums, quadratic in the difference.
 @pytest.mark.parametrize("types", ["f32 f32", "bf16 f32", "f32 bf16", "bf16 bf16"])
 @pytest.mark.parametrize("b", [1, 5, 31, 32, 33, 64, 65, 96, 97, 128])
 def test_metric_block_and_slab_edges(eg, orc, b, types):
     import synth_inputs as si
     kinds = [torch.bfloat16 if k == "bf16" else torch.float32 for k in types.split()]
-    for D in (3, 16, 18, 129, 1024, 1025, 1040, 5003, 16388):
+    for D in (3, 16, 18, 127, 129, 512, 514, 1024, 1025, 1040, 5003, 16388):
         a_t, a_r = (torch.from_numpy(a).to(k) for a, k in zip(si.noisy_pair(b, D, seed=7 + b + D), kinds))
         want = orc.sp_loss(a_t.float().numpy(), a_r.float().numpy())
         got = eg.plasticity(a_t.cuda(), a_r.cuda()).item()
