@@ -353,6 +353,15 @@ __device__ __forceinline__ void load_to_lds_b128(v4i rsrc, uint32_t lds_base, ui
                  : "memory", "m0");
 }
 
+// the same from a 64-bit address of each lane's own
+__device__ __forceinline__ void load_to_lds_b128(const void *src, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_base), "v"(src)
+                 : "memory", "m0");
+}
+
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

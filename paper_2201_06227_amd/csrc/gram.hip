@@ -76,9 +76,9 @@ constexpr int kFusedSlabs = 32, kFusedFillSlabs = 8;
 struct GramPlan {
     int nb;          // blocks of 32 samples
     int npair;       // workgroups (pairs of blocks) per chunk
-    int nslab;       // slabs of 16 features in D
+    int64_t nslab;   // slabs of 16 features in D
+    int64_t spc;     // slabs per chunk
     int nsplit;      // chunks of D
-    int spc;         // slabs per chunk
     int turns;       // (chunks per XCD) x (pairs)
     int fused;       // one chunk, finished by its workgroup
     int direct;      // whole slabs are loaded straight into LDS (else element by element)
@@ -90,14 +90,14 @@ static GramPlan plan_gram(int32_t b, int64_t D)
     p.nb = (b + 31) / 32;
     p.npair = p.nb <= 2 ? 1 : (p.nb == 3 ? 3 : 6);
     const int64_t nslab = (D + kSlab - 1) / kSlab;
-    p.nslab = (int)nslab;
+    p.nslab = nslab;
     // about one workgroup per CU (its LDS fills one), and at least one slab for every wave
     // (the pairs of a chunk share an XCD, so the CUs of an XCD bound the chunks dealt to it)
     int64_t want = 8 * (compute_units() / 8 / p.npair);
     const int64_t cap = (nslab + kGramWaves - 1) / kGramWaves;
     if (want > cap) want = cap;
     if (want < 1) want = 1;
-    p.spc = (int)((nslab + want - 1) / want);
+    p.spc = (nslab + want - 1) / want;
     p.nsplit = (int)((nslab + p.spc - 1) / p.spc);
     p.turns = (p.nsplit + 7) / 8 * p.npair;
     return p;
@@ -186,7 +186,11 @@ __device__ __forceinline__ double row_share(double aa, double gg, double ae, dou
 
 // KIND 0: one block (b <= 32); 1: two blocks and all three block products of W and B (b <= 64); 2: two of three
 // or four blocks, the off-diagonal products and those of the first block's diagonal if the pair's turn says so.
-template <int KIND, int TDT, int RDT>
+// LONG: rows whose byte offsets within a block of samples do not fit the 31 bits of a buffer offset (2^24 features and
+// more).  Each lane then addresses its 16 bytes with 64 bits; samples beyond b and slabs past the chunk's end repeat valid
+// ones (rows beyond b only reach entries that are never stored, a slab past the end is not contracted).  Filled
+// element by element, a round trip per slab, 16 x 2^24 fp32 took 2150 us; this form takes 558, 3.9 TB/s.
+template <int KIND, int TDT, int RDT, bool LONG>
 __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__restrict__ at, const void *__restrict__ ar,
                                                                   int b, int64_t D, GramPlan p, int turn0, float *__restrict__ part,
                                                                   uint32_t *__restrict__ counter, float *__restrict__ p_out)
@@ -211,8 +215,9 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     const int bp = KIND == 2 ? (pair < p.nb ? pair : pair - p.nb) : 0;
     const int bq = KIND == 2 ? (pair < p.nb ? (pair + 1 == p.nb ? 0 : pair + 1) : bp + 2) : 1;
     const bool diag_p = KIND != 2 || pair < p.nb;
-    const int slab0 = chunk * p.spc;
-    const int slab1 = slab0 + p.spc < p.nslab ? slab0 + p.spc : p.nslab;
+    using slab_t = std::conditional_t<LONG, int64_t, int>;
+    const slab_t slab0 = (slab_t)(chunk * p.spc);
+    const slab_t slab1 = (slab_t)(slab0 + p.spc < p.nslab ? slab0 + p.spc : p.nslab);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -239,16 +244,21 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
         rt[k] = descriptor(at, 32 * (k == 0 ? bp : bq), TDT == 0 ? 4 : 2);
         rr[k] = descriptor(ar, 32 * (k == 0 ? bp : bq), RDT == 0 ? 4 : 2);
     }
-    auto load_tile = [&](auto dt_c, const v4i &rsrc, int blk, int slab, bool ok, uint32_t dst, int i) {
+    auto load_tile = [&](auto dt_c, const v4i &rsrc, const void *base, int blk, slab_t slab, bool ok, uint32_t dst, int i) {
         constexpr int DT = decltype(dt_c)::value;
         using T = Tile<DT>;
         const int row = lane / T::kUnits, unit = (lane % T::kUnits) ^ ((row / (16 / T::kUnits)) % T::kUnits);
         const int rl = i * T::kRowsPerLoad + row;
+        if constexpr (LONG) {
+            const int64_t r64 = 32 * blk + rl < b ? 32 * blk + rl : b - 1;
+            load_to_lds_b128((const char *)base + r64 * D * (DT == 0 ? 4 : 2) + (ok ? slab : slab0) * T::kRow + unit * 16, dst + i * 1024);
+            return;
+        }
         const uint32_t off = ok && 32 * blk + rl < b ? (uint32_t)rl * (uint32_t)(D * (DT == 0 ? 4 : 2)) + (uint32_t)(slab * T::kRow + unit * 16) : kOob;
         load_to_lds_b128(rsrc, dst + i * 1024, off);
     };
     // element by element, with zeros beyond b and D (the last slab of a ragged D; rows that 4-byte accesses cannot address)
-    auto fill_tile = [&](auto dt_c, const void *base, int blk, int slab, uint8_t *dst) {
+    auto fill_tile = [&](auto dt_c, const void *base, int blk, slab_t slab, uint8_t *dst) {
         constexpr int DT = decltype(dt_c)::value;
         using T = Tile<DT>;
 #pragma unroll
@@ -268,23 +278,23 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     };
     using ct = std::integral_constant<int, TDT>;
     using cr = std::integral_constant<int, RDT>;
-    const int last_direct = p.direct ? (int)(D / kSlab) : 0;     // slabs below this one are loaded straight into LDS
+    const slab_t last_direct = p.direct ? (slab_t)(D / kSlab) : 0;   // slabs below this one are loaded straight into LDS
     // request q of the NLD of a slab (a slab past the end: no traffic, zeros)
-    auto request_one = [&](int slab, int end, int q) {
+    auto request_one = [&](slab_t slab, slab_t end, int q) {
         constexpr int nt = NBLK * TT::kLoads;
         if (q < nt) {
             const int k = q / TT::kLoads;
-            load_tile(ct{}, rt[k], k == 0 ? bp : bq, slab, slab < end, stage0 + k * TT::kBytes, q % TT::kLoads);
+            load_tile(ct{}, rt[k], at, k == 0 ? bp : bq, slab, slab < end, stage0 + k * TT::kBytes, q % TT::kLoads);
         } else {
             const int k = (q - nt) / TR::kLoads;
-            load_tile(cr{}, rr[k], k == 0 ? bp : bq, slab, slab < end, stage0 + NBLK * TT::kBytes + k * TR::kBytes, (q - nt) % TR::kLoads);
+            load_tile(cr{}, rr[k], ar, k == 0 ? bp : bq, slab, slab < end, stage0 + NBLK * TT::kBytes + k * TR::kBytes, (q - nt) % TR::kLoads);
         }
     };
-    auto request = [&](int slab, int end) {
+    auto request = [&](slab_t slab, slab_t end) {
 #pragma unroll
         for (int q = 0; q < NLD; ++q) request_one(slab, end, q);
     };
-    auto fill = [&](int slab) {
+    auto fill = [&](slab_t slab) {
         uint8_t *dst = stage;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the slab before has been read
 #pragma unroll
@@ -378,9 +388,9 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
         };
         // slabs first, first + 8, ... of the chunk: neighbouring waves take neighbouring slabs, i.e. the two halves
         // of a cache line at about the same time
-        const int first = slab0 + wave;
-        const int end = slab1 < last_direct ? slab1 : last_direct;
-        const int n = first < end ? (end - first + kGramWaves - 1) / kGramWaves : 0;
+        const slab_t first = slab0 + wave;
+        const slab_t end = slab1 < last_direct ? slab1 : last_direct;
+        const slab_t n = first < end ? (end - first + kGramWaves - 1) / kGramWaves : 0;
         if (n > 0) {
             // the stage is free again as soon as its raw values are in registers: one slab in registers, the next landing
             // (two stages per wave, i.e. 128 KB in flight per CU instead of 64, made no difference)
@@ -392,13 +402,13 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
 #pragma unroll
             for (int k = 0; k < kPieces; ++k) split_r(cur, k, rp);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            int ahead = first + kGramWaves;
+            slab_t ahead = first + kGramWaves;
             request(ahead, end);
             // Two steps per slab: the products of B beside the splits of D and S, the products of W beside the split of the
             // next slab's R and the requests for the slab after.  The pieces and the requests are placed between the
             // matrix instructions one by one: left to itself the compiler puts all of one kind first, and the two waves
             // of a SIMD, which start together, wait for the same pipe; a burst of requests holds the wave up.
-            for (int i = 0; i < n; ++i) {
+            for (slab_t i = 0; i < n; ++i) {
                 Split8 d[NBLK], x[NBLK], rn[NBLK];
                 int m = 0;                                       // (a constant everywhere: the code is straight-line)
                 constexpr int perB = (2 * kPieces + mfB - 1) / mfB;
@@ -435,7 +445,7 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
         // slabs that are filled element by element
-        for (int slab = first + n * kGramWaves; slab < slab1; slab += kGramWaves) {
+        for (slab_t slab = first + n * kGramWaves; slab < slab1; slab += kGramWaves) {
             fill(slab);
             Raw cur;
             Split8 rp[NBLK], d[NBLK], x[NBLK];
@@ -629,7 +639,6 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
 hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r, egeria_dtype r_dt,
                              int32_t b, int64_t D, float *p_out, void *ws_part, hipStream_t st, bool beside)
 {
-    if (D > (int64_t)0x7fffffff * kSlab / 2) return hipErrorInvalidValue;        // 32-bit slab numbers
     GramPlan p = plan_gram(b, D);
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
@@ -637,9 +646,9 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
     double *sums = (double *)((char *)ws_part + off_sums());
     float *part = (float *)((char *)ws_part + off_partials(b));
     const int tcode = t_dt == EGERIA_BF16 ? 1 : 0, rcode = r_dt == EGERIA_BF16 ? 1 : 0;
-    // straight into LDS: rows that start at 4-byte boundaries (what buffer loads need) and 32-bit byte offsets within
-    // a block of samples
-    p.direct = D * (tcode ? 2 : 4) % 4 == 0 && D * (rcode ? 2 : 4) % 4 == 0 && D < (1LL << 24) - 4096;
+    // straight into LDS: rows that start at 4-byte boundaries, which is what loads with the LDS modifier need
+    p.direct = D * (tcode ? 2 : 4) % 4 == 0 && D * (rcode ? 2 : 4) % 4 == 0;
+    const bool long_rows = D >= (1LL << 24) - 4096;              // 32 rows of fp32 and a row's own offsets below 2^31 bytes
     p.fused = p.nb == 1 && p.nslab <= (p.direct ? kFusedSlabs : kFusedFillSlabs);
     if (p.fused) {
         p.spc = p.nslab;
@@ -652,27 +661,32 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
     const dim3 grid((unsigned)(width * 8)), block(64 * kGramWaves);
     const size_t smem = p.fused ? kGramFused : kGramReduce;      // (covers the stages: 8 KB per wave at most)
     hipError_t e = hipSuccess;
-#define EGERIA_GRAM(K, T, R)                                                                           \
+#define EGERIA_GRAM(K, T, R, L)                                                                         \
     do {                                                                                               \
         static bool attr_set[kMaxDevices] = {};                                                        \
         if (!attr_set[dev]) {                                                                          \
-            e = hipFuncSetAttribute((const void *)gram_kernel<K, T, R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGramFused); \
+            e = hipFuncSetAttribute((const void *)gram_kernel<K, T, R, L>, hipFuncAttributeMaxDynamicSharedMemorySize, kGramFused); \
             if (e != hipSuccess) return e;                                                             \
             attr_set[dev] = true;                                                                      \
         }                                                                                              \
         for (int l = 0; l < launches && e == hipSuccess; ++l)                                          \
-            e = launch_k(EGERIA_KERNEL_GRAM, gram_kernel<K, T, R>, grid, block, smem, st, a_t, a_r, (int)b, D, p, l * width, part, counter, p_out); \
+            e = launch_k(EGERIA_KERNEL_GRAM, gram_kernel<K, T, R, L>, grid, block, smem, st, a_t, a_r, (int)b, D, p, l * width, part, counter, p_out); \
     } while (0)
-#define EGERIA_GRAM_DT(K)                                                                              \
+#define EGERIA_GRAM_DT(K, L)                                                                           \
     do {                                                                                               \
-        if (!tcode && !rcode) EGERIA_GRAM(K, 0, 0);                                                    \
-        else if (tcode && !rcode) EGERIA_GRAM(K, 1, 0);                                                \
-        else if (!tcode && rcode) EGERIA_GRAM(K, 0, 1);                                                \
-        else EGERIA_GRAM(K, 1, 1);                                                                     \
+        if (!tcode && !rcode) EGERIA_GRAM(K, 0, 0, L);                                                 \
+        else if (tcode && !rcode) EGERIA_GRAM(K, 1, 0, L);                                             \
+        else if (!tcode && rcode) EGERIA_GRAM(K, 0, 1, L);                                             \
+        else EGERIA_GRAM(K, 1, 1, L);                                                                  \
     } while (0)
-    if (p.nb == 1) EGERIA_GRAM_DT(0);
-    else if (p.nb == 2) EGERIA_GRAM_DT(1);
-    else EGERIA_GRAM_DT(2);
+#define EGERIA_GRAM_LONG(K)                                                                            \
+    do {                                                                                               \
+        if (long_rows) EGERIA_GRAM_DT(K, true); else EGERIA_GRAM_DT(K, false);                         \
+    } while (0)
+    if (p.nb == 1) EGERIA_GRAM_LONG(0);
+    else if (p.nb == 2) EGERIA_GRAM_LONG(1);
+    else EGERIA_GRAM_LONG(2);
+#undef EGERIA_GRAM_LONG
 #undef EGERIA_GRAM_DT
 #undef EGERIA_GRAM
     if (e != hipSuccess || p.fused) return e;

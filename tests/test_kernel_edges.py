@@ -56,6 +56,39 @@ def test_metric_block_and_slab_edges(eg, orc, b, types):
         assert abs(got - want) <= 1e-4 * abs(want) + 1e-12 * 4.0 / b, (b, D, types, got, want)
 
 
+# Rows of 2^24 features and more, which are addressed with 64 bits: one, two and three blocks of samples, whole slabs and
+# ragged ones, rows at 16-, 8-, 4- and 2-byte boundaries, the last size below the line.  Reference in fp64 on the same values.
+@pytest.mark.parametrize("b,D,types", [(3, (1 << 24) - 4112, "f32 f32"), (3, (1 << 24) - 4096, "f32 f32"), (2, (1 << 24) + 1, "f32 f32"),
+                                       (5, (1 << 24) + 18, "bf16 f32"), (2, (1 << 24) + 1, "f32 bf16"), (33, 1 << 24, "bf16 bf16"),
+                                       (70, (1 << 24) + 16, "f32 f32")])
+def test_metric_long_rows(eg, b, D, types):
+    kinds = [torch.bfloat16 if k == "bf16" else torch.float32 for k in types.split()]
+    g = torch.Generator(device="cuda").manual_seed(b)
+    r = torch.randn(b, D, generator=g, device="cuda")
+    t = (r + 0.05 * torch.randn(b, D, generator=g, device="cuda")).to(kinds[0])
+    r = r.to(kinds[1])
+    grams = [torch.zeros(b, b, dtype=torch.float64, device="cuda") for _ in range(2)]
+    for k in range(0, D, 1 << 21):
+        for gram, a in zip(grams, (t, r)):
+            part = a[:, k:k + (1 << 21)].double()
+            gram += part @ part.t().contiguous()
+    want = (torch.nn.functional.normalize(grams[0]) - torch.nn.functional.normalize(grams[1])).square().sum().item() / (b * b)
+    got = eg.plasticity(t, r).item()
+    assert abs(got - want) <= 1e-4 * want, (got, want)
+
+
+# One row of more than 2^34 features: nothing but the last one is set, so the score is 1 if it is seen and 0 if not.
+def test_metric_longest_row(eg):
+    D = (1 << 34) + 40
+    if torch.cuda.mem_get_info()[0] < 5 * D:
+        pytest.skip("needs 80 GB of device memory")
+    t, r = (torch.zeros(1, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    t[0, -1] = 1.0
+    assert eg.plasticity(t, r).item() == 1.0
+    del t, r
+    torch.cuda.empty_cache()
+
+
 # A non-finite activation makes the score NaN, also where the other activation's rows are all zeros (their Gram rows have
 # no norm, which takes the other branch of a row's share).
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
