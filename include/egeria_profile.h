@@ -54,6 +54,13 @@ egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, i
  * exercise the certified kernels on small shapes. */
 double egeria_profile_attention_threshold(double min_flops);
 
+/* Host-only: the output tile (rows x cols) and the K bytes per step with which an int8 layer of M output rows (pixels,
+ * tokens, samples), N outputs and k_bytes bytes per weight row runs; conv3x3 != 0: a 3x3 convolution (k_bytes = 9 *
+ * egeria_padded(c_in)).  For tests that have to reach a certain tile.  3x3 convolutions with 16 input and at most 32 output
+ * channels have a kernel of their own (with affine codes the one described here).  M, N, k_bytes >= 1. */
+egeria_status egeria_profile_gemm_tile(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3, int32_t *rows, int32_t *cols,
+                                       int32_t *k_step);
+
 /* What the device delivers to kernels shaped like this library's: one small complete kernel per kind, run
  * twice (the second run is timed with events on `stream`).  ms_out: duration of that run; work_out: what it
  * did - operations (matrix instructions: 2 per multiply-add) or bytes (LDS, L2 -> LDS, copy: read + written).

@@ -104,7 +104,7 @@ EXPORTS = [
     "egeria_cache_bytes", "egeria_cache_init", "egeria_cache_put", "egeria_cache_get", "egeria_profile_pause",
     "egeria_refresh_eval", "egeria_plasticity_noalloc", "egeria_profile_attention",
     "egeria_quantize_affine", "egeria_quantize_affine_workspace_bytes", "egeria_microbench",
-    "egeria_profile_attention_threshold",
+    "egeria_profile_attention_threshold", "egeria_profile_gemm_tile",
 ]
 
 (KERNEL_NONE, KERNEL_ABSMAX, KERNEL_QUANTIZE, KERNEL_GEMM, KERNEL_GRAM, KERNEL_ATTENTION, KERNEL_LAYERNORM,
@@ -175,6 +175,8 @@ def lib():
     L.egeria_profile_attention.argtypes = [_vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp]
     L.egeria_profile_attention_threshold.restype = ctypes.c_double
     L.egeria_profile_attention_threshold.argtypes = [ctypes.c_double]
+    L.egeria_profile_gemm_tile.restype = ctypes.c_int
+    L.egeria_profile_gemm_tile.argtypes = [_i64, _i32, _i64, _i32] + [ctypes.POINTER(_i32)] * 3
     L.egeria_microbench.restype = ctypes.c_int
     L.egeria_microbench.argtypes = [_i32, _i32, _vp, _sz, ctypes.POINTER(ctypes.c_float),
                                     ctypes.POINTER(ctypes.c_double), _vp]
@@ -550,6 +552,14 @@ MICRO_KINDS = ["mfma_i32_32x32x32_i8", "mfma_f32_32x32x16_bf16", "mfma_f32_32x32
 def attention_threshold(min_flops: float = -1.0) -> float:
     """egeria_profile_attention_threshold: sets (if >= 0) and returns the previous threshold."""
     return float(lib().egeria_profile_attention_threshold(float(min_flops)))
+
+
+def gemm_tile(M: int, N: int, k_bytes: int, conv3x3: bool = False):
+    """egeria_profile_gemm_tile: (rows, cols, K bytes per step) of the tile an int8 layer of these sizes runs with."""
+    out = [_i32(0) for _ in range(3)]
+    _check(lib().egeria_profile_gemm_tile(M, N, k_bytes, 1 if conv3x3 else 0, *[ctypes.byref(v) for v in out]),
+           "egeria_profile_gemm_tile")
+    return tuple(v.value for v in out)
 
 
 def microbench(kind: int, iters: int, scratch: torch.Tensor):

@@ -1174,6 +1174,14 @@ double egeria_profile_attention_threshold(double min_flops)
     return old;
 }
 
+egeria_status egeria_profile_gemm_tile(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3, int32_t *rows, int32_t *cols,
+                                       int32_t *k_step)
+{
+    if (M < 1 || N < 1 || k_bytes < 1 || !rows || !cols || !k_step) return EGERIA_ERR_INVALID_ARG;
+    gemm_tile(M, N, k_bytes, conv3x3 != 0, rows, cols, k_step);
+    return EGERIA_OK;
+}
+
 const char *egeria_status_string(egeria_status s)
 {
     switch (s) {

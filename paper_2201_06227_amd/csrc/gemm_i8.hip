@@ -440,8 +440,8 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         static_assert(32 % RPI == 0 && (size_t)NST * STAGE >= (size_t)NW * 32 * WS * 4, "the waves' blocks must fit the stage memory");
         int32_t *yt = (int32_t *)lds + wave_u * 32 * WS;
         const bool zp = ET == 0 && g.zp_in != nullptr, relu = g.act == 1, has_res = g.res_q != nullptr;
-        const int row_l = lane / LPR, unit = lane % LPR;
-        const bool active = row_l < RPI;
+        const bool active = lane / LPR < RPI;
+        const int row_l = active ? lane / LPR : 0, unit = lane % LPR;   // (an idle lane reads what lanes of row 0 read, in bounds)
         const int wcol = wn_u * WC + 4 * unit, col = n0 + wcol;
         // the four columns' scale, bias and residual multiplier (zero beyond N: what is computed there is zero)
         float sj[4], bj[4], rj[4];
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
 #pragma unroll
                 for (int r = 0; r < 16; ++r) yt[(lrow + 8 * (r >> 2) + (r & 3)) * WS + j * 32 + lcol] = acc_bits(acc[i][j][r]);
         };
-        auto get = [&](int p) { return *(const v4i *)&yt[(p * RPI + (active ? row_l : 0)) * WS + 4 * unit]; };
+        auto get = [&](int p) { return *(const v4i *)&yt[(p * RPI + row_l) * WS + 4 * unit]; };
         int32_t *zp_sum = (int32_t *)lds + NW * 32 * WS;         // affine codes: [16][BN], then a class per row (a launch
         uint8_t *zp_class = (uint8_t *)(zp_sum + 16 * BN);       // that has them brings the LDS for it)
         if (zp && CONV) {
@@ -1109,6 +1109,44 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 // long, so for short K only shapes with two workgroups per CU are considered
 // (one is in its K loop while the other stores), and for very short K, where
 // the kernel is a stream of stores, only the small shapes.
+static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
+{
+    int best = 0;
+    double best_cost = 0.0;
+    for (int i = 0; i < kNumShapes; ++i) {
+        const TileShape &sh = kShapes[i];
+        const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * (int64_t)((N + sh.bn - 1) / sh.bn);
+        if (sh.waves == 8) {
+            // eight waves on one large tile with whole-line K steps: linear layers with a long K that fill every
+            // compute unit.  (With K = 768 they win by 5-10 % when timed alone, where the fp32 output stays in the
+            // last-level cache, and lose as much inside an encoder layer, where it goes to HBM and the shapes
+            // with two workgroups per compute unit hide more of the store behind the other workgroup's K loop.)
+            if (conv3x3 || kp < 2048 || tiles < compute_units() / 2) continue;
+        }
+        if (sh.bm * sh.bn > 128 * 128 && kp < 512) continue;       // store bound: many small workgroups in flight
+        const int64_t slots = compute_units() * (int64_t)sh.resident;
+        const int64_t rounds = (tiles + slots - 1) / slots;
+        double cost = (double)rounds * sh.resident * sh.bm * sh.bn * sh.penalty;
+        // K of a few steps: the kernel is a stream of fp32 stores, and the more workgroups a CU holds the
+        // better they overlap (12544 x 1024 x 256: 128x64 with four per CU 17 us, 128x128 with two 21 us)
+        if (kp < 512) cost *= 1.0 + 0.15 * (4 - sh.resident);
+        if (best_cost == 0.0 || cost < best_cost) {
+            best_cost = cost;
+            best = i;
+        }
+    }
+    return best;
+}
+
+// Output tile and K step of an int8 layer of these sizes, for tests that have to reach a certain shape.
+void gemm_tile(int64_t M, int32_t N, int64_t kp, bool conv3x3, int32_t *rows, int32_t *cols, int32_t *k_step)
+{
+    const TileShape narrow = {128, 32, 64, 0, 4, 0.0}, &sh = N <= 32 ? narrow : kShapes[choose_shape(M, N, kp, conv3x3)];
+    *rows = sh.bm;
+    *cols = sh.bn;
+    *k_step = sh.bk;
+}
+
 // The float16 / float32 reference precisions: three tile shapes, chosen by how
 // many tiles the output makes.
 template <int ET>
@@ -1145,31 +1183,7 @@ hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
         return launch_k(EGERIA_KERNEL_GEMM, conv3x3_c16_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g);
     }
     if (g.N <= 32) return launch_variant<128, 32, 4, 1, 64>(g, st);
-    int best = 0;
-    double best_cost = 0.0;
-    for (int i = 0; i < kNumShapes; ++i) {
-        const TileShape &sh = kShapes[i];
-        const int64_t tiles = ((g.M + sh.bm - 1) / sh.bm) * (int64_t)((g.N + sh.bn - 1) / sh.bn);
-        if (sh.waves == 8) {
-            // eight waves on one large tile with whole-line K steps: linear layers with a long K that fill every
-            // compute unit.  (With K = 768 they win by 5-10 % when timed alone, where the fp32 output stays in the
-            // last-level cache, and lose as much inside an encoder layer, where it goes to HBM and the shapes
-            // with two workgroups per compute unit hide more of the store behind the other workgroup's K loop.)
-            if (g.conv3x3 || g.kp < 2048 || tiles < compute_units() / 2) continue;
-        }
-        if (sh.bm * sh.bn > 128 * 128 && g.kp < 512) continue;     // store bound: many small workgroups in flight
-        const int64_t slots = compute_units() * (int64_t)sh.resident;
-        const int64_t rounds = (tiles + slots - 1) / slots;
-        double cost = (double)rounds * sh.resident * sh.bm * sh.bn * sh.penalty;
-        // K of a few steps: the kernel is a stream of fp32 stores, and the more workgroups a CU holds the
-        // better they overlap (12544 x 1024 x 256: 128x64 with four per CU 17 us, 128x128 with two 21 us)
-        if (g.kp < 512) cost *= 1.0 + 0.15 * (4 - sh.resident);
-        if (best_cost == 0.0 || cost < best_cost) {
-            best_cost = cost;
-            best = i;
-        }
-    }
-    return launch_shape(best, g, st);
+    return launch_shape(choose_shape(g.M, g.N, g.kp, g.conv3x3), g, st);
 }
 
 }  // namespace egeria

@@ -183,3 +183,13 @@ def test_weight_table_refuses_other_ranks(eg, monkeypatch, shape):
     assert [(t.out, t.in_, t.kh, t.kw) for t in tab] == [(4, 5, 1, 1), (6, 7, 3, 2)]
     with pytest.raises(ValueError):
         eg.weight_table([torch.zeros(shape)], [q], [s])
+
+
+def test_tile_query(eg):
+    assert eg.gemm_tile(1000, 20, 112)[:2] == (128, 32)
+    for M, N, k, conv in ((130, 36, 64, False), (4728, 2304, 768, False), (12544, 256, 2304, True), (16384, 768, 3072, False)):
+        rows, cols, step = eg.gemm_tile(M, N, k, conv)
+        assert rows in (128, 256) and cols in (64, 128, 192, 256) and step in (64, 128)
+    for bad in ((0, 1, 16), (1, 0, 16), (1, 1, 0)):
+        with pytest.raises(eg.EgeriaError):
+            eg.gemm_tile(*bad)

@@ -152,6 +152,20 @@ def test_conv_epilogue_edges(eg, orc, b, c, h, w, mode):
         assert bool((plain[-64:] == 7.0).all()), "written past the end"
 
 
+# Affine 3x3 layers on 128x192 tiles, whose wave blocks of 96 columns leave lanes idle: the classes of border pixels are
+# looked up per row of the tile.  Columns in whole groups of four and ragged.
+@pytest.mark.parametrize("c", [132, 130])
+def test_affine_conv_on_wide_tiles(eg, c):
+    import gpu_common as gc
+    import synth_inputs as si
+    from oracle import affine_oracle as ao
+    from test_affine import _gpu_affine
+    wl = si.make_basic_block(b=10, c=c, h=71, w=72, seed=8)
+    assert eg.gemm_tile(10 * 71 * 72, c, 9 * eg.padded(c), True)[:2] == (128, 192)
+    got, _, _, _ = _gpu_affine(wl, with_taps=False)
+    assert np.array_equal(got.reshape(-1, c), gc.nhwc(ao.ref_forward(wl)["a_ref"]))
+
+
 # Operands made of whole 16-byte units (rows of 4 k values, planes of 4 k pixels) and of everything else; channel counts
 # with and without pad channels.
 @pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 4, 3), (2, 17, 7, 7), (5, 68, 2, 2), (300, 20, 1, 1)])
