@@ -689,16 +689,20 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     hipError_t e;
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
-    if constexpr (!LNF && WM * WN == 4) if (g.conv3x3) {
-        static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
-        if (!set[dev]) {
-            e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
-            if (e != hipSuccess) return e;
-            set[dev] = true;
+    if (g.conv3x3) {
+        if constexpr (LNF || WM * WN != 4) {
+            return hipErrorInvalidValue;                         // shapes for linear layers only
+        } else {
+            static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
+            if (!set[dev]) {
+                e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
+                if (e != hipSuccess) return e;
+                set[dev] = true;
+            }
+            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>, grid, block, smem, st, g,
+                            (int)tiles, tpx);
         }
-        return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>, grid, block, smem, st, g,
-                        (int)tiles, tpx);
     }
     static bool set[kMaxDevices] = {};
     if (!set[dev]) {
