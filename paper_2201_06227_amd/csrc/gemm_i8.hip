@@ -1121,11 +1121,14 @@ static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
         const TileShape &sh = kShapes[i];
         const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * (int64_t)((N + sh.bn - 1) / sh.bn);
         if (sh.waves == 8) {
-            // eight waves on one large tile with whole-line K steps: linear layers with a long K that fill every
-            // compute unit.  (With K = 768 they win by 5-10 % when timed alone, where the fp32 output stays in the
-            // last-level cache, and lose as much inside an encoder layer, where it goes to HBM and the shapes
-            // with two workgroups per compute unit hide more of the store behind the other workgroup's K loop.)
-            if (conv3x3 || kp < 2048 || tiles < compute_units() / 2) continue;
+            // eight waves on one large tile with whole-line K steps: linear layers with a long K.  (With K = 768 they win
+            // by 5-10 % when timed alone, where the fp32 output stays in the last-level cache, and lose as much
+            // inside an encoder layer, where it goes to HBM and the shapes with two workgroups per compute unit
+            // hide more of the store behind the other workgroup's K loop.)  One tile of 256x192 per compute unit, or as
+            // much work on fewer compute units: an encoder layer whose second feed-forward layer makes fewer tiles, us
+            // with the large tile / with 128x192 or 256x128: 256x192, 176 tiles 464 / 454, 192 485 / 476, 224 496 / 494,
+            // 240 521 / 520; 256x256, 200 tiles 619 / 616, 204 663 / 665, 224 882 / 910, 240 727 / 734, 252 753 / 760.
+            if (conv3x3 || kp < 2048 || tiles * sh.bm * sh.bn < (int64_t)compute_units() * 256 * 192) continue;
         }
         if (sh.bm * sh.bn > 128 * 128 && kp < 512) continue;       // store bound: many small workgroups in flight
         const int64_t slots = compute_units() * (int64_t)sh.resident;
