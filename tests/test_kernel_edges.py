@@ -128,12 +128,75 @@ def test_metric_batch_of_one(eg, D, types):
         assert eg.plasticity(t.to(kinds[0]).cuda(), r.to(kinds[1]).cuda()).item() == 0.0, seed
 
 
-# GEMM epilogue: rows and columns that end inside, at and just past a tile or a group of four columns, with and without a
-# residual, for the dynamic, static and affine paths (the parity tests hold the values to the oracle; here the observed
-# run, whose epilogue handles every element on its own, is the reference for the straight-line one).
+# Every output tile of the int8 GEMM with rows and columns that end inside it (the tile is asked for, so that a case
+# cannot come to run on another one), against the CPU oracle: fully connected layers (columns in whole groups of four
+# and ragged), with symmetric and affine codes.
+LINEAR_TILES = [((128, 32, 64), 1000, 20, 100), ((128, 64, 128), 257, 48, 100), ((128, 64, 64), 49805, 68, 64),
+                ((128, 128, 64), 44382, 140, 64), ((128, 128, 128), 49294, 68, 520), ((128, 192, 64), 43978, 132, 512),
+                ((256, 128, 64), 49395, 196, 512), ((256, 192, 128), 16240, 580, 2048), ((256, 256, 128), 16426, 652, 2048)]
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "affine"])
+@pytest.mark.parametrize("ragged", [0, 3])
+@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES, ids=["x".join(map(str, t[0])) for t in LINEAR_TILES])
+def test_linear_tiles_at_edges(eg, orc, tile, M, N, K, ragged, mode):
+    import gpu_common as gc
+    import synth_inputs as si
+    from oracle import affine_oracle as ao
+    from test_affine import _gpu_affine
+    N += ragged
+    assert eg.gemm_tile(M, N, eg.padded(K)) == tile
+    wl = si.make_fc(b=M, k=K, n=N, seed=9)
+    wl.biases[0] = np.linspace(-1.0, 1.0, N).astype(np.float32)
+    if mode == "affine":
+        got, want = _gpu_affine(wl, with_taps=False)[0], ao.ref_forward(wl)["a_ref"]
+    else:
+        got, want = gc.run_forward(wl, with_taps=False)[0], orc.ref_forward(wl)["a_ref"]
+    assert np.array_equal(got.reshape(M, N), want)
+
+
+# The same for 3x3 convolutions (whose affine codes look up the class of a border pixel per row of the tile): the block's first layer writes the maximum (dynamic), int8 codes (static scales) or fp32
+# for affine codes, its second one adds the skip connection.
+CONV_TILES = [((128, 64, 128), 1, 44, 15, 15), ((128, 64, 64), 11, 132, 54, 56), ((128, 128, 128), 12, 68, 64, 65),
+              ((128, 128, 64), 16, 68, 64, 65), ((128, 192, 64), 11, 132, 63, 64), ((256, 128, 64), 12, 196, 64, 65)]
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "affine ragged"])
+@pytest.mark.parametrize("tile,b,c,h,w", CONV_TILES, ids=["x".join(map(str, t[0])) for t in CONV_TILES])
+def test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode):
+    import gpu_common as gc
+    import synth_inputs as si
+    from oracle import affine_oracle as ao
+    from test_affine import _gpu_affine
+    c -= 2 if "ragged" in mode else 0
+    assert eg.gemm_tile(b * h * w, c, 9 * eg.padded(c), True) == tile
+    wl = si.make_basic_block(b=b, c=c, h=h, w=w, seed=10)
+    if "affine" in mode:
+        got, want = _gpu_affine(wl, with_taps=False)[0], ao.ref_forward(wl)["a_ref"]
+    else:
+        scales = np.array([0.03, 0.02], np.float32) if mode == "static" else None
+        got, want = gc.run_forward(wl, with_taps=False, act_scales=scales)[0], orc.ref_forward(wl, act_scales=scales)["a_ref"]
+    assert np.array_equal(got.reshape(-1, c), gc.nhwc(want))
+
+
+# ... and for the layers of an encoder (no activation, with and without the maximum) at a ragged number of tokens.
+def test_encoder_tiles_at_edges(eg, orc):
+    import gpu_common as gc
+    import synth_inputs as si
+    M = 24 * 197
+    assert [eg.gemm_tile(M, n, k)[:2] for n, k in ((2304, 768), (3072, 768), (768, 3072))] == [(128, 192), (256, 128), (128, 64)]
+    wl = si.make_bert(b=24, s=197, seed=11, train_act_dtype="f32")
+    got = gc.run_forward(wl, with_taps=False)[0]
+    gc.assert_within_ulp(got, orc.ref_forward(wl)["a_ref"][0], 1, "encoder layer")
+
+
+# GEMM epilogue of small modules: rows and columns that end inside, at and just past a tile or a group of four columns, with
+# and without a residual, for the dynamic, static, per-channel and affine paths.  The parity tests hold observed runs to the
+# oracle; here the observed run, which takes the general form of the epilogue, is the reference for the straight-line one.
+# (All of these run on 128x64 tiles; the others are above.)
 @pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "per_channel"])
 @pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 11, 12), (5, 68, 16, 13), (4, 130, 16, 16), (9, 64, 15, 17)])
-def test_conv_epilogue_edges(eg, orc, b, c, h, w, mode):
+def test_conv_epilogue_edges(eg, b, c, h, w, mode):
     import gpu_common as gc
     import synth_inputs as si
     for wl in (si.make_basic_block(b=b, c=c, h=h, w=w, seed=5), si.make_bottleneck(b=b, c_in=2 * c, c_mid=c, h=h, w=w, seed=6)):
@@ -150,20 +213,6 @@ def test_conv_epilogue_edges(eg, orc, b, c, h, w, mode):
         eg.ref_forward(ref, x, plain, ws)
         assert torch.equal(plain, seen), (wl.name, mode)
         assert bool((plain[-64:] == 7.0).all()), "written past the end"
-
-
-# Affine 3x3 layers on 128x192 tiles, whose wave blocks of 96 columns leave lanes idle: the classes of border pixels are
-# looked up per row of the tile.  Columns in whole groups of four and ragged.
-@pytest.mark.parametrize("c", [132, 130])
-def test_affine_conv_on_wide_tiles(eg, c):
-    import gpu_common as gc
-    import synth_inputs as si
-    from oracle import affine_oracle as ao
-    from test_affine import _gpu_affine
-    wl = si.make_basic_block(b=10, c=c, h=71, w=72, seed=8)
-    assert eg.gemm_tile(10 * 71 * 72, c, 9 * eg.padded(c), True)[:2] == (128, 192)
-    got, _, _, _ = _gpu_affine(wl, with_taps=False)
-    assert np.array_equal(got.reshape(-1, c), gc.nhwc(ao.ref_forward(wl)["a_ref"]))
 
 
 # Operands made of whole 16-byte units (rows of 4 k values, planes of 4 k pixels) and of everything else; channel counts
