@@ -340,6 +340,15 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
+// Between LDS writes of a wave and reads of what its other lanes have written (or the other way round): the wave's LDS
+// traffic is in order, so nothing is awaited; the compiler, which reasons about one lane, must not move either across.
+__device__ __forceinline__ void wave_lds_turn()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes
 // LDS bytes [lds_base + 16 l, lds_base + 16 l + 16) with what it reads at byte
 // offset voff of the buffer (zeros if voff is out of range).  Written as an

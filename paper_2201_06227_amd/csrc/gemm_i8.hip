@@ -465,10 +465,12 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         __syncthreads();                                // every wave has read its last operands
         // lane l of a 32x32 block holds column l % 32 and rows 8 * (r / 4) + 4 * (l / 32) + r % 4
         auto put = [&](int i) {
+            if (i > 0) wave_lds_turn();                 // the block before has been read
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) yt[(lrow + 8 * (r >> 2) + (r & 3)) * WS + j * 32 + lcol] = acc_bits(acc[i][j][r]);
+            wave_lds_turn();
         };
         auto get = [&](int p) { return *(const v4i *)&yt[(p * RPI + row_l) * WS + 4 * unit]; };
         int32_t *zp_sum = (int32_t *)lds + NW * 32 * WS;         // affine codes: [16][BN], then a class per row (a launch

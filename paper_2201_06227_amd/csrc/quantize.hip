@@ -667,7 +667,7 @@ __device__ __forceinline__ void quantize_channel(const WeightJob &jb, int oc, ui
     const uint32_t magic = (uint32_t)(0x100000000ull / (uint32_t)jb.hw) + 1u;   // k / hw = mulhi(k, magic) for k * hw < 2^32
     if (!direct && jb.cp != jb.c) {
         for (int o = lane * 16; o < jb.hw * jb.cp; o += 1024) *(uint4 *)(ldsrow + o) = make_uint4(0, 0, 0, 0);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_turn();
     }
     auto emit = [&](const Unit &x, int u) {
         if (direct) {
@@ -697,7 +697,7 @@ __device__ __forceinline__ void quantize_channel(const WeightJob &jb, int oc, ui
     if (direct) {
         for (int c = jb.c + 4 * lane; c < jb.cp; c += 256) *(uint32_t *)(q + c) = 0u;   // pad bytes (jb.c is a multiple of 4)
     } else {
-        __builtin_amdgcn_wave_barrier();                          // the wave's own LDS traffic is in order
+        wave_lds_turn();
         for (int o = lane * 16; o < jb.hw * jb.cp; o += 1024) *(uint4 *)(q + o) = *(const uint4 *)(ldsrow + o);
     }
 }
