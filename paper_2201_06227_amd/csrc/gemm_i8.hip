@@ -35,19 +35,9 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // well.  The eight-wave shapes take whole lines, two stages of them, and a
 // tile large enough that one workgroup per compute unit keeps two waves on
 // every SIMD.
-// LDS stages of a tile shape: one being read, the others being filled.
-constexpr int stages_for(int bm, int bn, int bk)
-{
-    const int stage = (bm + bn) * bk;
-    if (bk == 64) {
-        if (bm == 64 && bn == 768) return 3;           // the row-owning tile: three stages fill the 160 KB exactly
-        if (bm * bn < 256 * 192) return 3;
-        const int fit = 150 * 1024 / stage;
-        return fit > 6 ? 6 : fit;
-    }
-    if (3 * stage > 150 * 1024) return 2;
-    return 2 * stage <= 80 * 1024 ? 2 : 3;
-}
+// LDS stages: one being read, the others being filled.  (Three 64-byte stages of the row-owning 64x768 tile fill the 160 KB
+// exactly; of 128-byte steps two stages bring as many bytes ahead.)
+constexpr int stages_for(int bk) { return bk == 64 ? 3 : 2; }
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -125,7 +115,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     constexpr int A_CH = BM / kRowsPerChunk, B_CH = BN / kRowsPerChunk; // 1-KiB chunks per K step
     constexpr int A_IT = (A_CH + NW - 1) / NW, B_IT = (B_CH + NW - 1) / NW;         // chunks per wave
     constexpr int STAGE = (BM + BN) * kBK;
-    constexpr int NST = stages_for(BM, BN, BK);
+    constexpr int NST = stages_for(BK);
     constexpr int NLD = A_IT + B_IT;                                    // loads per wave and K step
     static_assert((NST - 2) * NLD < 64, "outstanding loads must fit the wait counter");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [NST][BM + BN][BK]
@@ -336,14 +326,6 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         mfma_all(fa1, fb1);
         hint();
         st = st1;
-        if (TM * TN == 16) {
-            // 256 accumulators per lane: name the accumulation registers as their home, or the
-            // allocator splits them between the two register files and spills inside the loop
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
-        }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the zero-filled K steps past the end
 
@@ -715,7 +697,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     if (tiles > 0x3fffffffLL) return hipErrorInvalidValue;
     const int tpx = (int)((tiles + 7) / 8);
     const dim3 grid((unsigned)(tpx * 8)), block(64 * WM * WN);
-    constexpr size_t stages = (size_t)stages_for(BM, BN, BK) * (BM + BN) * BK;
+    constexpr size_t stages = (size_t)stages_for(BK) * (BM + BN) * BK;
     // affine codes: weight-code sums and row classes behind the epilogue's block
     constexpr size_t affine = ((size_t)WM * 32 * (BN + 8 * WN) + 16 * BN) * 4 + BM, largest = stages > affine ? stages : affine;
     const size_t smem = g.zp_in ? largest : stages;
