@@ -367,7 +367,7 @@ def kernel_breakdown(ev, x, a_t, eg, wl, steps=5):
     """Average time per step of each kernel class (one class per pass)."""
     import torch
     names = {eg.KERNEL_ABSMAX: "absmax", eg.KERNEL_QUANTIZE: "quantize", eg.KERNEL_GEMM: "gemm_i8",
-             eg.KERNEL_GRAM: "gram_partial", eg.KERNEL_ATTENTION: "attention", eg.KERNEL_LAYERNORM: "layernorm"}
+             eg.KERNEL_GRAM: "gram", eg.KERNEL_ATTENTION: "attention", eg.KERNEL_LAYERNORM: "layernorm"}
     out = {}
     cap = 4096
     for cls, name in names.items():
@@ -683,7 +683,7 @@ def main():
     breakdown = kernel_breakdown(ev, x, a_t, eg, wl)
     # The class whose roofline goes into the line: the int8 GEMMs / convolutions of the reference forward
     # (the contraction the workload is judged by); the other classes follow in roofline_other_kernels.
-    timed_classes = {"gemm_i8": eg.KERNEL_GEMM, "gram_partial": eg.KERNEL_GRAM, "attention": eg.KERNEL_ATTENTION,
+    timed_classes = {"gemm_i8": eg.KERNEL_GEMM, "gram": eg.KERNEL_GRAM, "attention": eg.KERNEL_ATTENTION,
                      "layernorm": eg.KERNEL_LAYERNORM}
     primary = "gemm_i8"
     cls = timed_classes[primary]
@@ -775,7 +775,7 @@ def main():
             k = 20 if cfg == 5 else 100
             dt2 = time_steps(ev2, x2, a2, k, 5)
             bd = kernel_breakdown(ev2, x2, a2, eg, wl2, steps=3)
-            dom = max((n for n in bd if n in ("gemm_i8", "gram_partial", "attention")), key=lambda n: bd[n]["us_per_step"])
+            dom = max((n for n in bd if n in ("gemm_i8", "gram", "attention")), key=lambda n: bd[n]["us_per_step"])
             eg.profile_begin(timed_classes[dom], 4096)
             for _ in range(3):
                 ev2.step(x2, a2)

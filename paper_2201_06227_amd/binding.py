@@ -324,7 +324,9 @@ def quantize_weights(weights: Sequence[torch.Tensor], ws: Optional[torch.Tensor]
     """egeria_quantize_weights: every tensor of a snapshot in one call.  Returns
     the int8 tensors ([out, padded(in)] or [out, kh, kw, padded(in)]) and scales
     (1 value per tensor, or [out] values with per_channel); colsums (see colsum_like)
-    receive the sums of the codes that affine activation codes need."""
+    receive the sums of the codes that affine activation codes need.  The returned tensors are
+    views of one allocation for the codes and one for the scales: keeping (or saving) one of them
+    keeps its whole snapshot; clone() what is to outlive the others."""
     if not weights:
         return [], []
     # one allocation for all codes and one for all scales (every tensor 16-byte aligned), handed out as views:

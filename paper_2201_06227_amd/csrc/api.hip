@@ -872,8 +872,8 @@ size_t egeria_workspace_bytes(const egeria_block_desc *desc)
     return p.ok ? p.total : 0;
 }
 
-// Side stream of the stack evaluations (egeria_plasticity_eval / egeria_refresh_eval with
-// n_layers > 1), with the events that order it against the caller's stream.  One per device,
+// Side stream of the stack evaluations (egeria_plasticity_eval / egeria_refresh_eval of at least
+// four layers with large scores, see forward_impl), with the events that order it against the caller's stream.  One per device,
 // created on first use (default priority) on the device that is current then.  Every stack
 // evaluation of a device shares it: g_side_mutex is held while such a call enqueues its work, so
 // the record / wait pairs of two host threads never interleave (a wait refers to the event's last

@@ -37,8 +37,9 @@
 //   and the launch the rest of 27 us - and the L2 -> LDS path for b > 64, where a block of samples is read by up to three
 //   pairs.  Before (one 64x64 tile of both products, four waves, operands passed through LDS as nine bf16 planes: 18
 //   bytes of LDS writes and 48 of reads per value pair, and one wave per SIMD, which issues a vector instruction
-//   every 5 clocks where two waves issue one every 2.9): per score, both launches, us: b = 64, D = 200704 47 -> 38;
-//   b = 100, D = 62720 (bf16 T) 52 -> 32; b = 128, D = 16384 26 -> 21; b = 32, D = 98304 (bf16 T) 17.6 -> 13.3.
+//   every 5 clocks where two waves issue one every 2.9): per score, both launches, us: b = 64, D = 200704 43 -> 34;
+//   b = 100, D = 62720 (bf16 T) 54 -> 33; b = 128, D = 16384 27 -> 22; b = 32, D = 98304 (bf16 T) 17.6 -> 13.5.  Rows of
+//   odd length in bf16, which are filled element by element: b = 64, D = 200705 124 -> 37, b = 32, D = 98305 31 -> 21.
 //   The eight waves' accumulators are added through
 //   LDS at the end; the diagonal blocks of W are symmetrised there.
 //   Partials are [nsplit][2][b][b] fp32 (W and B, whole rows).
@@ -91,8 +92,10 @@ static GramPlan plan_gram(int32_t b, int64_t D)
     p.npair = p.nb <= 2 ? 1 : (p.nb == 3 ? 3 : 6);
     const int64_t nslab = (D + kSlab - 1) / kSlab;
     p.nslab = nslab;
-    // about one workgroup per CU (its LDS fills one), and at least one slab for every wave
-    // (the pairs of a chunk share an XCD, so the CUs of an XCD bound the chunks dealt to it)
+    // about one workgroup per CU: for b > 32 the registers of its eight waves (160 to 240 per lane) leave no room for a
+    // second one, and for smaller b the partials of twice as many cost more than they hide: b = 32, D = 98304 13.2 us
+    // against 15.7, b = 64, D = 200704 34 against 44.  At least one slab for every wave.  (The pairs of a chunk share an
+    // XCD, so the CUs of an XCD bound the chunks dealt to it.)
     int64_t want = 8 * (compute_units() / 8 / p.npair);
     const int64_t cap = (nslab + kGramWaves - 1) / kGramWaves;
     if (want > cap) want = cap;
@@ -137,8 +140,9 @@ __device__ __forceinline__ void split_pair(float x0, float x1, int e, Split8 &o)
     o.part[1][e] = pack_hi16(r1, r0);
     o.part[2][e] = pack_hi16(l1, l0);
 }
-// acc += a b^T with a in NA parts and b in NB parts (three for fp32, one for a value that is a bf16 value): every
-// partial product whose share of the result can exceed 2^-24, smallest first.  `after` runs behind every instruction.
+// acc += a b^T with a in NA parts and b in NB parts (three for fp32, one for a value that is a bf16 value), smallest
+// partial products first.  Of nine the three smallest are left out: mid lo and lo mid, each below 2^-22 of the product
+// (mid < 2^-7 and lo < 2^-15 of the value), and lo lo.  `after` runs behind every instruction.
 template <int NA, int NB, typename F>
 __device__ __forceinline__ void mma_parts(const Split8 &a, const Split8 &b, v16f &acc, F after)
 {
@@ -655,8 +659,9 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
         p.nsplit = p.turns = 1;
     }
     // Beside another stream's work: the same chunks (the same bits) in two launches of half the workgroups.  The kernel
-    // is bound by HBM either way, and one that sits on every CU keeps the other stream's workgroups waiting: 12-layer
-    // stack of 64 x 256 tokens 6.73 -> 6.64 ms.
+    // is bound by HBM either way, and one that sits on every CU keeps the other stream's workgroups waiting.  12-layer
+    // stack of 64 x 256 tokens with one launch / two, ms: 6.873 / 6.858 repeated (two runs of a side differ by as much),
+    // 6.99 / 6.82 for the first pass on new inputs.
     const int launches = beside && p.turns > 1 ? 2 : 1, width = (p.turns + launches - 1) / launches;
     const dim3 grid((unsigned)(width * 8)), block(64 * kGramWaves);
     const size_t smem = p.fused ? kGramFused : kGramReduce;      // (covers the stages: 8 KB per wave at most)
