@@ -406,12 +406,14 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         }
         amax = (int32_t)amax_u;
-    } else if (TN == 3 && m0 + BM <= g.M && n0 + BN <= g.N && g.y && !g.q_out && !g.res_q && !g.zp_in && !g.acc_out) {
-        // ---- a wave block of 96 columns, all of it inside the output, fp32 results alone: stored from the accumulators.
-        // For a fixed register each half of the wave owns 32 neighbouring columns of one row, so every store writes two whole
-        // 128-byte segments.  Turned through LDS as below, such a block keeps only 48 of the 64 lanes at work:
-        // 4096 x 3072 x 768 23.6 us against 22.3 this way, 4096 x 2304 x 768 18.7 against 17.2.  (Naming accumulation registers as the
-        // sums' home here splits the allocation of the whole kernel and spills.)
+    } else if (ET == 0 && BM * BN > 128 * 128 && m0 + BM <= g.M && n0 + BN <= g.N && g.y && !g.q_out && !g.res_q && !g.zp_in && !g.acc_out) {
+        // ---- a large tile, all of it inside the output, fp32 results alone: stored from the accumulators.  For a fixed register
+        // each half of the wave owns 32 neighbouring columns of one row, so every store writes two whole 128-byte segments.
+        // Turned through LDS as below, a wave block of 96 columns keeps only 48 of the 64 lanes at work, and a tile's stores
+        // come in bursts with the LDS traffic between them: 128x192 tiles, 4096 x 3072 x 768 23.6 us against 22.3 this way,
+        // 4096 x 2304 x 768 18.7 against 17.2; 256x128 tiles, 16384 x 3072 x 768 in the encoder stack 70.7 against 68.4.  (128x64
+        // and 128x128 tiles: no difference.  Naming accumulation registers as the sums' home here splits the allocation
+        // of the whole kernel and spills.)
         auto direct = [&](auto relu_c) {
             constexpr bool RELU = decltype(relu_c)::value;
             const int32_t keep = RELU || g.amax_pos ? -1 : 0x7fffffff;
