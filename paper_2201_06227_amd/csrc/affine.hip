@@ -31,22 +31,29 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
     if (!BF16 && ((uintptr_t)x & 15) == 0) {
         const float4 *x4 = (const float4 *)x;
         const int64_t n4 = n >> 2;
-        // four loads in flight per thread (indices clamped: a value seen twice changes no extremum)
-        for (int64_t i = first; i < n4; i += 4 * stride) {
-            float4 v[4];
+        auto take = [&](const float4 &v) {
+            const float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = x4[i + j * stride < n4 ? i + j * stride : i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    hi = fmaxf(hi, e[k]);
-                    nlo = fmaxf(nlo, -e[k]);
-                    const uint32_t a = abs_bits(e[k]);
-                    worst = worst > a ? worst : a;
-                }
+            for (int k = 0; k < 4; ++k) {
+                hi = fmaxf(hi, e[k]);
+                nlo = fmaxf(nlo, -e[k]);
+                const uint32_t a = abs_bits(e[k]);
+                worst = worst > a ? worst : a;
             }
+        };
+        if (n4 <= 4 * stride) {
+            // a tensor of at most four units per thread: all of them in flight (indices clamped: a value seen twice changes
+            // no extremum).  1 M values 3.4 us against 3.8 one by one.  Larger tensors read slower that way, a thread's four
+            // streams lying 4 MB apart: 5.2 M values 6.3 us against 5.9, 12.8 M 11.8 against 11.4, 50 M 40.4 against 38.
+            if (first < n4) {
+                float4 v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = x4[first + j * stride < n4 ? first + j * stride : first];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) take(v[j]);
+            }
+        } else {
+            for (int64_t i = first; i < n4; i += stride) take(x4[i]);
         }
         for (int64_t i = (n4 << 2) + first; i < n; i += stride) {
             const float v = ((const float *)x)[i];

@@ -216,6 +216,19 @@ def test_conv_epilogue_edges(eg, b, c, h, w, mode):
         assert bool((plain[-64:] == 7.0).all()), "written past the end"
 
 
+# Extrema of a tensor: at most four 16-byte units per thread, one more, ragged ends, the extrema among the last values.
+@pytest.mark.parametrize("n", [1, 3, 5, 1023, 4100, (1 << 22) - 1, 1 << 22, (1 << 22) + 4, (1 << 22) + 4099])
+def test_affine_extrema(eg, n):
+    from oracle import affine_oracle as ao
+    rng = np.random.default_rng(n % 89)
+    for at in (0, n // 2, n - 1):
+        x = rng.uniform(-1.0, 1.0, n).astype(np.float32)
+        x[at], x[(at + 7) % n] = 5.0, -3.0
+        q, s, zp = eg.quantize_affine(torch.from_numpy(x).cuda())
+        wq, ws, wzp = ao.quantize(x)
+        assert s.item() == ws and zp.item() == wzp and np.array_equal(q.cpu().numpy(), wq), at
+
+
 # Operands made of whole 16-byte units (rows of 4 k values, planes of 4 k pixels) and of everything else; channel counts
 # with and without pad channels.
 @pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 4, 3), (2, 17, 7, 7), (5, 68, 2, 2), (300, 20, 1, 1)])
