@@ -406,18 +406,40 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         }
         amax = (int32_t)amax_u;
-    } else if (ET == 0 && BM * BN > 128 * 128 && m0 + BM <= g.M && n0 + BN <= g.N && g.y && !g.q_out && !g.res_q && !g.zp_in && !g.acc_out) {
-        // ---- a large tile, all of it inside the output, fp32 results alone: stored from the accumulators.  For a fixed register
-        // each half of the wave owns 32 neighbouring columns of one row, so every store writes two whole 128-byte segments.
-        // Turned through LDS as below, a wave block of 96 columns keeps only 48 of the 64 lanes at work, and a tile's stores
-        // come in bursts with the LDS traffic between them: 128x192 tiles, 4096 x 3072 x 768 23.6 us against 22.3 this way,
-        // 4096 x 2304 x 768 18.7 against 17.2; 256x128 tiles, 16384 x 3072 x 768 in the encoder stack 70.7 against 68.4.  (128x64
-        // and 128x128 tiles: no difference.  Naming accumulation registers as the sums' home here splits the allocation
-        // of the whole kernel and spills.)
-        auto direct = [&](auto relu_c) {
-            constexpr bool RELU = decltype(relu_c)::value;
+    } else if (ET == 0 && m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
+               (BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q)) {
+        // ---- a tile that lies inside the output: stored from the accumulators.  For a fixed register each half of the wave owns
+        // 32 neighbouring columns of one row, so every store of y writes two whole 128-byte segments and nothing is tested.
+        // Turned through LDS as below, the stores come in bursts with LDS traffic between them, and a wave block of 96
+        // columns keeps only 48 of the 64 lanes at work.  Through LDS / this way, us: 200704 x 256 x 64 with a residual 64.4 /
+        // 56.4, 50176 x 512 x 128 26.3 / 24.8, 3x3 with int8 output 200704 x 64 x 576 24.8 / 22.8, 12544 x 256 x 2304 18.8 /
+        // 18.2; 4096 x 3072 x 768 (128x192) 23.6 / 22.3, 16384 x 3072 x 768 in the encoder stack (256x128) 70.7 / 68.4.  (Naming
+        // accumulation registers as the sums' home here splits the allocation of the whole kernel and spills; so do
+        // residuals and int8 outputs on tiles above 128x128, which take the form below.)
+        constexpr bool SMALL = BM * BN <= 128 * 128;
+        const bool has_res = SMALL && g.res_q != nullptr;
+        if (has_res) {
+            // the residual's codes of the tile through LDS (the stage memory is free now): one coalesced pass of 16-byte loads
+            constexpr int RU = BN / 16, RIT = (BM * RU + NT - 1) / NT;     // 16-byte units per row, units per thread
+            static_assert((size_t)NST * STAGE >= (size_t)BM * BN, "the residual tile must fit the stage memory");
+            v4i rv[RIT];
+#pragma unroll
+            for (int it = 0; it < RIT; ++it) {
+                const int u = tid + it * NT < BM * RU ? tid + it * NT : 0;
+                rv[it] = *(const v4i *)((const int8_t *)g.res_q + (m0 + u / RU) * g.res_ld + n0 + (u % RU) * 16);
+            }
+            __syncthreads();                                              // every wave has read its last operands
+#pragma unroll
+            for (int it = 0; it < RIT; ++it) {
+                const int u = tid + it * NT;
+                if (u < BM * RU) *(v4i *)&lds[(u / RU) * BN + (u % RU) * 16] = rv[it];
+            }
+            __syncthreads();
+        }
+        auto direct = [&](auto relu_c, auto res_c, auto qout_c) {
+            constexpr bool RELU = decltype(relu_c)::value, RES = decltype(res_c)::value, QOUT = decltype(qout_c)::value;
             const int32_t keep = RELU || g.amax_pos ? -1 : 0x7fffffff;
-            const uint32_t yoff = (uint32_t)(lrow * g.ldy + lcol);
+            const uint32_t yoff = (uint32_t)(lrow * g.ldy + lcol), qoff = QOUT ? (uint32_t)(lrow * g.q_ld + lcol) : 0u;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int col0 = n0 + (wn_u * TN + j) * 32;
@@ -425,12 +447,17 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
                 const float sj = g.sw_per_n ? sxv * g.sw[col0 + lcol] : s;     // one fp32 multiply
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    float *yb = g.y + (m0 + (wm_u * TM + i) * 32) * g.ldy + col0;
+                    const int64_t row0 = m0 + (wm_u * TM + i) * 32;
+                    float *yb = g.y + row0 * g.ldy + col0;
+                    int8_t *qb = g.q_out + row0 * g.q_ld + col0;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
+                        const int rr = 8 * (r >> 2) + (r & 3);
                         float v = fmaf((float)acc[i][j][r], sj, bj);
+                        if constexpr (RES) v = v + (float)(int8_t)lds[((wm_u * TM + i) * 32 + lrow + rr) * BN + (wn_u * TN + j) * 32 + lcol] * rs;
                         if (RELU) v = v > 0.0f ? v : 0.0f;
-                        yb[(size_t)(8 * (r >> 2) + (r & 3)) * g.ldy + yoff] = v;
+                        if (!QOUT || g.y) yb[(size_t)rr * g.ldy + yoff] = v;
+                        if (QOUT) qb[(size_t)rr * g.q_ld + qoff] = (int8_t)quant1(v, q_inv);
                         const int32_t bits = (int32_t)__float_as_uint(v) & keep;
                         amax = amax > bits ? amax : bits;
                     }
@@ -438,16 +465,23 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
                 }
             }
         };
-        if (g.act == 1) direct(std::true_type{}); else direct(std::false_type{});
+        using T = std::true_type;
+        using F = std::false_type;
+        bool done = false;
+        if constexpr (SMALL) {
+            done = g.q_out || has_res;
+            if (g.q_out) direct(T{}, F{}, T{});
+            else if (has_res) { if (g.act == 1) direct(T{}, T{}, F{}); else direct(F{}, T{}, F{}); }
+        }
+        if (!done) { if (g.act == 1) direct(T{}, F{}, F{}); else direct(F{}, F{}, F{}); }
     } else {
-        // ---- epilogue.  A wave's sums go through LDS (its own part of the stage memory, no barriers), a 32-row block at
-        // a time, and come back as four neighbouring columns of one row per lane: one 16-byte store of y, four packed
-        // codes, four residual codes in one load, the columns' scale and bias in registers.  Stores of y are raw buffer
-        // stores: what must not be written (rows beyond M, columns beyond N) lies outside the buffer, so edge tiles
-        // run the same straight code as interior ones.
-        // (Stores straight from the accumulators, two 128-byte row segments each, needed a specialised copy of the epilogue
-        // per combination of residual, activation and output; the general copy, for tiles at an edge and for affine
-        // codes, tested every element: 4728 x 2304 x 768 took 35.7 us where 4096 rows took 20.5.)
+        // ---- everything else: tiles at an edge, affine codes, observed runs, the float types.  A wave's sums go through LDS
+        // (its own part of the stage memory, no barriers), a 32-row block at a time, and come back as four neighbouring
+        // columns of one row per lane: one 16-byte store of y, four packed codes, four residual codes in one load, the
+        // columns' scale and bias in registers.  Stores of y are raw buffer stores: what must not be written (rows beyond M,
+        // columns beyond N) lies outside the buffer, so edge tiles run straight code as well.
+        // (From the accumulators every element of such a tile had to be tested: 4728 x 2304 x 768 took 35.7 us where 4096
+        // rows took 20.5; 19.3 this way.)
         constexpr int WC = TN * 32, WS = WC + 8;        // columns of a wave's block; words per row (pad: the two rows a
                                                         // write instruction touches fall into different banks)
         constexpr int LPR = WC / 4, RPI = 64 / LPR;     // lanes per row, rows per instruction (TN = 3: 48 lanes at work)
@@ -661,11 +695,8 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         } else if (has_res) fixed(T{}, F{}, T{}, F{}, F{});
         else if (q) { if constexpr (ET == 0) fixed(T{}, F{}, F{}, T{}, F{}); }
-        else if (relu) {
-            if (track) fixed(T{}, T{}, F{}, F{}, F{}); else fixed(T{}, F{}, F{}, F{}, F{});
-        } else {
-            if (track) fixed(F{}, T{}, F{}, F{}, F{}); else fixed(F{}, F{}, F{}, F{}, F{});
-        }
+        else if (relu) fixed(T{}, T{}, F{}, F{}, F{});
+        else fixed(F{}, T{}, F{}, F{}, F{});
     }
     if (g.absmax_out) {
         __shared__ uint32_t smw[NW];
