@@ -142,6 +142,12 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     const int zmul = (ET == 0 && g.zp_in) ? 128 - *g.zp_in : 0;
     const int rmul = (ET == 0 && g.zp_res) ? 128 - *g.zp_res : 0;
 
+    // which form the epilogue takes (decided here for the same reason)
+    int inside = m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
+                 (ET == 0 && BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q);
+    inside = __builtin_amdgcn_readfirstlane(inside);
+    asm volatile("" : "+s"(inside));
+
     // Operands go from global memory straight into LDS (buffer loads with the
     // LDS modifier): one such instruction of a wave fills 1 KiB, lane l writing
     // bytes [16 l, 16 l + 16) of it, i.e. unit l % UPR of row l / UPR of a chunk
@@ -406,8 +412,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         }
         amax = (int32_t)amax_u;
-    } else if (ET == 0 && m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
-               (BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q)) {
+    } else if (inside) {
         // ---- a tile that lies inside the output: stored from the accumulators.  For a fixed register each half of the wave owns
         // 32 neighbouring columns of one row, so every store of y writes two whole 128-byte segments and nothing is tested.
         // Turned through LDS as below, the stores come in bursts with LDS traffic between them, and a wave block of 96
@@ -415,8 +420,8 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         // 56.4, 50176 x 512 x 128 26.3 / 24.8, 3x3 with int8 output 200704 x 64 x 576 24.8 / 22.8, 12544 x 256 x 2304 18.8 /
         // 18.2; 4096 x 3072 x 768 (128x192) 23.6 / 22.3, 16384 x 3072 x 768 in the encoder stack (256x128) 70.7 / 68.4.  (Naming
         // accumulation registers as the sums' home here splits the allocation of the whole kernel and spills; so do
-        // residuals and int8 outputs on tiles above 128x128, which take the form below.)
-        constexpr bool SMALL = BM * BN <= 128 * 128;
+        // residuals and int8 outputs on tiles above 128x128, which take the form below, as do residuals of the float types.)
+        constexpr bool SMALL = ET == 0 && BM * BN <= 128 * 128;
         const bool has_res = SMALL && g.res_q != nullptr;
         if (has_res) {
             // the residual's codes of the tile through LDS (the stage memory is free now): one coalesced pass of 16-byte loads
@@ -475,7 +480,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         }
         if (!done) { if (g.act == 1) direct(T{}, F{}, F{}); else direct(F{}, F{}, F{}); }
     } else {
-        // ---- everything else: tiles at an edge, affine codes, observed runs, the float types.  A wave's sums go through LDS
+        // ---- everything else: tiles at an edge, affine codes, observed runs.  A wave's sums go through LDS
         // (its own part of the stage memory, no barriers), a 32-row block at a time, and come back as four neighbouring
         // columns of one row per lane: one 16-byte store of y, four packed codes, four residual codes in one load, the
         // columns' scale and bias in registers.  Stores of y are raw buffer stores: what must not be written (rows beyond M,
@@ -695,8 +700,11 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         } else if (has_res) fixed(T{}, F{}, T{}, F{}, F{});
         else if (q) { if constexpr (ET == 0) fixed(T{}, F{}, F{}, T{}, F{}); }
-        else if (relu) fixed(T{}, T{}, F{}, F{}, F{});
-        else fixed(F{}, T{}, F{}, F{}, F{});
+        else if (relu) {
+            if (track) fixed(T{}, T{}, F{}, F{}, F{}); else fixed(T{}, F{}, F{}, F{}, F{});
+        } else {
+            if (track) fixed(F{}, T{}, F{}, F{}, F{}); else fixed(F{}, F{}, F{}, F{}, F{});
+        }
     }
     if (g.absmax_out) {
         __shared__ uint32_t smw[NW];
