@@ -142,12 +142,6 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     const int zmul = (ET == 0 && g.zp_in) ? 128 - *g.zp_in : 0;
     const int rmul = (ET == 0 && g.zp_res) ? 128 - *g.zp_res : 0;
 
-    // which form the epilogue takes (decided here for the same reason)
-    int inside = m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
-                 (ET == 0 && BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q);
-    inside = __builtin_amdgcn_readfirstlane(inside);
-    asm volatile("" : "+s"(inside));
-
     // Operands go from global memory straight into LDS (buffer loads with the
     // LDS modifier): one such instruction of a wave fills 1 KiB, lane l writing
     // bytes [16 l, 16 l + 16) of it, i.e. unit l % UPR of row l / UPR of a chunk
@@ -290,6 +284,11 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     v4i fa0[TM], fb0[TN], fa1[TM], fb1[TN];
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p) fetch(p, p);
+    // which form the epilogue takes: decided while the first K steps are on their way
+    int inside = m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
+                 (ET == 0 && BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q);
+    inside = __builtin_amdgcn_readfirstlane(inside);
+    asm volatile("" : "+s"(inside));
     __builtin_amdgcn_s_waitcnt(kWaitNext);       // K step 0 landed
     __syncthreads();
     read_frags(0, 0, fa0, fb0);

@@ -220,8 +220,9 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
     const int bq = KIND == 2 ? (pair < p.nb ? (pair + 1 == p.nb ? 0 : pair + 1) : bp + 2) : 1;
     const bool diag_p = KIND != 2 || pair < p.nb;
     using slab_t = std::conditional_t<LONG, int64_t, int>;
-    const slab_t slab0 = (slab_t)(chunk * p.spc);
-    const slab_t slab1 = (slab_t)(slab0 + p.spc < p.nslab ? slab0 + p.spc : p.nslab);
+    const slab_t spc = (slab_t)p.spc, nslab = (slab_t)p.nslab;
+    const slab_t slab0 = chunk * spc;
+    const slab_t slab1 = slab0 + spc < nslab ? slab0 + spc : nslab;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
