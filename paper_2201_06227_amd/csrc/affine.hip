@@ -234,8 +234,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const int8_t *__restrict__ 
         if (t < taps) {
             const int8_t *row = w_q + ((int64_t)n * taps + t) * cp;
             for (int k = lane; k < cp; k += 64) s[t] += row[k];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s[t] += __shfl_xor(s[t], off, kWave);
+            s[t] = wave_reduce(s[t], [](int a, int b) { return a + b; });
         }
     }
     if (lane != 0) return;

@@ -293,8 +293,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
                     st[kb][qb][r] = key >= S ? -INFINITY : st[kb][qb][r] * scale;   // q.k first, then 1/sqrt(dh)
                     mx = fmax(mx, st[kb][qb][r]);
                 }
-            mx = fmax(mx, __shfl_xor(mx, 16, kWave));
-            mx = fmax(mx, __shfl_xor(mx, 32, kWave));
+            mx = pair_op<16>(mx, [](double a, double b) { return fmax(a, b); });
+            mx = pair_op<32>(mx, [](double a, double b) { return fmax(a, b); });
             const double mnew = fmax(mrun[qb], mx);      // finite: every tile holds at least one key
             const double corr = exp(mrun[qb] - mnew);
             double ps = 0.0;
@@ -305,8 +305,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
                     st[kb][qb][r] = exp(st[kb][qb][r] - mnew);
                     ps += st[kb][qb][r];
                 }
-            ps += __shfl_xor(ps, 16, kWave);
-            ps += __shfl_xor(ps, 32, kWave);
+            ps = pair_op<16>(ps, [](double a, double b) { return a + b; });
+            ps = pair_op<32>(ps, [](double a, double b) { return a + b; });
             lrun[qb] = lrun[qb] * corr + ps;
             mrun[qb] = mnew;
 #pragma unroll
@@ -529,8 +529,8 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
                 st[kb][r] = key < S ? sc : -INFINITY;
                 mx = fmaxf(mx, st[kb][r]);
             }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+        mx = pair_op<16>(mx, [](float a, float b) { return fmaxf(a, b); });
+        mx = pair_op<32>(mx, [](float a, float b) { return fmaxf(a, b); });
         const float mnew = fmaxf(mrun, mx);
         const float corr = __builtin_amdgcn_exp2f((mrun - mnew) * kLog2e);
         float ps = 0.0f;
@@ -541,8 +541,8 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
                 st[kb][r] = __builtin_amdgcn_exp2f((st[kb][r] - mnew) * kLog2e);
                 ps += st[kb][r];
             }
-        ps += __shfl_xor(ps, 16, kWave);
-        ps += __shfl_xor(ps, 32, kWave);
+        ps = pair_op<16>(ps, [](float a, float b) { return a + b; });
+        ps = pair_op<32>(ps, [](float a, float b) { return a + b; });
         lrun = lrun * corr + ps;
         mrun = mnew;
         // this tile's V^T P^T from a zero accumulator (step (kb, r) contracts keys 16 kb + 4 g + r, g = 0..3),
@@ -846,7 +846,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+        mx = pair_op<32>(mx, [](float a, float b) { return fmaxf(a, b); });
         const float mnew = fmaxf(mrun, mx);
         const float corr = __builtin_amdgcn_exp2f((mrun - mnew) * c2);
         const float shift = -mnew * c2;
@@ -856,7 +856,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
             sacc[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], c2, shift));
             ps += sacc[i];
         }
-        ps += __shfl_xor(ps, 32, kWave);
+        ps = pair_op<32>(ps, [](float a, float b) { return a + b; });
         lrun = lrun * corr + ps;
         mrun = mnew;
         // the lane's unit of slab s of P^T: its registers 8 s .. 8 s + 7
@@ -1075,9 +1075,7 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
             for (int d = 0; d < dh; ++d) acc = fma((double)qs[d], (double)kr[d], acc);   // odd head sizes: plain loop
         }
         const double sc = j < S ? acc * scale : -INFINITY;
-        double cm = sc;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) cm = fmax(cm, __shfl_xor(cm, off, kWave));
+        const double cm = wave_max(sc);
         __syncthreads();                                      // red is free (an earlier block, an earlier call)
         if (lane == 0) red[wave] = cm;
         __syncthreads();
@@ -1380,8 +1378,7 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
                             sc[kk] = lane + 64 * kk < S ? acc[kk] * scale : -INFINITY;
                             mx = fmax(mx, sc[kk]);
                         }
-#pragma unroll
-                        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, kWave));
+                        mx = wave_max(mx);
                         double l = 0.0, o = 0.0;
 #pragma unroll
                         for (int kk = 0; kk < 4; ++kk) {

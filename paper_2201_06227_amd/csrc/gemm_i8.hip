@@ -710,12 +710,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         if constexpr (NW == 4) {
             block_atomic_max((uint32_t)amax, g.absmax_out, smw);
         } else {
-            uint32_t v = (uint32_t)amax;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const uint32_t o = (uint32_t)__shfl_xor((int)v, off, kWave);
-                v = o > v ? o : v;
-            }
+            const uint32_t v = wave_max_u32((uint32_t)amax);
             if (lane == 0) smw[wave] = v;
             __syncthreads();
             if (tid == 0) {

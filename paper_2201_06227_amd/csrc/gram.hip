@@ -532,11 +532,9 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void gram_kernel(const void *__
             q[3][k] = e * e;
         }
 #pragma unroll
-        for (int off = 16; off > 0; off >>= 1)                   // (32 columns: no exchange between the halves of the wave)
+        for (int k = 0; k < RW; ++k)
 #pragma unroll
-            for (int k = 0; k < RW; ++k)
-#pragma unroll
-                for (int m = 0; m < 4; ++m) q[m][k] += __shfl_xor(q[m][k], off, kWave);
+            for (int m = 0; m < 4; ++m) q[m][k] = wave_sum<16>(q[m][k]);   // (32 columns: no exchange between the halves of the wave)
         if (lane == 0) {
 #pragma unroll
             for (int k = 0; k < RW; ++k)
@@ -594,8 +592,12 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
                 ab += (double)vb[u];
             }
     }
-#pragma unroll
-    for (int off = CS; off < 64; off <<= 1) { aw += __shfl_xor(aw, off, kWave); ab += __shfl_xor(ab, off, kWave); }
+    if constexpr (CS == 16) {
+        aw += lane_xor<16>(aw);
+        ab += lane_xor<16>(ab);
+        aw += lane_xor<32>(aw);
+        ab += lane_xor<32>(ab);
+    }
     if (lane < CS) { sm[0][wave][lane] = aw; sm[1][wave][lane] = ab; }
     __syncthreads();
     if (wave == 0) {
@@ -611,9 +613,7 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
             q[3] = e * e;
         }
 #pragma unroll
-        for (int off = CS / 2; off > 0; off >>= 1)
-#pragma unroll
-            for (int k = 0; k < kFinSums; ++k) q[k] += __shfl_xor(q[k], off, kWave);
+        for (int k = 0; k < kFinSums; ++k) q[k] = wave_sum<CS / 2>(q[k]);
         if (lane == 0) {
             // device-scope stores (they bypass the XCD's L2), waited for before the ticket is taken: no cache write-back
 #pragma unroll
