@@ -619,15 +619,15 @@ class ActivationCache:
 
 
 def profile_attention(qkv: torch.Tensor, heads: int, mode: int):
-    """egeria_profile_attention: (ctx [B, S, hidden], records [n, 2] int32 view or None)."""
+    """egeria_profile_attention: (ctx [B, S, hidden], error bounds [B, heads, S] or None)."""
     qkv = _dev(qkv)
     B, S, h3 = qkv.shape
     hidden = h3 // 3
     ctx = torch.empty((B, S, hidden), dtype=torch.float32, device=qkv.device)
-    rec = torch.zeros((B * heads * ((S + 63) // 64), 2), dtype=torch.int32, device=qkv.device) if mode == 1 else None
-    _check(lib().egeria_profile_attention(_ptr(qkv), B, S, hidden, heads, mode, _ptr(ctx), _ptr(rec), _stream()),
+    bounds = torch.zeros((B, heads, S), dtype=torch.float32, device=qkv.device) if mode == 1 else None
+    _check(lib().egeria_profile_attention(_ptr(qkv), B, S, hidden, heads, mode, _ptr(ctx), _ptr(bounds), _stream()),
            "egeria_profile_attention")
-    return ctx, rec
+    return ctx, bounds
 
 
 def profile_begin(kernel_class: int, max_launches: int) -> None:

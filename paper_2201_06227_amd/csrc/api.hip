@@ -457,9 +457,22 @@ egeria_status forward_float(Fwd &f, const void *x, egeria_dtype dt, float *a_ref
     return run_gemm(f, 2, f.qbuf(2), cmid_b, M, d->c_out, cmid_b, false, 0, 0, 0, one, 1, res, one, res_ld, a_ref, nullptr);
 }
 
-// Attention sizes (flops of the two products) from which unobserved runs take the certified fp32 kernels;
-// egeria_profile_attention_threshold lets tests run them on small shapes too.
-double g_attention_min_flops = 5.0e9;
+// Attention sizes from which unobserved runs take the certified approximate kernels (two launches) instead of the fp64 kernel
+// and a row quantiser; egeria_profile_attention_threshold lets tests run them on small shapes too.  The measure is the flops of
+// the two products as the fp64 kernel does them (heads padded to 64 dims), 29 us per 1e9 with whole tiles; the certified
+// kernels have 30 us of fixed cost.  Up to 64 tokens, one tile of that kernel, they do not pay at any batch (one layer, us,
+// fp64 / certified: 64 x 64 tokens of 768 149 / 164, 256 x 64 463 / 508; 64 x 80 202 / 192, 100 x 72 311 / 282); beyond 256
+// tokens a head's keys do not fit the LDS at once and they pay from twice the size (4 x 300 x 512 104 / 115, 2 x 384 x 1024
+// 127 / 139, 4 x 384 x 768 160 / 138); between, from 0.75e9: 12 x 128 x 768 115 / 113, 16 x 128 x 256 74 / 80, 24 x 128 x 384
+// (heads of 32) 113 / 100, 32 x 128 x 768 166 / 158, 24 x 197 x 768 241 / 191.  Heads that are no multiple of 8 dims take the
+// fp32 kernel and a launch for the maximum: from 5e9 flops.
+double g_attention_min_flops = 0.75e9;
+double attention_measure(const egeria_block_desc *d)
+{
+    const double pairs = (double)d->batch * d->heads * (double)d->seq * d->seq;
+    if (!attention_splits(d->hidden, d->heads)) return 0.15 * 4.0 * pairs * (d->hidden / d->heads);
+    return d->seq <= 64 ? 0.0 : (d->seq <= 256 ? 1.0 : 0.5) * 256.0 * pairs;
+}
 
 // One encoder layer: `cur` -> `out`.  slot 4l must already hold absmax(cur).
 egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *out, bool last)
@@ -477,19 +490,17 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
         EG_HIP(launch_quantize_rows(cur, EGERIA_F32, M, Hd, hp, f.amax(s0), f.n_amax(s0), f.stride_amax(s0), nullptr, xq,
                                     f.scale(s0), nullptr, ws_flag(f.ws), f.st));
     EG_OK(f.copy_tap_q(s0, xq, (size_t)(M * hp), f.scale(s0)));
-    EG_OK(run_gemm(f, s0, xq, hp, M, 3 * Hd, hp, false, 0, 0, 0, f.scale(s0), 0, nullptr, nullptr, 0, qkv, nullptr));
-    // The certified approximate attention is two or three launches with some tens of microseconds of fixed cost; it
-    // pays when the fp64 kernel would take longer than that (one layer of 32 x 128 tokens: fp64 46 us; the 12-layer
-    // stack of 64 x 256 tokens: 315 us).
-    const double attention_flops = 4.0 * d->batch * d->heads * (double)d->seq * d->seq * (Hd / d->heads);
-    if (f.taps || attention_flops < g_attention_min_flops) {
+    const bool certified = !f.taps && attention_measure(d) >= g_attention_min_flops;
+    EG_OK(run_gemm(f, s0, xq, hp, M, 3 * Hd, hp, false, 0, 0, 0, f.scale(s0), 0, nullptr, nullptr, 0, qkv,
+                   certified && attention_splits(Hd, d->heads) ? f.slot(6 * f.p.n_layers + l) : nullptr));
+    if (!certified) {
         // observed runs (and small ones): the context itself in fp64, then the plain quantiser
         EG_HIP(launch_attention(qkv, d->batch, d->seq, Hd, d->heads, ctx, f.slot(s0 + 1), f.st));
         EG_HIP(launch_quantize_rows(ctx, EGERIA_F32, M, Hd, hp, f.amax(s0 + 1), f.n_amax(s0 + 1), f.stride_amax(s0 + 1),
                                     nullptr, xq, f.scale(s0 + 1), nullptr, ws_flag(f.ws), f.st));
         EG_OK(f.copy_tap_q(s0 + 1, xq, (size_t)(M * hp), f.scale(s0 + 1)));
     } else {
-        // unobserved runs: fp32 matrix-core attention, codes and scale certified against the fp64 evaluation
+        // unobserved runs: approximate matrix-core attention, codes and scale certified against the fp64 evaluation
         EG_HIP(launch_attention_certified(qkv, d->batch, d->seq, Hd, d->heads, ctx, f.ws + f.p.off_rec,
                                           f.slot(s0 + 1), f.slot(6 * f.p.n_layers + l), f.slot(5 * f.p.n_layers + l), xq, hp,
                                           f.scale(s0 + 1), ws_flag(f.ws),
@@ -1156,14 +1167,14 @@ egeria_status egeria_profile_end(float *ms_out, int32_t capacity, int32_t *n_out
 }
 
 egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads,
-                                       int32_t mode, float *ctx, void *records, void *stream)
+                                       int32_t mode, float *ctx, float *bounds, void *stream)
 {
     if (!qkv || !ctx || B < 1 || S < 1 || hidden < 1 || heads < 1 || hidden % heads != 0) return EGERIA_ERR_INVALID_ARG;
     if (!aligned16(qkv) || !aligned16(ctx) || (mode != 0 && mode != 1)) return EGERIA_ERR_INVALID_ARG;
-    if (mode == 1 && (!records || !aligned16(records))) return EGERIA_ERR_INVALID_ARG;
+    if (mode == 1 && (!bounds || !aligned16(bounds))) return EGERIA_ERR_INVALID_ARG;
     if (hidden / heads > 64) return EGERIA_ERR_UNSUPPORTED;
     if (mode == 0) EG_HIP(launch_attention(qkv, B, S, hidden, heads, ctx, nullptr, (hipStream_t)stream));
-    else EG_HIP(launch_attention_fast(qkv, B, S, hidden, heads, ctx, records, (hipStream_t)stream));
+    else EG_HIP(launch_attention_fast(qkv, B, S, hidden, heads, ctx, bounds, (hipStream_t)stream));
     return EGERIA_OK;
 }
 

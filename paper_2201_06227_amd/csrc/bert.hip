@@ -359,20 +359,19 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
 
 // ---- the same attention in fp32 arithmetic on the matrix cores, with certified int8 codes ----------
 // Unobserved runs do not need the context as the fp64 evaluation gives it: all that leaves this stage
-// is the int8 input of the next GEMM and its scale.  Three launches (two with the bf16-split kernel, whose
-// workgroups settle the exact maximum themselves as they finish):
+// is the int8 input of the next GEMM and its scale.  Two launches, 1 and 3 (three with the fp32 kernel):
 //   1. an approximate attention with fp32 products and sums: attention_split_kernel (further down: every
-//      fp32 product as six bf16 partial products on the bf16 matrix cores; head dims in whole units of 8)
+//      fp32 product as three float16 partial products on the float16 matrix cores; head dims in whole units of 8)
 //      or attention_fast_kernel (here: the structure of the kernel above on v_mfma_f32_16x16x4f32, hardware
-//      exp2; any head size).  It stores an approximate context and, per 64 queries of a head, a record: the
-//      largest |context| it stored and an error bound E for its values (below).
-//   2. attention_absmax_exact_kernel: the tensor's absolute maximum as the fp64 evaluation gives it.  Every
+//      exp2; any head size).  It stores an approximate context, an error bound E per query of a head and what its
+//      workgroups know of the largest value.
+//   2. attention_absmax_exact_kernel (fp32 kernel only): the tensor's absolute maximum as the fp64 evaluation gives it.  Every
 //      value that can be the maximum (|x| + E >= largest |x| - largest E; as a rule one) is re-evaluated in fp64.
 //   3. quantize_attention_certify_kernel: the streaming map to codes.  code(x) = clamp(rne(x * inv)) is
 //      monotone in x, so an approximate value whose interval [x - E, x + E] maps to one code has that
 //      code; the others (a few in ten thousand) are re-evaluated in fp64, a wave per value, by the
 //      workgroup that met them.
-// The bound of a value x: E = 2^-24 * (max|v| of the head * (kErrBase + kErrPerScore * max|score| of the
+// The fp32 kernel's bound of a value x (the split kernel forms its own): E = 2^-24 * (max|v| of the head * (kErrBase + kErrPerScore * max|score| of the
 // workgroup) + kErrRel |x|).  It is an empirical bound with margin, not a proof: bench.py --attention-error
 // measures kernel 1 against the fp64 kernel on the twelve layers of the BERT-base-shaped stack (12.6 M
 // values each) and prints the largest error / E per layer.
@@ -381,7 +380,7 @@ constexpr float kErrBase = 2.0f, kErrPerScore = 0.5f;
 // ... plus a part that grows with the value itself (the drift of the matrix cores' accumulation is
 // proportional to the sums it carries): kErrRel * 2^-24 * |x|
 constexpr float kErrRel = 12.0f * 5.9604645e-8f;
-// error bound of one approximate context value x whose workgroup's record says err
+// error bound of one approximate context value x whose query's bound is err
 __device__ __forceinline__ float value_err(float err, float x) { return fmaf(kErrRel, fabsf(x), err); }
 struct AttnRecord {
     uint32_t amax_bits;     // largest |approximate context| of the workgroup's 64 queries x head dims
@@ -390,8 +389,8 @@ struct AttnRecord {
 
 __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__restrict__ qkv, int B, int S, int Hd,
                                                              int heads, int dh, float scale, float *__restrict__ ctx,
-                                                             AttnRecord *__restrict__ rec, int total, int per_xcd,
-                                                             uint32_t *__restrict__ amax_slot,
+                                                             float *__restrict__ err_q, AttnRecord *__restrict__ rec,
+                                                             int total, int per_xcd, uint32_t *__restrict__ amax_slot,
                                                              uint32_t *__restrict__ err_slot)
 {
     __shared__ __attribute__((aligned(16))) float sKb[2][kKeyTile][kKVPad];
@@ -599,7 +598,7 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
     const uint32_t sbits = wave_max_u32(__float_as_uint(smax));       // non-negative floats order like integers
     if (lane == 0) { red[0][wave] = amax; red[1][wave] = vmax; red[2][wave] = sbits; }
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {
         uint32_t a = 0, v = 0, sb = 0;
         for (int w = 0; w < 4; ++w) {
             a = a > red[0][w] ? a : red[0][w];
@@ -610,10 +609,11 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
         r.amax_bits = a;
         r.err = 5.9604645e-8f * __uint_as_float(v) * (kErrBase + kErrPerScore * __uint_as_float(sb));
         if (!(r.err <= 3.402823466e+38f)) r.amax_bits = 0x7f800000u;   // non-finite inputs: flagged downstream
-        rec[vid] = r;
+        if (qt * QT + tid < S) err_q[(int64_t)bh * S + qt * QT + tid] = r.err;
+        if (tid == 0 && rec) rec[vid] = r;
         // the largest of both over all workgroups, for the kernel that settles the exact maximum (atomically
         // combined words spread over ways; both are non-negative floats, whose bit patterns order like them)
-        if (amax_slot) {
+        if (tid == 0 && amax_slot) {
             uint32_t *wa = amax_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
             uint32_t *we = err_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
             const uint32_t eb = __float_as_uint(r.err);
@@ -623,13 +623,20 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
     }
 }
 
-// ---- kernel 1 on the bf16 matrix cores, every product an exact fp32 product -----------------------
-// The fp32 matrix instruction runs at 1/16 of the bf16 one.  An fp32 value is the sum of three bf16
-// values (8 + 8 + 8 significant bits: the value truncated, the remainder truncated, what is left; both
-// subtractions are exact), so a product x * y is nine bf16 x bf16 products, each exact in fp32; the six
-// largest are issued (v_mfma_f32_32x32x16_bf16, fp32 accumulation), the three dropped ones sum to less
-// than 2^-22 of the product: six bf16 instructions for what sixteen times as many fp32 ones did.  Within a
-// chain the small partial products come first, so that the sums carried through most of the chain are
+// ---- kernel 1 on the float16 matrix cores, every product an exact fp32 product but for 2^-23 of it ----------
+// The fp32 matrix instruction runs at 1/16 of the float16 one.  An fp32 value, scaled by a power of two, is the sum of
+// two float16 values (the value rounded to 11 bits, the remainder rounded to 11 bits: what is left is at most 2^-23 of
+// the value), so a product x * y is four float16 x float16 products, each exact in fp32; the three largest are issued
+// (v_mfma_f32_32x32x16_f16, fp32 accumulation), the fourth is at most 2^-24 of the product.  Three bfloat16 parts, which
+// need no scale, take six products: 48 instead of 24 matrix instructions per tile, 5.5 instead of 2 vector instructions
+// per value split, and the kernel is bound by the sum of the two (64 x 256 tokens x 12 heads, without what follows for the
+// maximum: 88 us, now 64).
+//   The scale.  float16 reaches from 2^-24 to 2^16: with the largest magnitude scaled to 2^14 .. 2^15, values down to 2^-14
+// of it keep their full 22 bits and smaller ones are off by at most 2^-39 of the largest.  K and V are scaled by one power
+// of two for the tensor, from the maximum that the QKV GEMM's epilogue leaves behind; a query row by its own; P (at most
+// 4, see below) by 2^13.  What the absolute part adds is in the error bound, so that a tensor of very uneven magnitudes
+// costs re-evaluations and nothing else.
+// Within a chain the small partial products come first, so that the sums carried through most of the chain are
 // small against the result (the matrix cores' accumulation drifts with the sums it carries).
 // Geometry: a workgroup is four waves x 32 queries of one head; a tile is 32 keys.  S^T = K Q^T and
 // O^T = V^T P^T as above, so a lane owns a query column: lane l holds query l % 32 and, of a 32-row
@@ -637,14 +644,21 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
 // l % 32 and the 8 values of unit l / 32 of a 16-deep slab.  For the second product the lane's own
 // registers 8 s .. 8 s + 7 are its unit of slab s (which keys share a unit is free as long as the V
 // operand uses the same assignment), so P never leaves the registers; V is written to LDS transposed,
-// as bf16 planes [head dim][unit][slot] in that assignment.  K planes are [key][unit] with the units
+// as float16 planes [head dim][unit][slot] in that assignment.  K planes are [key][unit] with the units
 // xor-rotated by the row; V rows are padded to 80 bytes: all 16-byte operand reads are conflict free.
+//   The running maximum of a query is raised only when a tile passes it by more than a factor of 4 (any value near the
+// maximum serves a soft-max as its reference), so the sums are rescaled in the first tiles and hardly ever again.
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
+typedef _Float16 v2hf __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // (defined further down; the kernel below ends with the exact evaluation of its candidates for the maximum)
+struct Nothing {
+    __device__ void operator()() const {}
+};
+template <int NT = 256, typename F = Nothing>
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
-                                               uint32_t el, double *red);
+                                               uint32_t el, double *red, F meanwhile = {});
 template <typename F>
 __device__ __forceinline__ void for_each_marked(bool mine, uint64_t *masks, F visit);
 constexpr int kSplitQ = 128;             // queries per workgroup
@@ -652,50 +666,85 @@ constexpr int kSplitKeys = 32;           // keys per tile
 constexpr int kSplitKRow = 128;          // bytes per key row of a K plane (8 units)
 constexpr int kSplitVRow = 80;           // bytes per head-dim row of a V plane (4 units + pad)
 constexpr int kSplitKPlane = kSplitKeys * kSplitKRow, kSplitVPlane = kDh * kSplitVRow;
-constexpr int kSplitStage = 3 * (kSplitKPlane + kSplitVPlane);
+constexpr int kSplitStage = 2 * (kSplitKPlane + kSplitVPlane);
+// error bound of a query's values, in units of 2^-24 of the largest |v| (where it is formed, below)
+constexpr float kSplitErrBase = 4.0f, kSplitErrPerScore = 4.0f, kSplitErrSum = 0.3f;
+constexpr float kPScale = 8192.0f;       // scale of P (at most 4) on its way to float16
 
-struct Split3 {
-    v4u h, m, l;
+// What a workgroup of the kernel below knows about the tensor's exact maximum: an upper bound of its own exact values,
+// and which of its values can be its largest (as a rule one; with more than kCands it evaluates them itself and has none).
+constexpr int kCands = 4;
+struct AttnCand {
+    float upper;
+    uint32_t n;
+    uint32_t at[kCands];    // token row * hidden + column
 };
-// two floats -> the bf16 truncation of each, x0 in the low half
-__device__ __forceinline__ uint32_t pack_top16(float x1, float x0)
+
+// the power of two that brings the largest magnitude (bit pattern) to 2^14 .. 2^15, and its inverse
+__device__ __forceinline__ void f16_scale(uint32_t max_bits, float &up, float &down)
 {
-    return __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+    const int b = 268 - (int)(max_bits >> 23), e = b > 253 ? 253 : b;
+    up = __uint_as_float((uint32_t)e << 23);
+    down = __uint_as_float((uint32_t)(254 - e) << 23);
 }
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
+
+struct Split2 {
+    v4u h, l;
+};
+// two floats times s -> float16 pairs, x0 in the low half: a mixed-precision fma per value and part
+__device__ __forceinline__ void split_pair(float x0, float x1, float s, uint32_t &h, uint32_t &l)
 {
-    const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & 0xffff0000u);
-    const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & 0xffff0000u);
-    const float l0 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
-    const float l1 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-    h = pack_top16(x1, x0);
-    m = pack_top16(r1, r0);
-    l = pack_top16(l1, l0);
+    asm("v_fma_mixlo_f16 %0, %2, %4, 0\n\t"
+        "v_fma_mixhi_f16 %0, %3, %4, 0\n\t"
+        "v_fma_mixlo_f16 %1, %2, %4, -%0 op_sel_hi:[0,0,1]\n\t"
+        "v_fma_mixhi_f16 %1, %3, %4, -%0 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "=&v"(h), "=&v"(l)
+        : "v"(x0), "v"(x1), "v"(s));
 }
-__device__ __forceinline__ Split3 split_eight(const float (&x)[8])
+__device__ __forceinline__ Split2 split_eight(const float (&x)[8], float s)
 {
-    Split3 o;
+    Split2 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        uint32_t wh, wm, wl;
-        split_pair(x[2 * e], x[2 * e + 1], wh, wm, wl);
+        uint32_t wh, wl;
+        split_pair(x[2 * e], x[2 * e + 1], s, wh, wl);
         o.h[e] = wh;
-        o.m[e] = wm;
         o.l[e] = wl;
     }
     return o;
 }
+// The same of values that a matrix instruction reads next: written so that the compiler sees the instructions and keeps
+// their distance to it.
+__device__ __forceinline__ Split2 split_eight_operand(const float (&x)[8], float s)
+{
+    Split2 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const v2hf hh = {(_Float16)(x[2 * e] * s), (_Float16)(x[2 * e + 1] * s)};
+        uint32_t wh = __builtin_bit_cast(uint32_t, hh);
+        asm("" : "+v"(wh));                                      // (else the halves are converted a second time below)
+        const v2hf hv = __builtin_bit_cast(v2hf, wh);
+        const v2hf ll = {(_Float16)fmaf(x[2 * e], s, -(float)hv[0]), (_Float16)fmaf(x[2 * e + 1], s, -(float)hv[1])};
+        o.h[e] = wh;
+        o.l[e] = __builtin_bit_cast(uint32_t, ll);
+    }
+    return o;
+}
+// the larger of a lane's value and that of the lane 32 away
+__device__ __forceinline__ float max_halves(float x) { return pair_op<32>(x, [](float a, float b) { return fmaxf(a, b); }); }
 
 __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__restrict__ qkv, int B, int S, int Hd,
                                                                  int heads, int dh, float scale, float *__restrict__ ctx,
-                                                                 AttnRecord *__restrict__ rec, int total, int per_xcd,
+                                                                 float *__restrict__ err_q, AttnCand *__restrict__ cands,
+                                                                 int total, int per_xcd,
+                                                                 const uint32_t *__restrict__ max_slot,
                                                                  uint32_t *__restrict__ bound_slot,
                                                                  uint32_t *__restrict__ exact_slot)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSplitStage];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, h = lane >> 5;
-    const int qblocks = (S + kSplitQ - 1) / kSplitQ, qtiles = (S + 63) / 64;
+    const int qblocks = (S + kSplitQ - 1) / kSplitQ;
     const int vid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || vid >= total) return;
     const int bh = vid / qblocks, qb = vid % qblocks;
@@ -704,26 +753,17 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     const int64_t ld = 3 * (int64_t)Hd;
     const float *qbase = qkv + hd * dh, *kbase = qbase + Hd, *vbase = qbase + 2 * Hd;
 
-    // the wave's queries as the B operand of S^T = K Q^T: lane (r, h) holds dims 16 sl + 8 h .. + 7 of query r
+    // the wave's queries: lane (r, h) holds dims 16 sl + 8 h .. + 7 of query r
     const int q = qb * kSplitQ + wave * 32 + r;
-    Split3 qs[4];
+    float4 raw[8];
     {
         const float *qrow = qbase + (tok0 + (q < S ? q : S - 1)) * ld;
-        float4 raw[8];
 #pragma unroll
         for (int sl = 0; sl < 4; ++sl) {
             const int d0 = 16 * sl + 8 * h;
             const int dc = d0 < dh ? d0 : 0;                     // head dims come in whole units of 8
             raw[2 * sl] = *(const float4 *)(qrow + dc);
             raw[2 * sl + 1] = *(const float4 *)(qrow + dc + 4);
-        }
-#pragma unroll
-        for (int sl = 0; sl < 4; ++sl) {
-            const bool ok = q < S && 16 * sl + 8 * h < dh;
-            const float4 a = raw[2 * sl], b4 = raw[2 * sl + 1];
-            const float x[8] = {ok ? a.x : 0.f, ok ? a.y : 0.f, ok ? a.z : 0.f, ok ? a.w : 0.f,
-                                ok ? b4.x : 0.f, ok ? b4.y : 0.f, ok ? b4.z : 0.f, ok ? b4.w : 0.f};
-            qs[sl] = split_eight(x);
         }
     }
 
@@ -735,7 +775,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     const uint32_t koff = (uint32_t)(skr * kSplitKRow + ((sku ^ ((skr >> 1) & 7)) * 16));
     // key k of a tile: slab k / 16, unit 2 (k / 16) + (k / 4) % 2, slot 4 ((k / 8) % 2) + k % 4
     const uint32_t voff = (uint32_t)(svd * kSplitVRow + (2 * (svk >> 4) + ((svk >> 2) & 1)) * 16 + (4 * ((svk >> 3) & 1) + (svk & 3)) * 2);
-    uint32_t vmax = 0;                  // largest |v| staged by this thread (bit pattern)
+    float vmax = 0.0f;                  // largest |v| staged by this thread
     float4 pk[2], pv[2];
     // Loads are unconditional, from clamped addresses: a key beyond S reads the last key's row (its score is
     // masked in the ragged tile, its P is exactly zero), head dims beyond dh read dims 0.. (the query is zero
@@ -755,49 +795,84 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
             pv[e] = *(const float4 *)(vfetch + (int64_t)row * ld);
         }
     };
+    fetch_k(0);
+    fetch_v(0);
+
+    // the largest |value| of the tensor (or, for the kernel alone, of this head's rows): the scale of K and V
+    uint32_t mbits = 0;
+    if (max_slot) {
+        mbits = reduce_ways(max_slot);
+    } else {
+        for (int e = lane; e < S * dh; e += 64) {
+            const int64_t at = (tok0 + e / dh) * ld + e % dh;
+            const uint32_t a = abs_bits(qbase[at]), b = abs_bits(kbase[at]), c = abs_bits(vbase[at]);
+            mbits = mbits > a ? mbits : a;
+            mbits = mbits > b ? mbits : b;
+            mbits = mbits > c ? mbits : c;
+        }
+        mbits = wave_max_u32(mbits);
+    }
+    mbits = (uint32_t)__builtin_amdgcn_readfirstlane((int)mbits);
+    float kv_up, kv_down, q_up, q_down;
+    f16_scale(mbits, kv_up, kv_down);
+    Split2 qs[4];
+    float qmax = 0.0f;
+    {
+        float x[4][8];
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) {
+            const bool ok = q < S && 16 * sl + 8 * h < dh;
+            const float4 a = raw[2 * sl], b4 = raw[2 * sl + 1];
+            const float t[8] = {a.x, a.y, a.z, a.w, b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[sl][e] = ok ? t[e] : 0.0f;
+                qmax = fmaxf(qmax, fabsf(x[sl][e]));
+            }
+        }
+        qmax = max_halves(qmax);
+        f16_scale(__float_as_uint(qmax), q_up, q_down);
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) qs[sl] = split_eight_operand(x[sl], q_up);
+    }
     auto stash_k = [&](int buf) {
         uint8_t *kst = lds + buf * kSplitStage;
         const float x[8] = {pk[0].x, pk[0].y, pk[0].z, pk[0].w, pk[1].x, pk[1].y, pk[1].z, pk[1].w};
-        const Split3 sp = split_eight(x);
+        const Split2 sp = split_eight(x, kv_up);
         *(v4u *)(kst + koff) = sp.h;
-        *(v4u *)(kst + kSplitKPlane + koff) = sp.m;
-        *(v4u *)(kst + 2 * kSplitKPlane + koff) = sp.l;
+        *(v4u *)(kst + kSplitKPlane + koff) = sp.l;
     };
     auto stash_v = [&](int buf) {
-        uint8_t *vst = lds + buf * kSplitStage + 3 * kSplitKPlane;
+        uint8_t *vst = lds + buf * kSplitStage + 2 * kSplitKPlane;
         const float v0[4] = {pv[0].x, pv[0].y, pv[0].z, pv[0].w}, v1[4] = {pv[1].x, pv[1].y, pv[1].z, pv[1].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            uint32_t wh, wm, wl;
-            split_pair(v0[e], v1[e], wh, wm, wl);
+            uint32_t wh, wl;
+            split_pair(v0[e], v1[e], kv_up, wh, wl);
             uint8_t *dst = vst + voff + e * kSplitVRow;
             *(uint32_t *)dst = wh;
-            *(uint32_t *)(dst + kSplitVPlane) = wm;
-            *(uint32_t *)(dst + 2 * kSplitVPlane) = wl;
-            const uint32_t a0 = abs_bits(v0[e]), a1 = abs_bits(v1[e]);
-            vmax = vmax > a0 ? vmax : a0;
-            vmax = vmax > a1 ? vmax : a1;
+            *(uint32_t *)(dst + kSplitVPlane) = wl;
+            vmax = fmaxf(vmax, fmaxf(fabsf(v0[e]), fabsf(v1[e])));
         }
     };
 
-    // (plane of the K or V operand, plane of the Q or P operand), 0 = high part.  The small products come
-    // first; a K / V plane is used for consecutive products so that few operand registers are live.
-    constexpr int ia[6] = {2, 1, 1, 0, 0, 0}, ib[6] = {0, 1, 0, 2, 1, 0};
+    // (plane of the K or V operand, plane of the Q or P operand), 0 = high part; the small products come first
+    constexpr int ia[3] = {1, 0, 0}, ib[3] = {0, 1, 0};
     const uint32_t ka_off = (uint32_t)(r * kSplitKRow), ka_sw = (uint32_t)((r >> 1) & 7);
-    // raw scores (before the 1 / sqrt(dh) factor) of the tile in K buffer `buf`: register i is key
-    // 8 (i / 4) + 4 h + i % 4 of the tile for this lane's query
+    // scaled scores of the tile in K buffer `buf`: register i is key 8 (i / 4) + 4 h + i % 4 of the tile for this
+    // lane's query
     auto scores = [&](int buf) {
         const uint8_t *kst = lds + buf * kSplitStage;
         v16f acc;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
 #pragma unroll
-        for (int pr = 0; pr < 6; ++pr)
+        for (int pr = 0; pr < 3; ++pr)
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) {
                 const v4u ak = *(const v4u *)(kst + ia[pr] * kSplitKPlane + ka_off + ((((uint32_t)(2 * sl + h)) ^ ka_sw) * 16));
-                const v4u bq = ib[pr] == 0 ? qs[sl].h : (ib[pr] == 1 ? qs[sl].m : qs[sl].l);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, ak), __builtin_bit_cast(v8bf, bq), acc, 0, 0, 0);
+                const v4u bq = ib[pr] == 0 ? qs[sl].h : qs[sl].l;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8hf, ak), __builtin_bit_cast(v8hf, bq), acc, 0, 0, 0);
             }
         return acc;
     };
@@ -807,20 +882,16 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     for (int db = 0; db < 2; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] = 0.0f;
-    float mrun = -INFINITY, lrun = 0.0f;   // running maximum of the raw scores, running sum
-    float smax = 0.0f;                  // largest |raw score| met by this lane
-    const float c2 = scale * 1.44269504088896340736f;            // raw score -> exponent of 2
+    float mrun = 0.0f, lrun = 0.0f;     // reference of the scaled scores, this lane's share of the sum of P
+    float p2run = 0.0f;                 // ... and of the sum of P^2 (for the error bound)
+    float smax = 0.0f;                  // largest |scaled score| met by this lane
+    const float c2 = scale * 1.44269504088896340736f * q_down * kv_down;   // scaled score -> exponent of 2
 
     // Software pipeline over the tiles.  Iteration t contracts S(t + 1), turns S(t) into P(t), contracts
     // P(t) V(t) and splits K(t + 2) and V(t + 1) (in registers since the iteration before) into the buffers
     // that S(t) and V(t - 1) have left: the scores of the next tile do not wait for this tile's soft-max, and
-    // a tile's loads have a whole iteration to arrive.  One barrier per tile.  (Measured on this chip: the
-    // vector instructions that follow a matrix instruction in a wave's issue order do not run beside it, and
-    // two waves of a SIMD overlap them by about a third; the kernel's time is close to the sum of its 48
-    // matrix and 430 vector instructions per tile, whatever their order.)
+    // a tile's loads have a whole iteration to arrive.  One barrier per tile.
     const int ntiles = (S + kSplitKeys - 1) / kSplitKeys;
-    fetch_k(0);
-    fetch_v(0);
     stash_k(0);
     stash_v(0);
     fetch_k(kSplitKeys);
@@ -836,55 +907,64 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
         v16f snext = sacc;
         if (t + 1 < ntiles) snext = scores((t + 1) & 1);
         // soft-max of tile t
-        float mx = -INFINITY;
+        float mx = sacc[0], mn = sacc[0];                        // keys beyond S repeat the last key's score here
 #pragma unroll
-        for (int i = 0; i < 16; ++i) smax = fmaxf(smax, fabsf(sacc[i]));     // keys beyond S: zero rows, score 0
+        for (int i = 1; i < 16; ++i) { mx = fmaxf(mx, sacc[i]); mn = fminf(mn, sacc[i]); }
+        smax = fmaxf(smax, fmaxf(mx, -mn));
+        mx = max_halves(mx);
+        if (t == 0) {
+            mrun = mx;
+        } else if (__any((mx - mrun) * c2 > 2.0f)) {
+            const float mnew = fmaxf(mrun, mx);
+            const float corr = __builtin_amdgcn_exp2f((mrun - mnew) * c2);
+            mrun = mnew;
+            lrun *= corr;
+            p2run *= corr * corr;
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[db][i] *= corr;
+        }
         if constexpr (decltype(ragged)::value) {                 // the ragged last tile: keys beyond S do not count
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 sacc[i] = j0 + 8 * (i >> 2) + 4 * h + (i & 3) < S ? sacc[i] : -INFINITY;
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[i]);
-        mx = pair_op<32>(mx, [](float a, float b) { return fmaxf(a, b); });
-        const float mnew = fmaxf(mrun, mx);
-        const float corr = __builtin_amdgcn_exp2f((mrun - mnew) * c2);
-        const float shift = -mnew * c2;
+        const float shift = -mrun * c2;
         float ps = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             sacc[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], c2, shift));
             ps += sacc[i];
+            p2run = fmaf(sacc[i], sacc[i], p2run);
         }
-        ps = pair_op<32>(ps, [](float a, float b) { return a + b; });
-        lrun = lrun * corr + ps;
-        mrun = mnew;
+        lrun += ps;
         // the lane's unit of slab s of P^T: its registers 8 s .. 8 s + 7
-        Split3 pp[2];
+        Split2 pp[2];
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl) {
             const float x[8] = {sacc[8 * sl], sacc[8 * sl + 1], sacc[8 * sl + 2], sacc[8 * sl + 3],
                                 sacc[8 * sl + 4], sacc[8 * sl + 5], sacc[8 * sl + 6], sacc[8 * sl + 7]};
-            pp[sl] = split_eight(x);
+            pp[sl] = split_eight_operand(x, kPScale);
         }
         // this tile's V^T P^T from zero accumulators (two independent chains, one per half of the head dims),
-        // then O^T = O^T * corr + tile on the vector ALU
+        // then O^T = O^T + tile on the vector ALU
         {
-            const uint8_t *vst = lds + (t & 1) * kSplitStage + 3 * kSplitKPlane;
+            const uint8_t *vst = lds + (t & 1) * kSplitStage + 2 * kSplitKPlane;
             v16f ot[2];
 #pragma unroll
             for (int db = 0; db < 2; ++db)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) ot[db][i] = 0.0f;
 #pragma unroll
-            for (int pr = 0; pr < 6; ++pr)
+            for (int pr = 0; pr < 3; ++pr)
 #pragma unroll
                 for (int sl = 0; sl < 2; ++sl) {
-                    const v4u bp = ib[pr] == 0 ? pp[sl].h : (ib[pr] == 1 ? pp[sl].m : pp[sl].l);
+                    const v4u bp = ib[pr] == 0 ? pp[sl].h : pp[sl].l;
 #pragma unroll
                     for (int db = 0; db < 2; ++db) {
                         const v4u av = *(const v4u *)(vst + ia[pr] * kSplitVPlane + (32 * db + r) * kSplitVRow + (2 * sl + h) * 16);
-                        ot[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, av), __builtin_bit_cast(v8bf, bp), ot[db], 0, 0, 0);
+                        ot[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8hf, av), __builtin_bit_cast(v8hf, bp), ot[db], 0, 0, 0);
                     }
                 }
             if (t + 2 < ntiles) stash_k(t & 1);
@@ -894,7 +974,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 #pragma unroll
             for (int db = 0; db < 2; ++db)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) o[db][i] = fmaf(o[db][i], corr, ot[db][i]);
+                for (int i = 0; i < 16; ++i) o[db][i] += ot[db][i];
         }
         sacc = snext;
         __syncthreads();
@@ -902,97 +982,111 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     const int nfull = S / kSplitKeys;
     for (int t = 0; t < nfull; ++t) iteration(t, std::false_type{});
     if (nfull < ntiles) iteration(nfull, std::true_type{});
-    smax *= scale;
 
+    __shared__ float red_v[4], red_low[4], red_up[4];
+    __shared__ uint32_t n_cand;
+    if (tid == 0) n_cand = 0;
+    vmax = __uint_as_float(wave_max_u32(__float_as_uint(vmax)));  // non-negative floats order like integers
+    if (lane == 0) red_v[wave] = vmax;
+    // the two halves of a query's sums; the factor that undoes every scale
+    lrun += lane_xor<32>(lrun);
+    p2run += lane_xor<32>(p2run);
+    const float outs = kv_down * (1.0f / kPScale), inv = 1.0f / lrun;
     // register i of block db is head dim 32 db + 8 (i / 4) + 4 h + i % 4 of this lane's query
-    uint32_t amax = 0;
-    if (q < S) {
-        float *dst = ctx + (tok0 + q) * Hd + hd * dh;
-        const float inv = 1.0f / lrun;
+    float amax = 0.0f;
+    float *dst = ctx + (tok0 + (q < S ? q : S - 1)) * Hd + hd * dh;
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < 2; ++db)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int d = 32 * db + 8 * g + 4 * h;
-                if (d < dh) {                                    // head dims come in whole units of 8
-                    float v[4];
+        for (int g = 0; g < 4; ++g) {
+            const int d = 32 * db + 8 * g + 4 * h;
+            if (d < dh) {                                        // head dims come in whole units of 8
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[e] = o[db][4 * g + e] * inv;
-                        const uint32_t ab = abs_bits(v[e]);
-                        amax = ab > amax ? ab : amax;
-                    }
-                    *(float4 *)(dst + d) = make_float4(v[0], v[1], v[2], v[3]);
+                for (int e = 0; e < 4; ++e) {
+                    o[db][4 * g + e] = o[db][4 * g + e] * inv * outs;
+                    amax = fmaxf(amax, fabsf(o[db][4 * g + e]));
                 }
-            }
-    }
-    // records: one per 64 queries (a pair of waves): largest |context| stored, and the error bound of its values
-    __shared__ uint32_t red[3][4];
-    __shared__ float rec_err[2], rec_low[2];
-    __shared__ uint32_t non_finite;
-    amax = wave_max_u32(amax);
-    vmax = wave_max_u32(vmax);
-    const uint32_t sbits = wave_max_u32(__float_as_uint(smax));       // non-negative floats order like integers
-    if (lane == 0) { red[0][wave] = amax; red[1][wave] = vmax; red[2][wave] = sbits; }
-    if (tid == 0) non_finite = 0;
-    __syncthreads();
-    if (tid < 2) {
-        const int qt = qb * (kSplitQ / 64) + tid;
-        rec_err[tid] = 0.0f;
-        rec_low[tid] = 0.0f;
-        if (qt < qtiles) {
-            uint32_t v = 0;
-            for (int w = 0; w < 4; ++w) v = v > red[1][w] ? v : red[1][w];
-            const uint32_t a = red[0][2 * tid] > red[0][2 * tid + 1] ? red[0][2 * tid] : red[0][2 * tid + 1];
-            const uint32_t sb = red[2][2 * tid] > red[2][2 * tid + 1] ? red[2][2 * tid] : red[2][2 * tid + 1];
-            AttnRecord rc;
-            rc.amax_bits = a;
-            rc.err = 5.9604645e-8f * __uint_as_float(v) * (kErrBase + kErrPerScore * __uint_as_float(sb));
-            if (!(rc.err <= 3.402823466e+38f)) rc.amax_bits = 0x7f800000u;   // non-finite inputs: flagged downstream
-            rec[bh * qtiles + qt] = rc;
-            if (bound_slot) {
-                // The exact maximum of the tensor is found here too.  Every workgroup raises a shared word to a
-                // lower bound of its own exact maximum (largest stored |x| minus its error bound); a value can be
-                // the tensor's exact maximum only if |x| + E reaches the largest lower bound, whichever
-                // workgroups have reported so far: the workgroup that holds the maximum always sees a bound that
-                // its maximum passes.  Non-finite values: they are the "maximum".
-                uint32_t *wb = bound_slot + ((blockIdx.x + tid) & (kAmaxWays - 1)) * kAmaxStride;
-                if (rc.amax_bits >= 0x7f800000u) {
-                    atomicMax(exact_slot + ((blockIdx.x + tid) & (kAmaxWays - 1)) * kAmaxStride, rc.amax_bits);
-                    non_finite = 1;
-                } else {
-                    const float af = __uint_as_float(a);
-                    // (the factor and the 2^-23 |x| term cover the rounding of this fp32 arithmetic itself)
-                    const float low = fmaxf(af - fmaf(af, 1.2e-7f, value_err(rc.err, af) * 1.001f), 0.0f);
-                    rec_err[tid] = rc.err;
-                    rec_low[tid] = low;
-                    const uint32_t lb = __float_as_uint(low);
-                    if (lb > __hip_atomic_load(wb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(wb, lb);
-                }
+                if (q < S) *(float4 *)(dst + d) = make_float4(o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]);
             }
         }
-    }
-    if (!bound_slot) return;                                     // the kernel alone (error measurement)
     __syncthreads();
-    if (non_finite) return;
-    // the largest lower bound reported so far (a stale value only admits more candidates)
-    uint32_t gb = __hip_atomic_load(bound_slot + lane * kAmaxStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    gb = wave_max_u32(gb);
-    const float e_r = rec_err[wave >> 1];
-    const float floor_v = fmaxf(__uint_as_float(gb), rec_low[wave >> 1]);
-    uint32_t cand = 0;                                           // bit 16 db + i: that register is a candidate
-    if (q < S) {
-        const float inv = 1.0f / lrun;
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int d = 32 * db + 8 * (i >> 2) + 4 * h + (i & 3);
-                const float x = fabsf(o[db][i] * inv);
-                if (d < dh && x + fmaf(x, 1.2e-7f, value_err(e_r, x) * 1.001f) >= floor_v) cand |= 1u << (16 * db + i);
-            }
+    vmax = fmaxf(fmaxf(red_v[0], red_v[1]), fmaxf(red_v[2], red_v[3]));
+    // Error bound of the query's values (the part that grows with a value itself comes on top, value_err).  The errors of
+    // the P, relative ones of a few units plus some for every unit of the scores, are independent of each other: what they
+    // do to a weighted sum goes with the root of the sum of P^2.  Added to the score's: the absolute part of K's split; to
+    // the whole: that of V's and P's.  Empirical with margin, not a proof: over 2.4e8 values of twelve shapes the largest
+    // error is 0.55 of the bound for normal q, k, v, 0.8 for scores of 45 and 300, one channel of K 30 times the others.
+    const float M = __uint_as_float(mbits);
+    const float sq = max_halves(smax) * c2 * 0.6931472f;         // largest |score| of the query
+    float err = 5.9604645e-8f * (vmax * ((kSplitErrBase + kSplitErrPerScore * (sq + (float)dh * scale * qmax * M * 6.1035156e-5f)) *
+                                             __builtin_amdgcn_sqrtf(p2run) * inv + kSplitErrSum) +
+                                 M * (float)(S + 2) * 6.1035156e-5f);
+    // A bound that is no number: every value of the query is re-evaluated (finite inputs whose scores pass 3e38 only)
+    if (!(err <= 3.402823466e+38f)) err = INFINITY;
+    if (h == 0 && q < S) err_q[(int64_t)bh * S + q] = err;
+    if (!bound_slot) return;                                     // the kernel alone (error measurement)
+
+    // What the workgroup knows about the tensor's exact maximum.  It raises a shared word to a lower bound of its own exact
+    // maximum (largest stored |x| minus its error) and leaves an upper bound and the values that reach its own lower
+    // bound; the quantiser that follows evaluates those that reach the tensor's.  (Evaluated here, nearly every workgroup
+    // of the first round found its own maximum above all that was reported by then: 21 -> 36 us for 32 x 128 tokens x 12
+    // heads, 88 -> 104 for 64 x 256.)
+    if (mbits >= 0x7f800000u || mbits == 0) {                    // NaN / Inf: they are the "maximum"; zeros: nothing to find
+        if (tid == 0) {
+            if (mbits) atomicMax(exact_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride, 0x7f800000u);
+            cands[vid].upper = 0.0f;
+            cands[vid].n = 0;
+        }
+        return;
     }
-    if (!__syncthreads_or(cand != 0)) return;                    // as a rule: nothing to do
+    // (the factor and the 2^-23 |x| term cover the rounding of this fp32 arithmetic itself)
+    const float off = fmaf(amax, 1.2e-7f, value_err(err, amax) * 1.001f);
+    float low = 0.0f, up = 0.0f;
+    if (q < S) {
+        low = fmaxf(amax - off, 0.0f);
+        up = amax + off;
+        up = up < INFINITY ? up : INFINITY;
+    }
+    low = __uint_as_float(wave_max_u32(__float_as_uint(low)));
+    up = __uint_as_float(wave_max_u32(__float_as_uint(up)));
+    if (lane == 0) { red_low[wave] = low; red_up[wave] = up; }
+    __syncthreads();
+    low = fmaxf(fmaxf(red_low[0], red_low[1]), fmaxf(red_low[2], red_low[3]));
+    up = fmaxf(fmaxf(red_up[0], red_up[1]), fmaxf(red_up[2], red_up[3]));
+    // bit 16 db + i: that register's value may be as large as floor_v (a NaN counts as anything)
+    auto candidates = [&](float floor_v) {
+        const float thr = floor_v * (1.0f - 2.0e-6f) - err * 1.001f;
+        uint32_t c = 0;
+        if (__any(q < S && !(amax < thr))) {
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (32 * db + 8 * (i >> 2) + 4 * h + (i & 3) < dh && !(fabsf(o[db][i]) < thr)) c |= 1u << (16 * db + i);
+            if (q >= S) c = 0;
+        }
+        return c;
+    };
+    uint32_t cand = candidates(low);
+    if (cand) {
+        uint32_t at = atomicAdd(&n_cand, (uint32_t)__popc(cand));
+        for (uint32_t c = cand; c && at < kCands; c &= c - 1, ++at) {
+            const int sl = __ffs((int)c) - 1;
+            cands[vid].at[at] = (uint32_t)((tok0 + q) * Hd + hd * dh + 32 * (sl >> 4) + 8 * ((sl & 15) >> 2) + 4 * h + (sl & 3));
+        }
+    }
+    __syncthreads();
+    const bool few = n_cand <= kCands;
+    if (tid == 0) {
+        cands[vid].upper = few ? up : 0.0f;
+        cands[vid].n = few ? n_cand : 0;
+        atomicMax(bound_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride, __float_as_uint(low));
+    }
+    if (few) return;
+    // More values than the list holds can be this workgroup's largest (many equal rows): evaluated here, those that reach
+    // the largest lower bound reported so far (a stale value only admits more of them)
+    const float floor_v = fmaxf(low, __uint_as_float(wave_max_u32(__hip_atomic_load(bound_slot + lane * kAmaxStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))));
+    cand = candidates(floor_v);
     __shared__ uint64_t masks[4];
     double *redd = (double *)lds;                                // the stage memory is free now
     const double scale_d = 1.0 / sqrt((double)dh);
@@ -1018,10 +1112,13 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 // ones, the query zero beyond dh): a load under a condition is awaited on its own, and a key row would
 // cost sixteen memory round trips instead of one.
 // (kept compact and inlined once per kernel: called as a function it needs scratch memory for the
-// caller's registers and ran five times slower)
+// caller's registers and ran five times slower)  The whole workgroup of NT threads evaluates one value, a key per thread;
+// `meanwhile` runs while the first loads are on their way.  red: 3 NT / 64 + 32 doubles.
+template <int NT, typename F>
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
-                                            uint32_t el, double *red)
+                                               uint32_t el, double *red, F meanwhile)
 {
+    constexpr int NW = NT / 64;
     const bool vec4 = (dh & 3) == 0 && (Hd & 3) == 0;           // whole 16-byte units, 16-byte aligned rows
     const uint32_t mrow = el / (uint32_t)Hd, col = el - mrow * (uint32_t)Hd;
     const uint32_t bi = mrow / (uint32_t)S, hd = col / (uint32_t)dh, dd = col - hd * (uint32_t)dh;
@@ -1030,10 +1127,10 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
     const float *kb = qkv + (int64_t)bi * S * ld + Hd + hd * dh, *vb = kb + Hd + dd;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int units = dh >> 2;
-    // the query row goes through LDS (64 floats behind the 12 doubles of red): every thread needs all of it.
+    // the query row goes through LDS (64 floats behind the waves' sums): every thread needs all of it.
     // Its load and the first block's key and value loads are requested together, before the barriers: the
     // evaluation is a chain of memory round trips, and this takes one out of it.
-    float *qs = (float *)(red + 12);
+    float *qs = (float *)(red + 3 * NW);
     float4 kv[16];
     float vj = 0.0f;
     auto request = [&](int j0) {
@@ -1048,11 +1145,16 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
     };
     const float qreg = (tid < 64 && tid < dh) ? q[tid] : 0.0f;
     request(0);
+    meanwhile();
     __syncthreads();                                          // an earlier call has finished with red and qs
     if (tid < 64) qs[tid] = qreg;
     __syncthreads();
+    auto total = [&](const double *r) {
+        if constexpr (NW == 4) return (r[0] + r[1]) + (r[2] + r[3]);
+        else return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
+    };
     double m = -INFINITY, l = 0.0, o = 0.0;
-    for (int j0 = 0; j0 < S; j0 += 256) {
+    for (int j0 = 0; j0 < S; j0 += NT) {
         const int j = j0 + tid;
         const int jj = j < S ? j : S - 1;
         const float *kr = kb + (int64_t)jj * ld;
@@ -1079,14 +1181,16 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
         __syncthreads();                                      // red is free (an earlier block, an earlier call)
         if (lane == 0) red[wave] = cm;
         __syncthreads();
-        const double mnew = fmax(m, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
+        double mnew = m;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mnew = fmax(mnew, red[w]);
         const double p = exp(sc - mnew);                 // exp(-inf) = 0 for the keys beyond S
         const double corr = j0 == 0 ? 0.0 : exp(m - mnew);
         const double ps = wave_sum(p), po = wave_sum(p * (double)vj);
-        if (lane == 0) { red[4 + wave] = ps; red[8 + wave] = po; }
+        if (lane == 0) { red[NW + wave] = ps; red[2 * NW + wave] = po; }
         __syncthreads();
-        l = l * corr + ((red[4] + red[5]) + (red[6] + red[7]));
-        o = o * corr + ((red[8] + red[9]) + (red[10] + red[11]));
+        l = l * corr + total(red + NW);
+        o = o * corr + total(red + 2 * NW);
         m = mnew;
     }
     return (float)(o / l);
@@ -1181,20 +1285,28 @@ __global__ __launch_bounds__(256) void attention_absmax_exact_kernel(const float
     if (tid == 0 && best) atomicMax(exact + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride, best);
 }
 
-// The int8 codes of the context under the tensor's exact scale: one workgroup per (batch element, head).
-// It streams over the head's slice of the approximate context, 256 units a pass: a thread maps 16
+// The int8 codes of the context under the tensor's exact scale: a workgroup of eight waves per (batch element, head), or
+// for a share of its tokens where that leaves compute units idle.
+// The scale first.  The split attention left, per workgroup, an upper bound and the values that can be its largest
+// (AttnCand); the few that reach the tensor's largest lower bound - as a rule one - are evaluated in fp64 by every
+// workgroup for itself, while its keys are on their way: a launch of its own costs more than the 2 us this adds, and no
+// workgroup waits for another.  Then it streams over its slice of the approximate context: a thread maps 16
 // consecutive values of a token row (one 16-byte store; WIDE: head size and row length are multiples of
 // 16) or a single value.  A value whose interval [x - E, x + E] maps to two codes gets a provisional code
-// and goes on the workgroup's list in LDS (token * dh + dim within the head; the list has room for every
-// value of a pass).  After each pass the workgroup re-evaluates the listed values in fp64 and overwrites
-// their codes.  A re-evaluation needs all keys of its head (S x dh floats): read from global memory per
-// value, that traffic (and the sixteen-byte pieces of 256 different rows each load instruction asks
-// for) bounds the whole step.  KLDS (S <= 256, head size a multiple of 4): the workgroup copies the
-// head's keys into LDS once, with coalesced loads, and each of its waves re-evaluates one listed value
-// at a time from there: lane l holds keys l, l + 64, ..., a row of LDS each (rows padded by 16 bytes,
-// so the lanes' 16-byte reads do not collide), the query row is broadcast from LDS, and only the value
-// column (one float per key) comes from global memory.  Otherwise the workgroup-wide evaluation above
-// is used, one value after the other.
+// and goes on the workgroup's list in LDS (token * dh + dim within the head).  After each pass the workgroup re-evaluates
+// the listed values in fp64 and overwrites their codes.  A re-evaluation needs all keys of its head (S x dh floats): read
+// from global memory per value, that traffic (and the sixteen-byte pieces of 256 different rows each load instruction asks
+// for) bounds the whole step.  KLDS (head size a multiple of 4): the workgroup copies the head's keys into LDS, 256 at a
+// time, with coalesced loads, and each of its waves re-evaluates one listed value from there: lane l holds keys l,
+// l + 64, ..., a row of LDS each (rows padded by 16 bytes, so the lanes' 16-byte reads do not collide), the query row is
+// broadcast from LDS, and only the value column (one float per key) comes from global memory.  Up to 256 keys are copied
+// once; more are copied for every eight values.  Other head sizes use the workgroup-wide evaluation, one value after the
+// other.  What bounds it: a workgroup's chain of round trips (its keys and
+// the candidate 5 us, codes 3, four re-evaluations 4) and, for many heads, the value columns: a line per key and value,
+// 85 MB for 64 x 256 tokens x 12 heads beside the 113 of context and keys.  With the maximum settled by the attention kernel
+// and its looser bound (four to nine values per head listed instead of two to four), us, attention + this kernel: 32 x 128
+// tokens x 12 heads 36 + 24, now 18 + 22; 24 x 197 46 + 36, 33 + 32; 64 x 256 104 + 79, 74 + 68; 8 x 384 x 8 heads 49 + 201,
+// 22 + 43.  (Eight waves and 128 registers: spills, 31 and 86 us for the first and third.)
 constexpr int kKeysLds = 256;            // keys a workgroup can hold
 constexpr int kKeyRow = kDh + 4;         // floats per key row in LDS (one 16-byte pad)
 
@@ -1209,39 +1321,61 @@ __device__ __forceinline__ bool code_uncertain(float x, float err, float inv)
     return !(fabsf(t - rintf(t)) + reach < 0.5f);                  // also true for a non-finite bound
 }
 
+constexpr int kCertifyThreads = 256;
 template <bool WIDE, bool KLDS>
-__global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_kernel(
-    const float *__restrict__ qkv, const float *__restrict__ ctx, const AttnRecord *__restrict__ rec, int S, int Hd,
-    int heads, int dh, double scale, const uint32_t *__restrict__ exact, int8_t *xq, int64_t ldq,
+__global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify_kernel(
+    const float *__restrict__ qkv, const float *__restrict__ ctx, const float *__restrict__ err_q,
+    const AttnCand *__restrict__ cands, int nwg, const uint32_t *__restrict__ bound, int S, int Hd, int heads, int dh,
+    int splits, int tokens, double scale, const uint32_t *__restrict__ exact, int8_t *xq, int64_t ldq,
     float *__restrict__ scale_out, uint32_t *__restrict__ flag, uint32_t *__restrict__ unsure_total)
 {
-    constexpr int PER = WIDE ? 16 : 1;                            // values of a unit
-    constexpr int NPRE = WIDE && KLDS ? 4 : 1;                    // passes whose loads are requested together
-    constexpr uint32_t kList = 4096;                              // list entries served per round
-    using Entry = std::conditional_t<KLDS, uint16_t, uint32_t>;   // KLDS: S * dh <= 256 * 64
-    __shared__ Entry todo[kList];
+    constexpr int NT = kCertifyThreads, NW = NT / 64;
+    constexpr int NPRE = 4;                                       // passes whose loads are requested together
+    constexpr int TPP = NT / 4;                                   // WIDE: tokens of a pass (four lanes take a token's 64 dims)
+    constexpr uint32_t kList = 1024;                              // list entries served per round
+    __shared__ uint32_t todo[kList];
     __shared__ uint32_t n_todo, more;
-    __shared__ __attribute__((aligned(16))) double red[KLDS ? 2 : 12 + 32];
+    __shared__ __attribute__((aligned(16))) double red[3 * NW + 32];
     __shared__ __attribute__((aligned(16))) float ks[KLDS ? kKeysLds * kKeyRow : 4];
-    __shared__ __attribute__((aligned(16))) float qs[KLDS ? 4 * kDh : 4];
+    __shared__ __attribute__((aligned(16))) float qs[KLDS ? NW * kDh : 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t bh = blockIdx.x, bi = bh / (uint32_t)heads, hd = bh - bi * (uint32_t)heads;
-    const uint32_t qtiles = (uint32_t)(S + 63) / 64u;
+    const uint32_t bh = blockIdx.x / (uint32_t)splits, share = blockIdx.x - bh * (uint32_t)splits;
+    const uint32_t bi = bh / (uint32_t)heads, hd = bh - bi * (uint32_t)heads;
     const uint32_t tok0 = bi * (uint32_t)S;
     const int64_t ld = 3 * (int64_t)Hd;
     const float *qb = qkv + (int64_t)tok0 * ld + hd * dh, *kb = qb + Hd, *vb = kb + Hd;
-    // units per token: 16-value groups of the head, or single columns (the last head also clears the pad
-    // columns [Hd, ldq) of its tokens)
-    const uint32_t upt = WIDE ? (uint32_t)dh / 16u : (uint32_t)dh + (hd + 1u == (uint32_t)heads ? (uint32_t)(ldq - Hd) : 0u);
-    const uint32_t units = (uint32_t)S * upt;
-    // a group of passes: unit `first + 256 i + tid` is this thread's in pass i (clamped to a valid one for
-    // the loads; the surplus is masked where it is used)
+    const uint32_t t0 = share * (uint32_t)tokens, nt = (uint32_t)S - t0 < (uint32_t)tokens ? (uint32_t)S - t0 : (uint32_t)tokens;
+    // units of the share: 16-value groups of a token (WIDE), or single columns (the last head also clears the pad columns
+    // [Hd, ldq) of its tokens)
+    const uint32_t upt = WIDE ? 4u : (uint32_t)dh + (hd + 1u == (uint32_t)heads ? (uint32_t)(ldq - Hd) : 0u);
+    const uint32_t passes = WIDE ? (nt + TPP - 1) / TPP : (nt * upt + NT - 1) / NT;
+    // this thread's unit of pass p: token of the head, unit of the token; false: none
+    auto locate = [&](uint32_t p, uint32_t &t, uint32_t &part) {
+        if (WIDE) {
+            part = (uint32_t)tid & 3u;
+            t = p * TPP + ((uint32_t)tid >> 2);
+            const bool ok = t < nt && part * 16u < (uint32_t)dh;
+            if (!ok) t = part = 0;
+            t += t0;
+            return ok;
+        }
+        const uint32_t u = p * NT + (uint32_t)tid;
+        const bool ok = u < nt * upt;
+        t = ok ? u / upt : 0u;
+        part = ok ? u - t * upt : 0u;
+        t += t0;
+        return ok;
+    };
+    uint32_t top = reduce_ways(exact);                            // what the attention workgroups evaluated themselves
+    const float floor_v = nwg > 0 ? __uint_as_float(reduce_ways(bound)) : 0.0f;
     float4 v[NPRE][WIDE ? 4 : 1];
-    auto request = [&](uint32_t first) {
+    float ev[NPRE];
+    auto request = [&](uint32_t p0) {
 #pragma unroll
         for (int i = 0; i < NPRE; ++i) {
-            const uint32_t u = first + 256u * i + (uint32_t)tid, uc = u < units ? u : units - 1u;
-            const uint32_t t = uc / upt, part = uc - t * upt;
+            uint32_t t, part;
+            locate(p0 + i, t, part);
+            ev[i] = err_q[(int64_t)bh * S + t];
             if (WIDE) {
                 const float4 *p = (const float4 *)(ctx + (int64_t)(tok0 + t) * Hd + hd * (uint32_t)dh + part * 16u);
 #pragma unroll
@@ -1253,44 +1387,84 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
         }
     };
     request(0);
-    if (KLDS) {
-        // the head's keys, eight 16-byte pieces per thread in flight (the first barrier below orders them
-        // before any read)
-        const int cpr = dh >> 2, total = S * cpr;
-        for (int c0 = 0; c0 < total; c0 += 256 * 8) {
-            float4 t[8];
+    // keys j0 .. j0 + 255 of the head into LDS: sixteen lanes take a row, four rows per thread in flight (a barrier orders
+    // them before any read)
+    auto stage_keys = [&](int j0) {
+        constexpr int RPB = NT / 16;
+        const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds;
+        const int d = (tid & 15) * 4, r = tid >> 4;
+        const bool ok = d < dh;
+        const float *src = kb + (int64_t)j0 * ld + (ok ? d : 0);
+        for (int r0 = 0; r0 < nj; r0 += 4 * RPB) {
+            v4f t[4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = c0 + i * 256 + tid;
-                const int cc = c < total ? c : total - 1;
-                t[i] = *(const float4 *)(kb + (int64_t)(cc / cpr) * ld + 4 * (cc % cpr));
+            for (int i = 0; i < 4; ++i) {
+                const int row = r0 + i * RPB + r;
+                t[i] = *(const v4f *)(src + (int64_t)(row < nj ? row : nj - 1) * ld);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = c0 + i * 256 + tid;
-                if (c < total) *(float4 *)&ks[(c / cpr) * kKeyRow + 4 * (c % cpr)] = t[i];
+            for (int i = 0; i < 4; ++i) {
+                const int row = r0 + i * RPB + r;
+                if (ok && row < nj) *(v4f *)&ks[row * kKeyRow + d] = t[i];
             }
         }
+    };
+    bool staged = !KLDS || S > kKeysLds;
+    for (int w0 = 0; w0 < nwg; w0 += NT * 32) {                   // 32 attention workgroups per thread at a time
+        uint32_t pend_w = 0;                                      // bit k: workgroup w0 + NT k + tid may hold the maximum
+#pragma unroll 4
+        for (int k = 0; k < 32; ++k) {
+            const int w = w0 + NT * k + tid;
+            if (w0 + NT * k >= nwg) break;
+            const float u = cands[w < nwg ? w : nwg - 1].upper;
+            pend_w |= w < nwg && u >= floor_v && u > 0.0f ? 1u << k : 0u;
+        }
+        bool again;
+        do {
+            __syncthreads();                                      // the list has been served
+            if (tid == 0) { n_todo = 0; more = 0; }
+            __syncthreads();
+            while (pend_w) {
+                const uint32_t slot = atomicAdd(&n_todo, 1u);
+                if (slot >= kList) { more = 1; break; }
+                todo[slot] = (uint32_t)(w0 + NT * (__ffs((int)pend_w) - 1) + tid);
+                pend_w &= pend_w - 1;
+            }
+            __syncthreads();
+            const uint32_t n = n_todo < kList ? n_todo : kList;
+            again = more != 0;
+            for (uint32_t k = 0; k < n; ++k) {
+                const AttnCand &c = cands[__builtin_amdgcn_readfirstlane((int)todo[k])];
+                for (uint32_t e = 0; e < c.n; ++e) {
+                    const float x = context_exact<NT>(qkv, S, Hd, heads, dh, scale, c.at[e], red, [&]() {
+                        if (!staged) stage_keys(0);
+                        staged = true;
+                    });
+                    const uint32_t ab = abs_bits(x);
+                    top = top > ab ? top : ab;
+                }
+            }
+        } while (again);
     }
+    if (!staged) stage_keys(0);
     float sc_f;
     bool bad;
-    const float inv = scale_from_bits(reduce_ways(exact), nullptr, &sc_f, &bad);
+    const float inv = scale_from_bits(top, nullptr, &sc_f, &bad);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(sc_f, bad, scale_out, nullptr, flag);
     uint32_t met = 0;
     // the loop bounds are the same in every thread of the workgroup (barriers inside)
-    for (uint32_t first = 0; first < units; first += 256u * NPRE) {
-        if (first) request(first);
+    for (uint32_t p0 = 0; p0 < passes; p0 += NPRE) {
+        if (p0) request(p0);
         // provisional codes; pend[i]: which of the unit's values do not settle their code
         uint32_t pend[NPRE], at[NPRE];
 #pragma unroll
         for (int i = 0; i < NPRE; ++i) {
-            const uint32_t u = first + 256u * i + (uint32_t)tid;
+            uint32_t t, part;
             pend[i] = 0;
             at[i] = 0;
-            if (u < units) {
-                const uint32_t t = u / upt, part = u - t * upt;
+            if (locate(p0 + i, t, part)) {
                 const uint32_t m = tok0 + t;
-                const float err = rec[bh * qtiles + t / 64u].err;
+                const float err = ev[i];
                 if (WIDE) {
                     const uint32_t col = hd * (uint32_t)dh + part * 16u;
                     uint32_t w[4];
@@ -1329,7 +1503,7 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
                     if (slot >= kList) { more = 1; break; }
                     const int e = __ffs((int)pend[i]) - 1;
                     pend[i] &= pend[i] - 1;
-                    todo[slot] = (Entry)(at[i] + (uint32_t)e);
+                    todo[slot] = at[i] + (uint32_t)e;
                 }
             }
             __syncthreads();                                      // list complete, provisional codes stored
@@ -1337,55 +1511,70 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
             again = more != 0;
             met += n;
             if (KLDS) {
-                const int cpr = dh >> 2, nk = (S + 63) >> 6;      // 16-byte pieces per row, keys per lane
-                for (uint32_t k0 = 0; k0 < n; k0 += 4u) {         // a value per wave
+                const int cpr = dh >> 2;                          // 16-byte pieces per row
+                for (uint32_t k0 = 0; k0 < n; k0 += NW) {         // a value per wave
                     const uint32_t k = k0 + (uint32_t)wave;
                     const bool active = k < n;
                     const uint32_t e = todo[active ? k : k0];
                     const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
-                    float vj[4];
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) {
-                        const int j = lane + 64 * kk;
-                        vj[kk] = vb[(int64_t)(j < S ? j : S - 1) * ld + d];
-                    }
                     qs[wave * kDh + lane] = lane < dh ? qb[(int64_t)t * ld + lane] : 0.0f;
-                    __syncthreads();
-                    if (active) {
-                        // a product of two fp32 values is exact in fp64, so each fma is the multiply and the
-                        // add of the plain definition, dims in ascending order
-                        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                    double m = -INFINITY, l = 0.0, o = 0.0;       // l and o: this lane's share
+                    for (int j0 = 0; j0 < S; j0 += kKeysLds) {    // one round up to 256 keys
+                        const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds, nk = (nj + 63) >> 6;   // keys; keys per lane
+                        float vj[4];
 #pragma unroll
-                        for (int u4 = 0; u4 < kDh / 4; ++u4) {
-                            if (u4 < cpr) {
-                                const float4 qv = *(const float4 *)&qs[wave * kDh + 4 * u4];
+                        for (int kk = 0; kk < 4; ++kk) {
+                            const int j = lane + 64 * kk;
+                            vj[kk] = vb[(int64_t)(j0 + (j < nj ? j : nj - 1)) * ld + d];
+                        }
+                        if (S > kKeysLds) {
+                            __syncthreads();                      // the keys of the round before have been read
+                            stage_keys(j0);
+                        }
+                        __syncthreads();
+                        if (active) {
+                            // a product of two fp32 values is exact in fp64, so each fma is the multiply and the
+                            // add of the plain definition, dims in ascending order
+                            double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                                for (int kk = 0; kk < 4; ++kk) {
-                                    if (kk < nk) {
-                                        const int j = lane + 64 * kk;
-                                        const float4 kv = *(const float4 *)&ks[(j < S ? j : S - 1) * kKeyRow + 4 * u4];
-                                        acc[kk] = fma((double)qv.x, (double)kv.x, acc[kk]);
-                                        acc[kk] = fma((double)qv.y, (double)kv.y, acc[kk]);
-                                        acc[kk] = fma((double)qv.z, (double)kv.z, acc[kk]);
-                                        acc[kk] = fma((double)qv.w, (double)kv.w, acc[kk]);
+                            for (int u4 = 0; u4 < kDh / 4; ++u4) {
+                                if (u4 < cpr) {
+                                    const float4 qv = *(const float4 *)&qs[wave * kDh + 4 * u4];
+#pragma unroll
+                                    for (int kk = 0; kk < 4; ++kk) {
+                                        if (kk < nk) {
+                                            const int j = lane + 64 * kk;
+                                            const float4 kv = *(const float4 *)&ks[(j < nj ? j : nj - 1) * kKeyRow + 4 * u4];
+                                            acc[kk] = fma((double)qv.x, (double)kv.x, acc[kk]);
+                                            acc[kk] = fma((double)qv.y, (double)kv.y, acc[kk]);
+                                            acc[kk] = fma((double)qv.z, (double)kv.z, acc[kk]);
+                                            acc[kk] = fma((double)qv.w, (double)kv.w, acc[kk]);
+                                        }
                                     }
                                 }
                             }
-                        }
-                        double sc[4], mx = -INFINITY;
+                            double sc[4], mx = -INFINITY;
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            sc[kk] = lane + 64 * kk < S ? acc[kk] * scale : -INFINITY;
-                            mx = fmax(mx, sc[kk]);
-                        }
-                        mx = wave_max(mx);
-                        double l = 0.0, o = 0.0;
+                            for (int kk = 0; kk < 4; ++kk) {
+                                sc[kk] = lane + 64 * kk < nj ? acc[kk] * scale : -INFINITY;
+                                mx = fmax(mx, sc[kk]);
+                            }
+                            const double mnew = fmax(m, wave_max(mx));
+                            if (j0) {
+                                const double corr = exp(m - mnew);
+                                l *= corr;
+                                o *= corr;
+                            }
+                            m = mnew;
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            const double pr = exp(sc[kk] - mx);      // exp(-inf) = 0 for the keys beyond S
-                            l += pr;
-                            o += pr * (double)vj[kk];
+                            for (int kk = 0; kk < 4; ++kk) {
+                                const double pr = exp(sc[kk] - m);   // exp(-inf) = 0 for the keys beyond S
+                                l += pr;
+                                o += pr * (double)vj[kk];
+                            }
                         }
+                    }
+                    if (active) {
                         l = wave_sum(l);
                         o = wave_sum(o);
                         if (lane == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1((float)(o / l), inv);
@@ -1396,7 +1585,7 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
                 for (uint32_t k = 0; k < n; ++k) {
                     const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)todo[k]);
                     const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
-                    const float x = context_exact(qkv, S, Hd, heads, dh, scale, (tok0 + t) * (uint32_t)Hd + hd * (uint32_t)dh + d, red);
+                    const float x = context_exact<NT>(qkv, S, Hd, heads, dh, scale, (tok0 + t) * (uint32_t)Hd + hd * (uint32_t)dh + d, red);
                     if (tid == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1(x, inv);
                 }
             }
@@ -1407,42 +1596,51 @@ __global__ __launch_bounds__(256, KLDS ? 2 : 3) void quantize_attention_certify_
 
 static bool attn_aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Scratch of the approximate attention: an error bound per query of a head, then what its workgroups know about the
+// exact maximum (split form: bounds and candidates; fp32 form: records)
+static size_t attention_bounds_bytes(int32_t B, int32_t S, int32_t heads) { return align_up((size_t)B * heads * S * 4, 256); }
 size_t attention_records_bytes(int32_t B, int32_t S, int32_t heads)
 {
-    return align_up((size_t)B * heads * ((S + 63) / 64) * sizeof(AttnRecord), 256);
+    const size_t split = (size_t)B * heads * ((S + kSplitQ - 1) / kSplitQ) * sizeof(AttnCand);
+    const size_t fp32 = (size_t)B * heads * ((S + 63) / 64) * sizeof(AttnRecord);
+    return attention_bounds_bytes(B, S, heads) + align_up(split > fp32 ? split : fp32, 256);
 }
 
-// Kernel 1: the bf16-split form when head dims come in whole units of 8 floats at 16-byte aligned addresses,
-// else the fp32 form.  Both fill the same records (one per 64 queries of a head).
+// Kernel 1 in the float16-split form: head dims in whole units of 8 floats at 16-byte aligned addresses; else the fp32 form.
+bool attention_splits(int32_t Hd, int32_t heads) { return ((Hd / heads) & 7) == 0 && (Hd & 3) == 0; }
+
+// rec: what follows the bounds in the scratch memory, or null (the kernel alone)
 static hipError_t launch_attention_approx(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                          AttnRecord *rec, uint32_t *amax_slot, uint32_t *err_slot, uint32_t *exact_slot,
-                                          hipStream_t st)
+                                          float *err_q, char *rec, const uint32_t *max_slot, uint32_t *amax_slot,
+                                          uint32_t *err_slot, uint32_t *exact_slot, hipStream_t st)
 {
     const int dh = Hd / heads;
     const float scale = (float)(1.0 / sqrt((double)dh));
-    if ((dh & 7) == 0 && (Hd & 3) == 0) {
+    if (attention_splits(Hd, heads)) {
         const int64_t grid = (int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ);
         const int per_xcd = (int)((grid + 7) / 8);
         return launch_k(EGERIA_KERNEL_ATTENTION, attention_split_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
-                        qkv, (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, rec, (int)grid, per_xcd, amax_slot, exact_slot);
+                        qkv, (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, err_q, (AttnCand *)rec,
+                        (int)grid, per_xcd, max_slot, rec ? amax_slot : nullptr, exact_slot);
     }
     const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
     const int per_xcd = (int)((grid + 7) / 8);
     return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
-                    (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, rec, (int)grid, per_xcd, amax_slot, err_slot);
+                    (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, err_q, (AttnRecord *)rec, (int)grid, per_xcd, amax_slot,
+                    err_slot);
 }
 
 // Kernel 1 alone (benchmark instrumentation: its error against the fp64 kernel): approximate context and the
-// records {largest |x| as a bit pattern, error bound E}, B * heads * ceil(S / 64) of them.
+// error bound E of every query of a head, fp32 [B, heads, S].
 hipError_t launch_attention_fast(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                 void *records, hipStream_t st)
+                                 float *bounds, hipStream_t st)
 {
     const int dh = Hd / heads;
     const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
     if (grid <= 0) return hipSuccess;
     if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
-    if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(records)) return hipErrorInvalidValue;
-    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, (AttnRecord *)records, nullptr, nullptr, nullptr, st);
+    if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(bounds)) return hipErrorInvalidValue;
+    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, bounds, nullptr, nullptr, nullptr, nullptr, nullptr, st);
 }
 
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
@@ -1458,23 +1656,37 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
     // 16-byte vector accesses may touch when the head size allows them
     if (dh > kDh || grid > 0x7ffffff0LL || M * Hd >= (1LL << 32) || ldq < Hd) return hipErrorInvalidValue;
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(xq) || !attn_aligned16(records)) return hipErrorInvalidValue;
-    AttnRecord *rec = (AttnRecord *)records;
+    float *err_q = (float *)records;
+    char *rec = (char *)records + attention_bounds_bytes(B, S, heads);
     const double scale = 1.0 / sqrt((double)dh);
-    hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, rec, amax_slot, err_slot, exact_slot, st);
+    const bool split = attention_splits(Hd, heads);
+    // (split form: err_slot holds the largest |value| of qkv, left by the GEMM that wrote it)
+    hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, err_q, rec, err_slot, amax_slot, err_slot, exact_slot, st);
     if (e != hipSuccess) return e;
     const int nrec = (int)grid;
-    // (the bf16-split kernel settles the exact maximum itself; the fp32 kernel leaves it to a launch of its own)
-    if (!((dh & 7) == 0 && (Hd & 3) == 0)) e = launch_k(EGERIA_KERNEL_NONE, attention_absmax_exact_kernel, dim3((unsigned)((nrec + 255) / 256)), dim3(256), 0, st, qkv,
+    // (the quantiser settles the exact maximum from the split kernel's candidates; the fp32 kernel leaves it to a launch of its own)
+    if (!split) e = launch_k(EGERIA_KERNEL_NONE, attention_absmax_exact_kernel, dim3((unsigned)((nrec + 255) / 256)), dim3(256), 0, st, qkv,
                  (const float *)ctx, (const AttnRecord *)rec, nrec, (const uint32_t *)amax_slot, (const uint32_t *)err_slot, (int)S,
                  (int)Hd, (int)heads, dh, scale, exact_slot);
     if (e != hipSuccess) return e;
     const bool wide = (dh & 15) == 0 && (Hd & 15) == 0 && ldq == Hd;
     if ((int64_t)S * (dh + (ldq - Hd)) >= (1LL << 31)) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((int64_t)B * heads);
-    const bool klds = S <= kKeysLds && (dh & 3) == 0 && (Hd & 3) == 0;
+    // a workgroup per head; heads are shared out where that leaves compute units idle (a workgroup's fixed part is half its
+    // time, so shares of less than 64 tokens do not pay)
+    const int64_t all_heads = (int64_t)B * heads;
+    int64_t splits = 2 * compute_units() / all_heads;
+    if (splits > (S + 63) / 64) splits = (S + 63) / 64;
+    if (splits < 1) splits = 1;
+    const int tokens = (int)((S + splits - 1) / splits);
+    splits = (S + tokens - 1) / tokens;
+    if (all_heads * splits > 0x7fffffffLL) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)(all_heads * splits);
+    const int nwg = split ? (int)((int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ)) : 0;
+    const bool klds = (dh & 3) == 0 && (Hd & 3) == 0;
     auto go = [&](auto kernel) {
-        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, dim3(blocks), dim3(256), 0, st, qkv, (const float *)ctx,
-                        (const AttnRecord *)rec, (int)S, (int)Hd, (int)heads, dh, scale, (const uint32_t *)exact_slot, xq,
+        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, dim3(blocks), dim3(kCertifyThreads), 0, st, qkv, (const float *)ctx,
+                        (const float *)err_q, (const AttnCand *)rec, nwg,
+                        (const uint32_t *)amax_slot, (int)S, (int)Hd, (int)heads, dh, (int)splits, tokens, scale, (const uint32_t *)exact_slot, xq,
                         ldq, scale_out, flag, unsure_total);
     };
     if (wide) return klds ? go(quantize_attention_certify_kernel<true, true>) : go(quantize_attention_certify_kernel<true, false>);

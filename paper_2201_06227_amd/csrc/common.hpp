@@ -323,7 +323,9 @@ hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, 
 // words (zero on entry), unsure_total (nullable) is incremented by the number of re-evaluated values.
 size_t attention_records_bytes(int32_t B, int32_t S, int32_t heads);
 hipError_t launch_attention_fast(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                 void *records, hipStream_t st);
+                                 float *bounds, hipStream_t st);
+// true if that attention wants the largest |value| of qkv in err_slot on entry (the form that splits operands)
+bool attention_splits(int32_t Hd, int32_t heads);
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
                                       void *records, uint32_t *amax_slot, uint32_t *err_slot, uint32_t *exact_slot,
                                       int8_t *xq, int64_t ldq, float *scale_out,

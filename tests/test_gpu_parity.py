@@ -549,11 +549,13 @@ def test_bert_modules_bit_exact_and_scored(eg, gc, orc, kw):
         assert p_close(p[l].item(), want, kw["b"]), (l, p[l].item(), want)
 
 
-# shapes that reach each variant of the certification kernel: keys held in LDS or read from global memory
-# (more than 256 keys, or a head size that is no multiple of 4), 16 values or one value per thread
+# shapes that reach each variant of the certification kernel: keys held in LDS (all of them, or 256 at a time) or read from
+# global memory (a head size that is no multiple of 4), 16 values or one value per thread
 ATTENTION_SHAPES = [dict(b=3, s=77, hidden=200, heads=5, ffn=328, n_layers=2),      # keys in LDS, single values
                     dict(b=2, s=200, hidden=128, heads=2, ffn=64, n_layers=2),      # keys in LDS, 16 per thread
-                    dict(b=1, s=300, hidden=96, heads=3, ffn=64, n_layers=2),       # keys from global memory, 16 per thread
+                    dict(b=1, s=300, hidden=96, heads=3, ffn=64, n_layers=2),       # keys in LDS in two rounds, 16 per thread
+                    dict(b=1, s=129, hidden=24, heads=3, ffn=64, n_layers=2),       # heads of 8, shares of a head's tokens
+                    dict(b=1, s=515, hidden=96, heads=2, ffn=64, n_layers=2),       # keys in three rounds, a token more than a share
                     dict(b=2, s=70, hidden=66, heads=3, ffn=40, n_layers=2)]        # head size 22: plain loop
 
 
@@ -576,6 +578,45 @@ def test_attention_paths_agree(eg, gc, kw):
     observed, _, _ = gc.run_forward(wl)
     assert torch.equal(outs[0], outs[1])
     assert np.array_equal(outs[0].cpu().numpy().reshape(observed.shape), observed)
+
+
+# what the certified kernels meet beyond ordinary activations: rows that tie for the tensor's maximum (the candidates of a
+# workgroup overflow its list), nothing but zeros, whole samples twice, scores in the hundreds, values that the split's scale
+# leaves few digits of (every code is re-evaluated: the list of the quantiser overflows)
+ATTENTION_INPUTS = ["equal tokens", "zeros", "equal samples", "large scores", "uneven values"]
+
+
+@pytest.mark.parametrize("inputs", ATTENTION_INPUTS)
+@pytest.mark.parametrize("kw", [dict(b=3, s=131, hidden=128, heads=2), dict(b=2, s=260, hidden=96, heads=4)],
+                         ids=["s131_dh64", "s260_dh24"])
+def test_attention_paths_agree_on_extreme_inputs(eg, gc, kw, inputs):
+    wl = si.make_bert(seed=71, ffn=64, n_layers=1, train_act_dtype="f32", **kw)
+    h = kw["hidden"]
+    x, wqkv = wl.x.copy(), wl.weights[0].copy()
+    per_channel = False
+    if inputs == "equal tokens":
+        x[:, 1:] = x[:, :1]
+    elif inputs == "zeros":
+        x[:] = 0.0
+    elif inputs == "equal samples":
+        x[1:] = x[:1]
+    elif inputs == "large scores":
+        wqkv[:2 * h] *= 12.0
+    else:
+        per_channel = True                       # (one scale for all would round the small rows to zero)
+        wqkv[2 * h:] *= np.float32(3.0e7)
+    wl.x, wl.weights[0] = np.ascontiguousarray(x), np.ascontiguousarray(wqkv)
+    ref = eg.make_reference(wl.kind, wl.dims, [gc.to_dev(w) for w in wl.weights], [None] * len(wl.weights), per_channel=per_channel)
+    ws = eg.workspace(eg.workspace_bytes(ref.desc), gc.DEV)
+    outs = []
+    for thr in (0.0, 1.0e30):
+        eg.attention_threshold(thr)
+        a = torch.empty(gc.a_ref_numel(wl), dtype=torch.float32, device=gc.DEV)
+        eg.ref_forward(ref, gc.to_dev(wl.x), a, ws)
+        torch.cuda.synchronize()
+        assert eg.check(ws) == eg.OK
+        outs.append(a)
+    assert torch.equal(outs[0], outs[1])
 
 
 @pytest.mark.parametrize("column", ["query", "value"])
