@@ -96,7 +96,7 @@ constexpr int resident_target(int bm, int bn)
     return bm * bn > 256 * 128 ? 1 : (bm * bn > 128 * 128 ? 2 : 3);
 }
 
-template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, bool LNF = false>
+template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, bool LNF = false, int NST = stages_for(BK)>
 __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g, int tiles,
                                                                                int tiles_per_xcd)
 {
@@ -115,7 +115,6 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     constexpr int A_CH = BM / kRowsPerChunk, B_CH = BN / kRowsPerChunk; // 1-KiB chunks per K step
     constexpr int A_IT = (A_CH + NW - 1) / NW, B_IT = (B_CH + NW - 1) / NW;         // chunks per wave
     constexpr int STAGE = (BM + BN) * kBK;
-    constexpr int NST = stages_for(BK);
     constexpr int NLD = A_IT + B_IT;                                    // loads per wave and K step
     static_assert((NST - 2) * NLD < 64, "outstanding loads must fit the wait counter");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [NST][BM + BN][BK]
@@ -167,29 +166,29 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     // chunk = wave + NW * it; the chunk's share of that is (chunk * 4) % UPR = (wave % 2) * 4 % UPR
     const int unit = (lane % UPR) ^ (((wave_u & 1) * 4 + rloc / SWR) % UPR);
     static_assert(A_CH % 2 == 0 && B_CH % 2 == 0, "a wave's chunks must keep their parity");
-    uint32_t a_base[A_IT];               // byte offset of the row (linear) or of the centre pixel (conv)
-    bool a_ok[A_IT];
-    int a_oh[A_IT], a_ow[A_IT];
+    // Byte offset of the lane's row of each chunk (linear) or of its centre pixel (conv).  A row that does not exist starts
+    // beyond the buffer, and the K offset is added with saturation, so it stays there: a linear request is one addition.
+    uint32_t a_base[A_IT];
+    uint32_t a_taps[CONV ? A_IT : 1];            // conv: bit t set if window position t of the pixel lies inside the image
 #pragma unroll
     for (int it = 0; it < A_IT; ++it) {
         const int r = ((wave_u + it * NW) % A_CH) * kRowsPerChunk + rloc;
         const int64_t m = m0 + r;
-        a_ok[it] = m < g.M;
-        a_base[it] = a_ok[it] ? (uint32_t)(m * (CONV ? (int64_t)g.cp : g.lda)) : 0u;
-        if (CONV) {
+        const bool ok = m < g.M;
+        a_base[it] = ok ? (uint32_t)(m * (CONV ? (int64_t)g.cp : g.lda)) : (CONV ? 0u : kOob);
+        if constexpr (CONV) {
             // the operand's extent is below 2^31 bytes, so m fits 32 bits (a 64-bit division is a long call)
             const uint32_t mrow = (uint32_t)m / (uint32_t)g.W;
-            a_ow[it] = (int)((uint32_t)m - mrow * (uint32_t)g.W);
-            a_oh[it] = (int)(mrow % (uint32_t)g.H);
+            const int ow = (int)((uint32_t)m - mrow * (uint32_t)g.W), oh = (int)(mrow % (uint32_t)g.H);
+            const uint32_t cols = (ow > 0 ? 1u : 0u) | 2u | (ow + 1 < g.W ? 4u : 0u);
+            a_taps[it] = !ok ? 0u : (oh > 0 ? cols : 0u) | cols << 3 | (oh + 1 < g.H ? cols << 6 : 0u);
         }
     }
     uint32_t b_base[B_IT];
-    bool b_ok[B_IT];
 #pragma unroll
     for (int it = 0; it < B_IT; ++it) {
         const int r = ((wave_u + it * NW) % B_CH) * kRowsPerChunk + rloc;
-        b_ok[it] = n0 + r < g.N;
-        b_base[it] = b_ok[it] ? (uint32_t)(n0 + r) * (uint32_t)g.kp : 0u;
+        b_base[it] = n0 + r < g.N ? (uint32_t)(n0 + r) * (uint32_t)g.kp : kOob;
     }
 
     // Requests for K step kt into LDS stage `stage`, one 1-KiB chunk per call
@@ -197,28 +196,46 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     // per K step (the waits below count them): where a tile has fewer chunks
     // than that, waves fetch a chunk twice, writing the same bytes.
     struct StepAddr {
-        int k0, dh, dw, delta;
-        bool k_ok;
+        uint32_t k;              // the lane's K offset of the step, beyond any buffer past the end of K
+        uint32_t delta, tap;     // conv: what it adds to a centre pixel's offset, and the bit of its window position
     };
     // The row-owning tile: every workgroup streams the whole weight matrix, so all of them would ask the L2 for
     // the same rows at the same time; each starts at a K step of its own instead (integer sums do not depend
     // on the order).  Steps past the end of K stay past the end.
     const int nk_all = (g.kp + kBK - 1) / kBK;
     const int k_rot = LNF ? tile % nk_all : 0;
+    // conv, pixels of a K step and more (cp >= BK): the steps come in order, so the window position of a step's first byte
+    // (tap_s, which ends at K offset tap_end) is followed with scalars and a lane is at that position or the next one.  Per
+    // lane and step a division took some 60 vector instructions and the border tests 8 per request, a thousand clocks of a
+    // step whose MFMAs take 130 to 260 (2450 x 512 x 4608, 128x64
+    // tiles: 30 -> 22.6 us).
+    int tap_s = 0, tap_end = g.cp;
+    auto tap_offset = [&](int tap) {             // K offset -> offset from the centre pixel, at window position tap
+        const int kh = (tap >= 3 ? 1 : 0) + (tap >= 6 ? 1 : 0);
+        return (uint32_t)((((kh - 1) * g.W + (tap - 3 * kh - 1)) - tap) * g.cp);
+    };
     auto step_addr = [&](int kt) {
         StepAddr sa;
         if (LNF && kt < nk_all) kt = kt + k_rot < nk_all ? kt + k_rot : kt + k_rot - nk_all;
-        sa.k0 = kt * kBK + unit * 16;
-        sa.k_ok = sa.k0 < g.kp;
-        sa.dh = 0;
-        sa.dw = 0;
-        sa.delta = sa.k0;
-        if (CONV) {
-            const int tap = sa.k0 / g.cp;
-            const int kh = tap / 3;
-            sa.dh = kh - 1;
-            sa.dw = tap - kh * 3 - 1;
-            sa.delta = (sa.dh * g.W + sa.dw) * g.cp + (sa.k0 - tap * g.cp);
+        const int k0 = kt * kBK + unit * 16;
+        const bool k_ok = k0 < g.kp;
+        sa.k = k_ok ? (uint32_t)k0 : kOob;
+        sa.delta = 0;
+        sa.tap = 0;
+        if constexpr (CONV) {
+            if (g.cp >= kBK) {
+                if (kt * kBK >= tap_end) { ++tap_s; tap_end += g.cp; }
+                const bool next = k0 >= tap_end;
+                sa.delta = (uint32_t)k0 + (next ? tap_offset(tap_s + 1) : tap_offset(tap_s));
+                sa.tap = next ? 2u << tap_s : 1u << tap_s;
+            } else {
+                int tap = 0;                     // k0 / cp, by counting
+#pragma unroll
+                for (int i = 1; i < 9; ++i) tap += k0 >= i * g.cp ? 1 : 0;
+                sa.delta = (uint32_t)k0 + tap_offset(tap);
+                sa.tap = 1u << tap;
+            }
+            sa.tap = k_ok ? sa.tap : 0u;
         }
         return sa;
     };
@@ -227,14 +244,14 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         if (idx < A_IT) {
             const int it = idx;
             const int chunk = (wave_u + it * NW) % A_CH;
-            bool ok = a_ok[it] && sa.k_ok;
-            if (CONV)
-                ok = ok && (unsigned)(a_oh[it] + sa.dh) < (unsigned)g.H && (unsigned)(a_ow[it] + sa.dw) < (unsigned)g.W;
-            load_to_lds_b128(rsrc_a, sA + chunk * 1024, ok ? a_base[it] + (uint32_t)sa.delta : kOob);
+            uint32_t at;
+            if constexpr (CONV) at = (a_taps[it] & sa.tap) ? a_base[it] + sa.delta : kOob;
+            else at = __builtin_elementwise_add_sat(a_base[it], sa.k);
+            load_to_lds_b128(rsrc_a, sA + chunk * 1024, at);
         } else {
             const int it = idx - A_IT;
             const int chunk = (wave_u + it * NW) % B_CH;
-            load_to_lds_b128(rsrc_w, sB + chunk * 1024, (b_ok[it] && sa.k_ok) ? b_base[it] + (uint32_t)sa.k0 : kOob);
+            load_to_lds_b128(rsrc_w, sB + chunk * 1024, __builtin_elementwise_add_sat(b_base[it], sa.k));
         }
     };
     auto fetch = [&](int kt, int stage) {
@@ -724,7 +741,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int ET = 0, bool LNF = false>
+template <int BM, int BN, int WM, int WN, int BK, int ET = 0, bool LNF = false, int NST = stages_for(BK)>
 static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
 {
     const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
@@ -732,7 +749,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     if (tiles > 0x3fffffffLL) return hipErrorInvalidValue;
     const int tpx = (int)((tiles + 7) / 8);
     const dim3 grid((unsigned)(tpx * 8)), block(64 * WM * WN);
-    constexpr size_t stages = (size_t)stages_for(BK) * (BM + BN) * BK;
+    constexpr size_t stages = (size_t)NST * (BM + BN) * BK;
     // affine codes: weight-code sums and row classes behind the epilogue's block
     constexpr size_t affine = ((size_t)WM * 32 * (BN + 8 * WN) + 16 * BN) * 4 + BM, largest = stages > affine ? stages : affine;
     const size_t smem = g.zp_in ? largest : stages;
@@ -745,24 +762,24 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
         } else {
             static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
             if (!set[dev]) {
-                e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>,
+                e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
                 if (e != hipSuccess) return e;
                 set[dev] = true;
             }
-            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET>, grid, block, smem, st, g,
+            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>, grid, block, smem, st, g,
                             (int)tiles, tpx);
         }
     }
     static bool set[kMaxDevices] = {};
     if (!set[dev]) {
-        e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF>,
+        e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF, NST>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
         if (e != hipSuccess) return e;
         set[dev] = true;
     }
     // (instrumentation: the launch that also normalises its rows is timed with the layer norms, whose bytes bound it)
-    return launch_k(LNF ? EGERIA_KERNEL_LAYERNORM : EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF>,
+    return launch_k(LNF ? EGERIA_KERNEL_LAYERNORM : EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF, NST>,
                     grid, block, smem, st, g, (int)tiles, tpx);
 }
 
@@ -1134,23 +1151,29 @@ struct TileShape {
     int bm, bn, bk, resident, waves;
     double penalty;
 };
-constexpr int kNumShapes = 8;
-static const TileShape kShapes[kNumShapes] = {
+constexpr int kNumShapes = 8, kDeepSmall = 8, kDeepMid = 9, kDeepLarge = 10;
+static const TileShape kShapes[kNumShapes + 3] = {
     {256, 128, 64, 2, 4, 1.06},  {128, 192, 64, 2, 4, 1.10}, {128, 128, 64, 3, 4, 1.20},  {128, 128, 128, 2, 4, 1.22},
     {128, 64, 64, 4, 4, 1.40},   {128, 64, 128, 3, 4, 1.38}, {256, 256, 128, 1, 8, 1.00}, {256, 192, 128, 1, 8, 1.02},
+    // three stages of whole lines, for layers that bring a compute unit one workgroup or two (chosen by rule, not by price)
+    {64, 64, 128, 3, 4, 0.0},    {128, 64, 128, 2, 4, 0.0},  {128, 128, 128, 1, 4, 0.0},
 };
 
+template <int ET>
 static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 {
     switch (i) {
-    case 0: return launch_variant<256, 128, 2, 2, 64>(g, st);
-    case 1: return launch_variant<128, 192, 2, 2, 64>(g, st);
-    case 2: return launch_variant<128, 128, 2, 2, 64>(g, st);
-    case 3: return launch_variant<128, 128, 2, 2, 128>(g, st);
-    case 4: return launch_variant<128, 64, 2, 2, 64>(g, st);
-    case 5: return launch_variant<128, 64, 2, 2, 128>(g, st);
-    case 6: return launch_variant<256, 256, 2, 4, 128>(g, st);
-    case 7: return launch_variant<256, 192, 4, 2, 128>(g, st);
+    case 0: return launch_variant<256, 128, 2, 2, 64, ET>(g, st);
+    case 1: return launch_variant<128, 192, 2, 2, 64, ET>(g, st);
+    case 2: return launch_variant<128, 128, 2, 2, 64, ET>(g, st);
+    case 3: return launch_variant<128, 128, 2, 2, 128, ET>(g, st);
+    case 4: return launch_variant<128, 64, 2, 2, 64, ET>(g, st);
+    case 5: return launch_variant<128, 64, 2, 2, 128, ET>(g, st);
+    case 6: return launch_variant<256, 256, 2, 4, 128, ET>(g, st);
+    case 7: return launch_variant<256, 192, 4, 2, 128, ET>(g, st);
+    case kDeepSmall: return launch_variant<64, 64, 2, 2, 128, ET, false, 3>(g, st);
+    case kDeepMid: return launch_variant<128, 64, 2, 2, 128, ET, false, 3>(g, st);
+    case kDeepLarge: return launch_variant<128, 128, 2, 2, 128, ET, false, 3>(g, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1163,8 +1186,22 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 // long, so for short K only shapes with two workgroups per CU are considered
 // (one is in its K loop while the other stores), and for very short K, where
 // the kernel is a stream of stores, only the small shapes.
+//   Layers with few tiles come first.  A workgroup alone on its compute unit has nothing to hide its round trips behind: with
+// two stages of whole lines every K step waits for the one it requested, 1400 clocks of a 128x64 step; with three stages the
+// step takes what LDS needs, 24 KB written at 62 bytes per clock, 48 read at 235 and some 180 clocks of barrier, 770 (a fourth
+// stage changes nothing).  64x64 tiles as long as they bring 1.5 workgroups per compute unit, or 2.25 where 128x64 tiles would
+// start a second round; else 128x64 tiles that fill one round at most, else, from K of 1024 bytes on, 128x128 tiles that do.
+// us, chosen by price / 64x64 / 128x64 / 128x128 with three stages: 2450 x 512 x 2048 12.6 / 8.7 / 9.7 / 12.4, 2000 x 768 x 3072
+// 17.3 / 11.8 / 12.0 / 14.9, 128 x 4096 x 4096 20.6 / 11.6 / 13.5 / 17.8, 32 x 512 x 512 5.1 / 4.2 / 5.0 / 6.0, 4480 x 512 x 1024
+// 9.6 / 8.5 / 9.0 / 9.2, 4096 x 512 x 2048 13.0 / 11.4 / 9.8 / 12.2, 4096 x 768 x 3072 20.4 / 18.6 / 18.8 / 17.1, 12544 x 256 x
+// 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7, 8000 x 512 x 1536 14.2 / 15.5 / 14.4 / 13.4; 4096 x 768 x 768 8.5 with all of them.
 static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
 {
+    const int64_t cu = compute_units(), t64 = ((M + 63) / 64) * ((N + 63) / 64), t128x64 = ((M + 127) / 128) * ((N + 63) / 64),
+                  t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    if (2 * t64 <= 3 * cu || (t128x64 > cu && 4 * t64 <= 9 * cu)) return kDeepSmall;
+    if (t128x64 <= cu) return kDeepMid;
+    if (t128 <= cu && kp >= 1024) return kDeepLarge;
     int best = 0;
     double best_cost = 0.0;
     for (int i = 0; i < kNumShapes; ++i) {
@@ -1204,16 +1241,13 @@ void gemm_tile(int64_t M, int32_t N, int64_t kp, bool conv3x3, int32_t *rows, in
     *k_step = sh.bk;
 }
 
-// The float16 / float32 reference precisions: three tile shapes, chosen by how
-// many tiles the output makes.
-template <int ET>
-static hipError_t launch_float(const GemmArgs &g, hipStream_t st)
+// The float32 reference precision (bound by its matrix instructions): three tile shapes, chosen by how many tiles the output
+// makes.
+static hipError_t launch_float32(const GemmArgs &g, hipStream_t st)
 {
-    if (g.q_out || g.absmax_out) return hipErrorInvalidValue;
-    if (g.N <= 32) return launch_variant<128, 32, 4, 1, 64, ET>(g, st);
     const int64_t t128 = ((g.M + 127) / 128) * (int64_t)((g.N + 127) / 128);
-    if (t128 >= 512) return launch_variant<128, 128, 2, 2, 64, ET>(g, st);
-    return launch_variant<128, 64, 2, 2, 64, ET>(g, st);
+    if (t128 >= 512) return launch_variant<128, 128, 2, 2, 64, 2>(g, st);
+    return launch_variant<128, 64, 2, 2, 64, 2>(g, st);
 }
 
 bool gemm_layernorm_fusable(int32_t N, const void *ln_out, const void *ln_res, const void *gamma, const void *beta)
@@ -1230,9 +1264,15 @@ hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
         if (!gemm_layernorm_fusable(g.N, g.ln_out, g.ln_res, g.ln_gamma, g.ln_beta)) return hipErrorInvalidValue;
         return launch_variant<64, 768, 1, 8, 64, 0, true>(g, st);
     }
-    if (g.et == 1) return launch_float<1>(g, st);
-    if (g.et == 2) return launch_float<2>(g, st);
-    if (g.et != 0) return hipErrorInvalidValue;
+    if (g.et == 1 || g.et == 2) {
+        if (g.q_out || g.absmax_out) return hipErrorInvalidValue;
+        if (g.et == 2) return g.N <= 32 ? launch_variant<128, 32, 4, 1, 64, 2>(g, st) : launch_float32(g, st);
+        // float16: a byte of K costs what one of int8 does, in the matrix cores and on the way to them, so the same choice
+        // (128x128 and 128x64 tiles with 64-byte steps only / now, us: 4096 x 2304 x 768 29 / 26, 4096 x 768 x 3072 38 / 28,
+        // 12544 x 256 x 1024 17 / 13.7, 12544 x 256 x 256 (3x3) 33 / 26)
+        if (g.N <= 32) return launch_variant<128, 32, 4, 1, 64, 1>(g, st);
+        return launch_shape<1>(choose_shape(g.M, g.N, g.kp, g.conv3x3), g, st);
+    }
     if (g.conv3x3 && g.cp == 16 && g.N <= 32 && !g.zp_in) {   // (symmetric codes only)
         const int64_t blocks = (g.M + 127) / 128;
         if (blocks <= 0) return hipSuccess;
@@ -1240,7 +1280,7 @@ hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
         return launch_k(EGERIA_KERNEL_GEMM, conv3x3_c16_kernel, dim3((unsigned)blocks), dim3(256), 0, st, g);
     }
     if (g.N <= 32) return launch_variant<128, 32, 4, 1, 64>(g, st);
-    return launch_shape(choose_shape(g.M, g.N, g.kp, g.conv3x3), g, st);
+    return launch_shape<0>(choose_shape(g.M, g.N, g.kp, g.conv3x3), g, st);
 }
 
 }  // namespace egeria
