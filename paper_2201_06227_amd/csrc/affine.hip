@@ -14,6 +14,9 @@
 // Two launches per quantise point: the extrema as per-workgroup partial results
 // (plain stores), then the codes, every workgroup reducing the partial results
 // to the same scale and zero point.  HBM-bound: 4 n bytes read twice, n written.
+// The output of a ReLU has no negative values, so its extrema are 0 and the
+// maximum that the convolution's epilogue keeps anyway: such a point is the code
+// pass alone.
 #include "common.hpp"
 
 namespace egeria {
@@ -23,8 +26,12 @@ namespace {
 constexpr int kMinMaxBlocks = 1024;
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x, int64_t n, uint32_t *__restrict__ partials)
+__global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x, int64_t n, uint32_t *__restrict__ partials,
+                                                     uint32_t *__restrict__ reset, int n_reset)
 {
+    if (blockIdx.x == 0) {               // clears the maximum words of the module's later quantise points
+        for (int t = threadIdx.x; t < n_reset * kAmaxWays; t += blockDim.x) reset[(size_t)t * kAmaxStride] = 0u;
+    }
     float hi = 0.0f, nlo = 0.0f;       // max(x, 0) and max(-x, 0)
     uint32_t worst = 0;                // largest |x| bit pattern: above 0x7f7fffff for NaN and infinities
     const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
@@ -102,12 +109,14 @@ enum AffineForm { kAny = 0, kRows = 1, kPlanes = 2 };
 template <bool BF16, int FORM>
 __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__restrict__ x, int64_t n, int64_t c, int64_t hw,
                                                               int64_t cp, const uint32_t *__restrict__ partials, int nb,
-                                                              int store_offset, uint8_t *__restrict__ q,
+                                                              const uint32_t *__restrict__ relu_max, int store_offset, uint8_t *__restrict__ q,
                                                               float *__restrict__ scale_out, int32_t *__restrict__ zp_out,
                                                               uint32_t *__restrict__ flag)
 {
     uint32_t hb = 0, lb = 0;
-    {
+    if (relu_max) {
+        hb = relu_max[(threadIdx.x & (kAmaxWays - 1)) * kAmaxStride];
+    } else {
         // all candidates requested together (repeats of the last one change nothing)
         uint2 cand[kMinMaxBlocks / 256];
 #pragma unroll
@@ -267,16 +276,17 @@ int minmax_blocks(int64_t n)
 
 size_t affine_partial_bytes() { return (size_t)kMinMaxBlocks * 2 * sizeof(uint32_t); }
 
-hipError_t launch_minmax(const void *x, egeria_dtype dt, int64_t n, uint32_t *partials, hipStream_t st)
+hipError_t launch_minmax(const void *x, egeria_dtype dt, int64_t n, uint32_t *partials, uint32_t *reset, int n_reset,
+                         hipStream_t st)
 {
     const dim3 grid((unsigned)minmax_blocks(n)), block(256);
-    if (dt == EGERIA_BF16) return launch_k(EGERIA_KERNEL_ABSMAX, minmax_kernel<true>, grid, block, 0, st, x, n, partials);
-    return launch_k(EGERIA_KERNEL_ABSMAX, minmax_kernel<false>, grid, block, 0, st, x, n, partials);
+    if (dt == EGERIA_BF16) return launch_k(EGERIA_KERNEL_ABSMAX, minmax_kernel<true>, grid, block, 0, st, x, n, partials, reset, n_reset);
+    return launch_k(EGERIA_KERNEL_ABSMAX, minmax_kernel<false>, grid, block, 0, st, x, n, partials, reset, n_reset);
 }
 
 hipError_t launch_quantize_affine(const void *x, egeria_dtype dt, int64_t n, int64_t c, int64_t hw, int64_t cp,
-                                  const uint32_t *partials, int nb, int store_offset, void *q, float *scale_out,
-                                  int32_t *zp_out, uint32_t *flag, hipStream_t st)
+                                  const uint32_t *partials, int nb, const uint32_t *relu_max, int store_offset, void *q,
+                                  float *scale_out, int32_t *zp_out, uint32_t *flag, hipStream_t st)
 {
     // whole 16-byte units of fp32 take the wide forms; bf16, odd rows and planes, and other addresses the general one
     const bool wide = dt == EGERIA_F32 && ((uintptr_t)x & 15) == 0;
@@ -286,7 +296,7 @@ hipError_t launch_quantize_affine(const void *x, egeria_dtype dt, int64_t n, int
     if (blocks > 8192) blocks = 8192;
     const dim3 grid((unsigned)blocks), block(256);
     auto go = [&](auto kernel) {
-        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cp, partials, nb, store_offset,
+        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cp, partials, nb, relu_max, store_offset,
                         (uint8_t *)q, scale_out, zp_out, flag);
     };
     if (dt == EGERIA_BF16) return go(quantize_affine_kernel<true, kAny>);

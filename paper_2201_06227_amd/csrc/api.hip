@@ -194,17 +194,21 @@ struct Fwd {
     // affine activation codes: scratch of the extrema pass, zero point of quantise point i
     uint32_t *aff_partials() const { return (uint32_t *)(ws + p.off_aff); }
     int32_t *zp(int i) const { return (int32_t *)(ws + p.off_aff + affine_partial_bytes()) + i; }
-    // quantise point `slot`: [n, c, hw] channel planes (hw = 1: matrix rows) -> stored codes in qbuf(qi)
-    egeria_status quantize_affine(const void *src, egeria_dtype dt, int64_t n, int64_t c, int64_t hw, int qi, int slot) const
+    // quantise point `slot_i`: [n, c, hw] channel planes (hw = 1: matrix rows) -> stored codes in qbuf(qi).  after_relu: the
+    // tensor is a ReLU's output and the GEMM that wrote it has left its maximum in slot(slot_i), which the extrema pass of
+    // the module's input cleared.  (12544 x 256 at both inner points of a bottleneck: two launches and 26 MB read less.)
+    egeria_status quantize_affine(const void *src, egeria_dtype dt, int64_t n, int64_t c, int64_t hw, int qi, int slot_i,
+                                  bool after_relu = false) const
     {
         const int64_t total = n * c * hw;
-        EG_HIP(launch_minmax(src, dt, total, aff_partials(), st));
-        EG_HIP(launch_quantize_affine(src, dt, n, c, hw, pad16(c), aff_partials(), minmax_blocks(total), 128, qbuf(qi),
-                                      scale(slot), zp(slot), ws_flag(ws), st));
-        const egeria_tap *t = tap(slot);
+        if (!after_relu) EG_HIP(launch_minmax(src, dt, total, aff_partials(), ws_absmax(ws, 0),
+                                       d->kind == EGERIA_BASIC_BLOCK || d->kind == EGERIA_BOTTLENECK ? p.slots : 0, st));
+        EG_HIP(launch_quantize_affine(src, dt, n, c, hw, pad16(c), aff_partials(), minmax_blocks(total),
+                                      after_relu ? slot(slot_i) : nullptr, 128, qbuf(qi), scale(slot_i), zp(slot_i), ws_flag(ws), st));
+        const egeria_tap *t = tap(slot_i);
         if (t && t->x_q) EG_HIP(hipMemcpyAsync(t->x_q, qbuf(qi), (size_t)(n * hw * pad16(c)), hipMemcpyDeviceToDevice, st));
-        if (t && t->x_scale) EG_HIP(hipMemcpyAsync(t->x_scale, scale(slot), 4, hipMemcpyDeviceToDevice, st));
-        if (t && t->x_zp) EG_HIP(hipMemcpyAsync(t->x_zp, zp(slot), 4, hipMemcpyDeviceToDevice, st));
+        if (t && t->x_scale) EG_HIP(hipMemcpyAsync(t->x_scale, scale(slot_i), 4, hipMemcpyDeviceToDevice, st));
+        if (t && t->x_zp) EG_HIP(hipMemcpyAsync(t->x_zp, zp(slot_i), 4, hipMemcpyDeviceToDevice, st));
         return EGERIA_OK;
     }
 
@@ -529,36 +533,36 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
 }
 
 // The FC and convolution modules with affine uint8 activation codes (Section 5: the framework's
-// default activation code).  Every quantise point is an extrema pass and a code pass of its own; the
-// contraction and the epilogue are the symmetric path's, with the zero points handed to the epilogue.
+// default activation code).  The input's quantise point is an extrema pass and a code pass, the later ones,
+// whose tensors come out of a ReLU, a code pass with the maximum of the GEMM before; the contraction and the epilogue are the symmetric path's, with the zero points handed to the epilogue.
 egeria_status forward_affine(Fwd &f, const void *x, egeria_dtype dt, float *a_ref)
 {
     const egeria_block_desc *d = f.d;
     auto gemm = [&](int li, int qi, int64_t lda, int64_t M, int32_t N, int32_t kp, bool conv, int32_t cp, int slot,
-                    const int8_t *res, int64_t res_ld, float *y) {
+                    const int8_t *res, int64_t res_ld, float *y, uint32_t *max_out) {
         return run_gemm(f, li, f.qbuf(qi), lda, M, N, kp, conv, d->height, d->width, cp, f.scale(slot), 1, res,
-                        res ? f.scale(0) : nullptr, res_ld, y, nullptr, false, true, nullptr, 0, nullptr, f.zp(slot),
+                        res ? f.scale(0) : nullptr, res_ld, y, max_out, false, true, nullptr, 0, nullptr, f.zp(slot),
                         res ? f.zp(0) : nullptr);
     };
     if (d->kind == EGERIA_FC_RELU) {
         const int32_t kp = (int32_t)pad16(d->c_in);
         EG_OK(f.quantize_affine(x, dt, d->batch, d->c_in, 1, 0, 0));
-        return gemm(0, 0, kp, d->batch, d->c_out, kp, false, 0, 0, nullptr, 0, a_ref);
+        return gemm(0, 0, kp, d->batch, d->c_out, kp, false, 0, 0, nullptr, 0, a_ref, nullptr);
     }
     const int64_t M = f.p.M, hw = (int64_t)d->height * d->width;
     const int32_t cin_p = (int32_t)pad16(d->c_in), cmid_p = (int32_t)pad16(d->c_mid);
     EG_OK(f.quantize_affine(x, dt, d->batch, d->c_in, hw, 0, 0));
     const int8_t *res = d->has_residual ? f.qbuf(0) : nullptr;
     if (d->kind == EGERIA_BASIC_BLOCK) {
-        EG_OK(gemm(0, 0, 0, M, d->c_mid, 9 * cin_p, true, cin_p, 0, nullptr, 0, f.fbuf(0)));
-        EG_OK(f.quantize_affine(f.fbuf(0), EGERIA_F32, M, d->c_mid, 1, 1, 1));
-        return gemm(1, 1, 0, M, d->c_out, 9 * cmid_p, true, cmid_p, 1, res, cin_p, a_ref);
+        EG_OK(gemm(0, 0, 0, M, d->c_mid, 9 * cin_p, true, cin_p, 0, nullptr, 0, f.fbuf(0), f.slot(1)));
+        EG_OK(f.quantize_affine(f.fbuf(0), EGERIA_F32, M, d->c_mid, 1, 1, 1, true));
+        return gemm(1, 1, 0, M, d->c_out, 9 * cmid_p, true, cmid_p, 1, res, cin_p, a_ref, nullptr);
     }
-    EG_OK(gemm(0, 0, cin_p, M, d->c_mid, cin_p, false, 0, 0, nullptr, 0, f.fbuf(0)));
-    EG_OK(f.quantize_affine(f.fbuf(0), EGERIA_F32, M, d->c_mid, 1, 1, 1));
-    EG_OK(gemm(1, 1, 0, M, d->c_mid, 9 * cmid_p, true, cmid_p, 1, nullptr, 0, f.fbuf(1)));
-    EG_OK(f.quantize_affine(f.fbuf(1), EGERIA_F32, M, d->c_mid, 1, 2, 2));
-    return gemm(2, 2, cmid_p, M, d->c_out, cmid_p, false, 0, 2, res, cin_p, a_ref);
+    EG_OK(gemm(0, 0, cin_p, M, d->c_mid, cin_p, false, 0, 0, nullptr, 0, f.fbuf(0), f.slot(1)));
+    EG_OK(f.quantize_affine(f.fbuf(0), EGERIA_F32, M, d->c_mid, 1, 1, 1, true));
+    EG_OK(gemm(1, 1, 0, M, d->c_mid, 9 * cmid_p, true, cmid_p, 1, nullptr, 0, f.fbuf(1), f.slot(2)));
+    EG_OK(f.quantize_affine(f.fbuf(1), EGERIA_F32, M, d->c_mid, 1, 2, 2, true));
+    return gemm(2, 2, cmid_p, M, d->c_out, cmid_p, false, 0, 2, res, cin_p, a_ref, nullptr);
 }
 
 // One encoder layer with affine uint8 activation codes: the four linear layers as above, attention in its
@@ -760,9 +764,9 @@ egeria_status egeria_quantize_affine(const void *x, egeria_dtype dt, int64_t n, 
     if (ws_bytes < egeria_quantize_affine_workspace_bytes()) return EGERIA_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     uint32_t *partials = (uint32_t *)((char *)ws + 256);
-    EG_HIP(launch_minmax(x, dt, n, partials, st));
-    EG_HIP(launch_quantize_affine(x, dt, 1, n, 1, pad16(n), partials, minmax_blocks(n), 0, q, scale_out, zp_out, ws_flag(ws),
-                                  st));
+    EG_HIP(launch_minmax(x, dt, n, partials, nullptr, 0, st));
+    EG_HIP(launch_quantize_affine(x, dt, 1, n, 1, pad16(n), partials, minmax_blocks(n), nullptr, 0, q, scale_out, zp_out,
+                                  ws_flag(ws), st));
     return EGERIA_OK;
 }
 

@@ -214,10 +214,13 @@ hipError_t launch_cast_chlast(const void *x, egeria_dtype dt, int64_t n, int64_t
 // store_offset: 128 for the GEMM operand form, 0 for plain uint8 codes.
 int minmax_blocks(int64_t n);
 size_t affine_partial_bytes();
-hipError_t launch_minmax(const void *x, egeria_dtype dt, int64_t n, uint32_t *partials, hipStream_t st);
+// (clears the first n_reset maximum slots as well)
+hipError_t launch_minmax(const void *x, egeria_dtype dt, int64_t n, uint32_t *partials, uint32_t *reset, int n_reset,
+                         hipStream_t st);
+// relu_max: null, or the maximum slot of a tensor without negative values, which then takes the place of the partials
 hipError_t launch_quantize_affine(const void *x, egeria_dtype dt, int64_t n, int64_t c, int64_t hw, int64_t cp,
-                                  const uint32_t *partials, int nb, int store_offset, void *q, float *scale_out,
-                                  int32_t *zp_out, uint32_t *flag, hipStream_t st);
+                                  const uint32_t *partials, int nb, const uint32_t *relu_max, int store_offset, void *q,
+                                  float *scale_out, int32_t *zp_out, uint32_t *flag, hipStream_t st);
 // Sums of the int8 weight codes [out, taps, cp] per output channel: int32 [out] for taps = 1, and for a 3x3
 // kernel (taps = 9) int32 [16, out], class c leaving out the window positions outside the image for a pixel
 // in the first row (c & 1), last row (c & 2), first column (c & 4), last column (c & 8).

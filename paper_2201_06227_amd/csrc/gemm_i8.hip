@@ -706,11 +706,12 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         using T = std::true_type;
         using F = std::false_type;
         const bool track = g.absmax_out != nullptr, q = g.q_out != nullptr;
-        const bool rare = !vec || g.acc_out || (track && (has_res || zp || q)) || (q && (!relu || has_res || zp)) || (has_res && !relu);
+        const bool rare = !vec || g.acc_out || (track && (has_res || q || (zp && !relu))) || (q && (!relu || has_res || zp)) || (has_res && !relu);
         if (rare) general();
         else if (zp) {
             if constexpr (ET == 0) {
                 if (has_res) fixed(T{}, F{}, T{}, F{}, T{});
+                else if (track) fixed(T{}, T{}, F{}, F{}, T{});
                 else if (relu) fixed(T{}, F{}, F{}, F{}, T{});
                 else fixed(F{}, F{}, F{}, F{}, T{});
             }

@@ -255,6 +255,29 @@ def test_affine_reference_matches_oracle(name, make):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("make", [lambda: si.make_basic_block(b=2, c=20, h=9, w=11, seed=51),
+                                  lambda: si.make_bottleneck(b=3, c_in=64, c_mid=32, h=8, w=8, seed=52),
+                                  lambda: si.make_bottleneck(b=2, c_in=24, c_mid=13, h=6, w=5, seed=53)])
+def test_affine_inner_extrema_are_this_runs(make):
+    """The extrema of the inner layers come from the GEMM's epilogue: a second run in the same workspace on a smaller
+    input keeps nothing of the first one's, and an infinite inner activation is flagged."""
+    from paper_2201_06227_amd import binding as eg
+    import tests.gpu_common as gc
+    wl = make()
+    first, _, ref, ws = _gpu_affine(wl, with_taps=False)
+    x = wl.x
+    wl.x = x * np.float32(0.03125)
+    a_ref = torch.empty(first.size, dtype=torch.float32, device=gc.DEV)
+    eg.ref_forward(ref, gc.to_dev(wl.x), a_ref, ws)
+    want = gc.nhwc(ao.ref_forward(wl)["a_ref"]).reshape(-1)
+    assert np.array_equal(a_ref.cpu().numpy(), want)
+    assert eg.check(ws) == eg.OK
+    eg.ref_forward(ref, gc.to_dev(np.full_like(x, 3e38)), a_ref, ws)     # finite input, sums of the first layer are not
+    torch.cuda.synchronize()
+    assert eg.check(ws) != eg.OK
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("cfg", [1, 2, 3, 4])
 def test_affine_reference_score(cfg, orc_lib=None):
     """Plasticity against the affine reference (Eq. 1): within 1e-4 of the fp64 metric on the oracle's A_R."""
