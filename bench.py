@@ -497,7 +497,7 @@ def activation_cache_timing(eg, device, with_oracle):
     avg_s = sum(ms) * 1e-3 / len(ms)
     res = {"rows": f"{b} x {D} fp32 (8.4 MB per mini-batch), window {window}", "put_plus_get_us": round(dt * 1e6, 2),
            "minibatches_per_s": round(1.0 / dt, 1), "served_rows_match": ok,
-           "roofline": {"kernel": "cache_scatter_kernel / cache_gather_kernel", "bound": "hbm",
+           "roofline": {"kernel": "cache_put_kernel / cache_gather_kernel", "bound": "hbm",
                         "achieved": round(byts / avg_s / 1e9, 3), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                         "frac": round(byts / avg_s / 1e9 / PEAK_HBM_GBS, 4), "traffic": None,
                         "avg_launch_us": round(avg_s * 1e6, 3), "algorithmic_bytes_per_launch": byts}}

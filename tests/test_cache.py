@@ -117,7 +117,11 @@ CACHE_CASES = [dict(window=5, batch=8, D=4, dt="f32", universe=30),       # 16-b
                dict(window=3, batch=7, D=3, dt="bf16", universe=20),      # 6-byte rows: 2-byte copies
                dict(window=1, batch=4, D=64, dt="f32", universe=6),
                dict(window=5, batch=128, D=16384, dt="f32", universe=2000),   # rows of the basic block, two chunks each
-               dict(window=2, batch=64, D=50180, dt="bf16", universe=100)]    # ragged last chunk
+               dict(window=2, batch=64, D=50180, dt="bf16", universe=100),    # ragged last chunk
+               # rows that no 16-byte unit divides, over several chunks (2- and 4-byte aligned; tails of 2 and 12 bytes)
+               dict(window=3, batch=9, D=16393, dt="bf16", universe=40), dict(window=2, batch=5, D=20483, dt="f32", universe=16),
+               # a put of more than 64 workgroups that they do not divide; a window whose table more threads rebuild
+               dict(window=2, batch=67, D=8195, dt="f32", universe=90), dict(window=300, batch=32, D=33000, dt="bf16", universe=300)]
 
 
 @pytest.mark.gpu
