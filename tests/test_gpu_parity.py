@@ -159,6 +159,30 @@ def test_quantize_weights_batch_bit_exact(eg, gc, orc, name):
             gc.assert_int8_rows(q.cpu().numpy(), wq)
 
 
+@pytest.mark.parametrize("shapes", [[(33, 24), (257, 768), (5, 40), (70, 1008), (300, 77)], [(130, 72, 3, 3), (64, 200), (19, 1000)],
+                                    [(4101, 2048), (2050, 4104), (13, 8)]], ids=["rows", "mixed", "large"])
+def test_quantize_weights_bf16_bit_exact(eg, gc, orc, shapes):
+    """bf16 snapshots with one scale per tensor: whole and ragged 16-byte units, padded rows, a set large enough for the
+    longer shares, and the extreme value at either end of a tensor."""
+    g = torch.Generator().manual_seed(len(shapes[0]))
+    ws = [(torch.randn(*sh, generator=g) * (0.02 + 0.3 * i)).to(torch.bfloat16) for i, sh in enumerate(shapes)]
+    ws[0].view(-1)[-1] = -9.0
+    ws[1].view(-1)[0] = 11.0
+    wsp = eg.workspace(eg.quantize_weights_workspace_bytes(len(ws)))
+    w_q, scales = eg.quantize_weights([w.to(gc.DEV) for w in ws], ws=wsp)
+    assert eg.check(wsp) == eg.OK
+    for w, q, s in zip(ws, w_q, scales):
+        wq, wsc = orc.quantize(w.float().numpy())
+        assert s.item() == wsc
+        if w.ndim == 4:
+            gc.assert_conv_q(q.cpu().numpy().reshape(-1, q.shape[-1]), wq)
+        else:
+            gc.assert_int8_rows(q.cpu().numpy(), wq)
+    ws[-1].view(-1)[-1] = float("inf")
+    eg.quantize_weights([w.to(gc.DEV) for w in ws], ws=wsp)
+    assert eg.check(wsp) == eg.ERR_NONFINITE
+
+
 def test_quantize_weights_batch_flags_and_empty(eg, gc, orc):
     ws = eg.workspace(eg.quantize_weights_workspace_bytes(3))
     good = np.ones((4, 20), np.float32)
