@@ -37,6 +37,8 @@ PEAK_BF16_MFMA_TFLOPS = 2500.0
 # partial products per fp32 product, so the rate of fp32-product flops the matrix cores can sustain
 # is a sixth of the bf16 peak.  The algorithmic flop count (2 b^2 D per product) is priced against it.
 PEAK_GRAM_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6.0
+# The approximate attention of unobserved runs: three float16 partial products per fp32 product (float16 runs at bf16's rate)
+PEAK_ATTENTION_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 3.0
 
 
 def layernorm_in_gemm(wl):
@@ -198,15 +200,17 @@ def roofline_for(wl, cls, durations_ms, eg, steps, cfg=None, force_mfma=False):
     names = {eg.KERNEL_GRAM: "gram_kernel",
              eg.KERNEL_GEMM: "conv3x3_c16_fused_kernel" if small_conv else "gemm_i8_kernel",
              eg.KERNEL_ATTENTION: "attention_split_kernel", eg.KERNEL_LAYERNORM: "layernorm_vec_kernel"}
-    att_peak = PEAK_GRAM_TFLOPS
+    att_peak = PEAK_ATTENTION_TFLOPS
     if cls == eg.KERNEL_ATTENTION:
-        # which kernel an unobserved run takes (the library's rule): below 5 GFLOP the fp64 kernel; above it the
-        # approximate kernel with certified codes, on the bf16 matrix cores when head dims come in units of 8
+        # which kernel an unobserved run takes (the library's rule): the fp64 kernel up to 64 tokens and for small
+        # sizes; else the approximate kernel with certified codes, on the float16 matrix cores when head dims come in units of 8
         d = wl.dims
         dh = d["hidden"] // d["heads"]
-        if 4.0 * d["batch"] * d["heads"] * d["seq"] ** 2 * dh < 5.0e9:
+        pairs, plain = float(d["batch"] * d["heads"] * d["seq"] ** 2), dh % 8 or d["hidden"] % 4
+        size = 0.6 * pairs * dh if plain else (0.0 if d["seq"] <= 64 else 256.0 * pairs / (1 if d["seq"] <= 256 else 2))
+        if size < eg.attention_threshold():
             names[cls], att_peak = "attention_kernel", PEAK_F64_MFMA_TFLOPS
-        elif dh % 8 or d["hidden"] % 4:
+        elif plain:
             names[cls], att_peak = "attention_fast_kernel", PEAK_F32_MFMA_TFLOPS
     fused_ln = cls == eg.KERNEL_LAYERNORM and layernorm_in_gemm(wl)
     if not work or not durations_ms:
@@ -222,7 +226,7 @@ def roofline_for(wl, cls, durations_ms, eg, steps, cfg=None, force_mfma=False):
     if cls == eg.KERNEL_GEMM:
         peak_c, unit_c, scale = PEAK_I8_TOPS, "TOP/s", 1e12
     elif cls == eg.KERNEL_ATTENTION:
-        # unobserved runs of the large shapes: exact fp32 products as six bf16 partial products each, fp32 sums
+        # unobserved runs of the large shapes: fp32 products as three float16 partial products each, fp32 sums
         # (the values that decide an int8 code are re-evaluated in fp64 by the kernels that follow)
         peak_c, unit_c, scale = att_peak, "TFLOP/s", 1e12
     elif cls == eg.KERNEL_LAYERNORM:
