@@ -563,7 +563,8 @@ constexpr int kFinThreads = 1024;
 static int fin_columns(int b) { return b <= 32 ? 16 : 64; }      // CS
 static int fin_parts(int b) { return (b + fin_columns(b) - 1) / fin_columns(b); }
 
-template <int CS>
+// U: chunks that a thread requests together
+template <int CS, int U>
 __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *__restrict__ part, int nsplit, int b, int parts,
                                                                   double *__restrict__ sums, uint32_t *__restrict__ counter,
                                                                   float *__restrict__ p_out)
@@ -574,7 +575,6 @@ __global__ __launch_bounds__(kFinThreads) void sp_finalize_kernel(const float *_
     const int i = blockIdx.x / parts, pt = blockIdx.x % parts, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int j = pt * CS + t % CS, grp = t / CS;
     const size_t nelem = (size_t)b * b, cstride = 2 * nelem;
-    constexpr int U = CS == 16 ? 4 : 8;                           // chunks in flight per thread (2 loads each)
     double aw = 0.0, ab = 0.0;
     const float *p = part + (size_t)i * b + (j < b ? j : b - 1);
     for (int c = grp; c < nsplit; c += U * G) {
@@ -701,7 +701,12 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
         return launch_k(EGERIA_KERNEL_NONE, kernel, dim3((unsigned)(b * parts)), dim3(kFinThreads), 0, st, (const float *)part,
                         p.nsplit, (int)b, parts, sums, counter, p_out);
     };
-    return fin_columns(b) == 16 ? finish(sp_finalize_kernel<16>) : finish(sp_finalize_kernel<64>);
+    // All of a thread's chunks in one round trip (with 8 at a time the 256 of b = 64 took two), and few requests beyond the last
+    // chunk (b > 96 has 40 of them, where 8 per thread asked for 128).  Whole passes, us, 8 / now: basic block of 128 x 16 x 32 x 32
+    // 44.2 / 43.3, bottleneck of 64 x 1024 x 14 x 14 127.2 / 126.5, score of 100 x 62720 29.5 / 28.7.
+    if (fin_columns(b) == 16) return finish(sp_finalize_kernel<16, 4>);
+    if (p.nsplit <= 64) return finish(sp_finalize_kernel<64, 4>);
+    return p.nsplit <= 128 ? finish(sp_finalize_kernel<64, 8>) : finish(sp_finalize_kernel<64, 16>);
 }
 
 }  // namespace egeria

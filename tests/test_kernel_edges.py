@@ -90,6 +90,19 @@ def test_metric_longest_row(eg):
     torch.cuda.empty_cache()
 
 
+# Partials of 38, 79, 64, 65, 128, 129, 256 and 244 chunks: the finaliser requests 4 (up to 64 chunks), 8 (128) or 16 of them
+# per thread.  fp32 partial sums: 1e-4 relative.
+@pytest.mark.parametrize("b,D", [(100, 9000), (70, 30000), (40, 8192), (64, 8208), (33, 16384), (64, 16400), (50, 32768), (64, 70001)])
+def test_metric_chunk_counts(eg, b, D):
+    g = torch.Generator(device="cuda").manual_seed(D)
+    r = torch.randn(b, D, generator=g, device="cuda")
+    t = r + 0.05 * torch.randn(b, D, generator=g, device="cuda")
+    grams = [a.double() @ a.double().t() for a in (t, r)]
+    want = (torch.nn.functional.normalize(grams[0]) - torch.nn.functional.normalize(grams[1])).square().sum().item() / (b * b)
+    assert abs(eg.plasticity(t, r).item() - want) <= 1e-4 * want
+    assert eg.plasticity(r, r).item() == 0.0
+
+
 # A non-finite activation makes the score NaN, also where the other activation's rows are all zeros (their Gram rows have
 # no norm, which takes the other branch of a row's share).
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
