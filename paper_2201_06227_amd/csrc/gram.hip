@@ -701,12 +701,11 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
         return launch_k(EGERIA_KERNEL_NONE, kernel, dim3((unsigned)(b * parts)), dim3(kFinThreads), 0, st, (const float *)part,
                         p.nsplit, (int)b, parts, sums, counter, p_out);
     };
-    // All of a thread's chunks in one round trip (with 8 at a time the 256 of b = 64 took two), and few requests beyond the last
-    // chunk (b > 96 has 40 of them, where 8 per thread asked for 128).  Whole passes, us, 8 / now: basic block of 128 x 16 x 32 x 32
-    // 44.2 / 43.3, bottleneck of 64 x 1024 x 14 x 14 127.2 / 126.5, score of 100 x 62720 29.5 / 28.7.
+    // Few requests beyond the last chunk: b > 96 has 40 of them, where 8 per thread asked for 128.  Whole passes, us, 8 / 4: basic
+    // block of 128 x 16 x 32 x 32 44.2 / 43.5, score of 100 x 62720 29.5 / 28.8.  (16 per thread, one round trip for the 256 chunks
+    // of b = 64 instead of two, made no difference: bottleneck of 64 x 1024 x 14 x 14 127.2 / 127.0.)
     if (fin_columns(b) == 16) return finish(sp_finalize_kernel<16, 4>);
-    if (p.nsplit <= 64) return finish(sp_finalize_kernel<64, 4>);
-    return p.nsplit <= 128 ? finish(sp_finalize_kernel<64, 8>) : finish(sp_finalize_kernel<64, 16>);
+    return p.nsplit <= 64 ? finish(sp_finalize_kernel<64, 4>) : finish(sp_finalize_kernel<64, 8>);
 }
 
 }  // namespace egeria

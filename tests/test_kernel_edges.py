@@ -90,8 +90,8 @@ def test_metric_longest_row(eg):
     torch.cuda.empty_cache()
 
 
-# Partials of 38, 79, 64, 65, 128, 129, 256 and 244 chunks: the finaliser requests 4 (up to 64 chunks), 8 (128) or 16 of them
-# per thread.  fp32 partial sums: 1e-4 relative.
+# Partials of 38, 79, 64, 65, 128, 129, 256 and 244 chunks: the finaliser requests 4 (up to 64 chunks) or 8 of them
+# per thread together.  fp32 partial sums: 1e-4 relative.
 @pytest.mark.parametrize("b,D", [(100, 9000), (70, 30000), (40, 8192), (64, 8208), (33, 16384), (64, 16400), (50, 32768), (64, 70001)])
 def test_metric_chunk_counts(eg, b, D):
     g = torch.Generator(device="cuda").manual_seed(D)
