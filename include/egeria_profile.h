@@ -60,6 +60,9 @@ double egeria_profile_attention_threshold(double min_flops);
  * channels have a kernel of their own (with affine codes the one described here).  M, N, k_bytes >= 1. */
 egeria_status egeria_profile_gemm_tile(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3, int32_t *rows, int32_t *cols,
                                        int32_t *k_step);
+/* ... and how many K steps that kernel holds in LDS (tiles of one size come with two stages and with three); 0 for sizes that
+ * egeria_profile_gemm_tile refuses. */
+int32_t egeria_profile_gemm_stages(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3);
 
 /* What the device delivers to kernels shaped like this library's: one small complete kernel per kind, run
  * twice (the second run is timed with events on `stream`).  ms_out: duration of that run; work_out: what it

@@ -104,7 +104,7 @@ EXPORTS = [
     "egeria_cache_bytes", "egeria_cache_init", "egeria_cache_put", "egeria_cache_get", "egeria_profile_pause",
     "egeria_refresh_eval", "egeria_plasticity_noalloc", "egeria_profile_attention",
     "egeria_quantize_affine", "egeria_quantize_affine_workspace_bytes", "egeria_microbench",
-    "egeria_profile_attention_threshold", "egeria_profile_gemm_tile",
+    "egeria_profile_attention_threshold", "egeria_profile_gemm_tile", "egeria_profile_gemm_stages",
 ]
 
 (KERNEL_NONE, KERNEL_ABSMAX, KERNEL_QUANTIZE, KERNEL_GEMM, KERNEL_GRAM, KERNEL_ATTENTION, KERNEL_LAYERNORM,
@@ -177,6 +177,8 @@ def lib():
     L.egeria_profile_attention_threshold.argtypes = [ctypes.c_double]
     L.egeria_profile_gemm_tile.restype = ctypes.c_int
     L.egeria_profile_gemm_tile.argtypes = [_i64, _i32, _i64, _i32] + [ctypes.POINTER(_i32)] * 3
+    L.egeria_profile_gemm_stages.restype = _i32
+    L.egeria_profile_gemm_stages.argtypes = [_i64, _i32, _i64, _i32]
     L.egeria_microbench.restype = ctypes.c_int
     L.egeria_microbench.argtypes = [_i32, _i32, _vp, _sz, ctypes.POINTER(ctypes.c_float),
                                     ctypes.POINTER(ctypes.c_double), _vp]
@@ -562,6 +564,11 @@ def gemm_tile(M: int, N: int, k_bytes: int, conv3x3: bool = False):
     _check(lib().egeria_profile_gemm_tile(M, N, k_bytes, 1 if conv3x3 else 0, *[ctypes.byref(v) for v in out]),
            "egeria_profile_gemm_tile")
     return tuple(v.value for v in out)
+
+
+def gemm_stages(M: int, N: int, k_bytes: int, conv3x3: bool = False) -> int:
+    """egeria_profile_gemm_stages: K steps in LDS of the kernel that an int8 layer of these sizes runs with."""
+    return int(lib().egeria_profile_gemm_stages(M, N, k_bytes, 1 if conv3x3 else 0))
 
 
 def microbench(kind: int, iters: int, scratch: torch.Tensor):

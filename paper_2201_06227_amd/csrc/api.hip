@@ -1203,6 +1203,11 @@ egeria_status egeria_profile_gemm_tile(int64_t M, int32_t N, int64_t k_bytes, in
     return EGERIA_OK;
 }
 
+int32_t egeria_profile_gemm_stages(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3)
+{
+    return M < 1 || N < 1 || k_bytes < 1 ? 0 : gemm_stages(M, N, k_bytes, conv3x3 != 0);
+}
+
 const char *egeria_status_string(egeria_status s)
 {
     switch (s) {

@@ -280,6 +280,7 @@ struct GemmArgs {
 };
 hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st);
 void gemm_tile(int64_t M, int32_t N, int64_t kp, bool conv3x3, int32_t *rows, int32_t *cols, int32_t *k_step);
+int gemm_stages(int64_t M, int32_t N, int64_t kp, bool conv3x3);
 // true if launch_gemm_i8 can take the layer norm of an [M, N] output into the GEMM's launch
 bool gemm_layernorm_fusable(int32_t N, const void *ln_out, const void *ln_res, const void *gamma, const void *beta);
 

@@ -1190,19 +1190,26 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 //   Layers with few tiles come first.  A workgroup alone on its compute unit has nothing to hide its round trips behind: with
 // two stages of whole lines every K step waits for the one it requested, 1400 clocks of a 128x64 step; with three stages the
 // step takes what LDS needs, 24 KB written at 62 bytes per clock, 48 read at 235 and some 180 clocks of barrier, 770 (a fourth
-// stage changes nothing).  64x64 tiles as long as they bring 1.5 workgroups per compute unit, or 2.25 where 128x64 tiles would
-// start a second round; else 128x64 tiles that fill one round at most, else, from K of 1024 bytes on, 128x128 tiles that do.
+// stage changes nothing).  Three stages: 64x64 tiles as long as they bring 1.5 workgroups per compute unit, or 2.25 where 128x64
+// tiles would start a second round; else 128x64 tiles that fill one round at most; else, from K of 1024 bytes on, 128x128 tiles
+// up to 4/5 of a round and 128x64 tiles, two per compute unit, up to 7/4 rounds (from 4/5 on the ranking differs from shape to
+// shape: 128x128 tiles gain 5 to 8 % for 768 columns and nothing for 256 and 512; 128x64 ones are near the best).  Layers of four 128x64 tiles or fewer take those: 64x64 ones make no difference (257 x 48 x 112 5.2 us with
+// either, 130 x 36 x 64 4.6 / 4.9, 225 x 44 x 432 (3x3) 7.3 / 7.6).
 // us, chosen by price / 64x64 / 128x64 / 128x128 with three stages: 2450 x 512 x 2048 12.6 / 8.7 / 9.7 / 12.4, 2000 x 768 x 3072
 // 17.3 / 11.8 / 12.0 / 14.9, 128 x 4096 x 4096 20.6 / 11.6 / 13.5 / 17.8, 32 x 512 x 512 5.1 / 4.2 / 5.0 / 6.0, 4480 x 512 x 1024
 // 9.6 / 8.5 / 9.0 / 9.2, 4096 x 512 x 2048 13.0 / 11.4 / 9.8 / 12.2, 4096 x 768 x 3072 20.4 / 18.6 / 18.8 / 17.1, 12544 x 256 x
-// 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7, 8000 x 512 x 1536 14.2 / 15.5 / 14.4 / 13.4; 4096 x 768 x 768 8.5 with all of them.
+// 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7; 4096 x 768 x 768 8.5 with all of them.  Beyond 4/5 of a round of 128x128 tiles (another
+// run), us: 4728 x 768 x 3072 (222 tiles) 23.1 / 25.3 / 21.9 / 20.7, 10500 x 260 x 2340 (3x3, 249) 23.1 / 26.8 / 21.8 / 20.6, 8000 x
+// 512 x 1536 (252) 16.1 / 17.1 / 17.1 / 16.0, 16000 x 256 x 2048 (250) 19.0 / 20.9 / 20.2 / 19.1, 5376 x 768 x 3072 (252) 24.4 /
+// 25.6 / 23.8 / 22.5.
 static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
 {
     const int64_t cu = compute_units(), t64 = ((M + 63) / 64) * ((N + 63) / 64), t128x64 = ((M + 127) / 128) * ((N + 63) / 64),
                   t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (2 * t64 <= 3 * cu || (t128x64 > cu && 4 * t64 <= 9 * cu)) return kDeepSmall;
+    if (t128x64 > 4 && (2 * t64 <= 3 * cu || (t128x64 > cu && 4 * t64 <= 9 * cu))) return kDeepSmall;
     if (t128x64 <= cu) return kDeepMid;
-    if (t128 <= cu && kp >= 1024) return kDeepLarge;
+    if (5 * t128 <= 4 * cu && kp >= 1024) return kDeepLarge;
+    if (4 * t128x64 <= 7 * cu && kp >= 1024) return kDeepMid;
     int best = 0;
     double best_cost = 0.0;
     for (int i = 0; i < kNumShapes; ++i) {
@@ -1231,6 +1238,14 @@ static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
         }
     }
     return best;
+}
+
+// K steps in LDS of the kernel that an int8 layer of these sizes runs with (gemm_tile names its output tile).
+int gemm_stages(int64_t M, int32_t N, int64_t kp, bool conv3x3)
+{
+    if (N <= 32) return stages_for(64);
+    const int i = choose_shape(M, N, kp, conv3x3);
+    return i >= kNumShapes ? 3 : stages_for(kShapes[i].bk);
 }
 
 // Output tile and K step of an int8 layer of these sizes, for tests that have to reach a certain shape.

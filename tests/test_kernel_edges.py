@@ -145,17 +145,14 @@ def test_metric_batch_of_one(eg, D, types):
 # Every output tile of the int8 GEMM with rows and columns that end inside it (the tile is asked for, so that a case
 # cannot come to run on another one), against the CPU oracle: fully connected layers (columns in whole groups of four
 # and ragged), with symmetric and affine codes.
-# (128x64 with whole lines comes with two stages, chosen by price, and with three, by rule, as do 64x64 and the first 128x128.)
-LINEAR_TILES = [((128, 32, 64), 1000, 20, 100), ((64, 64, 128), 257, 48, 100), ((128, 64, 128), 4000, 772, 520),
-                ((128, 64, 128), 3970, 484, 100), ((128, 128, 128), 7990, 484, 1030),
-                ((128, 64, 64), 49805, 68, 64),
+LINEAR_TILES = [((128, 32, 64), 1000, 20, 100), ((128, 64, 128), 257, 48, 100), ((128, 64, 64), 49805, 68, 64),
                 ((128, 128, 64), 44382, 140, 64), ((128, 128, 128), 49294, 68, 520), ((128, 192, 64), 43978, 132, 512),
                 ((256, 128, 64), 49395, 196, 512), ((256, 192, 128), 16240, 580, 2048), ((256, 256, 128), 16426, 652, 2048)]
 
 
 @pytest.mark.parametrize("mode", ["dynamic", "affine"])
 @pytest.mark.parametrize("ragged", [0, 3])
-@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES, ids=["x".join(map(str, t[0])) + f"_M{t[1]}" for t in LINEAR_TILES])
+@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES, ids=["x".join(map(str, t[0])) for t in LINEAR_TILES])
 def test_linear_tiles_at_edges(eg, orc, tile, M, N, K, ragged, mode):
     import gpu_common as gc
     import synth_inputs as si
@@ -172,17 +169,27 @@ def test_linear_tiles_at_edges(eg, orc, tile, M, N, K, ragged, mode):
     assert np.array_equal(got.reshape(M, N), want)
 
 
+# Tiles that come with two stages of whole lines (chosen by price) and with three (by rule).
+LINEAR_STAGES = [((64, 64, 128), 3, 700, 200, 520), ((128, 64, 128), 2, 4000, 772, 520), ((128, 64, 128), 3, 3970, 484, 100),
+                 ((128, 64, 128), 3, 10500, 260, 1030), ((128, 128, 128), 3, 5990, 484, 1030)]
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "affine"])
+@pytest.mark.parametrize("ragged", [0, 3])
+@pytest.mark.parametrize("tile,stages,M,N,K", LINEAR_STAGES, ids=["x".join(map(str, t[0])) + f"_{t[1]}stages_M{t[2]}" for t in LINEAR_STAGES])
+def test_linear_stages_at_edges(eg, orc, tile, stages, M, N, K, ragged, mode):
+    assert eg.gemm_stages(M, N + ragged, eg.padded(K)) == stages
+    test_linear_tiles_at_edges(eg, orc, tile, M, N, K, ragged, mode)
+
+
 # The same for 3x3 convolutions (whose affine codes look up the class of a border pixel per row of the tile): the block's first layer writes the maximum (dynamic), int8 codes (static scales) or fp32
 # for affine codes, its second one adds the skip connection.
-# (c = 132 and 260: window positions of more than a K step that end inside one.)
-CONV_TILES = [((64, 64, 128), 1, 44, 15, 15), ((64, 64, 128), 3, 132, 15, 17), ((128, 64, 128), 36, 132, 29, 28),
-              ((128, 64, 128), 40, 132, 14, 15), ((128, 128, 128), 50, 260, 14, 15),
-              ((128, 64, 64), 11, 132, 54, 56), ((128, 128, 128), 12, 68, 64, 65),
+CONV_TILES = [((128, 64, 128), 1, 44, 15, 15), ((128, 64, 64), 11, 132, 54, 56), ((128, 128, 128), 12, 68, 64, 65),
               ((128, 128, 64), 16, 68, 64, 65), ((128, 192, 64), 11, 132, 63, 64), ((256, 128, 64), 12, 196, 64, 65)]
 
 
 @pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "affine ragged"])
-@pytest.mark.parametrize("tile,b,c,h,w", CONV_TILES, ids=["x".join(map(str, t[0])) + f"_b{t[1]}" for t in CONV_TILES])
+@pytest.mark.parametrize("tile,b,c,h,w", CONV_TILES, ids=["x".join(map(str, t[0])) for t in CONV_TILES])
 def test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode):
     import gpu_common as gc
     import synth_inputs as si
@@ -199,12 +206,24 @@ def test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode):
     assert np.array_equal(got.reshape(-1, c), gc.nhwc(want))
 
 
+# (c = 132 and 260: window positions of more than a K step that end inside one.)
+CONV_STAGES = [((64, 64, 128), 3, 4, 44, 15, 15), ((64, 64, 128), 3, 3, 132, 15, 17), ((128, 64, 128), 2, 36, 132, 29, 28),
+               ((128, 64, 128), 3, 40, 132, 14, 15), ((128, 64, 128), 3, 50, 260, 14, 15), ((128, 128, 128), 3, 38, 260, 14, 15)]
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "affine ragged"])
+@pytest.mark.parametrize("tile,stages,b,c,h,w", CONV_STAGES, ids=["x".join(map(str, t[0])) + f"_{t[1]}stages_b{t[2]}" for t in CONV_STAGES])
+def test_conv_stages_at_edges(eg, orc, tile, stages, b, c, h, w, mode):
+    assert eg.gemm_stages(b * h * w, c, 9 * eg.padded(c), True) == stages
+    test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode)
+
+
 # ... and for the layers of an encoder (no activation, with and without the maximum) at a ragged number of tokens.
 def test_encoder_tiles_at_edges(eg, orc):
     import gpu_common as gc
     import synth_inputs as si
     M = 24 * 197
-    assert [eg.gemm_tile(M, n, k)[:2] for n, k in ((2304, 768), (3072, 768), (768, 3072))] == [(128, 192), (256, 128), (128, 128)]
+    assert [eg.gemm_tile(M, n, k)[:2] for n, k in ((2304, 768), (3072, 768), (768, 3072))] == [(128, 192), (256, 128), (128, 64)]
     wl = si.make_bert(b=24, s=197, seed=11, train_act_dtype="f32")
     got = gc.run_forward(wl, with_taps=False)[0]
     gc.assert_within_ulp(got, orc.ref_forward(wl)["a_ref"][0], 1, "encoder layer")
@@ -213,7 +232,7 @@ def test_encoder_tiles_at_edges(eg, orc):
 # GEMM epilogue of small modules: rows and columns that end inside, at and just past a tile or a group of four columns, with
 # and without a residual, for the dynamic, static, per-channel and affine paths.  The parity tests hold observed runs to the
 # oracle; here the observed run, which takes the general form of the epilogue, is the reference for the straight-line one.
-# (All of these run on 64x64 tiles; the others are above.)
+# (All of these run on 64x64 or 128x64 tiles; the others are above.)
 @pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "per_channel"])
 @pytest.mark.parametrize("b,c,h,w", [(1, 36, 3, 5), (2, 64, 8, 8), (3, 33, 11, 12), (5, 68, 16, 13), (4, 130, 16, 16), (9, 64, 15, 17)])
 def test_conv_epilogue_edges(eg, b, c, h, w, mode):
