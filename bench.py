@@ -613,7 +613,7 @@ def attention_error(cfg, device):
     print("layer  absmax(ctx)  max|v|  median E/unit  median err/unit  p99.99 err/unit  max err/unit  max err/E  values with err > E  uncertain codes (fraction)")
     for l in range(n):
         c64, _ = eg.profile_attention(qkvs[l], heads, 0)
-        c32, E = eg.profile_attention(qkvs[l], heads, 1)
+        c32, E = eg.profile_attention_bounds(qkvs[l], heads)
         torch.cuda.synchronize()
         E_el = E.permute(0, 2, 1)[..., None].expand(b, S, heads, dh).reshape(b, S, H) + 12.0 * 2.0 ** -24 * c32.abs()
         v = qkvs[l][:, :, 2 * H:].reshape(b, S, heads, dh)

@@ -38,14 +38,20 @@ egeria_status egeria_profile_begin(int32_t kernel_class, int32_t max_launches);
 egeria_status egeria_profile_pause(int32_t paused);
 egeria_status egeria_profile_end(float *ms_out, int32_t capacity, int32_t *n_out);
 
-/* The attention of a Transformer layer on its own, for measuring the approximate kernel's error against the fp64
+/* The attention of a Transformer layer on its own, for measuring the approximate kernels' error against the fp64
  * one (bench.py --attention-error).  qkv: fp32 [B, S, 3 * hidden] (q | k | v per token), ctx: fp32
- * [B, S, hidden] out.  mode 0: the fp64 kernel of observed runs.  mode 1: the approximate matrix-core kernel of
- * unobserved runs; bounds then receives the error bound E of every query of a head, fp32 [B, heads, S] (DEVICE,
- * 16-byte aligned; ignored in mode 0; a value x is off by at most E + 12 * 2^-24 |x|).  Limits as for the Transformer
- * kinds of egeria_ref_forward. */
+ * [B, S, hidden] out.  mode 0: the fp64 kernel of observed runs.  mode 1: the fp32 matrix-core kernel (unobserved runs take
+ * it where heads are no multiple of 8 dims); records then receives B * heads * ceil(S / 64) pairs {uint32 bit pattern of the
+ * largest |ctx| of a workgroup's 64 queries x head dims, fp32 error bound E of those values} (DEVICE, 16-byte
+ * aligned; ignored in mode 0; a value x is off by at most E + 12 * 2^-24 |x|).  Limits as for the Transformer kinds of
+ * egeria_ref_forward. */
 egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads,
-                                       int32_t mode, float *ctx, float *bounds, void *stream);
+                                       int32_t mode, float *ctx, void *records, void *stream);
+/* ... and the approximate kernel that unobserved runs take for this head size, on operands scaled as there.  bounds: the
+ * error bound E of every query of a head, fp32 [B, heads, S] out (DEVICE, 16-byte aligned, bounds_bytes long; the meaning of E
+ * as above).  ws: DEVICE scratch, at least egeria_quantize_workspace_bytes(). */
+egeria_status egeria_profile_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads, float *ctx,
+                                              float *bounds, size_t bounds_bytes, void *ws, size_t ws_bytes, void *stream);
 
 /* Unobserved runs of the Transformer kinds evaluate attention with the certified approximate kernels when its size, in
  * flops as the fp64 kernel does them (256 * batch * heads * seq^2; half of that beyond 256 tokens, none up to 64, where they

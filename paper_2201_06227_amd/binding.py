@@ -102,7 +102,7 @@ EXPORTS = [
     "egeria_profile_end", "egeria_quantize_weights", "egeria_quantize_weights_workspace_bytes",
     "egeria_freeze_init", "egeria_freeze_observe",
     "egeria_cache_bytes", "egeria_cache_init", "egeria_cache_put", "egeria_cache_get", "egeria_profile_pause",
-    "egeria_refresh_eval", "egeria_plasticity_noalloc", "egeria_profile_attention",
+    "egeria_refresh_eval", "egeria_plasticity_noalloc", "egeria_profile_attention", "egeria_profile_attention_bounds",
     "egeria_quantize_affine", "egeria_quantize_affine_workspace_bytes", "egeria_microbench",
     "egeria_profile_attention_threshold", "egeria_profile_gemm_tile", "egeria_profile_gemm_stages",
 ]
@@ -173,6 +173,8 @@ def lib():
     L.egeria_profile_end.argtypes = [ctypes.POINTER(ctypes.c_float), _i32, ctypes.POINTER(_i32)]
     L.egeria_profile_attention.restype = ctypes.c_int
     L.egeria_profile_attention.argtypes = [_vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp]
+    L.egeria_profile_attention_bounds.restype = ctypes.c_int
+    L.egeria_profile_attention_bounds.argtypes = [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _sz, _vp, _sz, _vp]
     L.egeria_profile_attention_threshold.restype = ctypes.c_double
     L.egeria_profile_attention_threshold.argtypes = [ctypes.c_double]
     L.egeria_profile_gemm_tile.restype = ctypes.c_int
@@ -626,14 +628,27 @@ class ActivationCache:
 
 
 def profile_attention(qkv: torch.Tensor, heads: int, mode: int):
-    """egeria_profile_attention: (ctx [B, S, hidden], error bounds [B, heads, S] or None)."""
+    """egeria_profile_attention: (ctx [B, S, hidden], records [n, 2] int32 view or None)."""
     qkv = _dev(qkv)
     B, S, h3 = qkv.shape
     hidden = h3 // 3
     ctx = torch.empty((B, S, hidden), dtype=torch.float32, device=qkv.device)
-    bounds = torch.zeros((B, heads, S), dtype=torch.float32, device=qkv.device) if mode == 1 else None
-    _check(lib().egeria_profile_attention(_ptr(qkv), B, S, hidden, heads, mode, _ptr(ctx), _ptr(bounds), _stream()),
+    rec = torch.zeros((B * heads * ((S + 63) // 64), 2), dtype=torch.int32, device=qkv.device) if mode == 1 else None
+    _check(lib().egeria_profile_attention(_ptr(qkv), B, S, hidden, heads, mode, _ptr(ctx), _ptr(rec), _stream()),
            "egeria_profile_attention")
+    return ctx, rec
+
+
+def profile_attention_bounds(qkv: torch.Tensor, heads: int):
+    """egeria_profile_attention_bounds: (ctx [B, S, hidden], error bounds [B, heads, S])."""
+    qkv = _dev(qkv)
+    B, S, h3 = qkv.shape
+    hidden = h3 // 3
+    ctx = torch.empty((B, S, hidden), dtype=torch.float32, device=qkv.device)
+    bounds = torch.empty((B, heads, S), dtype=torch.float32, device=qkv.device)
+    ws = workspace(int(lib().egeria_quantize_workspace_bytes()), qkv.device)
+    _check(lib().egeria_profile_attention_bounds(_ptr(qkv), B, S, hidden, heads, _ptr(ctx), _ptr(bounds), 4 * bounds.numel(),
+                                                 _ptr(ws), ws.numel(), _stream()), "egeria_profile_attention_bounds")
     return ctx, bounds
 
 

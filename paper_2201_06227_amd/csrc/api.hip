@@ -1177,14 +1177,25 @@ egeria_status egeria_profile_end(float *ms_out, int32_t capacity, int32_t *n_out
 }
 
 egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads,
-                                       int32_t mode, float *ctx, float *bounds, void *stream)
+                                       int32_t mode, float *ctx, void *records, void *stream)
 {
     if (!qkv || !ctx || B < 1 || S < 1 || hidden < 1 || heads < 1 || hidden % heads != 0) return EGERIA_ERR_INVALID_ARG;
     if (!aligned16(qkv) || !aligned16(ctx) || (mode != 0 && mode != 1)) return EGERIA_ERR_INVALID_ARG;
-    if (mode == 1 && (!bounds || !aligned16(bounds))) return EGERIA_ERR_INVALID_ARG;
+    if (mode == 1 && (!records || !aligned16(records))) return EGERIA_ERR_INVALID_ARG;
     if (hidden / heads > 64) return EGERIA_ERR_UNSUPPORTED;
     if (mode == 0) EG_HIP(launch_attention(qkv, B, S, hidden, heads, ctx, nullptr, (hipStream_t)stream));
-    else EG_HIP(launch_attention_fast(qkv, B, S, hidden, heads, ctx, bounds, (hipStream_t)stream));
+    else EG_HIP(launch_attention_fp32(qkv, B, S, hidden, heads, ctx, records, (hipStream_t)stream));
+    return EGERIA_OK;
+}
+
+egeria_status egeria_profile_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads, float *ctx,
+                                              float *bounds, size_t bounds_bytes, void *ws, size_t ws_bytes, void *stream)
+{
+    if (!qkv || !ctx || !bounds || !ws || B < 1 || S < 1 || hidden < 1 || heads < 1 || hidden % heads != 0) return EGERIA_ERR_INVALID_ARG;
+    if (!aligned16(qkv) || !aligned16(ctx) || !aligned16(bounds) || !aligned16(ws)) return EGERIA_ERR_INVALID_ARG;
+    if (hidden / heads > 64) return EGERIA_ERR_UNSUPPORTED;
+    if (bounds_bytes < (size_t)B * heads * S * 4 || ws_bytes < header_bytes(1)) return EGERIA_ERR_WORKSPACE_TOO_SMALL;
+    EG_HIP(launch_attention_bounds(qkv, B, S, hidden, heads, ctx, bounds, ws_absmax(ws, 0), (hipStream_t)stream));
     return EGERIA_OK;
 }
 

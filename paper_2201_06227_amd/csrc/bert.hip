@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
         r.amax_bits = a;
         r.err = 5.9604645e-8f * __uint_as_float(v) * (kErrBase + kErrPerScore * __uint_as_float(sb));
         if (!(r.err <= 3.402823466e+38f)) r.amax_bits = 0x7f800000u;   // non-finite inputs: flagged downstream
-        if (qt * QT + tid < S) err_q[(int64_t)bh * S + qt * QT + tid] = r.err;
+        if (err_q && qt * QT + tid < S) err_q[(int64_t)bh * S + qt * QT + tid] = r.err;
         if (tid == 0 && rec) rec[vid] = r;
         // the largest of both over all workgroups, for the kernel that settles the exact maximum (atomically
         // combined words spread over ways; both are non-negative floats, whose bit patterns order like them)
@@ -798,21 +798,8 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     fetch_k(0);
     fetch_v(0);
 
-    // the largest |value| of the tensor (or, for the kernel alone, of this head's rows): the scale of K and V
-    uint32_t mbits = 0;
-    if (max_slot) {
-        mbits = reduce_ways(max_slot);
-    } else {
-        for (int e = lane; e < S * dh; e += 64) {
-            const int64_t at = (tok0 + e / dh) * ld + e % dh;
-            const uint32_t a = abs_bits(qbase[at]), b = abs_bits(kbase[at]), c = abs_bits(vbase[at]);
-            mbits = mbits > a ? mbits : a;
-            mbits = mbits > b ? mbits : b;
-            mbits = mbits > c ? mbits : c;
-        }
-        mbits = wave_max_u32(mbits);
-    }
-    mbits = (uint32_t)__builtin_amdgcn_readfirstlane((int)mbits);
+    // the largest |value| of the tensor: the scale of K and V
+    const uint32_t mbits = (uint32_t)__builtin_amdgcn_readfirstlane((int)reduce_ways(max_slot));
     float kv_up, kv_down, q_up, q_down;
     f16_scale(mbits, kv_up, kv_down);
     Split2 qs[4];
@@ -1630,17 +1617,52 @@ static hipError_t launch_attention_approx(const float *qkv, int32_t B, int32_t S
                     err_slot);
 }
 
-// Kernel 1 alone (benchmark instrumentation: its error against the fp64 kernel): approximate context and the
-// error bound E of every query of a head, fp32 [B, heads, S].
-hipError_t launch_attention_fast(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                 float *bounds, hipStream_t st)
+// The largest |value| of a tensor into the words of a maximum slot, a workgroup per word (runs have it from the GEMM's epilogue).
+__global__ __launch_bounds__(256) void tensor_max_kernel(const float *__restrict__ x, int64_t n, uint32_t *__restrict__ slot)
+{
+    __shared__ uint32_t sm[4];
+    uint32_t m = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += kAmaxWays * 256) {
+        const uint32_t a = abs_bits(x[i]);
+        m = m > a ? m : a;
+    }
+    m = wave_max_u32(m);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) m = m > sm[w] ? m : sm[w];
+        slot[blockIdx.x * kAmaxStride] = m;
+    }
+}
+
+// Kernel 1 alone (benchmark instrumentation: its error against the fp64 kernel), on operands scaled as in a run: approximate
+// context and the error bound E of every query of a head, fp32 [B, heads, S].  max_slot: scratch, a maximum slot.
+hipError_t launch_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
+                                   float *bounds, uint32_t *max_slot, hipStream_t st)
 {
     const int dh = Hd / heads;
     const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
     if (grid <= 0) return hipSuccess;
     if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(bounds)) return hipErrorInvalidValue;
-    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, bounds, nullptr, nullptr, nullptr, nullptr, nullptr, st);
+    const hipError_t e = launch_k(EGERIA_KERNEL_NONE, tensor_max_kernel, dim3(kAmaxWays), dim3(256), 0, st, qkv, (int64_t)B * S * 3 * Hd, max_slot);
+    if (e != hipSuccess) return e;
+    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, bounds, nullptr, max_slot, nullptr, nullptr, nullptr, st);
+}
+
+// The fp32 form of kernel 1 alone, any head size: approximate context and a record per 64 queries of a head.
+hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
+                                 void *records, hipStream_t st)
+{
+    const int dh = Hd / heads;
+    const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
+    if (grid <= 0) return hipSuccess;
+    if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
+    if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(records)) return hipErrorInvalidValue;
+    const int per_xcd = (int)((grid + 7) / 8);
+    return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
+                    (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx, (float *)nullptr,
+                    (AttnRecord *)records, (int)grid, per_xcd, (uint32_t *)nullptr, (uint32_t *)nullptr);
 }
 
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,

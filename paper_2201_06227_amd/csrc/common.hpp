@@ -326,8 +326,10 @@ hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, 
 // attention_records_bytes(...) bytes of scratch, amax_slot, err_slot and exact_slot atomically combined maximum
 // words (zero on entry), unsure_total (nullable) is incremented by the number of re-evaluated values.
 size_t attention_records_bytes(int32_t B, int32_t S, int32_t heads);
-hipError_t launch_attention_fast(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                 float *bounds, hipStream_t st);
+hipError_t launch_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
+                                   float *bounds, uint32_t *max_slot, hipStream_t st);
+hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
+                                 void *records, hipStream_t st);
 // true if that attention wants the largest |value| of qkv in err_slot on entry (the form that splits operands)
 bool attention_splits(int32_t Hd, int32_t heads);
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,

@@ -197,3 +197,13 @@ def test_tile_query(eg):
     for bad in ((0, 1, 16), (1, 0, 16), (1, 1, 0)):
         with pytest.raises(eg.EgeriaError):
             eg.gemm_tile(*bad)
+
+
+def test_attention_bounds_refuse_short_buffers(eg):
+    fake = ctypes.c_void_p(0x1000)          # never dereferenced: validation fails first
+    call = eg.lib().egeria_profile_attention_bounds
+    ws = eg.quantize_workspace_bytes()
+    assert call(fake, 2, 70, 32, 2, fake, fake, 2 * 2 * 70 * 4 - 1, fake, ws, None) == eg.ERR_WORKSPACE_TOO_SMALL
+    assert call(fake, 2, 70, 32, 2, fake, fake, 2 * 2 * 70 * 4, fake, ws - 1, None) == eg.ERR_WORKSPACE_TOO_SMALL
+    assert call(fake, 2, 70, 32, 2, fake, None, 1 << 20, fake, ws, None) == eg.ERR_INVALID_ARG
+    assert call(fake, 2, 70, 130, 2, fake, fake, 1 << 20, fake, ws, None) == eg.ERR_UNSUPPORTED

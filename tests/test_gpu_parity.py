@@ -604,6 +604,30 @@ def test_attention_paths_agree(eg, gc, kw):
     assert np.array_equal(outs[0].cpu().numpy().reshape(observed.shape), observed)
 
 
+@pytest.mark.parametrize("S,heads,dh", [(64, 2, 16), (131, 3, 16), (200, 2, 64), (70, 3, 22)])
+def test_profile_attention_writes_its_records_only(eg, gc, S, heads, dh):
+    """The measuring entry leaves one pair per 64 queries of a head, whatever the kernel behind it, and the error of each
+    value within the bound of its pair."""
+    B, H = 2, heads * dh
+    qkv = torch.randn(B, S, 3 * H, generator=torch.Generator().manual_seed(S)).to(gc.DEV)
+    tiles = (S + 63) // 64
+    n = B * heads * tiles
+    rec = torch.full((2 * n + B * heads * S,), 7, dtype=torch.int32, device=gc.DEV)
+    ctx = torch.empty(B, S, H, device=gc.DEV)
+    assert eg.lib().egeria_profile_attention(qkv.data_ptr(), B, S, H, heads, 1, ctx.data_ptr(), rec.data_ptr(),
+                                             torch.cuda.current_stream().cuda_stream) == eg.OK
+    exact, _ = eg.profile_attention(qkv, heads, 0)
+    torch.cuda.synchronize()
+    assert bool((rec[2 * n:] == 7).all())
+    pairs = rec[:2 * n].view(torch.float32).reshape(B, heads, tiles, 2).cpu()
+    c, e = (t.reshape(B, S, heads, dh).permute(0, 2, 1, 3).cpu() for t in (ctx, exact))
+    for t in range(tiles):
+        part = c[:, :, 64 * t:64 * t + 64]
+        assert torch.equal(pairs[:, :, t, 0], part.abs().amax((2, 3)))
+        err = (part.double() - e[:, :, 64 * t:64 * t + 64].double()).abs() - 12 * 2.0 ** -24 * part.double().abs()
+        assert bool((err.amax((2, 3)) <= pairs[:, :, t, 1].double()).all())
+
+
 # what the certified kernels meet beyond ordinary activations: rows that tie for the tensor's maximum (the candidates of a
 # workgroup overflow its list), nothing but zeros, whole samples twice, scores in the hundreds, values that the split's scale
 # leaves few digits of (every code is re-evaluated: the list of the quantiser overflows)
