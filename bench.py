@@ -582,7 +582,8 @@ def microbench(device):
 def attention_error(cfg, device):
     """Error of the approximate matrix-core attention kernel against the fp64 one, layer by layer, on the qkv
     tensors of the workload's own reference forward, set against the bound the certified quantiser works
-    with: E of the query + 12 * 2^-24 |x|.  Prints a text table."""
+    with: E of the query + 12 * 2^-24 |x|; then the same for kinds of q, k, v whose rounding errors add up.  Prints
+    text tables."""
     import ctypes
     import torch
     import synth_inputs as si
@@ -611,14 +612,21 @@ def attention_error(cfg, device):
     print(f"# {WORKLOAD_NAMES[cfg]}: the approximate attention kernel (attention_split_kernel when head dims come in units of 8, else attention_fast_kernel) against attention_kernel (fp64), per layer")
     print("# err = |fast - fp64| per context value; E = the certified quantiser's bound for that value; unit = 2^-24 * max|v| of the head")
     print("layer  absmax(ctx)  max|v|  median E/unit  median err/unit  p99.99 err/unit  max err/unit  max err/E  values with err > E  uncertain codes (fraction)")
-    for l in range(n):
-        c64, _ = eg.profile_attention(qkvs[l], heads, 0)
-        c32, E = eg.profile_attention_bounds(qkvs[l], heads)
+
+    def against_bound(qkv, heads):
+        b, S, h3 = qkv.shape
+        H = h3 // 3
+        dh = H // heads
+        c64, _ = eg.profile_attention(qkv, heads, 0)
+        c32, E = eg.profile_attention_bounds(qkv, heads)
         torch.cuda.synchronize()
         E_el = E.permute(0, 2, 1)[..., None].expand(b, S, heads, dh).reshape(b, S, H) + 12.0 * 2.0 ** -24 * c32.abs()
-        v = qkvs[l][:, :, 2 * H:].reshape(b, S, heads, dh)
+        v = qkv[:, :, 2 * H:].reshape(b, S, heads, dh)
         unit = (v.abs().amax(dim=(1, 3)) * 2.0 ** -24)[:, None, :, None].expand(b, S, heads, dh).reshape(b, S, H)
-        err = (c32.double() - c64.double()).abs().float()
+        return c64, c32, E_el, v, unit, (c32.double() - c64.double()).abs().float()
+
+    for l in range(n):
+        c64, c32, E_el, v, unit, err = against_bound(qkvs[l], heads)
         r_unit = (err / unit).flatten()
         r_E = err / E_el
         absmax = c64.abs().max().item()
@@ -629,6 +637,17 @@ def attention_error(cfg, device):
         p9999 = torch.topk(r_unit, k).values[-1].item()
         print(f"{l:5d}  {absmax:11.4f}  {v.abs().max().item():6.3f}  {(E_el / unit).median().item():13.3f}  {r_unit.median().item():15.3f}  {p9999:15.3f}  "
               f"{r_unit.max().item():12.3f}  {r_E.max().item():9.3f}  {int((r_E > 1).sum().item()):19d}  {(lo != hi).float().mean().item():.2e}")
+    print()
+    print("# kinds of q, k, v (synth_inputs.attention_qkv) at 2 x 131 tokens x 3 heads of 64, 2 x 256 x 12 of 64, 1 x 515 x 4 of 48, 2 x 300 x 4 of 8, 1 x 2048 x 2 of 64:")
+    print("# largest err / E of each, and the largest and the median E of all, in units of 2^-24 * max|v| of the head")
+    for kind in si.ATTENTION_KINDS:
+        worst, e_units = [], []
+        for kb, ks, kh, kd in ((2, 131, 3, 64), (2, 256, 12, 64), (1, 515, 4, 48), (2, 300, 4, 8), (1, 2048, 2, 64)):
+            _, _, E_el, _, unit, err = against_bound(torch.from_numpy(si.attention_qkv(kind, kb, ks, kh, kd)).to(dev), kh)
+            worst.append((err / E_el).max().item())
+            e_units.append((E_el / unit).flatten())
+        e_units = torch.cat(e_units)
+        print(f"{kind:26s}" + "".join(f"{w:7.3f}" for w in worst) + f"  {e_units.max().item():9.1f}  {e_units.median().item():8.2f}")
 
 
 def main():

@@ -667,8 +667,8 @@ constexpr int kSplitKRow = 128;          // bytes per key row of a K plane (8 un
 constexpr int kSplitVRow = 80;           // bytes per head-dim row of a V plane (4 units + pad)
 constexpr int kSplitKPlane = kSplitKeys * kSplitKRow, kSplitVPlane = kDh * kSplitVRow;
 constexpr int kSplitStage = 2 * (kSplitKPlane + kSplitVPlane);
-// error bound of a query's values, in units of 2^-24 of the largest |v| (where it is formed, below)
-constexpr float kSplitErrBase = 4.0f, kSplitErrPerScore = 4.0f, kSplitErrSum = 0.3f;
+// relative errors that make up the error bound of a query's values, in units of 2^-24 (where it is formed, below)
+constexpr float kSplitErrBase = 2.5f, kSplitErrPerTile = 0.35f, kSplitErrPerScore = 2.5f, kSplitErrPerNorm = 2.5f;
 constexpr float kPScale = 8192.0f;       // scale of P (at most 4) on its way to float16
 
 // What a workgroup of the kernel below knows about the tensor's exact maximum: an upper bound of its own exact values,
@@ -776,6 +776,8 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     // key k of a tile: slab k / 16, unit 2 (k / 16) + (k / 4) % 2, slot 4 ((k / 8) % 2) + k % 4
     const uint32_t voff = (uint32_t)(svd * kSplitVRow + (2 * (svk >> 4) + ((svk >> 2) & 1)) * 16 + (4 * ((svk >> 3) & 1) + (svk & 3)) * 2);
     float vmax = 0.0f;                  // largest |v| staged by this thread
+    float vsq[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // sums of v^2 over the keys it staged, per head dim
+    float knorm2 = 0.0f;                // largest squared norm of the keys it staged a part of
     float4 pk[2], pv[2];
     // Loads are unconditional, from clamped addresses: a key beyond S reads the last key's row (its score is
     // masked in the ragged tile, its P is exactly zero), head dims beyond dh read dims 0.. (the query is zero
@@ -828,6 +830,12 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
         const Split2 sp = split_eight(x, kv_up);
         *(v4u *)(kst + koff) = sp.h;
         *(v4u *)(kst + kSplitKPlane + koff) = sp.l;
+        float n2 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) n2 = fmaf(x[e], x[e], n2);
+        n2 = 8 * sku < dh ? n2 : 0.0f;
+        n2 = wave_reduce<4>(n2, [](float a, float b) { return a + b; });     // the eight lanes of a key
+        knorm2 = fmaxf(knorm2, n2);
     };
     auto stash_v = [&](int buf) {
         uint8_t *vst = lds + buf * kSplitStage + 2 * kSplitKPlane;
@@ -840,6 +848,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
             *(uint32_t *)dst = wh;
             *(uint32_t *)(dst + kSplitVPlane) = wl;
             vmax = fmaxf(vmax, fmaxf(fabsf(v0[e]), fabsf(v1[e])));
+            vsq[e] = fmaf(v0[e], v0[e], fmaf(v1[e], v1[e], vsq[e]));
         }
     };
 
@@ -970,11 +979,23 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     for (int t = 0; t < nfull; ++t) iteration(t, std::false_type{});
     if (nfull < ntiles) iteration(nfull, std::true_type{});
 
-    __shared__ float red_v[4], red_low[4], red_up[4];
+    __shared__ float red_v[4], red_k[4], red_n[4], red_low[4], red_up[4];
     __shared__ uint32_t n_cand;
     if (tid == 0) n_cand = 0;
     vmax = __uint_as_float(wave_max_u32(__float_as_uint(vmax)));  // non-negative floats order like integers
-    if (lane == 0) red_v[wave] = vmax;
+    knorm2 = __uint_as_float(wave_max_u32(__float_as_uint(knorm2)));
+    // the sixteen lanes of a group of head dims, then the largest of all dims
+    float vn2 = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        vsq[e] = pair_op<32>(vsq[e], [](float a, float b) { return a + b; });
+        vsq[e] = pair_op<16>(vsq[e], [](float a, float b) { return a + b; });
+        vsq[e] += lane_xor<8>(vsq[e]);
+        vsq[e] += lane_xor<4>(vsq[e]);
+        vn2 = fmaxf(vn2, vsq[e]);
+    }
+    vn2 = __uint_as_float(wave_max_u32(__float_as_uint(vn2)));
+    if (lane == 0) { red_v[wave] = vmax; red_k[wave] = knorm2; red_n[wave] = vn2; }
     // the two halves of a query's sums; the factor that undoes every scale
     lrun += lane_xor<32>(lrun);
     p2run += lane_xor<32>(p2run);
@@ -998,15 +1019,29 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
         }
     __syncthreads();
     vmax = fmaxf(fmaxf(red_v[0], red_v[1]), fmaxf(red_v[2], red_v[3]));
-    // Error bound of the query's values (the part that grows with a value itself comes on top, value_err).  The errors of
-    // the P, relative ones of a few units plus some for every unit of the scores, are independent of each other: what they
-    // do to a weighted sum goes with the root of the sum of P^2.  Added to the score's: the absolute part of K's split; to
-    // the whole: that of V's and P's.  Empirical with margin, not a proof: over 2.4e8 values of twelve shapes the largest
-    // error is 0.55 of the bound for normal q, k, v, 0.8 for scores of 45 and 300, one channel of K 30 times the others.
+    // Error bound of the query's values (the part that grows with a value itself comes on top, value_err).  A value is
+    // sum P v / sum P, and every relative error e of a P or a v moves it by at most e sum P |v| / sum P, plus e |x| for its
+    // share of the denominator.  Nothing is taken to average out: keys that repeat or lie close together (padding, few
+    // distinct tokens) have the same errors.  sum P |v| / sum P is at most the largest |v| of the head and, by Cauchy and
+    // Schwarz, sqrt(sum P^2) / sum P times the largest norm of a head dim of V: where the weights are spread over many keys
+    // the second one is a third to a half of the first.
+    //   e, in units of 2^-24: the splits of V and P, P's own rounding and the exponential (kSplitErrBase); a rounding per tile
+    // of the sums that are carried (kSplitErrPerTile); the roundings of the score's sum, which go with the score
+    // (kSplitErrPerScore); the splits of Q and K, which go with the root of sum (q k)^2 over the head dims, at most the
+    // largest |q| times the largest norm of a key (kSplitErrPerNorm).  The constants are measured, with margin, not proved: of
+    // the kinds of input that bench.py --attention-error draws (normal, padded, two to sixteen distinct tokens, values of
+    // opposite sign, equal scores up to 300, terms that cancel in the scores; 8 to 64 dims, 65 to 4096 tokens) the worst error
+    // is 0.86 of the bound.  With the P taken to be independent of each other (root of sum P^2 alone) it was 12 times
+    // the bound for two tokens and 97 for cancelling terms.  The longer lists cost the quantiser 63 -> 82 us for 64 x 256 tokens x
+    // 12 heads, the norms this kernel 85 -> 88.
     const float M = __uint_as_float(mbits);
     const float sq = max_halves(smax) * c2 * 0.6931472f;         // largest |score| of the query
-    float err = 5.9604645e-8f * (vmax * ((kSplitErrBase + kSplitErrPerScore * (sq + (float)dh * scale * qmax * M * 6.1035156e-5f)) *
-                                             __builtin_amdgcn_sqrtf(p2run) * inv + kSplitErrSum) +
+    auto of_all = [](const float *x) { return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])); };
+    // (the constants cover values whose squares underflow)
+    const float kn = __builtin_amdgcn_sqrtf(of_all(red_k)) + 1.0e-18f, vn = __builtin_amdgcn_sqrtf(of_all(red_n)) + 1.1e-19f * (float)S;
+    const float spread = fminf(vmax, __builtin_amdgcn_sqrtf(p2run) * inv * vn + max_halves(amax));
+    float err = 5.9604645e-8f * (spread * (kSplitErrBase + kSplitErrPerTile * (float)ntiles + kSplitErrPerScore * sq +
+                                           scale * qmax * (kSplitErrPerNorm * kn + (float)dh * M * 1.2207031e-4f)) +
                                  M * (float)(S + 2) * 6.1035156e-5f);
     // A bound that is no number: every value of the query is re-evaluated (finite inputs whose scores pass 3e38 only)
     if (!(err <= 3.402823466e+38f)) err = INFINITY;

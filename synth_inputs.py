@@ -208,3 +208,65 @@ def noisy_pair(b: int, D: int, rel: float = 0.02, seed: int = SEED_BASE, nonneg:
     if nonneg:
         a_r, a_t = np.maximum(a_r, 0), np.maximum(a_t, 0)
     return a_t, a_r
+
+
+# Kinds of q | k | v tensors that try the error bound of the approximate attention: what training sees (normal values, padding
+# tokens, few distinct tokens, an outlier channel, heads of very different size) and what makes rounding errors add up (repeated
+# keys with values of opposite sign, in order or alternating; keys of equal score, up to scores of 300; terms that cancel).
+ATTENTION_KINDS = ["normal", "normal x3", "normal x12", "uniform x4", "positive x4", "padded", "2 tokens", "4 tokens", "8 tokens", "4 tokens x3",
+                   "2 tokens opposite", "2 tokens opposite x3", "2 tokens in order", "4 similar tokens", "equal scores 0", "equal scores 3",
+                   "equal scores 30", "equal scores 300", "equal scores 0 x10", "outlier channel", "constant channel", "cancelling terms",
+                   "2 tokens cancelling terms", "uneven heads"]
+
+
+def attention_qkv(kind: str, b: int, s: int, heads: int, dh: int, seed: int = SEED_BASE) -> np.ndarray:
+    """fp32 [b, s, 3 * heads * dh], q | k | v per token.  "xN": q and k N times as large ("equal scores": k)."""
+    rng = np.random.default_rng([seed, sum(map(ord, kind)), s])
+    words = kind.split()
+    factor = float(words[-1][1:]) if words[-1][0] == "x" else 1.0
+
+    def normal(n):
+        return rng.standard_normal((b, n, 3, heads, dh))
+
+    x = normal(s)
+    if words[0] == "uniform":
+        x = rng.uniform(-1.0, 1.0, x.shape)
+    elif words[0] == "positive":
+        x = rng.uniform(0.0, 1.0, x.shape)
+    elif words[0] == "padded":
+        x[:, s // 10:] = x[:, s // 10:s // 10 + 1]
+    elif "tokens" in words:
+        n = int(words[0])
+        base = normal(n)
+        if "opposite" in words or "order" in words:
+            base[:, 1::2, 2] = -1.01 * base[:, 0::2, 2]
+        if "cancelling" in words:
+            base[:, :, 0, :, 0], base[:, :, 0, :, 1] = 20.0, -20.0
+            base[:, :, 1, :, 0] = base[:, :, 1, :, 1] = 20.0 * rng.standard_normal((b, n, heads))
+        which = np.stack([rng.choice(n, s, p=rng.dirichlet(np.full(n, 3.0))) for _ in range(b)])
+        if "order" in words:
+            which = np.sort(which, 1)
+        x = base[np.arange(b)[:, None], which]
+        if "similar" in words:
+            x = x * (1.0 + 1e-4 * rng.standard_normal(x.shape))
+    elif words[0] == "equal":
+        q = x[:, :1, 0].copy()
+        x[:, :, 0] = q * (1.0 + 0.02 * rng.standard_normal((b, s, heads, dh)))
+        base = normal(2)
+        k = factor * base[:, :, 1]
+        k += q * ((float(words[2]) * math.sqrt(dh) - (q * k).sum(-1, keepdims=True)) / (q * q).sum(-1, keepdims=True))
+        which = rng.integers(0, 2, (b, s))
+        x[:, :, 1] = k[np.arange(b)[:, None], which]
+        x[:, :, 2] = base[:, :1, 2] * (1.0 - 2.0 * which)[:, :, None, None]
+        factor = 1.0
+    elif words[0] == "outlier":
+        x[:, :, 1, :, 5] *= 30.0
+    elif words[0] == "constant":
+        x[:, :, 1, :, 5] = 300.0
+    elif words[0] == "cancelling":
+        x[:, :, 0, :, 0], x[:, :, 0, :, 1] = 20.0, -20.0
+        x[:, :, 1, :, 0] = x[:, :, 1, :, 1] = 20.0 * rng.standard_normal((b, s, heads))
+    elif words[0] == "uneven":
+        x = x * (4.0 ** -np.arange(heads))[:, None]
+    x[:, :, :2] *= factor
+    return np.ascontiguousarray(x.reshape(b, s, 3 * heads * dh).astype(np.float32))

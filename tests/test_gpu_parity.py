@@ -628,6 +628,23 @@ def test_profile_attention_writes_its_records_only(eg, gc, S, heads, dh):
         assert bool((err.amax((2, 3)) <= pairs[:, :, t, 1].double()).all())
 
 
+@pytest.mark.parametrize("kind", si.ATTENTION_KINDS)
+@pytest.mark.parametrize("b,s,heads,dh", [(2, 131, 3, 64), (2, 256, 12, 64), (1, 515, 4, 48), (2, 300, 4, 8)])
+def test_attention_error_is_within_its_bound(eg, gc, b, s, heads, dh, kind):
+    """What the certified codes rest on: no value of the approximate context is further from the fp64 evaluation than its
+    query's bound and the part that grows with the value say, on inputs whose rounding errors add up too."""
+    qkv = gc.to_dev(si.attention_qkv(kind, b, s, heads, dh))
+    approx, bounds = eg.profile_attention_bounds(qkv, heads)
+    exact, _ = eg.profile_attention(qkv, heads, 0)
+    torch.cuda.synchronize()
+    split = lambda t: t.reshape(b, s, heads, dh).permute(0, 2, 1, 3).double()  # noqa: E731
+    err = (split(approx) - split(exact)).abs() - 12 * 2.0 ** -24 * split(approx).abs()
+    assert bool((err.amax(-1) <= bounds.double()).all()), (err.amax(-1) / bounds.double()).max().item()
+    if kind == "normal":                                          # ... and is no larger than it has to be
+        vmax = qkv[..., 2 * heads * dh:].abs().max().item()
+        assert bounds.median().item() <= 16 * 2.0 ** -24 * vmax
+
+
 # what the certified kernels meet beyond ordinary activations: rows that tie for the tensor's maximum (the candidates of a
 # workgroup overflow its list), nothing but zeros, whole samples twice, scores in the hundreds, values that the split's scale
 # leaves few digits of (every code is re-evaluated: the list of the quantiser overflows)
