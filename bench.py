@@ -30,7 +30,6 @@ WORKLOAD_NAMES = {
 PEAK_HBM_GBS = 8000.0
 PEAK_I8_TOPS = 5033.0        # dense int8 MFMA, 256 CUs x 8192 op/clk x 2.4 GHz
 PEAK_F64_MFMA_TFLOPS = 78.6
-PEAK_F32_MFMA_TFLOPS = 157.3
 PEAK_F64_VALU_TFLOPS = 78.6
 PEAK_BF16_MFMA_TFLOPS = 2500.0
 # The metric's two Gram products multiply fp32 values exactly on the bf16 matrix cores: six bf16
@@ -202,16 +201,14 @@ def roofline_for(wl, cls, durations_ms, eg, steps, cfg=None, force_mfma=False):
              eg.KERNEL_ATTENTION: "attention_split_kernel", eg.KERNEL_LAYERNORM: "layernorm_vec_kernel"}
     att_peak = PEAK_ATTENTION_TFLOPS
     if cls == eg.KERNEL_ATTENTION:
-        # which kernel an unobserved run takes (the library's rule): the fp64 kernel up to 64 tokens and for small
-        # sizes; else the approximate kernel with certified codes, on the float16 matrix cores when head dims come in units of 8
+        # which kernel an unobserved run takes (the library's rule): the fp64 kernel up to 64 tokens, for small sizes and for
+        # heads that are no multiple of 8 dims; else the approximate kernel with certified codes, on the float16 matrix cores
         d = wl.dims
         dh = d["hidden"] // d["heads"]
-        pairs, plain = float(d["batch"] * d["heads"] * d["seq"] ** 2), dh % 8 or d["hidden"] % 4
-        size = 0.6 * pairs * dh if plain else (0.0 if d["seq"] <= 64 else 256.0 * pairs / (1 if d["seq"] <= 256 else 2))
-        if size < eg.attention_threshold():
+        pairs = float(d["batch"] * d["heads"] * d["seq"] ** 2)
+        size = 0.0 if d["seq"] <= 64 else 256.0 * pairs / (1 if d["seq"] <= 256 else 2)
+        if dh % 8 or size < eg.attention_threshold():
             names[cls], att_peak = "attention_kernel", PEAK_F64_MFMA_TFLOPS
-        elif plain:
-            names[cls], att_peak = "attention_fast_kernel", PEAK_F32_MFMA_TFLOPS
     fused_ln = cls == eg.KERNEL_LAYERNORM and layernorm_in_gemm(wl)
     if not work or not durations_ms:
         return None
@@ -609,7 +606,7 @@ def attention_error(cfg, device):
     ws = eg.workspace(eg.workspace_bytes(ref.desc), dev)
     eg.ref_forward(ref, torch.from_numpy(wl.x).to(dev), a_ref, ws, taps)
     torch.cuda.synchronize()
-    print(f"# {WORKLOAD_NAMES[cfg]}: the approximate attention kernel (attention_split_kernel when head dims come in units of 8, else attention_fast_kernel) against attention_kernel (fp64), per layer")
+    print(f"# {WORKLOAD_NAMES[cfg]}: the approximate attention kernel (attention_split_kernel) against attention_kernel (fp64), per layer")
     print("# err = |fast - fp64| per context value; E = the certified quantiser's bound for that value; unit = 2^-24 * max|v| of the head")
     print("layer  absmax(ctx)  max|v|  median E/unit  median err/unit  p99.99 err/unit  max err/unit  max err/E  values with err > E  uncertain codes (fraction)")
 

@@ -40,14 +40,15 @@ egeria_status egeria_profile_end(float *ms_out, int32_t capacity, int32_t *n_out
 
 /* The attention of a Transformer layer on its own, for measuring the approximate kernels' error against the fp64
  * one (bench.py --attention-error).  qkv: fp32 [B, S, 3 * hidden] (q | k | v per token), ctx: fp32
- * [B, S, hidden] out.  mode 0: the fp64 kernel of observed runs.  mode 1: the fp32 matrix-core kernel (unobserved runs take
- * it where heads are no multiple of 8 dims); records then receives B * heads * ceil(S / 64) pairs {uint32 bit pattern of the
+ * [B, S, hidden] out.  mode 0: the fp64 kernel of observed runs.  mode 1: a kernel in fp32 on the matrix cores, for
+ * comparison (no run takes it); records then receives B * heads * ceil(S / 64) pairs {uint32 bit pattern of the
  * largest |ctx| of a workgroup's 64 queries x head dims, fp32 error bound E of those values} (DEVICE, 16-byte
  * aligned; ignored in mode 0; a value x is off by at most E + 12 * 2^-24 |x|).  Limits as for the Transformer kinds of
  * egeria_ref_forward. */
 egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads,
                                        int32_t mode, float *ctx, void *records, void *stream);
-/* ... and the approximate kernel that unobserved runs take for this head size, on operands scaled as there.  bounds: the
+/* ... and the approximate kernel of unobserved runs, on operands scaled as there (head size hidden / heads a multiple of 8:
+ * others have none and are refused).  bounds: the
  * error bound E of every query of a head, fp32 [B, heads, S] out (DEVICE, 16-byte aligned, bounds_bytes long; the meaning of E
  * as above).  ws: DEVICE scratch, at least egeria_quantize_workspace_bytes(). */
 egeria_status egeria_profile_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads, float *ctx,

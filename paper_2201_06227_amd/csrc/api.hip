@@ -468,13 +468,12 @@ egeria_status forward_float(Fwd &f, const void *x, egeria_dtype dt, float *a_ref
 // fp64 / certified: 64 x 64 tokens of 768 149 / 164, 256 x 64 463 / 508; 64 x 80 202 / 192, 100 x 72 311 / 282); beyond 256
 // tokens a head's keys do not fit the LDS at once and they pay from twice the size (4 x 300 x 512 104 / 115, 2 x 384 x 1024
 // 127 / 139, 4 x 384 x 768 160 / 138); between, from 0.75e9: 12 x 128 x 768 115 / 113, 16 x 128 x 256 74 / 80, 24 x 128 x 384
-// (heads of 32) 113 / 100, 32 x 128 x 768 166 / 158, 24 x 197 x 768 241 / 191.  Heads that are no multiple of 8 dims take the
-// fp32 kernel and a launch for the maximum: from 5e9 flops.
+// (heads of 32) 113 / 100, 32 x 128 x 768 166 / 158, 24 x 197 x 768 241 / 191.  (Heads that are no multiple of 8 dims
+// have no certified kernels.)
 double g_attention_min_flops = 0.75e9;
 double attention_measure(const egeria_block_desc *d)
 {
     const double pairs = (double)d->batch * d->heads * (double)d->seq * d->seq;
-    if (!attention_splits(d->hidden, d->heads)) return 0.15 * 4.0 * pairs * (d->hidden / d->heads);
     return d->seq <= 64 ? 0.0 : (d->seq <= 256 ? 1.0 : 0.5) * 256.0 * pairs;
 }
 
@@ -494,11 +493,11 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
         EG_HIP(launch_quantize_rows(cur, EGERIA_F32, M, Hd, hp, f.amax(s0), f.n_amax(s0), f.stride_amax(s0), nullptr, xq,
                                     f.scale(s0), nullptr, ws_flag(f.ws), f.st));
     EG_OK(f.copy_tap_q(s0, xq, (size_t)(M * hp), f.scale(s0)));
-    const bool certified = !f.taps && attention_measure(d) >= g_attention_min_flops;
+    const bool certified = !f.taps && attention_splits(Hd, d->heads) && attention_measure(d) >= g_attention_min_flops;
     EG_OK(run_gemm(f, s0, xq, hp, M, 3 * Hd, hp, false, 0, 0, 0, f.scale(s0), 0, nullptr, nullptr, 0, qkv,
-                   certified && attention_splits(Hd, d->heads) ? f.slot(6 * f.p.n_layers + l) : nullptr));
+                   certified ? f.slot(6 * f.p.n_layers + l) : nullptr));
     if (!certified) {
-        // observed runs (and small ones): the context itself in fp64, then the plain quantiser
+        // observed runs (small ones and other head sizes too): the context itself in fp64, then the plain quantiser
         EG_HIP(launch_attention(qkv, d->batch, d->seq, Hd, d->heads, ctx, f.slot(s0 + 1), f.st));
         EG_HIP(launch_quantize_rows(ctx, EGERIA_F32, M, Hd, hp, f.amax(s0 + 1), f.n_amax(s0 + 1), f.stride_amax(s0 + 1),
                                     nullptr, xq, f.scale(s0 + 1), nullptr, ws_flag(f.ws), f.st));
@@ -506,7 +505,7 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
     } else {
         // unobserved runs: approximate matrix-core attention, codes and scale certified against the fp64 evaluation
         EG_HIP(launch_attention_certified(qkv, d->batch, d->seq, Hd, d->heads, ctx, f.ws + f.p.off_rec,
-                                          f.slot(s0 + 1), f.slot(6 * f.p.n_layers + l), f.slot(5 * f.p.n_layers + l), xq, hp,
+                                          f.slot(6 * f.p.n_layers + l), f.slot(s0 + 1), f.slot(5 * f.p.n_layers + l), xq, hp,
                                           f.scale(s0 + 1), ws_flag(f.ws),
                                           ws_flag(f.ws) + kUnsureWord, f.st));
     }
@@ -1193,7 +1192,7 @@ egeria_status egeria_profile_attention_bounds(const float *qkv, int32_t B, int32
 {
     if (!qkv || !ctx || !bounds || !ws || B < 1 || S < 1 || hidden < 1 || heads < 1 || hidden % heads != 0) return EGERIA_ERR_INVALID_ARG;
     if (!aligned16(qkv) || !aligned16(ctx) || !aligned16(bounds) || !aligned16(ws)) return EGERIA_ERR_INVALID_ARG;
-    if (hidden / heads > 64) return EGERIA_ERR_UNSUPPORTED;
+    if (hidden / heads > 64 || !attention_splits(hidden, heads)) return EGERIA_ERR_UNSUPPORTED;
     if (bounds_bytes < (size_t)B * heads * S * 4 || ws_bytes < header_bytes(1)) return EGERIA_ERR_WORKSPACE_TOO_SMALL;
     EG_HIP(launch_attention_bounds(qkv, B, S, hidden, heads, ctx, bounds, ws_absmax(ws, 0), (hipStream_t)stream));
     return EGERIA_OK;

@@ -357,26 +357,28 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
     }
 }
 
-// ---- the same attention in fp32 arithmetic on the matrix cores, with certified int8 codes ----------
+// ---- the same attention in approximate arithmetic on the matrix cores, with certified int8 codes ----------
 // Unobserved runs do not need the context as the fp64 evaluation gives it: all that leaves this stage
-// is the int8 input of the next GEMM and its scale.  Two launches, 1 and 3 (three with the fp32 kernel):
-//   1. an approximate attention with fp32 products and sums: attention_split_kernel (further down: every
-//      fp32 product as three float16 partial products on the float16 matrix cores; head dims in whole units of 8)
-//      or attention_fast_kernel (here: the structure of the kernel above on v_mfma_f32_16x16x4f32, hardware
-//      exp2; any head size).  It stores an approximate context, an error bound E per query of a head and what its
-//      workgroups know of the largest value.
-//   2. attention_absmax_exact_kernel (fp32 kernel only): the tensor's absolute maximum as the fp64 evaluation gives it.  Every
-//      value that can be the maximum (|x| + E >= largest |x| - largest E; as a rule one) is re-evaluated in fp64.
-//   3. quantize_attention_certify_kernel: the streaming map to codes.  code(x) = clamp(rne(x * inv)) is
+// is the int8 input of the next GEMM and its scale.  Two launches, for head dims in whole units of 8:
+//   1. an approximate attention with fp32 sums: attention_split_kernel (further down: every fp32 product as three float16
+//      partial products on the float16 matrix cores).  It stores an approximate context, an error bound E per query of a head
+//      and what its workgroups know of the largest value.
+//   2. quantize_attention_certify_kernel: the streaming map to codes.  code(x) = clamp(rne(x * inv)) is
 //      monotone in x, so an approximate value whose interval [x - E, x + E] maps to one code has that
 //      code; the others (a few in ten thousand) are re-evaluated in fp64, a wave per value, by the
 //      workgroup that met them.
-// The fp32 kernel's bound of a value x (the split kernel forms its own): E = 2^-24 * (max|v| of the head * (kErrBase + kErrPerScore * max|score| of the
-// workgroup) + kErrRel |x|).  It is an empirical bound with margin, not a proof: bench.py --attention-error
-// measures kernel 1 against the fp64 kernel on the twelve layers of the BERT-base-shaped stack (12.6 M
-// values each) and prints the largest error / E per layer.
+// Other head sizes take the fp64 kernel at every size.  An approximate kernel in fp32 (here: the structure of the kernel above
+// on v_mfma_f32_16x16x4f32, hardware exp2; any head size) gains nothing on them: with the bound that holds for it (below) one
+// layer of 64 x 256 tokens x 12 heads of 55 took 1446 us, in fp64 498; with half the bound's lists 572 and 510.  It is left for
+// measurement.
+// The fp32 kernel's bound of a value x (the split kernel forms its own, per query and tighter, and says what the parts stand
+// for): E = 2^-24 * (max|v| of the head * (kErrBase + kErrPerTile * tiles of 32 keys + kErrPerScore * max|score| of the workgroup +
+// kErrPerNorm * max|q| of the workgroup * largest norm of a key / sqrt(dh)) + kErrRel |x|).  It is an empirical bound with margin,
+// not a proof: bench.py --attention-error measures both kernels against the fp64 kernel on the twelve layers of the
+// BERT-base-shaped stack (12.6 M values each) and on inputs whose rounding errors add up.  (With 2 + max|score| / 2 alone the
+// error was up to 35 times the bound for tokens that repeat, 2 times for uniform values with scores of 17.)
 typedef float v4f __attribute__((ext_vector_type(4)));
-constexpr float kErrBase = 2.0f, kErrPerScore = 0.5f;
+constexpr float kErrBase = 3.0f, kErrPerTile = 0.25f, kErrPerScore = 4.0f, kErrPerNorm = 2.5f;
 // ... plus a part that grows with the value itself (the drift of the matrix cores' accumulation is
 // proportional to the sums it carries): kErrRel * 2^-24 * |x|
 constexpr float kErrRel = 12.0f * 5.9604645e-8f;
@@ -389,9 +391,7 @@ struct AttnRecord {
 
 __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__restrict__ qkv, int B, int S, int Hd,
                                                              int heads, int dh, float scale, float *__restrict__ ctx,
-                                                             float *__restrict__ err_q, AttnRecord *__restrict__ rec,
-                                                             int total, int per_xcd, uint32_t *__restrict__ amax_slot,
-                                                             uint32_t *__restrict__ err_slot)
+                                                             AttnRecord *__restrict__ rec, int total, int per_xcd)
 {
     __shared__ __attribute__((aligned(16))) float sKb[2][kKeyTile][kKVPad];
     __shared__ __attribute__((aligned(16))) float sVb[2][kKeyTile][kKVPad];
@@ -445,6 +445,7 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
     float mrun = -INFINITY, lrun = 0.0f;
     float smax = 0.0f;                  // largest |score| met by this lane
     uint32_t vmax = 0;                  // largest |v| staged by this thread (bit pattern)
+    float knorm2 = 0.0f;                // largest squared norm of the keys it staged a part of
     float4 pk[2], pv[2];
     auto fetch = [&](int j0) {
 #pragma unroll
@@ -475,6 +476,8 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
             const int sl = tid + it * 256, kr = sl >> 4, d = (sl & 15) * 4;
             *(float4 *)&sKb[stage][kr][d] = pk[it];
             *(float4 *)&sVb[stage][kr][d] = pv[it];
+            const float n2 = fmaf(pk[it].x, pk[it].x, fmaf(pk[it].y, pk[it].y, fmaf(pk[it].z, pk[it].z, pk[it].w * pk[it].w)));
+            knorm2 = fmaxf(knorm2, wave_reduce<8>(n2, [](float a, float b) { return a + b; }));   // the sixteen lanes of a key
             uint32_t a0 = abs_bits(pv[it].x), a1 = abs_bits(pv[it].y), a2 = abs_bits(pv[it].z), a3 = abs_bits(pv[it].w);
             a0 = a0 > a1 ? a0 : a1;
             a2 = a2 > a3 ? a2 : a3;
@@ -592,34 +595,33 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
         }
     }
     // the workgroup's record: largest |context| stored, and the error bound of its values
-    __shared__ uint32_t red[3][4];
+    __shared__ uint32_t red[5][4];
+    float qmax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) qmax = fmaxf(qmax, fabsf(qr[i]));
+    const uint32_t kbits = wave_max_u32(__float_as_uint(knorm2)), qbits = wave_max_u32(__float_as_uint(qmax));
     amax = wave_max_u32(amax);
     vmax = wave_max_u32(vmax);
     const uint32_t sbits = wave_max_u32(__float_as_uint(smax));       // non-negative floats order like integers
-    if (lane == 0) { red[0][wave] = amax; red[1][wave] = vmax; red[2][wave] = sbits; }
+    if (lane == 0) { red[0][wave] = amax; red[1][wave] = vmax; red[2][wave] = sbits; red[3][wave] = kbits; red[4][wave] = qbits; }
     __syncthreads();
-    if (tid < 64) {
-        uint32_t a = 0, v = 0, sb = 0;
+    if (tid == 0) {
+        uint32_t a = 0, v = 0, sb = 0, kb = 0, qb = 0;
         for (int w = 0; w < 4; ++w) {
             a = a > red[0][w] ? a : red[0][w];
             v = v > red[1][w] ? v : red[1][w];
             sb = sb > red[2][w] ? sb : red[2][w];
+            kb = kb > red[3][w] ? kb : red[3][w];
+            qb = qb > red[4][w] ? qb : red[4][w];
         }
         AttnRecord r;
         r.amax_bits = a;
-        r.err = 5.9604645e-8f * __uint_as_float(v) * (kErrBase + kErrPerScore * __uint_as_float(sb));
+        // (the constant in the norm covers keys whose squares underflow)
+        r.err = 5.9604645e-8f * __uint_as_float(v) *
+                (kErrBase + kErrPerTile * (float)((S + kKeyTile - 1) / kKeyTile) + kErrPerScore * __uint_as_float(sb) +
+                 kErrPerNorm * scale * __uint_as_float(qb) * (__builtin_amdgcn_sqrtf(__uint_as_float(kb)) + 1.0e-18f));
         if (!(r.err <= 3.402823466e+38f)) r.amax_bits = 0x7f800000u;   // non-finite inputs: flagged downstream
-        if (err_q && qt * QT + tid < S) err_q[(int64_t)bh * S + qt * QT + tid] = r.err;
-        if (tid == 0 && rec) rec[vid] = r;
-        // the largest of both over all workgroups, for the kernel that settles the exact maximum (atomically
-        // combined words spread over ways; both are non-negative floats, whose bit patterns order like them)
-        if (tid == 0 && amax_slot) {
-            uint32_t *wa = amax_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
-            uint32_t *we = err_slot + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
-            const uint32_t eb = __float_as_uint(r.err);
-            if (r.amax_bits > __hip_atomic_load(wa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(wa, r.amax_bits);
-            if (eb > __hip_atomic_load(we, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(we, eb);
-        }
+        rec[vid] = r;
     }
 }
 
@@ -656,7 +658,7 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 struct Nothing {
     __device__ void operator()() const {}
 };
-template <int NT = 256, typename F = Nothing>
+template <typename F = Nothing>
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
                                                uint32_t el, double *red, F meanwhile = {});
 template <typename F>
@@ -1134,14 +1136,12 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 // ones, the query zero beyond dh): a load under a condition is awaited on its own, and a key row would
 // cost sixteen memory round trips instead of one.
 // (kept compact and inlined once per kernel: called as a function it needs scratch memory for the
-// caller's registers and ran five times slower)  The whole workgroup of NT threads evaluates one value, a key per thread;
-// `meanwhile` runs while the first loads are on their way.  red: 3 NT / 64 + 32 doubles.
-template <int NT, typename F>
+// caller's registers and ran five times slower)  The whole workgroup of 256 threads evaluates one value, a key per thread;
+// `meanwhile` runs while the first loads are on their way.  Head dims in whole units of 4 floats.  red: 12 + 32 doubles.
+template <typename F>
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
                                                uint32_t el, double *red, F meanwhile)
 {
-    constexpr int NW = NT / 64;
-    const bool vec4 = (dh & 3) == 0 && (Hd & 3) == 0;           // whole 16-byte units, 16-byte aligned rows
     const uint32_t mrow = el / (uint32_t)Hd, col = el - mrow * (uint32_t)Hd;
     const uint32_t bi = mrow / (uint32_t)S, hd = col / (uint32_t)dh, dd = col - hd * (uint32_t)dh;
     const int64_t ld = 3 * (int64_t)Hd;
@@ -1152,7 +1152,7 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
     // the query row goes through LDS (64 floats behind the waves' sums): every thread needs all of it.
     // Its load and the first block's key and value loads are requested together, before the barriers: the
     // evaluation is a chain of memory round trips, and this takes one out of it.
-    float *qs = (float *)(red + 3 * NW);
+    float *qs = (float *)(red + 12);
     float4 kv[16];
     float vj = 0.0f;
     auto request = [&](int j0) {
@@ -1160,10 +1160,8 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
         const int jj = j < S ? j : S - 1;
         const float *kr = kb + (int64_t)jj * ld;
         vj = vb[(int64_t)jj * ld];
-        if (vec4) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) kv[u] = *(const float4 *)(kr + 4 * (u < units ? u : units - 1));
-        }
+        for (int u = 0; u < 16; ++u) kv[u] = *(const float4 *)(kr + 4 * (u < units ? u : units - 1));
     };
     const float qreg = (tid < 64 && tid < dh) ? q[tid] : 0.0f;
     request(0);
@@ -1171,48 +1169,36 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
     __syncthreads();                                          // an earlier call has finished with red and qs
     if (tid < 64) qs[tid] = qreg;
     __syncthreads();
-    auto total = [&](const double *r) {
-        if constexpr (NW == 4) return (r[0] + r[1]) + (r[2] + r[3]);
-        else return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
-    };
     double m = -INFINITY, l = 0.0, o = 0.0;
-    for (int j0 = 0; j0 < S; j0 += NT) {
+    for (int j0 = 0; j0 < S; j0 += 256) {
         const int j = j0 + tid;
-        const int jj = j < S ? j : S - 1;
-        const float *kr = kb + (int64_t)jj * ld;
         if (j0) request(j0);
         // a product of two fp32 values is exact in fp64, so each fma below is the multiply and the
         // add of the plain definition, in its order (dims ascending)
         double acc = 0.0;
-        if (vec4) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                if (u < units) {
-                    const float4 qv = *(const float4 *)&qs[4 * u];
-                    acc = fma((double)qv.x, (double)kv[u].x, acc);
-                    acc = fma((double)qv.y, (double)kv[u].y, acc);
-                    acc = fma((double)qv.z, (double)kv[u].z, acc);
-                    acc = fma((double)qv.w, (double)kv[u].w, acc);
-                }
+        for (int u = 0; u < 16; ++u) {
+            if (u < units) {
+                const float4 qv = *(const float4 *)&qs[4 * u];
+                acc = fma((double)qv.x, (double)kv[u].x, acc);
+                acc = fma((double)qv.y, (double)kv[u].y, acc);
+                acc = fma((double)qv.z, (double)kv[u].z, acc);
+                acc = fma((double)qv.w, (double)kv[u].w, acc);
             }
-        } else {
-            for (int d = 0; d < dh; ++d) acc = fma((double)qs[d], (double)kr[d], acc);   // odd head sizes: plain loop
         }
         const double sc = j < S ? acc * scale : -INFINITY;
         const double cm = wave_max(sc);
         __syncthreads();                                      // red is free (an earlier block, an earlier call)
         if (lane == 0) red[wave] = cm;
         __syncthreads();
-        double mnew = m;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) mnew = fmax(mnew, red[w]);
+        const double mnew = fmax(m, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
         const double p = exp(sc - mnew);                 // exp(-inf) = 0 for the keys beyond S
         const double corr = j0 == 0 ? 0.0 : exp(m - mnew);
         const double ps = wave_sum(p), po = wave_sum(p * (double)vj);
-        if (lane == 0) { red[NW + wave] = ps; red[2 * NW + wave] = po; }
+        if (lane == 0) { red[4 + wave] = ps; red[8 + wave] = po; }
         __syncthreads();
-        l = l * corr + total(red + NW);
-        o = o * corr + total(red + 2 * NW);
+        l = l * corr + ((red[4] + red[5]) + (red[6] + red[7]));
+        o = o * corr + ((red[8] + red[9]) + (red[10] + red[11]));
         m = mnew;
     }
     return (float)(o / l);
@@ -1235,76 +1221,6 @@ __device__ __forceinline__ void for_each_marked(bool mine, uint64_t *masks, F vi
             visit(w * 64 + src);
         }
     }
-}
-
-// Exact absolute maximum of the context.  The largest stored |x| (A) and the largest E over all records come
-// from two atomically combined words the first kernel filled; a value can be the exact maximum only if
-// |x| + E_record >= A - E_max.  A thread tests one record (a workgroup per 256 records: one memory round
-// trip for the whole grid, where a workgroup per record took six waves of workgroups); for the records that
-// pass (as a rule one in the whole tensor) the workgroup rescans the record's 64 x dh values and
-// re-evaluates those that pass the test.  The value that holds A passes, so the word `exact` ends up with
-// the exact maximum (it starts at zero: cleared by the chain's first kernel).
-__global__ __launch_bounds__(256) void attention_absmax_exact_kernel(const float *__restrict__ qkv,
-                                                                     const float *__restrict__ ctx,
-                                                                     const AttnRecord *__restrict__ rec, int nrec,
-                                                                     const uint32_t *__restrict__ amax_slot,
-                                                                     const uint32_t *__restrict__ err_slot,
-                                                                     int S, int Hd, int heads, int dh, double scale,
-                                                                     uint32_t *__restrict__ exact)
-{
-    __shared__ __attribute__((aligned(16))) double red[12 + 32];
-    __shared__ uint64_t masks_rec[4], masks[4];
-    __shared__ float err_s;
-    const int tid = threadIdx.x;
-    const int rid = blockIdx.x * 256 + tid;
-    const AttnRecord mine = rec[rid < nrec ? rid : nrec - 1];
-    const uint32_t a = reduce_ways(amax_slot);
-    const float e = __uint_as_float(reduce_ways(err_slot));
-    if (a >= 0x7f800000u) {                                   // NaN / Inf in the tensor: it is the "maximum"
-        if (blockIdx.x == 0 && tid == 0) atomicMax(exact, a);
-        return;
-    }
-    const float A = __uint_as_float(a);
-    const float floor_v = A - value_err(e, A);                // values below this cannot be the maximum
-    const float mine_max = __uint_as_float(mine.amax_bits);
-    const bool holds = rid < nrec && mine_max + value_err(mine.err, mine_max) >= floor_v;
-    const int qtiles = (S + 63) / 64;
-    uint32_t best = 0;
-    for_each_marked(holds, masks_rec, [&](int kr) {
-        const int r = blockIdx.x * 256 + kr;
-        __syncthreads();                                      // err_s is free
-        if (tid == kr) err_s = mine.err;                      // the record is in that thread's registers
-        __syncthreads();
-        const float r_err = err_s;
-        const int bh = r / qtiles, qt = r % qtiles;
-        const int bi = bh / heads, hd = bh % heads;
-        const int64_t tok0 = (int64_t)bi * S;
-        const int nq = S - qt * 64 < 64 ? S - qt * 64 : 64;
-        const int n_el = nq * dh;
-        // the record's values, sixteen per thread requested together (indices clamped, the surplus masked
-        // below); candidates are then taken 256 values at a time and re-evaluated one by one by the workgroup
-        float xs[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int idx = k * 256 + tid < n_el ? k * 256 + tid : 0;
-            xs[k] = fabsf(ctx[(tok0 + qt * 64 + idx / dh) * Hd + hd * dh + idx % dh]);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int base = k * 256;
-            if (base < n_el) {
-                const bool cand = base + tid < n_el && xs[k] + value_err(r_err, xs[k]) >= floor_v;
-                for_each_marked(cand, masks, [&](int kv) {
-                    const int cidx = base + kv;
-                    const int qq = qt * 64 + cidx / dh, d = cidx % dh;
-                    const float x = context_exact(qkv, S, Hd, heads, dh, scale, (uint32_t)((tok0 + qq) * Hd + hd * dh + d), red);
-                    const uint32_t ab = abs_bits(x);
-                    best = best > ab ? best : ab;
-                });
-            }
-        }
-    });
-    if (tid == 0 && best) atomicMax(exact + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride, best);
 }
 
 // The int8 codes of the context under the tensor's exact scale: a workgroup of eight waves per (batch element, head), or
@@ -1344,7 +1260,7 @@ __device__ __forceinline__ bool code_uncertain(float x, float err, float inv)
 }
 
 constexpr int kCertifyThreads = 256;
-template <bool WIDE, bool KLDS>
+template <bool WIDE>
 __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify_kernel(
     const float *__restrict__ qkv, const float *__restrict__ ctx, const float *__restrict__ err_q,
     const AttnCand *__restrict__ cands, int nwg, const uint32_t *__restrict__ bound, int S, int Hd, int heads, int dh,
@@ -1357,9 +1273,9 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
     constexpr uint32_t kList = 1024;                              // list entries served per round
     __shared__ uint32_t todo[kList];
     __shared__ uint32_t n_todo, more;
-    __shared__ __attribute__((aligned(16))) double red[3 * NW + 32];
-    __shared__ __attribute__((aligned(16))) float ks[KLDS ? kKeysLds * kKeyRow : 4];
-    __shared__ __attribute__((aligned(16))) float qs[KLDS ? NW * kDh : 4];
+    __shared__ __attribute__((aligned(16))) double red[12 + 32];
+    __shared__ __attribute__((aligned(16))) float ks[kKeysLds * kKeyRow];
+    __shared__ __attribute__((aligned(16))) float qs[NW * kDh];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t bh = blockIdx.x / (uint32_t)splits, share = blockIdx.x - bh * (uint32_t)splits;
     const uint32_t bi = bh / (uint32_t)heads, hd = bh - bi * (uint32_t)heads;
@@ -1389,7 +1305,7 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
         return ok;
     };
     uint32_t top = reduce_ways(exact);                            // what the attention workgroups evaluated themselves
-    const float floor_v = nwg > 0 ? __uint_as_float(reduce_ways(bound)) : 0.0f;
+    const float floor_v = __uint_as_float(reduce_ways(bound));
     float4 v[NPRE][WIDE ? 4 : 1];
     float ev[NPRE];
     auto request = [&](uint32_t p0) {
@@ -1431,7 +1347,7 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
             }
         }
     };
-    bool staged = !KLDS || S > kKeysLds;
+    bool staged = S > kKeysLds;
     for (int w0 = 0; w0 < nwg; w0 += NT * 32) {                   // 32 attention workgroups per thread at a time
         uint32_t pend_w = 0;                                      // bit k: workgroup w0 + NT k + tid may hold the maximum
 #pragma unroll 4
@@ -1458,7 +1374,7 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
             for (uint32_t k = 0; k < n; ++k) {
                 const AttnCand &c = cands[__builtin_amdgcn_readfirstlane((int)todo[k])];
                 for (uint32_t e = 0; e < c.n; ++e) {
-                    const float x = context_exact<NT>(qkv, S, Hd, heads, dh, scale, c.at[e], red, [&]() {
+                    const float x = context_exact(qkv, S, Hd, heads, dh, scale, c.at[e], red, [&]() {
                         if (!staged) stage_keys(0);
                         staged = true;
                     });
@@ -1532,84 +1448,75 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
             const uint32_t n = n_todo < kList ? n_todo : kList;
             again = more != 0;
             met += n;
-            if (KLDS) {
-                const int cpr = dh >> 2;                          // 16-byte pieces per row
-                for (uint32_t k0 = 0; k0 < n; k0 += NW) {         // a value per wave
-                    const uint32_t k = k0 + (uint32_t)wave;
-                    const bool active = k < n;
-                    const uint32_t e = todo[active ? k : k0];
-                    const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
-                    qs[wave * kDh + lane] = lane < dh ? qb[(int64_t)t * ld + lane] : 0.0f;
-                    double m = -INFINITY, l = 0.0, o = 0.0;       // l and o: this lane's share
-                    for (int j0 = 0; j0 < S; j0 += kKeysLds) {    // one round up to 256 keys
-                        const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds, nk = (nj + 63) >> 6;   // keys; keys per lane
-                        float vj[4];
+            const int cpr = dh >> 2;                          // 16-byte pieces per row
+            for (uint32_t k0 = 0; k0 < n; k0 += NW) {         // a value per wave
+                const uint32_t k = k0 + (uint32_t)wave;
+                const bool active = k < n;
+                const uint32_t e = todo[active ? k : k0];
+                const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
+                qs[wave * kDh + lane] = lane < dh ? qb[(int64_t)t * ld + lane] : 0.0f;
+                double m = -INFINITY, l = 0.0, o = 0.0;       // l and o: this lane's share
+                for (int j0 = 0; j0 < S; j0 += kKeysLds) {    // one round up to 256 keys
+                    const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds, nk = (nj + 63) >> 6;   // keys; keys per lane
+                    float vj[4];
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            const int j = lane + 64 * kk;
-                            vj[kk] = vb[(int64_t)(j0 + (j < nj ? j : nj - 1)) * ld + d];
-                        }
-                        if (S > kKeysLds) {
-                            __syncthreads();                      // the keys of the round before have been read
-                            stage_keys(j0);
-                        }
-                        __syncthreads();
-                        if (active) {
-                            // a product of two fp32 values is exact in fp64, so each fma is the multiply and the
-                            // add of the plain definition, dims in ascending order
-                            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                    for (int kk = 0; kk < 4; ++kk) {
+                        const int j = lane + 64 * kk;
+                        vj[kk] = vb[(int64_t)(j0 + (j < nj ? j : nj - 1)) * ld + d];
+                    }
+                    if (S > kKeysLds) {
+                        __syncthreads();                      // the keys of the round before have been read
+                        stage_keys(j0);
+                    }
+                    __syncthreads();
+                    if (active) {
+                        // a product of two fp32 values is exact in fp64, so each fma is the multiply and the
+                        // add of the plain definition, dims in ascending order
+                        double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                            for (int u4 = 0; u4 < kDh / 4; ++u4) {
-                                if (u4 < cpr) {
-                                    const float4 qv = *(const float4 *)&qs[wave * kDh + 4 * u4];
+                        for (int u4 = 0; u4 < kDh / 4; ++u4) {
+                            if (u4 < cpr) {
+                                const float4 qv = *(const float4 *)&qs[wave * kDh + 4 * u4];
 #pragma unroll
-                                    for (int kk = 0; kk < 4; ++kk) {
-                                        if (kk < nk) {
-                                            const int j = lane + 64 * kk;
-                                            const float4 kv = *(const float4 *)&ks[(j < nj ? j : nj - 1) * kKeyRow + 4 * u4];
-                                            acc[kk] = fma((double)qv.x, (double)kv.x, acc[kk]);
-                                            acc[kk] = fma((double)qv.y, (double)kv.y, acc[kk]);
-                                            acc[kk] = fma((double)qv.z, (double)kv.z, acc[kk]);
-                                            acc[kk] = fma((double)qv.w, (double)kv.w, acc[kk]);
-                                        }
+                                for (int kk = 0; kk < 4; ++kk) {
+                                    if (kk < nk) {
+                                        const int j = lane + 64 * kk;
+                                        const float4 kv = *(const float4 *)&ks[(j < nj ? j : nj - 1) * kKeyRow + 4 * u4];
+                                        acc[kk] = fma((double)qv.x, (double)kv.x, acc[kk]);
+                                        acc[kk] = fma((double)qv.y, (double)kv.y, acc[kk]);
+                                        acc[kk] = fma((double)qv.z, (double)kv.z, acc[kk]);
+                                        acc[kk] = fma((double)qv.w, (double)kv.w, acc[kk]);
                                     }
                                 }
                             }
-                            double sc[4], mx = -INFINITY;
+                        }
+                        double sc[4], mx = -INFINITY;
 #pragma unroll
-                            for (int kk = 0; kk < 4; ++kk) {
-                                sc[kk] = lane + 64 * kk < nj ? acc[kk] * scale : -INFINITY;
-                                mx = fmax(mx, sc[kk]);
-                            }
-                            const double mnew = fmax(m, wave_max(mx));
-                            if (j0) {
-                                const double corr = exp(m - mnew);
-                                l *= corr;
-                                o *= corr;
-                            }
-                            m = mnew;
+                        for (int kk = 0; kk < 4; ++kk) {
+                            sc[kk] = lane + 64 * kk < nj ? acc[kk] * scale : -INFINITY;
+                            mx = fmax(mx, sc[kk]);
+                        }
+                        const double mnew = fmax(m, wave_max(mx));
+                        if (j0) {
+                            const double corr = exp(m - mnew);
+                            l *= corr;
+                            o *= corr;
+                        }
+                        m = mnew;
 #pragma unroll
-                            for (int kk = 0; kk < 4; ++kk) {
-                                const double pr = exp(sc[kk] - m);   // exp(-inf) = 0 for the keys beyond S
-                                l += pr;
-                                o += pr * (double)vj[kk];
-                            }
+                        for (int kk = 0; kk < 4; ++kk) {
+                            const double pr = exp(sc[kk] - m);   // exp(-inf) = 0 for the keys beyond S
+                            l += pr;
+                            o += pr * (double)vj[kk];
                         }
                     }
-                    if (active) {
-                        l = wave_sum(l);
-                        o = wave_sum(o);
-                        if (lane == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1((float)(o / l), inv);
-                    }
-                    __syncthreads();                              // qs is free
                 }
-            } else {
-                for (uint32_t k = 0; k < n; ++k) {
-                    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)todo[k]);
-                    const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
-                    const float x = context_exact<NT>(qkv, S, Hd, heads, dh, scale, (tok0 + t) * (uint32_t)Hd + hd * (uint32_t)dh + d, red);
-                    if (tid == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1(x, inv);
+                if (active) {
+                    l = wave_sum(l);
+                    o = wave_sum(o);
+                    if (lane == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1((float)(o / l), inv);
                 }
+                __syncthreads();                              // qs is free
             }
         } while (again);
     }
@@ -1618,38 +1525,27 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
 
 static bool attn_aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Scratch of the approximate attention: an error bound per query of a head, then what its workgroups know about the
-// exact maximum (split form: bounds and candidates; fp32 form: records)
+// Scratch of the approximate attention: an error bound per query of a head, then what its workgroups know about the exact
+// maximum
 static size_t attention_bounds_bytes(int32_t B, int32_t S, int32_t heads) { return align_up((size_t)B * heads * S * 4, 256); }
 size_t attention_records_bytes(int32_t B, int32_t S, int32_t heads)
 {
-    const size_t split = (size_t)B * heads * ((S + kSplitQ - 1) / kSplitQ) * sizeof(AttnCand);
-    const size_t fp32 = (size_t)B * heads * ((S + 63) / 64) * sizeof(AttnRecord);
-    return attention_bounds_bytes(B, S, heads) + align_up(split > fp32 ? split : fp32, 256);
+    return attention_bounds_bytes(B, S, heads) + align_up((size_t)B * heads * ((S + kSplitQ - 1) / kSplitQ) * sizeof(AttnCand), 256);
 }
 
-// Kernel 1 in the float16-split form: head dims in whole units of 8 floats at 16-byte aligned addresses; else the fp32 form.
 bool attention_splits(int32_t Hd, int32_t heads) { return ((Hd / heads) & 7) == 0 && (Hd & 3) == 0; }
 
-// rec: what follows the bounds in the scratch memory, or null (the kernel alone)
+// cands, bound_slot, exact_slot: null for the kernel alone
 static hipError_t launch_attention_approx(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                          float *err_q, char *rec, const uint32_t *max_slot, uint32_t *amax_slot,
-                                          uint32_t *err_slot, uint32_t *exact_slot, hipStream_t st)
+                                          float *err_q, AttnCand *cands, const uint32_t *max_slot, uint32_t *bound_slot,
+                                          uint32_t *exact_slot, hipStream_t st)
 {
     const int dh = Hd / heads;
-    const float scale = (float)(1.0 / sqrt((double)dh));
-    if (attention_splits(Hd, heads)) {
-        const int64_t grid = (int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ);
-        const int per_xcd = (int)((grid + 7) / 8);
-        return launch_k(EGERIA_KERNEL_ATTENTION, attention_split_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
-                        qkv, (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, err_q, (AttnCand *)rec,
-                        (int)grid, per_xcd, max_slot, rec ? amax_slot : nullptr, exact_slot);
-    }
-    const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
+    const int64_t grid = (int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ);
     const int per_xcd = (int)((grid + 7) / 8);
-    return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
-                    (int)B, (int)S, (int)Hd, (int)heads, dh, scale, ctx, err_q, (AttnRecord *)rec, (int)grid, per_xcd, amax_slot,
-                    err_slot);
+    return launch_k(EGERIA_KERNEL_ATTENTION, attention_split_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
+                    qkv, (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx, err_q, cands,
+                    (int)grid, per_xcd, max_slot, bound_slot, exact_slot);
 }
 
 // The largest |value| of a tensor into the words of a maximum slot, a workgroup per word (runs have it from the GEMM's epilogue).
@@ -1678,14 +1574,14 @@ hipError_t launch_attention_bounds(const float *qkv, int32_t B, int32_t S, int32
     const int dh = Hd / heads;
     const int64_t grid = (int64_t)B * heads * ((S + 63) / 64);
     if (grid <= 0) return hipSuccess;
-    if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
+    if (dh > kDh || !attention_splits(Hd, heads) || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(bounds)) return hipErrorInvalidValue;
     const hipError_t e = launch_k(EGERIA_KERNEL_NONE, tensor_max_kernel, dim3(kAmaxWays), dim3(256), 0, st, qkv, (int64_t)B * S * 3 * Hd, max_slot);
     if (e != hipSuccess) return e;
-    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, bounds, nullptr, max_slot, nullptr, nullptr, nullptr, st);
+    return launch_attention_approx(qkv, B, S, Hd, heads, ctx, bounds, nullptr, max_slot, nullptr, nullptr, st);
 }
 
-// The fp32 form of kernel 1 alone, any head size: approximate context and a record per 64 queries of a head.
+// The fp32 kernel, any head size: approximate context and a record per 64 queries of a head.
 hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
                                  void *records, hipStream_t st)
 {
@@ -1696,35 +1592,25 @@ hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(records)) return hipErrorInvalidValue;
     const int per_xcd = (int)((grid + 7) / 8);
     return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
-                    (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx, (float *)nullptr,
-                    (AttnRecord *)records, (int)grid, per_xcd, (uint32_t *)nullptr, (uint32_t *)nullptr);
+                    (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx,
+                    (AttnRecord *)records, (int)grid, per_xcd);
 }
 
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                      void *records, uint32_t *amax_slot, uint32_t *err_slot, uint32_t *exact_slot, int8_t *xq, int64_t ldq, float *scale_out,
-                                      uint32_t *flag, uint32_t *unsure_total, hipStream_t st)
+                                      void *records, const uint32_t *max_slot, uint32_t *bound_slot, uint32_t *exact_slot,
+                                      int8_t *xq, int64_t ldq, float *scale_out, uint32_t *flag, uint32_t *unsure_total,
+                                      hipStream_t st)
 {
     const int dh = Hd / heads;
-    const int qtiles = (S + 63) / 64;
-    const int64_t grid = (int64_t)B * heads * qtiles;
-    const int64_t M = (int64_t)B * S;
-    if (grid <= 0) return hipSuccess;
-    // what the kernels assume: heads of at most 64 dims, 32-bit indices of the context's values, rows that
-    // 16-byte vector accesses may touch when the head size allows them
-    if (dh > kDh || grid > 0x7ffffff0LL || M * Hd >= (1LL << 32) || ldq < Hd) return hipErrorInvalidValue;
+    const int64_t nwg = (int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ), M = (int64_t)B * S;
+    if (nwg <= 0) return hipSuccess;
+    // what the kernels assume: heads of at most 64 dims in whole units of 8, 32-bit indices of the context's values, rows that
+    // 16-byte vector accesses may touch
+    if (dh > kDh || !attention_splits(Hd, heads) || nwg > 0x7ffffff0LL || M * Hd >= (1LL << 32) || ldq < Hd) return hipErrorInvalidValue;
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(xq) || !attn_aligned16(records)) return hipErrorInvalidValue;
     float *err_q = (float *)records;
-    char *rec = (char *)records + attention_bounds_bytes(B, S, heads);
-    const double scale = 1.0 / sqrt((double)dh);
-    const bool split = attention_splits(Hd, heads);
-    // (split form: err_slot holds the largest |value| of qkv, left by the GEMM that wrote it)
-    hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, err_q, rec, err_slot, amax_slot, err_slot, exact_slot, st);
-    if (e != hipSuccess) return e;
-    const int nrec = (int)grid;
-    // (the quantiser settles the exact maximum from the split kernel's candidates; the fp32 kernel leaves it to a launch of its own)
-    if (!split) e = launch_k(EGERIA_KERNEL_NONE, attention_absmax_exact_kernel, dim3((unsigned)((nrec + 255) / 256)), dim3(256), 0, st, qkv,
-                 (const float *)ctx, (const AttnRecord *)rec, nrec, (const uint32_t *)amax_slot, (const uint32_t *)err_slot, (int)S,
-                 (int)Hd, (int)heads, dh, scale, exact_slot);
+    AttnCand *cands = (AttnCand *)((char *)records + attention_bounds_bytes(B, S, heads));
+    const hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, err_q, cands, max_slot, bound_slot, exact_slot, st);
     if (e != hipSuccess) return e;
     const bool wide = (dh & 15) == 0 && (Hd & 15) == 0 && ldq == Hd;
     if ((int64_t)S * (dh + (ldq - Hd)) >= (1LL << 31)) return hipErrorInvalidValue;
@@ -1737,17 +1623,13 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
     const int tokens = (int)((S + splits - 1) / splits);
     splits = (S + tokens - 1) / tokens;
     if (all_heads * splits > 0x7fffffffLL) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)(all_heads * splits);
-    const int nwg = split ? (int)((int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ)) : 0;
-    const bool klds = (dh & 3) == 0 && (Hd & 3) == 0;
     auto go = [&](auto kernel) {
-        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, dim3(blocks), dim3(kCertifyThreads), 0, st, qkv, (const float *)ctx,
-                        (const float *)err_q, (const AttnCand *)rec, nwg,
-                        (const uint32_t *)amax_slot, (int)S, (int)Hd, (int)heads, dh, (int)splits, tokens, scale, (const uint32_t *)exact_slot, xq,
-                        ldq, scale_out, flag, unsure_total);
+        return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, dim3((unsigned)(all_heads * splits)), dim3(kCertifyThreads), 0, st, qkv,
+                        (const float *)ctx, (const float *)err_q, (const AttnCand *)cands, (int)nwg, (const uint32_t *)bound_slot,
+                        (int)S, (int)Hd, (int)heads, dh, (int)splits, tokens, 1.0 / sqrt((double)dh), (const uint32_t *)exact_slot,
+                        xq, ldq, scale_out, flag, unsure_total);
     };
-    if (wide) return klds ? go(quantize_attention_certify_kernel<true, true>) : go(quantize_attention_certify_kernel<true, false>);
-    return klds ? go(quantize_attention_certify_kernel<false, true>) : go(quantize_attention_certify_kernel<false, false>);
+    return wide ? go(quantize_attention_certify_kernel<true>) : go(quantize_attention_certify_kernel<false>);
 }
 
 hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads,

@@ -320,22 +320,22 @@ hipError_t launch_layernorm(const float *x, const float *res, int64_t rows, int3
 hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads,
                             float *ctx, uint32_t *absmax_out, hipStream_t st);
 
-// The same attention for unobserved runs: fp32 matrix-core arithmetic, then the int8 codes [B*S, ldq] and
-// the scale of the context as the fp64 evaluation defines them (values whose code the approximate result
-// does not settle are re-evaluated in fp64).  ctx receives the approximate context (scratch), records
-// attention_records_bytes(...) bytes of scratch, amax_slot, err_slot and exact_slot atomically combined maximum
-// words (zero on entry), unsure_total (nullable) is incremented by the number of re-evaluated values.
+// The same attention for unobserved runs, head dims in whole units of 8 (attention_splits): approximate matrix-core
+// arithmetic, then the int8 codes [B*S, ldq] and the scale of the context as the fp64 evaluation defines them (values whose
+// code the approximate result does not settle are re-evaluated in fp64).  max_slot: the largest |value| of qkv.  ctx receives
+// the approximate context (scratch), records attention_records_bytes(...) bytes of scratch, bound_slot and exact_slot are
+// atomically combined maximum words (zero on entry), unsure_total (nullable) is incremented by the number of re-evaluated values.
 size_t attention_records_bytes(int32_t B, int32_t S, int32_t heads);
+bool attention_splits(int32_t Hd, int32_t heads);
+hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
+                                      void *records, const uint32_t *max_slot, uint32_t *bound_slot, uint32_t *exact_slot,
+                                      int8_t *xq, int64_t ldq, float *scale_out, uint32_t *flag, uint32_t *unsure_total,
+                                      hipStream_t st);
+// For measurement: its first kernel alone with the error bounds (max_slot: scratch), and an fp32 kernel for any head size.
 hipError_t launch_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
                                    float *bounds, uint32_t *max_slot, hipStream_t st);
 hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
                                  void *records, hipStream_t st);
-// true if that attention wants the largest |value| of qkv in err_slot on entry (the form that splits operands)
-bool attention_splits(int32_t Hd, int32_t heads);
-hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
-                                      void *records, uint32_t *amax_slot, uint32_t *err_slot, uint32_t *exact_slot,
-                                      int8_t *xq, int64_t ldq, float *scale_out,
-                                      uint32_t *flag, uint32_t *unsure_total, hipStream_t st);
 
 // Training plasticity.  ws_part must hold plasticity_partial_bytes(b, D).  beside: the launch shares the device with
 // another stream's work.

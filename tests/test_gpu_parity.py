@@ -580,7 +580,7 @@ ATTENTION_SHAPES = [dict(b=3, s=77, hidden=200, heads=5, ffn=328, n_layers=2),  
                     dict(b=1, s=300, hidden=96, heads=3, ffn=64, n_layers=2),       # keys in LDS in two rounds, 16 per thread
                     dict(b=1, s=129, hidden=24, heads=3, ffn=64, n_layers=2),       # heads of 8, shares of a head's tokens
                     dict(b=1, s=515, hidden=96, heads=2, ffn=64, n_layers=2),       # keys in three rounds, a token more than a share
-                    dict(b=2, s=70, hidden=66, heads=3, ffn=40, n_layers=2)]        # head size 22: plain loop
+                    dict(b=2, s=70, hidden=66, heads=3, ffn=40, n_layers=2)]        # head size 22: the fp64 kernel
 
 
 @pytest.mark.parametrize("kw", ATTENTION_SHAPES, ids=lambda k: "b{b}_s{s}_h{hidden}_heads{heads}".format(**k))
@@ -604,12 +604,13 @@ def test_attention_paths_agree(eg, gc, kw):
     assert np.array_equal(outs[0].cpu().numpy().reshape(observed.shape), observed)
 
 
+@pytest.mark.parametrize("kind", ["normal", "uniform x4", "2 tokens in order", "equal scores 30", "2 tokens cancelling terms"])
 @pytest.mark.parametrize("S,heads,dh", [(64, 2, 16), (131, 3, 16), (200, 2, 64), (70, 3, 22)])
-def test_profile_attention_writes_its_records_only(eg, gc, S, heads, dh):
-    """The measuring entry leaves one pair per 64 queries of a head, whatever the kernel behind it, and the error of each
-    value within the bound of its pair."""
+def test_profile_attention_writes_its_records_only(eg, gc, S, heads, dh, kind):
+    """The measuring entry leaves one pair per 64 queries of a head and nothing behind them, and the error of each value is
+    within the bound of its pair."""
     B, H = 2, heads * dh
-    qkv = torch.randn(B, S, 3 * H, generator=torch.Generator().manual_seed(S)).to(gc.DEV)
+    qkv = gc.to_dev(si.attention_qkv(kind, B, S, heads, dh))
     tiles = (S + 63) // 64
     n = B * heads * tiles
     rec = torch.full((2 * n + B * heads * S,), 7, dtype=torch.int32, device=gc.DEV)
