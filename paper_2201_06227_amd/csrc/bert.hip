@@ -923,16 +923,13 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 #pragma unroll
                 for (int i = 0; i < 16; ++i) o[db][i] *= corr;
         }
-        if constexpr (decltype(ragged)::value) {                 // the ragged last tile: keys beyond S do not count
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                sacc[i] = j0 + 8 * (i >> 2) + 4 * h + (i & 3) < S ? sacc[i] : -INFINITY;
-        }
         const float shift = -mrun * c2;
         float ps = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             sacc[i] = __builtin_amdgcn_exp2f(fmaf(sacc[i], c2, shift));
+            // the ragged last tile: keys beyond S do not count (an infinite score would meet a factor c2 that is zero)
+            if constexpr (decltype(ragged)::value) sacc[i] = j0 + 8 * (i >> 2) + 4 * h + (i & 3) < S ? sacc[i] : 0.0f;
             ps += sacc[i];
             p2run = fmaf(sacc[i], sacc[i], p2run);
         }

@@ -646,6 +646,18 @@ def test_attention_error_is_within_its_bound(eg, gc, b, s, heads, dh, kind):
         assert bounds.median().item() <= 16 * 2.0 ** -24 * vmax
 
 
+@pytest.mark.parametrize("factor", [1e-3, 0.0])
+@pytest.mark.parametrize("s", [20, 128, 131])
+def test_attention_bound_of_zero_queries_is_a_number(eg, gc, s, factor):
+    """Query rows of zeros beside small values, and nothing but zeros: the scores are zero, the bounds finite, so that the
+    quantiser does not re-evaluate every value."""
+    qkv = si.attention_qkv("normal", 2, s, 2, 32) * np.float32(factor)
+    qkv[:, ::3, :64] = 0.0
+    ctx, bounds = eg.profile_attention_bounds(gc.to_dev(qkv), 2)
+    assert bool(torch.isfinite(ctx).all()) and bool(torch.isfinite(bounds).all())
+    assert bounds.max().item() <= 1e-6 * factor
+
+
 # what the certified kernels meet beyond ordinary activations: rows that tie for the tensor's maximum (the candidates of a
 # workgroup overflow its list), nothing but zeros, whole samples twice, scores in the hundreds, values that the split's scale
 # leaves few digits of (every code is re-evaluated: the list of the quantiser overflows)
