@@ -359,11 +359,13 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
 
 // ---- the same attention in approximate arithmetic on the matrix cores, with certified int8 codes ----------
 // Unobserved runs do not need the context as the fp64 evaluation gives it: all that leaves this stage
-// is the int8 input of the next GEMM and its scale.  Two launches, for head dims in whole units of 8:
+// is the int8 input of the next GEMM and its scale.  Three launches, for head dims in whole units of 8:
 //   1. an approximate attention with fp32 sums: attention_split_kernel (further down: every fp32 product as three float16
 //      partial products on the float16 matrix cores).  It stores an approximate context, an error bound E per query of a head
 //      and what its workgroups know of the largest value.
-//   2. quantize_attention_certify_kernel: the streaming map to codes.  code(x) = clamp(rne(x * inv)) is
+//   2. attention_settle_kernel: the tensor's absolute maximum as the fp64 evaluation gives it, from the values that can be it
+//      (as a rule one).
+//   3. quantize_attention_certify_kernel: the streaming map to codes.  code(x) = clamp(rne(x * inv)) is
 //      monotone in x, so an approximate value whose interval [x - E, x + E] maps to one code has that
 //      code; the others (a few in ten thousand) are re-evaluated in fp64, a wave per value, by the
 //      workgroup that met them.
@@ -655,12 +657,8 @@ typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
 typedef _Float16 v2hf __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // (defined further down; the kernel below ends with the exact evaluation of its candidates for the maximum)
-struct Nothing {
-    __device__ void operator()() const {}
-};
-template <typename F = Nothing>
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
-                                               uint32_t el, double *red, F meanwhile = {});
+                                               uint32_t el, double *red);
 template <typename F>
 __device__ __forceinline__ void for_each_marked(bool mine, uint64_t *masks, F visit);
 constexpr int kSplitQ = 128;             // queries per workgroup
@@ -1049,7 +1047,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 
     // What the workgroup knows about the tensor's exact maximum.  It raises a shared word to a lower bound of its own exact
     // maximum (largest stored |x| minus its error) and leaves an upper bound and the values that reach its own lower
-    // bound; the quantiser that follows evaluates those that reach the tensor's.  (Evaluated here, nearly every workgroup
+    // bound; the launch that follows evaluates those that reach the tensor's.  (Evaluated here, nearly every workgroup
     // of the first round found its own maximum above all that was reported by then: 21 -> 36 us for 32 x 128 tokens x 12
     // heads, 88 -> 104 for 64 x 256.)
     if (mbits >= 0x7f800000u || mbits == 0) {                    // NaN / Inf: they are the "maximum"; zeros: nothing to find
@@ -1133,11 +1131,10 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
 // ones, the query zero beyond dh): a load under a condition is awaited on its own, and a key row would
 // cost sixteen memory round trips instead of one.
 // (kept compact and inlined once per kernel: called as a function it needs scratch memory for the
-// caller's registers and ran five times slower)  The whole workgroup of 256 threads evaluates one value, a key per thread;
-// `meanwhile` runs while the first loads are on their way.  Head dims in whole units of 4 floats.  red: 12 + 32 doubles.
-template <typename F>
+// caller's registers and ran five times slower)  The whole workgroup of 256 threads evaluates one value, a key per thread.
+// Head dims in whole units of 4 floats.  red: 12 + 32 doubles.
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
-                                               uint32_t el, double *red, F meanwhile)
+                                               uint32_t el, double *red)
 {
     const uint32_t mrow = el / (uint32_t)Hd, col = el - mrow * (uint32_t)Hd;
     const uint32_t bi = mrow / (uint32_t)S, hd = col / (uint32_t)dh, dd = col - hd * (uint32_t)dh;
@@ -1162,7 +1159,6 @@ __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, in
     };
     const float qreg = (tid < 64 && tid < dh) ? q[tid] : 0.0f;
     request(0);
-    meanwhile();
     __syncthreads();                                          // an earlier call has finished with red and qs
     if (tid < 64) qs[tid] = qreg;
     __syncthreads();
@@ -1220,28 +1216,50 @@ __device__ __forceinline__ void for_each_marked(bool mine, uint64_t *masks, F vi
     }
 }
 
-// The int8 codes of the context under the tensor's exact scale: a workgroup of eight waves per (batch element, head), or
-// for a share of its tokens where that leaves compute units idle.
-// The scale first.  The split attention left, per workgroup, an upper bound and the values that can be its largest
-// (AttnCand); the few that reach the tensor's largest lower bound - as a rule one - are evaluated in fp64 by every
-// workgroup for itself, while its keys are on their way: a launch of its own costs more than the 2 us this adds, and no
-// workgroup waits for another.  Then it streams over its slice of the approximate context: a thread maps 16
-// consecutive values of a token row (one 16-byte store; WIDE: head size and row length are multiples of
+// The exact maximum from the candidates: a thread per attention workgroup; if that can hold the maximum, the whole workgroup
+// evaluates its candidates.  As a rule there is one in the tensor, but equal samples tie, at the same place of each: sixteen
+// attention workgroups to a workgroup here share them out.  (With this in the certifying quantiser, where every
+// workgroup read all bounds and evaluated all candidates for itself, the time went with the square of the batch: one layer
+// of 768 x 12 heads, us, distinct / equal samples of 256 tokens: batch 64 354 / 1010, now 345 / 363;
+// 512 2363 / 43187, now 2170 / 2297.)
+constexpr int kSettleWorkgroups = 16;      // (a power of two)
+__global__ __launch_bounds__(256) void attention_settle_kernel(const float *__restrict__ qkv, const AttnCand *__restrict__ cands,
+                                                               int nwg, const uint32_t *__restrict__ bound, int S, int Hd, int heads,
+                                                               int dh, double scale, uint32_t *__restrict__ exact)
+{
+    __shared__ __attribute__((aligned(16))) double red[12 + 32];
+    __shared__ uint64_t masks[4];
+    __shared__ AttnCand sc[kSettleWorkgroups];
+    const int w = blockIdx.x * kSettleWorkgroups + (int)(threadIdx.x & (kSettleWorkgroups - 1));
+    const AttnCand mine = cands[w < nwg ? w : nwg - 1];
+    const float floor_v = __uint_as_float(reduce_ways(bound));
+    if (threadIdx.x < kSettleWorkgroups) sc[threadIdx.x] = mine;
+    uint32_t best = 0;
+    for_each_marked(threadIdx.x < kSettleWorkgroups && w < nwg && mine.upper >= floor_v && mine.upper > 0.0f, masks, [&](int k) {
+        const AttnCand &c = sc[k];
+        for (uint32_t e = 0; e < c.n; ++e) {
+            const uint32_t ab = abs_bits(context_exact(qkv, S, Hd, heads, dh, scale, c.at[e], red));
+            best = best > ab ? best : ab;
+        }
+    });
+    if (threadIdx.x == 0 && best) atomicMax(exact + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride, best);
+}
+
+// The int8 codes of the context under the tensor's exact scale: a workgroup of four waves per (batch element, head), or
+// for a share of its tokens where that leaves compute units idle.  It streams over its slice of the approximate context: a
+// thread maps 16 consecutive values of a token row (one 16-byte store; WIDE: head size and row length are multiples of
 // 16) or a single value.  A value whose interval [x - E, x + E] maps to two codes gets a provisional code
 // and goes on the workgroup's list in LDS (token * dh + dim within the head).  After each pass the workgroup re-evaluates
 // the listed values in fp64 and overwrites their codes.  A re-evaluation needs all keys of its head (S x dh floats): read
 // from global memory per value, that traffic (and the sixteen-byte pieces of 256 different rows each load instruction asks
-// for) bounds the whole step.  KLDS (head size a multiple of 4): the workgroup copies the head's keys into LDS, 256 at a
+// for) would bound the whole step.  The workgroup copies the head's keys into LDS, 256 at a
 // time, with coalesced loads, and each of its waves re-evaluates one listed value from there: lane l holds keys l,
 // l + 64, ..., a row of LDS each (rows padded by 16 bytes, so the lanes' 16-byte reads do not collide), the query row is
 // broadcast from LDS, and only the value column (one float per key) comes from global memory.  Up to 256 keys are copied
-// once; more are copied for every eight values.  Other head sizes use the workgroup-wide evaluation, one value after the
-// other.  What bounds it: a workgroup's chain of round trips (its keys and
-// the candidate 5 us, codes 3, four re-evaluations 4) and, for many heads, the value columns: a line per key and value,
-// 85 MB for 64 x 256 tokens x 12 heads beside the 113 of context and keys.  With the maximum settled by the attention kernel
-// and its looser bound (four to nine values per head listed instead of two to four), us, attention + this kernel: 32 x 128
-// tokens x 12 heads 36 + 24, now 18 + 22; 24 x 197 46 + 36, 33 + 32; 64 x 256 104 + 79, 74 + 68; 8 x 384 x 8 heads 49 + 201,
-// 22 + 43.  (Eight waves and 128 registers: spills, 31 and 86 us for the first and third.)
+// once; more are copied for every four values.  What bounds it: a workgroup's chain of round trips (its keys 4 us, codes 3,
+// four re-evaluations 4, of which it has one to three) and, for many heads, the value columns: a line per key and value
+// listed, four to twelve of them per head and 256 tokens.  64 x 256 tokens x 12 heads, us: attention 87, settling the
+// maximum 9, this kernel 64 (82 with the settling inside).  (Eight waves and 128 registers: spills, 30 % longer.)
 constexpr int kKeysLds = 256;            // keys a workgroup can hold
 constexpr int kKeyRow = kDh + 4;         // floats per key row in LDS (one 16-byte pad)
 
@@ -1260,8 +1278,7 @@ constexpr int kCertifyThreads = 256;
 template <bool WIDE>
 __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify_kernel(
     const float *__restrict__ qkv, const float *__restrict__ ctx, const float *__restrict__ err_q,
-    const AttnCand *__restrict__ cands, int nwg, const uint32_t *__restrict__ bound, int S, int Hd, int heads, int dh,
-    int splits, int tokens, double scale, const uint32_t *__restrict__ exact, int8_t *xq, int64_t ldq,
+    int S, int Hd, int heads, int dh, int splits, int tokens, double scale, const uint32_t *__restrict__ exact, int8_t *xq, int64_t ldq,
     float *__restrict__ scale_out, uint32_t *__restrict__ flag, uint32_t *__restrict__ unsure_total)
 {
     constexpr int NT = kCertifyThreads, NW = NT / 64;
@@ -1270,7 +1287,6 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
     constexpr uint32_t kList = 1024;                              // list entries served per round
     __shared__ uint32_t todo[kList];
     __shared__ uint32_t n_todo, more;
-    __shared__ __attribute__((aligned(16))) double red[12 + 32];
     __shared__ __attribute__((aligned(16))) float ks[kKeysLds * kKeyRow];
     __shared__ __attribute__((aligned(16))) float qs[NW * kDh];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1301,8 +1317,6 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
         t += t0;
         return ok;
     };
-    uint32_t top = reduce_ways(exact);                            // what the attention workgroups evaluated themselves
-    const float floor_v = __uint_as_float(reduce_ways(bound));
     float4 v[NPRE][WIDE ? 4 : 1];
     float ev[NPRE];
     auto request = [&](uint32_t p0) {
@@ -1344,47 +1358,10 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
             }
         }
     };
-    bool staged = S > kKeysLds;
-    for (int w0 = 0; w0 < nwg; w0 += NT * 32) {                   // 32 attention workgroups per thread at a time
-        uint32_t pend_w = 0;                                      // bit k: workgroup w0 + NT k + tid may hold the maximum
-#pragma unroll 4
-        for (int k = 0; k < 32; ++k) {
-            const int w = w0 + NT * k + tid;
-            if (w0 + NT * k >= nwg) break;
-            const float u = cands[w < nwg ? w : nwg - 1].upper;
-            pend_w |= w < nwg && u >= floor_v && u > 0.0f ? 1u << k : 0u;
-        }
-        bool again;
-        do {
-            __syncthreads();                                      // the list has been served
-            if (tid == 0) { n_todo = 0; more = 0; }
-            __syncthreads();
-            while (pend_w) {
-                const uint32_t slot = atomicAdd(&n_todo, 1u);
-                if (slot >= kList) { more = 1; break; }
-                todo[slot] = (uint32_t)(w0 + NT * (__ffs((int)pend_w) - 1) + tid);
-                pend_w &= pend_w - 1;
-            }
-            __syncthreads();
-            const uint32_t n = n_todo < kList ? n_todo : kList;
-            again = more != 0;
-            for (uint32_t k = 0; k < n; ++k) {
-                const AttnCand &c = cands[__builtin_amdgcn_readfirstlane((int)todo[k])];
-                for (uint32_t e = 0; e < c.n; ++e) {
-                    const float x = context_exact(qkv, S, Hd, heads, dh, scale, c.at[e], red, [&]() {
-                        if (!staged) stage_keys(0);
-                        staged = true;
-                    });
-                    const uint32_t ab = abs_bits(x);
-                    top = top > ab ? top : ab;
-                }
-            }
-        } while (again);
-    }
-    if (!staged) stage_keys(0);
+    if (S <= kKeysLds) stage_keys(0);
     float sc_f;
     bool bad;
-    const float inv = scale_from_bits(top, nullptr, &sc_f, &bad);
+    const float inv = scale_from_bits(reduce_ways(exact), nullptr, &sc_f, &bad);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(sc_f, bad, scale_out, nullptr, flag);
     uint32_t met = 0;
     // the loop bounds are the same in every thread of the workgroup (barriers inside)
@@ -1607,7 +1584,11 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(xq) || !attn_aligned16(records)) return hipErrorInvalidValue;
     float *err_q = (float *)records;
     AttnCand *cands = (AttnCand *)((char *)records + attention_bounds_bytes(B, S, heads));
-    const hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, err_q, cands, max_slot, bound_slot, exact_slot, st);
+    const double scale = 1.0 / sqrt((double)dh);
+    hipError_t e = launch_attention_approx(qkv, B, S, Hd, heads, ctx, err_q, cands, max_slot, bound_slot, exact_slot, st);
+    if (e != hipSuccess) return e;
+    e = launch_k(EGERIA_KERNEL_NONE, attention_settle_kernel, dim3((unsigned)((nwg + kSettleWorkgroups - 1) / kSettleWorkgroups)), dim3(256), 0, st,
+                 qkv, (const AttnCand *)cands, (int)nwg, (const uint32_t *)bound_slot, (int)S, (int)Hd, (int)heads, dh, scale, exact_slot);
     if (e != hipSuccess) return e;
     const bool wide = (dh & 15) == 0 && (Hd & 15) == 0 && ldq == Hd;
     if ((int64_t)S * (dh + (ldq - Hd)) >= (1LL << 31)) return hipErrorInvalidValue;
@@ -1622,9 +1603,8 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
     if (all_heads * splits > 0x7fffffffLL) return hipErrorInvalidValue;
     auto go = [&](auto kernel) {
         return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, dim3((unsigned)(all_heads * splits)), dim3(kCertifyThreads), 0, st, qkv,
-                        (const float *)ctx, (const float *)err_q, (const AttnCand *)cands, (int)nwg, (const uint32_t *)bound_slot,
-                        (int)S, (int)Hd, (int)heads, dh, (int)splits, tokens, 1.0 / sqrt((double)dh), (const uint32_t *)exact_slot,
-                        xq, ldq, scale_out, flag, unsure_total);
+                        (const float *)ctx, (const float *)err_q, (int)S, (int)Hd, (int)heads, dh, (int)splits, tokens, scale,
+                        (const uint32_t *)exact_slot, xq, ldq, scale_out, flag, unsure_total);
     };
     return wide ? go(quantize_attention_certify_kernel<true>) : go(quantize_attention_certify_kernel<false>);
 }

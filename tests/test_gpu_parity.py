@@ -697,6 +697,34 @@ def test_attention_paths_agree_on_extreme_inputs(eg, gc, kw, inputs):
     assert torch.equal(outs[0], outs[1])
 
 
+def test_equal_samples_share_the_search_for_the_maximum(eg, gc):
+    """Samples that occur several times tie for the tensor's maximum; each tie is evaluated once, not by every workgroup
+    that quantises (which took ten times as long as distinct samples here)."""
+    b, s, h = 256, 128, 256
+    wl = si.make_bert(b=b, s=s, hidden=h, heads=4, ffn=64, n_layers=1, seed=72, train_act_dtype="f32")
+    ref = gc.build_reference(wl)
+    ws = eg.workspace(eg.workspace_bytes(ref.desc), gc.DEV)
+    x = gc.to_dev(wl.x)
+    same = x[:1].expand_as(x).contiguous()
+    outs, times = [], []
+    for inp, thr in ((x, 0.0), (same, 0.0), (same, 1.0e30)):
+        eg.attention_threshold(thr)
+        a = torch.empty(gc.a_ref_numel(wl), dtype=torch.float32, device=gc.DEV)
+        best = float("inf")
+        for _ in range(5):
+            start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            eg.ref_forward(ref, inp, a, ws)
+            stop.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(stop))
+        outs.append(a)
+        times.append(best)
+    assert eg.check(ws) == eg.OK
+    assert torch.equal(outs[1], outs[2])
+    assert times[1] <= 3.0 * times[0], times
+
+
 @pytest.mark.parametrize("column", ["query", "value"])
 def test_attention_reports_non_finite_values(eg, gc, column):
     """An infinite bias in the QKV layer puts non-finite values into the attention (finite inputs and weights
