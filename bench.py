@@ -204,10 +204,7 @@ def roofline_for(wl, cls, durations_ms, eg, steps, cfg=None, force_mfma=False):
         # which kernel an unobserved run takes (the library's rule): the fp64 kernel up to 64 tokens, for small sizes and for
         # heads that are no multiple of 8 dims; else the approximate kernel with certified codes, on the float16 matrix cores
         d = wl.dims
-        dh = d["hidden"] // d["heads"]
-        pairs = float(d["batch"] * d["heads"] * d["seq"] ** 2)
-        size = 0.0 if d["seq"] <= 64 else 256.0 * pairs / (1 if d["seq"] <= 256 else 2)
-        if dh % 8 or size < eg.attention_threshold():
+        if not eg.attention_certified(d["batch"], d["seq"], d["hidden"], d["heads"]):
             names[cls], att_peak = "attention_kernel", PEAK_F64_MFMA_TFLOPS
     fused_ln = cls == eg.KERNEL_LAYERNORM and layernorm_in_gemm(wl)
     if not work or not durations_ms:

@@ -54,12 +54,14 @@ egeria_status egeria_profile_attention(const float *qkv, int32_t B, int32_t S, i
 egeria_status egeria_profile_attention_bounds(const float *qkv, int32_t B, int32_t S, int32_t hidden, int32_t heads, float *ctx,
                                               float *bounds, size_t bounds_bytes, void *ws, size_t ws_bytes, void *stream);
 
-/* Unobserved runs of the Transformer kinds evaluate attention with the certified approximate kernels when its size, in
- * flops as the fp64 kernel does them (256 * batch * heads * seq^2; half of that beyond 256 tokens, none up to 64, where they
- * do not pay), reaches this threshold (default 0.75e9), with the fp64 kernel below it; the results are the same.  Sets the
- * threshold (a negative value leaves it unchanged; 0: every size) and returns the previous one; process-wide, for tests that
- * exercise the certified kernels on small shapes. */
+/* Unobserved runs of the Transformer kinds evaluate attention with the certified approximate kernels (head sizes that are
+ * multiples of 8) when the two products take at least this many flops (4 * batch * heads * seq^2 * head size), with the fp64
+ * kernel below it: the results are the same.  The default, 5e9, stands for the library's own rule, by batch, tokens and head
+ * size, of where that is faster.  Sets the threshold (a negative value leaves it unchanged) and returns the previous one;
+ * process-wide, for tests that exercise the certified kernels on small shapes. */
 double egeria_profile_attention_threshold(double min_flops);
+/* Host-only: 1 if unobserved runs of these sizes take the certified kernels at the present threshold, else 0. */
+int32_t egeria_profile_attention_certified(int32_t B, int32_t S, int32_t hidden, int32_t heads);
 
 /* Host-only: the output tile (rows x cols) and the K bytes per step with which an int8 layer of M output rows (pixels,
  * tokens, samples), N outputs and k_bytes bytes per weight row runs; conv3x3 != 0: a 3x3 convolution (k_bytes = 9 *

@@ -104,7 +104,7 @@ EXPORTS = [
     "egeria_cache_bytes", "egeria_cache_init", "egeria_cache_put", "egeria_cache_get", "egeria_profile_pause",
     "egeria_refresh_eval", "egeria_plasticity_noalloc", "egeria_profile_attention", "egeria_profile_attention_bounds",
     "egeria_quantize_affine", "egeria_quantize_affine_workspace_bytes", "egeria_microbench",
-    "egeria_profile_attention_threshold", "egeria_profile_gemm_tile", "egeria_profile_gemm_stages",
+    "egeria_profile_attention_threshold", "egeria_profile_attention_certified", "egeria_profile_gemm_tile", "egeria_profile_gemm_stages",
 ]
 
 (KERNEL_NONE, KERNEL_ABSMAX, KERNEL_QUANTIZE, KERNEL_GEMM, KERNEL_GRAM, KERNEL_ATTENTION, KERNEL_LAYERNORM,
@@ -177,6 +177,8 @@ def lib():
     L.egeria_profile_attention_bounds.argtypes = [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _sz, _vp, _sz, _vp]
     L.egeria_profile_attention_threshold.restype = ctypes.c_double
     L.egeria_profile_attention_threshold.argtypes = [ctypes.c_double]
+    L.egeria_profile_attention_certified.restype = _i32
+    L.egeria_profile_attention_certified.argtypes = [_i32] * 4
     L.egeria_profile_gemm_tile.restype = ctypes.c_int
     L.egeria_profile_gemm_tile.argtypes = [_i64, _i32, _i64, _i32] + [ctypes.POINTER(_i32)] * 3
     L.egeria_profile_gemm_stages.restype = _i32
@@ -558,6 +560,11 @@ MICRO_KINDS = ["mfma_i32_32x32x32_i8", "mfma_f32_32x32x16_bf16", "mfma_f32_32x32
 def attention_threshold(min_flops: float = -1.0) -> float:
     """egeria_profile_attention_threshold: sets (if >= 0) and returns the previous threshold."""
     return float(lib().egeria_profile_attention_threshold(float(min_flops)))
+
+
+def attention_certified(batch: int, seq: int, hidden: int, heads: int) -> bool:
+    """egeria_profile_attention_certified: whether unobserved runs of these sizes take the certified kernels."""
+    return bool(lib().egeria_profile_attention_certified(batch, seq, hidden, heads))
 
 
 def gemm_tile(M: int, N: int, k_bytes: int, conv3x3: bool = False):

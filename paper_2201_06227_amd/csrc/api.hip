@@ -461,20 +461,29 @@ egeria_status forward_float(Fwd &f, const void *x, egeria_dtype dt, float *a_ref
     return run_gemm(f, 2, f.qbuf(2), cmid_b, M, d->c_out, cmid_b, false, 0, 0, 0, one, 1, res, one, res_ld, a_ref, nullptr);
 }
 
-// Attention sizes from which unobserved runs take the certified approximate kernels (two launches) instead of the fp64 kernel
-// and a row quantiser; egeria_profile_attention_threshold lets tests run them on small shapes too.  The measure is the flops of
-// the two products as the fp64 kernel does them (heads padded to 64 dims), 29 us per 1e9 with whole tiles; the certified
-// kernels have 30 us of fixed cost.  Up to 64 tokens, one tile of that kernel, they do not pay at any batch (one layer, us,
-// fp64 / certified: 64 x 64 tokens of 768 149 / 164, 256 x 64 463 / 508; 64 x 80 202 / 192, 100 x 72 311 / 282); beyond 256
-// tokens a head's keys do not fit the LDS at once and they pay from twice the size (4 x 300 x 512 104 / 115, 2 x 384 x 1024
-// 127 / 139, 4 x 384 x 768 160 / 138); between, from 0.75e9: 12 x 128 x 768 115 / 113, 16 x 128 x 256 74 / 80, 24 x 128 x 384
-// (heads of 32) 113 / 100, 32 x 128 x 768 166 / 158, 24 x 197 x 768 241 / 191.  (Heads that are no multiple of 8 dims
-// have no certified kernels.)
-double g_attention_min_flops = 0.75e9;
-double attention_measure(const egeria_block_desc *d)
+// Which unobserved runs take the certified approximate attention (three launches) instead of the fp64 kernel and a row
+// quantiser.  kAttentionRule stands for the rule below; any other value set through egeria_profile_attention_threshold is a
+// number of flops (of the two products) from which they do, so that tests can run them on small shapes too.
+constexpr double kAttentionRule = 5.0e9;
+double g_attention_min_flops = kAttentionRule;
+// The measure is the work of the fp64 kernel in whole tiles (64 queries x 32 keys, heads padded to 64 dims, 29 us per 1e9
+// flops); heads of 32 dims and less cost the certified kernels half as much.  Up to 64 tokens, one tile of that kernel, they do
+// not pay at any batch; up to 256 from 1.75e9 on, and for every 256 tokens more (a listed value reads all keys of its head,
+// and the more there are the more values are listed) from twice as much; beyond 1024 fp64 is faster at any batch that was
+// tried.  One layer, us, fp64 / certified: 12 x 128 x 768 90 / 93, 32 x 128 x 768 (1.6e9) 127 / 127, 24 x 128 x 384 (heads of 32,
+// 2.4e9) 98 / 94, 64 x 80 x 768 (2.4e9) 150 / 141, 12 x 197 x 768 (2.1e9) 138 / 124, 24 x 197 x 768 193 / 161, 12 x 256 x 768 150 /
+// 128, 64 x 256 x 768 468 / 345; 8 x 300 x 768 (2.5e9) 134 / 149, 8 x 384 x 768 (3.6e9) 184 / 173, 4 x 512 x 768 (3.2e9) 163 / 167, 8 x
+// 512 x 768 (6.4e9) 226 / 203; 4 x 768 x 768 (7.2e9) 286 / 238; 4 x 1024 x 512 (8.6e9) 260 / 292, 8 x 1024 x 768 (26e9) 684 / 529;
+// 2 x 2048 x 512 443 / 634, 16 x 2048 x 768 4578 / 5002.
+bool attention_certified(int32_t batch, int32_t seq, int32_t hidden, int32_t heads)
 {
-    const double pairs = (double)d->batch * d->heads * (double)d->seq * d->seq;
-    return d->seq <= 64 ? 0.0 : (d->seq <= 256 ? 1.0 : 0.5) * 256.0 * pairs;
+    if (!attention_splits(hidden, heads)) return false;
+    const int32_t dh = hidden / heads;
+    const double b = (double)batch * heads, s = seq;
+    if (g_attention_min_flops != kAttentionRule) return 4.0 * b * s * s * dh >= g_attention_min_flops;
+    if (seq <= 64 || seq > 1024) return false;
+    const double work = 256.0 * b * (double)((seq + 63) / 64 * 64) * (double)((seq + 31) / 32 * 32);
+    return work * (64.0 / (dh > 32 ? dh : 32)) >= 1.75e9 * (double)(1 << ((seq - 1) / 256));
 }
 
 // One encoder layer: `cur` -> `out`.  slot 4l must already hold absmax(cur).
@@ -493,7 +502,7 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
         EG_HIP(launch_quantize_rows(cur, EGERIA_F32, M, Hd, hp, f.amax(s0), f.n_amax(s0), f.stride_amax(s0), nullptr, xq,
                                     f.scale(s0), nullptr, ws_flag(f.ws), f.st));
     EG_OK(f.copy_tap_q(s0, xq, (size_t)(M * hp), f.scale(s0)));
-    const bool certified = !f.taps && attention_splits(Hd, d->heads) && attention_measure(d) >= g_attention_min_flops;
+    const bool certified = !f.taps && attention_certified(d->batch, d->seq, Hd, d->heads);
     EG_OK(run_gemm(f, s0, xq, hp, M, 3 * Hd, hp, false, 0, 0, 0, f.scale(s0), 0, nullptr, nullptr, 0, qkv,
                    certified ? f.slot(6 * f.p.n_layers + l) : nullptr));
     if (!certified) {
@@ -1203,6 +1212,12 @@ double egeria_profile_attention_threshold(double min_flops)
     const double old = g_attention_min_flops;
     if (min_flops >= 0.0) g_attention_min_flops = min_flops;
     return old;
+}
+
+int32_t egeria_profile_attention_certified(int32_t B, int32_t S, int32_t hidden, int32_t heads)
+{
+    if (B < 1 || S < 1 || hidden < 1 || heads < 1 || hidden % heads != 0 || hidden / heads > 64) return 0;
+    return attention_certified(B, S, hidden, heads) ? 1 : 0;
 }
 
 egeria_status egeria_profile_gemm_tile(int64_t M, int32_t N, int64_t k_bytes, int32_t conv3x3, int32_t *rows, int32_t *cols,

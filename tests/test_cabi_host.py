@@ -207,3 +207,26 @@ def test_attention_bounds_refuse_short_buffers(eg):
     assert call(fake, 2, 70, 32, 2, fake, fake, 2 * 2 * 70 * 4, fake, ws - 1, None) == eg.ERR_WORKSPACE_TOO_SMALL
     assert call(fake, 2, 70, 32, 2, fake, None, 1 << 20, fake, ws, None) == eg.ERR_INVALID_ARG
     assert call(fake, 2, 70, 130, 2, fake, fake, 1 << 20, fake, ws, None) == eg.ERR_UNSUPPORTED
+
+
+def test_attention_threshold_is_in_flops_of_the_products(eg):
+    """4 * batch * heads * seq^2 * head size, as callers were told; the default stands for the library's own rule and can be
+    put back like any other value."""
+    old = eg.attention_threshold()
+    assert old == 5.0e9
+    rule = [(32, 128, 768, 12), (24, 197, 768, 12), (64, 256, 768, 12), (4, 64, 128, 2), (1000, 64, 768, 12), (64, 256, 744, 12)]
+    by_rule = [eg.attention_certified(*k) for k in rule]
+    assert by_rule == [False, True, True, False, False, False]
+    try:
+        for sizes in ((2, 70, 128, 4), (3, 131, 96, 12), (8, 300, 512, 8)):
+            b, s, hidden, heads = sizes
+            flops = 4.0 * b * s * s * hidden
+            assert eg.attention_threshold(flops) >= 0.0 and eg.attention_certified(*sizes)
+            eg.attention_threshold(flops + 1.0)
+            assert not eg.attention_certified(*sizes)
+        eg.attention_threshold(0.0)
+        assert eg.attention_certified(1, 1, 8, 1) and not eg.attention_certified(64, 256, 744, 12)
+        assert eg.attention_threshold(-1.0) == 0.0
+    finally:
+        eg.attention_threshold(old)
+    assert [eg.attention_certified(*k) for k in rule] == by_rule
