@@ -218,6 +218,53 @@ def test_conv_stages_at_edges(eg, orc, tile, stages, b, c, h, w, mode):
     test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode)
 
 
+# float16 layers choose among the same tiles (a K of half as many values has as many bytes): every one of them with rows and
+# columns that end inside, layer by layer against fp64 sums of the operands that the run itself recorded (products of float16
+# values are exact in fp32; sums of up to 2340 of them, 4e-6 of the largest output).  The observed and the unobserved run agree bit
+# for bit (asserted by the helper).
+def _check_float16(wl, eg, conv):
+    from test_float_ref import _gpu_float_forward
+    a_ref, taps, _ref, _ws = _gpu_float_forward(wl, "f16")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda().double()  # noqa: E731
+    for i, t in enumerate(taps):
+        x, w = dev(t["x"]), dev(wl.weights[i].astype(np.float16).astype(np.float32))
+        if conv:
+            b, c, h, wd = wl.x.shape
+            p = torch.nn.functional.pad(x.reshape(b, h, wd, c), (0, 0, 1, 1, 1, 1))
+            y = sum(p[:, kh:kh + h, kw:kw + wd].reshape(-1, c) @ w[:, :, kh, kw].t().contiguous() for kh in range(3) for kw in range(3))
+        else:
+            y = x @ w.t().contiguous()
+        y += dev(wl.biases[i])
+        if conv and i == 1:
+            y += dev(taps[0]["x"])                                # the skip connection
+        y = y.clamp_min(0.0).float().cpu().numpy()
+        tol = 4e-6 * np.abs(y).max()
+        assert np.abs(t["y"] - y).max() <= tol, i
+    assert np.abs(a_ref.reshape(y.shape) - y).max() <= tol
+
+
+@pytest.mark.parametrize("ragged", [0, 3])
+@pytest.mark.parametrize("tile,stages,M,N,K", [(t, None, M, N, K) for t, M, N, K in LINEAR_TILES] + LINEAR_STAGES)
+def test_float16_linear_tiles_at_edges(eg, tile, stages, M, N, K, ragged):
+    import synth_inputs as si
+    N, K = N + ragged, K // 2
+    k_bytes = eg.op_row_bytes(K, eg.REF_F16)
+    assert eg.gemm_tile(M, N, k_bytes) == tile and stages in (None, eg.gemm_stages(M, N, k_bytes))
+    wl = si.make_fc(b=M, k=K, n=N, seed=9)
+    wl.biases[0] = np.linspace(-1.0, 1.0, N).astype(np.float32)
+    _check_float16(wl, eg, False)
+
+
+@pytest.mark.parametrize("ragged", [0, 3])
+@pytest.mark.parametrize("tile,stages,b,c,h,w", [(t, None, *d) for t, *d in CONV_TILES] + CONV_STAGES)
+def test_float16_conv_tiles_at_edges(eg, tile, stages, b, c, h, w, ragged):
+    import synth_inputs as si
+    c -= ragged                                                   # (twice the bytes of K keep all of these tiles)
+    k_bytes = 9 * eg.op_row_bytes(c, eg.REF_F16)
+    assert eg.gemm_tile(b * h * w, c, k_bytes, True) == tile and stages in (None, eg.gemm_stages(b * h * w, c, k_bytes, True))
+    _check_float16(si.make_basic_block(b=b, c=c, h=h, w=w, seed=10), eg, True)
+
+
 # ... and for the layers of an encoder (no activation, with and without the maximum) at a ragged number of tokens.
 def test_encoder_tiles_at_edges(eg, orc):
     import gpu_common as gc
