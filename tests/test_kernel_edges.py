@@ -276,6 +276,26 @@ def test_encoder_tiles_at_edges(eg, orc):
     gc.assert_within_ulp(got, orc.ref_forward(wl)["a_ref"][0], 1, "encoder layer")
 
 
+# ... and the tiles of eight waves without an activation, in an encoder layer of 16 x 257 tokens (sums of up to 4096 products).
+def test_float16_encoder_tiles_at_edges(eg):
+    import synth_inputs as si
+    from test_float_ref import _gpu_float_forward
+    M, H = 16 * 257, 1024
+    assert [eg.gemm_tile(M, n, 2 * k) for n, k in ((3 * H, H), (H, H), (4 * H, H))] == [(256, 256, 128), (128, 64, 128), (256, 192, 128)]
+    wl = si.make_bert(b=16, s=257, hidden=H, heads=16, ffn=4 * H, seed=13, train_act_dtype="f32")
+    _a, taps, _ref, _ws = _gpu_float_forward(wl, "f16")          # (the unobserved run agrees bit for bit)
+    for i, t in enumerate(taps):
+        x, w = (torch.from_numpy(a).cuda().double() for a in (t["x"], wl.weights[i].astype(np.float16).astype(np.float32)))
+        y = x @ w.t().contiguous()
+        tol = 6e-6 * y.abs().max().item()
+        assert np.abs(t["acc"] - y.float().cpu().numpy()).max() <= tol, i
+        if wl.biases[i] is not None:
+            y += torch.from_numpy(wl.biases[i]).cuda().double()
+        if i == 2:
+            y = torch.nn.functional.gelu(y)
+        assert np.abs(t["y"] - y.float().cpu().numpy()).max() <= tol, i
+
+
 # GEMM epilogue of small modules: rows and columns that end inside, at and just past a tile or a group of four columns, with
 # and without a residual, for the dynamic, static, per-channel and affine paths.  The parity tests hold observed runs to the
 # oracle; here the observed run, which takes the general form of the epilogue, is the reference for the straight-line one.
