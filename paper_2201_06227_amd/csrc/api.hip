@@ -477,7 +477,8 @@ double g_attention_min_flops = kAttentionRule;
 // 2 x 2048 x 512 443 / 634, 16 x 2048 x 768 4578 / 5002.
 bool attention_certified(int32_t batch, int32_t seq, int32_t hidden, int32_t heads)
 {
-    if (!attention_splits(hidden, heads)) return false;
+    // (the certified kernels index the context's values in 32 bits)
+    if (!attention_splits(hidden, heads) || (int64_t)batch * seq * hidden >= (1LL << 32)) return false;
     const int32_t dh = hidden / heads;
     const double b = (double)batch * heads, s = seq;
     if (g_attention_min_flops != kAttentionRule) return 4.0 * b * s * s * dh >= g_attention_min_flops;

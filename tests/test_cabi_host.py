@@ -226,6 +226,8 @@ def test_attention_threshold_is_in_flops_of_the_products(eg):
             assert not eg.attention_certified(*sizes)
         eg.attention_threshold(0.0)
         assert eg.attention_certified(1, 1, 8, 1) and not eg.attention_certified(64, 256, 744, 12)
+        # contexts of 2^32 values and more have no certified kernels, at any threshold
+        assert eg.attention_certified(7281, 768, 768, 12) and not eg.attention_certified(7282, 768, 768, 12)
         assert eg.attention_threshold(-1.0) == 0.0
     finally:
         eg.attention_threshold(old)
