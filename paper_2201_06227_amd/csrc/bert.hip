@@ -627,14 +627,14 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
     }
 }
 
-// ---- kernel 1 on the float16 matrix cores, every product an exact fp32 product but for 2^-23 of it ----------
+// ---- kernel 1: the approximate attention on the float16 matrix cores, products of fp32 values to 22 bits ----------
 // The fp32 matrix instruction runs at 1/16 of the float16 one.  An fp32 value, scaled by a power of two, is the sum of
 // two float16 values (the value rounded to 11 bits, the remainder rounded to 11 bits: what is left is at most 2^-23 of
 // the value), so a product x * y is four float16 x float16 products, each exact in fp32; the three largest are issued
-// (v_mfma_f32_32x32x16_f16, fp32 accumulation), the fourth is at most 2^-24 of the product.  Three bfloat16 parts, which
+// (v_mfma_f32_32x32x16_f16, fp32 accumulation), the fourth is at most 2^-22 of the product.  Three bfloat16 parts, which
 // need no scale, take six products: 48 instead of 24 matrix instructions per tile, 5.5 instead of 2 vector instructions
-// per value split, and the kernel is bound by the sum of the two (64 x 256 tokens x 12 heads, without what follows for the
-// maximum: 88 us, now 64).
+// per value split, and the kernel is bound by the sum of the two (64 x 256 tokens x 12 heads, without the norms for the error bound and
+// what follows for the maximum: 88 us, with two float16 parts 64).
 //   The scale.  float16 reaches from 2^-24 to 2^16: with the largest magnitude scaled to 2^14 .. 2^15, values down to 2^-14
 // of it keep their full 22 bits and smaller ones are off by at most 2^-39 of the largest.  K and V are scaled by one power
 // of two for the tensor, from the maximum that the QKV GEMM's epilogue leaves behind; a query row by its own; P (at most

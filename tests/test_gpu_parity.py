@@ -660,8 +660,8 @@ def test_attention_bound_of_zero_queries_is_a_number(eg, gc, s, factor):
 
 # what the certified kernels meet beyond ordinary activations: rows that tie for the tensor's maximum (the candidates of a
 # workgroup overflow its list), nothing but zeros, whole samples twice, scores in the hundreds, values that the split's scale
-# leaves few digits of (every code is re-evaluated: the list of the quantiser overflows)
-ATTENTION_INPUTS = ["equal tokens", "zeros", "equal samples", "large scores", "uneven values"]
+# leaves few digits of (every code is re-evaluated: the list of the quantiser overflows), three tokens in uneven shares, padding
+ATTENTION_INPUTS = ["equal tokens", "zeros", "equal samples", "large scores", "uneven values", "few tokens", "padding"]
 
 
 @pytest.mark.parametrize("inputs", ATTENTION_INPUTS)
@@ -680,6 +680,10 @@ def test_attention_paths_agree_on_extreme_inputs(eg, gc, kw, inputs):
         x[1:] = x[:1]
     elif inputs == "large scores":
         wqkv[:2 * h] *= 12.0
+    elif inputs == "few tokens":
+        x = x[:, np.random.default_rng(5).choice(3, x.shape[1], p=[0.6, 0.3, 0.1])]
+    elif inputs == "padding":
+        x[:, x.shape[1] // 4:] = x[:, :1]
     else:
         per_channel = True                       # (one scale for all would round the small rows to zero)
         wqkv[2 * h:] *= np.float32(3.0e7)
