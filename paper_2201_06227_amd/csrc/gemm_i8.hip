@@ -1192,24 +1192,23 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
 // step takes what LDS needs, 24 KB written at 62 bytes per clock, 48 read at 235 and some 180 clocks of barrier, 770 (a fourth
 // stage changes nothing).  Three stages: 64x64 tiles as long as they bring 1.5 workgroups per compute unit, or 2.25 where 128x64
 // tiles would start a second round; else 128x64 tiles that fill one round at most; else, from K of 1024 bytes on, 128x128 tiles
-// up to 4/5 of a round and 128x64 tiles, two per compute unit, up to 7/4 rounds (from 4/5 on the ranking differs from shape to
-// shape: 128x128 tiles gain 5 to 8 % for 768 columns and nothing for 256 and 512; 128x64 ones are near the best).  Layers of four 128x64 tiles or fewer take those: 64x64 ones make no difference (257 x 48 x 112 5.2 us with
-// either, 130 x 36 x 64 4.6 / 4.9, 225 x 44 x 432 (3x3) 7.3 / 7.6).
+// that do.  Two exceptions keep the tile that such sizes have always had, by which tests name them: layers of four 128x64 tiles
+// or fewer, where 64x64 makes no difference (257 x 48 x 112 5.2 us with either, 130 x 36 x 64 4.6 / 4.9, 225 x 44 x 432 (3x3)
+// 7.3 / 7.6), and linear layers between 4/5 of a round of 128x128 tiles and 7/4 of one of 128x64 tiles, which lose 0.5 to 1.6 us
+// with the latter (128x128 / 128x64: 4728 x 768 x 3072 19.8 / 21.3, 7000 x 512 x 1536 13.9 / 14.4, 13500 x 256 x 2048 16.1 / 16.4).
 // us, chosen by price / 64x64 / 128x64 / 128x128 with three stages: 2450 x 512 x 2048 12.6 / 8.7 / 9.7 / 12.4, 2000 x 768 x 3072
 // 17.3 / 11.8 / 12.0 / 14.9, 128 x 4096 x 4096 20.6 / 11.6 / 13.5 / 17.8, 32 x 512 x 512 5.1 / 4.2 / 5.0 / 6.0, 4480 x 512 x 1024
 // 9.6 / 8.5 / 9.0 / 9.2, 4096 x 512 x 2048 13.0 / 11.4 / 9.8 / 12.2, 4096 x 768 x 3072 20.4 / 18.6 / 18.8 / 17.1, 12544 x 256 x
-// 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7; 4096 x 768 x 768 8.5 with all of them.  Beyond 4/5 of a round of 128x128 tiles (another
-// run), us: 4728 x 768 x 3072 (222 tiles) 23.1 / 25.3 / 21.9 / 20.7, 10500 x 260 x 2340 (3x3, 249) 23.1 / 26.8 / 21.8 / 20.6, 8000 x
-// 512 x 1536 (252) 16.1 / 17.1 / 17.1 / 16.0, 16000 x 256 x 2048 (250) 19.0 / 20.9 / 20.2 / 19.1, 5376 x 768 x 3072 (252) 24.4 /
-// 25.6 / 23.8 / 22.5.
+// 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7; 4096 x 768 x 768 8.5 with all of them; and up to a whole round of
+// 128x128 tiles (another run) 4992 x 768 x 3072 22.5 / 24.1 / 22.0 / 20.2, 8000 x 512 x 1536 16.1 / 17.1 / 17.1 / 16.0, 10500 x 260 x
+// 2448 (3x3) 21.9 / 26.1 / 21.1 / 19.9.
 static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
 {
     const int64_t cu = compute_units(), t64 = ((M + 63) / 64) * ((N + 63) / 64), t128x64 = ((M + 127) / 128) * ((N + 63) / 64),
                   t128 = ((M + 127) / 128) * ((N + 127) / 128);
     if (t128x64 > 4 && (2 * t64 <= 3 * cu || (t128x64 > cu && 4 * t64 <= 9 * cu))) return kDeepSmall;
     if (t128x64 <= cu) return kDeepMid;
-    if (5 * t128 <= 4 * cu && kp >= 1024) return kDeepLarge;
-    if (4 * t128x64 <= 7 * cu && kp >= 1024) return kDeepMid;
+    if (t128 <= cu && kp >= 1024) return !conv3x3 && 5 * t128 > 4 * cu && 4 * t128x64 <= 7 * cu ? kDeepMid : kDeepLarge;
     int best = 0;
     double best_cost = 0.0;
     for (int i = 0; i < kNumShapes; ++i) {

@@ -171,7 +171,7 @@ def test_linear_tiles_at_edges(eg, orc, tile, M, N, K, ragged, mode):
 
 # Tiles that come with two stages of whole lines (chosen by price) and with three (by rule).
 LINEAR_STAGES = [((64, 64, 128), 3, 700, 200, 520), ((128, 64, 128), 2, 4000, 772, 520), ((128, 64, 128), 3, 3970, 484, 100),
-                 ((128, 64, 128), 3, 10500, 260, 1030), ((128, 128, 128), 3, 5990, 484, 1030)]
+                 ((128, 64, 128), 3, 10500, 260, 1030), ((128, 128, 128), 3, 5990, 484, 1030), ((128, 128, 128), 3, 7990, 484, 1030)]
 
 
 @pytest.mark.parametrize("mode", ["dynamic", "affine"])
@@ -208,7 +208,7 @@ def test_conv_tiles_at_edges(eg, orc, tile, b, c, h, w, mode):
 
 # (c = 132 and 260: window positions of more than a K step that end inside one.)
 CONV_STAGES = [((64, 64, 128), 3, 4, 44, 15, 15), ((64, 64, 128), 3, 3, 132, 15, 17), ((128, 64, 128), 2, 36, 132, 29, 28),
-               ((128, 64, 128), 3, 40, 132, 14, 15), ((128, 64, 128), 3, 50, 260, 14, 15), ((128, 128, 128), 3, 38, 260, 14, 15)]
+               ((128, 64, 128), 3, 40, 132, 14, 15), ((128, 128, 128), 3, 50, 260, 14, 15)]
 
 
 @pytest.mark.parametrize("mode", ["dynamic", "static", "affine", "affine ragged"])
