@@ -1025,12 +1025,13 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     //   e, in units of 2^-24: the splits of V and P, P's own rounding and the exponential (kSplitErrBase); a rounding per tile
     // of the sums that are carried (kSplitErrPerTile); the roundings of the score's sum, which go with the score
     // (kSplitErrPerScore); the splits of Q and K, which go with the root of sum (q k)^2 over the head dims, at most the
-    // largest |q| times the largest norm of a key (kSplitErrPerNorm).  The constants are measured, with margin, not proved: of
-    // the kinds of input that bench.py --attention-error draws (normal, padded, two to sixteen distinct tokens, values of
-    // opposite sign, equal scores up to 300, terms that cancel in the scores; 8 to 64 dims, 65 to 4096 tokens) the worst error
-    // is 0.86 of the bound.  With the P taken to be independent of each other (root of sum P^2 alone) it was 12 times
-    // the bound for two tokens and 97 for cancelling terms.  The longer lists cost the quantiser 63 -> 82 us for 64 x 256 tokens x
-    // 12 heads, the norms this kernel 85 -> 88.
+    // largest |q| times the largest norm of a key (kSplitErrPerNorm).  The constants are measured, with margin, not proved:
+    // bench.py --attention-error sets the error against the bound for two dozen kinds of input (normal, padded, two to eight
+    // distinct tokens, values of opposite sign, equal scores up to 300, terms that cancel in the scores) at 8 to 64 dims and 131
+    // to 2048 tokens; the worst is 0.71 of it (0.86 over more seeds and 65 to 4096 tokens).  With the P taken to be independent
+    // of each other (root of sum P^2 alone) it was 12 times the bound for two tokens and 97 for cancelling terms.  The longer
+    // lists cost the quantiser 63 -> 82 us for 64 x 256 tokens x 12 heads (with the maximum settled in it), the norms this kernel
+    // 85 -> 88.
     const float M = __uint_as_float(mbits);
     const float sq = max_halves(smax) * c2 * 0.6931472f;         // largest |score| of the query
     auto of_all = [](const float *x) { return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])); };
