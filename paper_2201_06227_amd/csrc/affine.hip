@@ -34,10 +34,11 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
     }
     float hi = 0.0f, nlo = 0.0f;       // max(x, 0) and max(-x, 0)
     uint32_t worst = 0;                // largest |x| bit pattern: above 0x7f7fffff for NaN and infinities
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const uint32_t piece = xcd_piece(blockIdx.x, gridDim.x);
     if (!BF16 && ((uintptr_t)x & 15) == 0) {
         const float4 *x4 = (const float4 *)x;
-        const int64_t n4 = n >> 2;
+        const int64_t n4 = n >> 2, per = (int64_t)((uint64_t)(n4 + gridDim.x - 1) / gridDim.x), beg = (int64_t)piece * per;
+        const int64_t end = beg + per < n4 ? beg + per : n4;
         auto take = [&](const float4 &v) {
             const float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -48,21 +49,15 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
                 worst = worst > a ? worst : a;
             }
         };
-        if (n4 <= 4 * stride) {
-            // a tensor of at most four units per thread: all of them in flight (indices clamped: a value seen twice changes
-            // no extremum).  1 M values 3.4 us against 3.8 one by one.  Larger tensors read slower that way, a thread's four
-            // streams lying 4 MB apart: 5.2 M values 6.3 us against 5.9, 12.8 M 11.8 against 11.4, 50 M 40.4 against 38.
-            if (first < n4) {
-                float4 v[4];
+        // four units of a thread in flight (indices clamped: a value seen twice changes no extremum)
+        for (int64_t i = beg + threadIdx.x; i < end; i += 1024) {
+            float4 v[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = x4[first + j * stride < n4 ? first + j * stride : first];
+            for (int j = 0; j < 4; ++j) v[j] = x4[i + 256 * j < end ? i + 256 * j : end - 1];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) take(v[j]);
-            }
-        } else {
-            for (int64_t i = first; i < n4; i += stride) take(x4[i]);
+            for (int j = 0; j < 4; ++j) take(v[j]);
         }
-        for (int64_t i = (n4 << 2) + first; i < n; i += stride) {
+        for (int64_t i = piece == 0 ? (n4 << 2) + threadIdx.x : n; i < n; i += 256) {
             const float v = ((const float *)x)[i];
             hi = fmaxf(hi, v);
             nlo = fmaxf(nlo, -v);
@@ -70,6 +65,7 @@ __global__ __launch_bounds__(256) void minmax_kernel(const void *__restrict__ x,
             worst = worst > a ? worst : a;
         }
     } else {
+        const int64_t first = (int64_t)piece * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
         for (int64_t i = first; i < n; i += stride) {
             const float v = BF16 ? bf16_to_f32(((const uint16_t *)x)[i]) : ((const float *)x)[i];
             hi = fmaxf(hi, v);
@@ -111,7 +107,7 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
                                                               int64_t cp, const uint32_t *__restrict__ partials, int nb,
                                                               const uint32_t *__restrict__ relu_max, int store_offset, uint8_t *__restrict__ q,
                                                               float *__restrict__ scale_out, int32_t *__restrict__ zp_out,
-                                                              uint32_t *__restrict__ flag)
+                                                              uint32_t *__restrict__ flag, int64_t per)
 {
     uint32_t hb = 0, lb = 0;
     if (relu_max) {
@@ -158,12 +154,12 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
         code = code < 0 ? 0 : (code > 255 ? 255 : code);
         return (uint32_t)(code - store_offset) & 0xffu;
     };
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * per, first = beg + threadIdx.x, last = beg + per;
     const int64_t upr = cp >> 4;
     if constexpr (FORM == kRows) {
-        const int64_t total = n * upr;
+        const int64_t total = n * upr, end = last < total ? last : total;
         const bool narrow = total < (1LL << 32);
-        for (int64_t u = first; u < total; u += stride) {
+        for (int64_t u = first; u < end; u += 256) {
             const int64_t row = narrow ? (int64_t)((uint32_t)u / (uint32_t)upr) : u / upr, c0 = (u - row * upr) * 16;
             const float4 *src = (const float4 *)((const float *)x + row * c);
             float4 v[4];
@@ -177,9 +173,9 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
         }
         return;
     } else if constexpr (FORM == kPlanes) {
-        const int64_t pg = hw >> 2, total = n * upr * pg;   // groups of four pixels
+        const int64_t pg = hw >> 2, total = n * upr * pg, end = last < total ? last : total;   // groups of four pixels
         const bool narrow = total < (1LL << 32);
-        for (int64_t u = first; u < total; u += stride) {
+        for (int64_t u = first; u < end; u += 256) {
             const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)pg) : u / pg, p = (u - rest * pg) * 4;
             const int64_t img = narrow ? (int64_t)((uint32_t)rest / (uint32_t)upr) : rest / upr, ch0 = (rest - img * upr) * 16;
             const float *src = (const float *)x + (img * c + ch0) * hw + p;
@@ -200,11 +196,11 @@ __global__ __launch_bounds__(256) void quantize_affine_kernel(const void *__rest
         }
         return;
     }
-    const int64_t total = n * hw * upr;
+    const int64_t total = n * hw * upr, end = last < total ? last : total;
     const bool narrow = total < (1LL << 32);
-    for (int64_t u = first; u < total; u += stride) {
-        const int64_t per = hw == 1 ? upr : hw;
-        const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)per) : u / per, at = u - rest * per;
+    for (int64_t u = first; u < end; u += 256) {
+        const int64_t line = hw == 1 ? upr : hw;
+        const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)line) : u / line, at = u - rest * line;
         int64_t img, p, unit;
         if (hw == 1) {
             img = rest;
@@ -291,13 +287,11 @@ hipError_t launch_quantize_affine(const void *x, egeria_dtype dt, int64_t n, int
     // whole 16-byte units of fp32 take the wide forms; bf16, odd rows and planes, and other addresses the general one
     const bool wide = dt == EGERIA_F32 && ((uintptr_t)x & 15) == 0;
     const int form = wide && hw == 1 && (c & 3) == 0 ? kRows : (wide && hw > 1 && (hw & 3) == 0 ? kPlanes : kAny);
-    int64_t blocks = (n * hw * (cp >> 4) / (form == kPlanes ? 4 : 1) + 255) / 256;
-    if (blocks < 1) blocks = 1;                            // scale and zero point are still written
-    if (blocks > 8192) blocks = 8192;
-    const dim3 grid((unsigned)blocks), block(256);
+    const UnitShare sh = share_units(n * hw * (cp >> 4) / (form == kPlanes ? 4 : 1));   // (one workgroup at least: scale and zero point are still written)
+    const dim3 grid(sh.blocks), block(256);
     auto go = [&](auto kernel) {
         return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cp, partials, nb, relu_max, store_offset,
-                        (uint8_t *)q, scale_out, zp_out, flag);
+                        (uint8_t *)q, scale_out, zp_out, flag, sh.per);
     };
     if (dt == EGERIA_BF16) return go(quantize_affine_kernel<true, kAny>);
     if (form == kRows) return go(quantize_affine_kernel<false, kRows>);

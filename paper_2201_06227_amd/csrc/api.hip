@@ -1108,9 +1108,10 @@ egeria_status egeria_refresh_eval(const egeria_weight *w, int32_t n_w, void *ws_
                 units = qj.rows * (cp / 16) * (hw / 4);
             }
         }
-        int64_t blocks = (units + 255) / 256;
-        qj.nblk = (int32_t)(blocks > 8192 ? 8192 : blocks);
-        if (qj.nblk < 1) qj.kind = 0;
+        const UnitShare sh = share_units(units);
+        qj.nblk = (int32_t)sh.blocks;
+        qj.per = sh.per;
+        if (units < 1) qj.kind = 0;
     }
     bool carried = false, codes = false;
     EG_OK(quantize_weights_impl(w, n_w, ws_w, ws_w_bytes, stream, job.n > 0 ? &job : nullptr, &carried,

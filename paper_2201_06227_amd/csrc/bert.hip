@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
                                                         uint32_t *__restrict__ absmax_out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t row = (int64_t)xcd_piece(blockIdx.x, gridDim.x) * 4 + wave;
     uint32_t amax = 0;
     if (row < rows) {
         const float *xr = x + row * H;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
                                                             uint32_t *__restrict__ absmax_out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t row = (int64_t)xcd_piece(blockIdx.x, gridDim.x) * 4 + wave;
     const int nv = H >> 2;
     uint32_t amax = 0;
     if (row < rows) {
@@ -147,8 +147,7 @@ template <int QB>
 __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict__ qkv, int B, int S,
                                                         int Hd, int heads, int dh, double scale,
                                                         float *__restrict__ ctx,
-                                                        uint32_t *__restrict__ absmax_out, int total,
-                                                        int per_xcd)
+                                                        uint32_t *__restrict__ absmax_out)
 {
     __shared__ __attribute__((aligned(16))) float sKb[2][kKeyTile][kKVPad];   // two stages
     __shared__ __attribute__((aligned(16))) float sVb[2][kKeyTile][kKVPad];
@@ -156,11 +155,9 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
     const int c = lane & 15, g = lane >> 4;
     constexpr int QT = 64 * QB;          // queries per workgroup
     const int qtiles = (S + QT - 1) / QT;
-    // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD is given a
-    // contiguous range of (batch, head, query tile) so that the query tiles of
+    // Each XCD is given a contiguous range of (batch, head, query tile), so that the query tiles of
     // one head, which re-read the same K and V, share an L2.
-    const int vid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || vid >= total) return;
+    const int vid = (int)xcd_piece(blockIdx.x, gridDim.x);
     const int bh = vid / qtiles, qt = vid % qtiles;
     const int bi = bh / heads, hd = bh % heads;
     const int64_t tok0 = (int64_t)bi * S;
@@ -393,7 +390,7 @@ struct AttnRecord {
 
 __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__restrict__ qkv, int B, int S, int Hd,
                                                              int heads, int dh, float scale, float *__restrict__ ctx,
-                                                             AttnRecord *__restrict__ rec, int total, int per_xcd)
+                                                             AttnRecord *__restrict__ rec)
 {
     __shared__ __attribute__((aligned(16))) float sKb[2][kKeyTile][kKVPad];
     __shared__ __attribute__((aligned(16))) float sVb[2][kKeyTile][kKVPad];
@@ -401,8 +398,7 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
     const int c = lane & 15, g = lane >> 4;
     constexpr int QT = 64;
     const int qtiles = (S + QT - 1) / QT;
-    const int vid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || vid >= total) return;
+    const int vid = (int)xcd_piece(blockIdx.x, gridDim.x);
     const int bh = vid / qtiles, qt = vid % qtiles;
     const int bi = bh / heads, hd = bh % heads;
     const int64_t tok0 = (int64_t)bi * S;
@@ -736,7 +732,6 @@ __device__ __forceinline__ float max_halves(float x) { return pair_op<32>(x, [](
 __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__restrict__ qkv, int B, int S, int Hd,
                                                                  int heads, int dh, float scale, float *__restrict__ ctx,
                                                                  float *__restrict__ err_q, AttnCand *__restrict__ cands,
-                                                                 int total, int per_xcd,
                                                                  const uint32_t *__restrict__ max_slot,
                                                                  uint32_t *__restrict__ bound_slot,
                                                                  uint32_t *__restrict__ exact_slot)
@@ -745,8 +740,7 @@ __global__ __launch_bounds__(256, 2) void attention_split_kernel(const float *__
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, h = lane >> 5;
     const int qblocks = (S + kSplitQ - 1) / kSplitQ;
-    const int vid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || vid >= total) return;
+    const int vid = (int)xcd_piece(blockIdx.x, gridDim.x);
     const int bh = vid / qblocks, qb = vid % qblocks;
     const int bi = bh / heads, hd = bh % heads;
     const int64_t tok0 = (int64_t)bi * S;
@@ -1291,7 +1285,7 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
     __shared__ __attribute__((aligned(16))) float ks[kKeysLds * kKeyRow];
     __shared__ __attribute__((aligned(16))) float qs[NW * kDh];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t bh = blockIdx.x / (uint32_t)splits, share = blockIdx.x - bh * (uint32_t)splits;
+    const uint32_t piece = xcd_piece(blockIdx.x, gridDim.x), bh = piece / (uint32_t)splits, share = piece - bh * (uint32_t)splits;
     const uint32_t bi = bh / (uint32_t)heads, hd = bh - bi * (uint32_t)heads;
     const uint32_t tok0 = bi * (uint32_t)S;
     const int64_t ld = 3 * (int64_t)Hd;
@@ -1517,10 +1511,9 @@ static hipError_t launch_attention_approx(const float *qkv, int32_t B, int32_t S
 {
     const int dh = Hd / heads;
     const int64_t grid = (int64_t)B * heads * ((S + kSplitQ - 1) / kSplitQ);
-    const int per_xcd = (int)((grid + 7) / 8);
-    return launch_k(EGERIA_KERNEL_ATTENTION, attention_split_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
+    return launch_k(EGERIA_KERNEL_ATTENTION, attention_split_kernel, dim3((unsigned)grid), dim3(256), 0, st,
                     qkv, (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx, err_q, cands,
-                    (int)grid, per_xcd, max_slot, bound_slot, exact_slot);
+                    max_slot, bound_slot, exact_slot);
 }
 
 // The largest |value| of a tensor into the words of a maximum slot, a workgroup per word (runs have it from the GEMM's epilogue).
@@ -1565,10 +1558,9 @@ hipError_t launch_attention_fp32(const float *qkv, int32_t B, int32_t S, int32_t
     if (grid <= 0) return hipSuccess;
     if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
     if (!attn_aligned16(qkv) || !attn_aligned16(ctx) || !attn_aligned16(records)) return hipErrorInvalidValue;
-    const int per_xcd = (int)((grid + 7) / 8);
-    return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
+    return launch_k(EGERIA_KERNEL_ATTENTION, attention_fast_kernel, dim3((unsigned)grid), dim3(256), 0, st, qkv,
                     (int)B, (int)S, (int)Hd, (int)heads, dh, (float)(1.0 / sqrt((double)dh)), ctx,
-                    (AttnRecord *)records, (int)grid, per_xcd);
+                    (AttnRecord *)records);
 }
 
 hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads, float *ctx,
@@ -1619,9 +1611,8 @@ hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, 
     const int64_t grid = (int64_t)B * heads * qtiles;
     if (grid <= 0) return hipSuccess;
     if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
-    const int per_xcd = (int)((grid + 7) / 8);
-    return launch_k(EGERIA_KERNEL_ATTENTION, attention_kernel<QB>, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st, qkv,
-                    (int)B, (int)S, (int)Hd, (int)heads, dh, 1.0 / sqrt((double)dh), ctx, absmax_out, (int)grid, per_xcd);
+    return launch_k(EGERIA_KERNEL_ATTENTION, attention_kernel<QB>, dim3((unsigned)grid), dim3(256), 0, st, qkv,
+                    (int)B, (int)S, (int)Hd, (int)heads, dh, 1.0 / sqrt((double)dh), ctx, absmax_out);
 }
 
 }  // namespace egeria

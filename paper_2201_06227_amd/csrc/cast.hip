@@ -38,16 +38,17 @@ enum CastForm { kAny = 0, kRows = 1, kPlanes = 2 };
 template <bool SRC_BF16, int ET, int FORM>
 __global__ __launch_bounds__(256) void cast_chlast_kernel(const void *__restrict__ x, int64_t n, int64_t c,
                                                           int64_t hw, int64_t cpe, uint8_t *__restrict__ out,
-                                                          float *__restrict__ one)
+                                                          float *__restrict__ one, int64_t share)
 {
     constexpr int EPU = ET == 1 ? 8 : 4;                  // elements per 16-byte unit
     if (one && blockIdx.x == 0 && threadIdx.x == 0) *one = 1.0f;
     const int64_t upr = cpe / EPU;                        // units per pixel
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * share;
     const int64_t per = hw == 1 ? upr : (FORM == kPlanes ? hw >> 2 : hw);
     const int64_t total = n * upr * (hw == 1 ? 1 : per);
+    const int64_t end = beg + share < total ? beg + share : total;
     const bool narrow = total < (1LL << 32);
-    for (int64_t u = first; u < total; u += stride) {
+    for (int64_t u = beg + threadIdx.x; u < end; u += 256) {
         const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)per) : u / per, at = u - rest * per;
         int64_t img = rest, unit = at, p = 0;
         if (hw != 1) {
@@ -108,11 +109,9 @@ hipError_t launch_cast_chlast(const void *x, egeria_dtype dt, int64_t n, int64_t
     const bool wide = dt != EGERIA_BF16 && ((uintptr_t)x & 15) == 0;
     const int form = wide && hw == 1 && (c & 3) == 0 ? kRows : (wide && hw > 1 && (hw & 3) == 0 ? kPlanes : kAny);
     const int64_t total = n * hw * (cpe / (et == 1 ? 8 : 4)) / (form == kPlanes ? 4 : 1);
-    int64_t blocks = (total + 255) / 256;
-    if (blocks < 1) blocks = 1;                            // the 1.0f is still written
-    if (blocks > 8192) blocks = 8192;
-    const dim3 grid((unsigned)blocks), block(256);
-    auto go = [&](auto kernel) { return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cpe, (uint8_t *)out, one); };
+    const UnitShare sh = share_units(total);               // (one workgroup at least: the 1.0f is still written)
+    const dim3 grid(sh.blocks), block(256);
+    auto go = [&](auto kernel) { return launch_k(EGERIA_KERNEL_QUANTIZE, kernel, grid, block, 0, st, x, n, c, hw, cpe, (uint8_t *)out, one, sh.per); };
     if (dt == EGERIA_BF16) return et == 1 ? go(cast_chlast_kernel<true, 1, kAny>) : go(cast_chlast_kernel<true, 2, kAny>);
     if (form == kRows) return et == 1 ? go(cast_chlast_kernel<false, 1, kRows>) : go(cast_chlast_kernel<false, 2, kRows>);
     if (form == kPlanes) return et == 1 ? go(cast_chlast_kernel<false, 1, kPlanes>) : go(cast_chlast_kernel<false, 2, kPlanes>);

@@ -78,6 +78,19 @@ struct ProfileState {
 };
 extern ProfileState g_profile;
 
+// How `units` independent pieces of work are dealt to workgroups of 256 threads: workgroup p (see xcd_piece) takes the
+// `per` units from p * per on, one for each thread where `most` workgroups are enough for that.
+struct UnitShare {
+    unsigned blocks;
+    int64_t per;
+};
+inline UnitShare share_units(int64_t units, int64_t most = 16384)
+{
+    const int64_t per = (units + most * 256 - 1) / (most * 256) * 256;
+    if (units <= 0) return {1u, 256};
+    return {(unsigned)((units + per - 1) / per), per};
+}
+
 // Every kernel of the library is launched through here.  When timing of class
 // `cls` is armed, the launch carries a start/stop event pair that receives the
 // dispatch's own begin and end timestamps.
@@ -190,6 +203,7 @@ struct InputQuantJob {
     float *scale_out;
     uint32_t *flag;
     int32_t nblk;
+    int64_t per;            // units per workgroup (share_units)
 };
 // one_launch: every job has nblk == 1.  partials: total_blocks words.  extra, xq: nullable; xq is
 // taken only together with extra and only by a two-launch snapshot.
@@ -347,6 +361,18 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
 #ifdef __HIPCC__
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
+
+// Which of the launch's n pieces workgroup blk takes.  Workgroup ids go round the 8 XCDs, and each XCD has an L2 of its own
+// that keeps its contents from one kernel to the next.  So every kernel of a chain deals its work in order of memory, a
+// contiguous eighth to each XCD: much of what an XCD reads it has written, or read, itself a launch ago.  Pieces dealt round
+// the XCDs / this way, us: codes of the rows of a 16384 x 768 layer output 17.2 / 15.2, second pass over a snapshot and 64 x
+// 1024 x 14 x 14 images 15.4 / 13.5; bottleneck step of those images 132.3 / 128.5, affine forward of 110 x 512 x 14 x 14 72.8 /
+// 67.6, two encoder layers of 10 x 128 x 256 151 / 143.  (Alone in a loop, 4096 x 768 read back and mapped to codes 6.9 / 2.4.)
+__device__ __forceinline__ uint32_t xcd_piece(uint32_t blk, uint32_t n)
+{
+    const uint32_t x = blk & 7u, rest = n & 7u;
+    return x * (n >> 3) + (x < rest ? x : rest) + (blk >> 3);
+}
 
 // Between LDS writes of a wave and reads of what its other lanes have written (or the other way round): the wave's LDS
 // traffic is in order, so nothing is awaited; the compiler, which reasons about one lane, must not move either across.

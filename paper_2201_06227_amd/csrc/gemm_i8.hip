@@ -97,8 +97,7 @@ constexpr int resident_target(int bm, int bn)
 }
 
 template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, bool LNF = false, int NST = stages_for(BK)>
-__global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g, int tiles,
-                                                                               int tiles_per_xcd)
+__global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g)
 {
     typedef typename AccOf<ET>::type acc_t;
     typedef typename ResOf<ET>::type res_t;
@@ -119,10 +118,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     static_assert((NST - 2) * NLD < 64, "outstanding loads must fit the wait counter");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [NST][BM + BN][BK]
 
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int tile = xcd * tiles_per_xcd + local;
-    if (local >= tiles_per_xcd || tile >= tiles) return;
-
+    const int tile = (int)xcd_piece(blockIdx.x, gridDim.x);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int wm = wave / WN, wn = wave % WN;
@@ -748,8 +744,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
     if (tiles <= 0) return hipSuccess;
     if (tiles > 0x3fffffffLL) return hipErrorInvalidValue;
-    const int tpx = (int)((tiles + 7) / 8);
-    const dim3 grid((unsigned)(tpx * 8)), block(64 * WM * WN);
+    const dim3 grid((unsigned)tiles), block(64 * WM * WN);
     constexpr size_t stages = (size_t)NST * (BM + BN) * BK;
     // affine codes: weight-code sums and row classes behind the epilogue's block
     constexpr size_t affine = ((size_t)WM * 32 * (BN + 8 * WN) + 16 * BN) * 4 + BM, largest = stages > affine ? stages : affine;
@@ -768,8 +763,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
                 if (e != hipSuccess) return e;
                 set[dev] = true;
             }
-            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>, grid, block, smem, st, g,
-                            (int)tiles, tpx);
+            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>, grid, block, smem, st, g);
         }
     }
     static bool set[kMaxDevices] = {};
@@ -781,7 +775,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     }
     // (instrumentation: the launch that also normalises its rows is timed with the layer norms, whose bytes bound it)
     return launch_k(LNF ? EGERIA_KERNEL_LAYERNORM : EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF, NST>,
-                    grid, block, smem, st, g, (int)tiles, tpx);
+                    grid, block, smem, st, g);
 }
 
 // ---- 3x3 convolution with at most 16 input channels and at most 32 outputs ----------------
@@ -795,7 +789,8 @@ __global__ __launch_bounds__(256) void conv3x3_c16_kernel(const GemmArgs g)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int p = lane & 31, h = lane >> 5;
-    const int64_t m = ((int64_t)blockIdx.x * 4 + wave) * 32 + p;
+    const uint32_t blk = xcd_piece(blockIdx.x, gridDim.x);
+    const int64_t m = ((int64_t)blk * 4 + wave) * 32 + p;
     const bool m_ok = m < g.M;
     // the operand's extent is below 2^31 bytes, so pixel indices fit 32 bits (64-bit division is slow)
     const uint32_t mrow = (uint32_t)m / (uint32_t)g.W;
@@ -808,7 +803,7 @@ __global__ __launch_bounds__(256) void conv3x3_c16_kernel(const GemmArgs g)
     const bool res16 = g.res_q != nullptr && g.res_ld == 16;
     v4i resv = {0, 0, 0, 0};
     if (res16 && threadIdx.x < 128) {
-        const int64_t pix = (int64_t)blockIdx.x * 128 + threadIdx.x;
+        const int64_t pix = (int64_t)blk * 128 + threadIdx.x;
         if (pix < g.M) resv = *(const v4i *)(g.res_q + pix * 16);
     }
     v4i fa[5], fb[5];
@@ -830,7 +825,7 @@ __global__ __launch_bounds__(256) void conv3x3_c16_kernel(const GemmArgs g)
     const int col = p;
     const bool col_ok = col < g.N;
     const float bc = (g.bias && col_ok) ? g.bias[col] : 0.0f;
-    const int64_t mw = ((int64_t)blockIdx.x * 4 + wave) * 32;
+    const int64_t mw = ((int64_t)blk * 4 + wave) * 32;
     const float q_inv = g.q_out ? (float)(1.0 / (double)*g.q_scale) : 0.0f;
     if (res16) {
         if (threadIdx.x < 128) *(v4i *)&sres[threadIdx.x * 16] = resv;
@@ -961,7 +956,7 @@ __global__ __launch_bounds__(256) void conv3x3_c16_fused_kernel(const GemmArgs g
     float *sbias = (float *)(sdyn + 128 * 16), *ssw = sbias + 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int p = lane & 31, h = lane >> 5;
-    const int m0 = blockIdx.x * 128, M = (int)g.M;
+    const int m0 = (int)xcd_piece(blockIdx.x, gridDim.x) * 128, M = (int)g.M;
     const uint32_t hw = (uint32_t)g.H * (uint32_t)g.W;
     const int halo = g.W + 1, npix = 128 + 2 * halo;
     const int xes = XBF16 ? 2 : 4;

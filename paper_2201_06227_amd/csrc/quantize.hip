@@ -15,9 +15,10 @@ __device__ __forceinline__ uint32_t max4_bits(float4 v)
     return a > c ? a : c;
 }
 
-// Each workgroup writes the maximum of its grid-stride share to partials[blockIdx.x]
+// Each workgroup writes the maximum of its share, a contiguous piece of the tensor, to partials[blk]
 // (bit pattern of |x|, so NaN and Inf order above every finite value).
-// (workgroup blk of nblks; a device function so that other kernels can carry the pass along).
+// (workgroup blk of nblks; a device function so that other kernels can carry the pass along.  Workgroup 0's id is a multiple
+// of 8.)
 template <bool BF16>
 __device__ __forceinline__ void absmax_share(const void *__restrict__ xv, int64_t n, uint32_t *__restrict__ partials,
                                              uint32_t *__restrict__ reset, int n_reset, int blk, int nblks)
@@ -29,46 +30,45 @@ __device__ __forceinline__ void absmax_share(const void *__restrict__ xv, int64_
         // counter of re-evaluated attention values starts every chain at zero as well
         if (n_reset > 0 && threadIdx.x == 0) reset[kUnsureWord - kHeaderFixedWords] = 0u;
     }
-    const int64_t tid = (int64_t)blk * blockDim.x + threadIdx.x;
-    const int64_t nthreads = (int64_t)nblks * blockDim.x;
+    const uint32_t piece = xcd_piece((uint32_t)blk, (uint32_t)nblks);
     uint32_t m = 0;
+    // 16-byte units of the piece, four of a thread's in flight (the last index repeated: a value seen twice changes nothing)
+    auto units = [&](int64_t nu, auto unit_max) {
+        const int64_t per = (int64_t)((uint64_t)(nu + nblks - 1) / (uint32_t)nblks), beg = (int64_t)piece * per;
+        const int64_t end = beg + per < nu ? beg + per : nu;
+        for (int64_t i = beg + threadIdx.x; i < end; i += 1024) {
+            uint4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = ((const uint4 *)xv)[i + 256 * k < end ? i + 256 * k : end - 1];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t a = unit_max(v[k]);
+                m = m > a ? m : a;
+            }
+        }
+    };
     if (!BF16) {
-        const float *x = (const float *)xv;
-        const int64_t n4 = n >> 2;
-        const float4 *x4 = (const float4 *)x;
-        int64_t i = tid;
-        for (; i + 3 * nthreads < n4; i += 4 * nthreads) {           // four independent loads in flight
-            const float4 v0 = x4[i], v1 = x4[i + nthreads], v2 = x4[i + 2 * nthreads], v3 = x4[i + 3 * nthreads];
-            uint32_t a = max4_bits(v0), b = max4_bits(v1), c = max4_bits(v2), d = max4_bits(v3);
-            a = a > b ? a : b;
-            c = c > d ? c : d;
-            a = a > c ? a : c;
-            m = m > a ? m : a;
-        }
-        for (; i < n4; i += nthreads) {
-            const uint32_t a = max4_bits(x4[i]);
-            m = m > a ? m : a;
-        }
-        for (int64_t k = (n4 << 2) + tid; k < n; k += nthreads) {
-            const uint32_t a = abs_bits(x[k]);
-            m = m > a ? m : a;
-        }
+        units(n >> 2, [&](const uint4 &v) {
+            return max4_bits(make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)));
+        });
     } else {
-        const uint16_t *x = (const uint16_t *)xv;
-        const int64_t n8 = n >> 3;
-        const uint4 *x8 = (const uint4 *)x;
-        for (int64_t i = tid; i < n8; i += nthreads) {
-            uint4 v = x8[i];
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        units(n >> 3, [&](const uint4 &v) {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            uint32_t r = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 uint32_t lo = (w[j] << 16) & 0x7fffffffu, hi = w[j] & 0x7fff0000u;
                 lo = lo > hi ? lo : hi;
-                m = m > lo ? m : lo;
+                r = r > lo ? r : lo;
             }
-        }
-        for (int64_t i = (n8 << 3) + tid; i < n; i += nthreads) {
-            uint32_t a = ((uint32_t)x[i] << 16) & 0x7fffffffu;
+            return r;
+        });
+    }
+    // the values after the last whole unit
+    if (piece == 0) {
+        const int64_t k = (BF16 ? n >> 3 << 3 : n >> 2 << 2) + threadIdx.x;
+        if (k < n) {
+            const uint32_t a = BF16 ? ((uint32_t)((const uint16_t *)xv)[k] << 16) & 0x7fffffffu : abs_bits(((const float *)xv)[k]);
             m = m > a ? m : a;
         }
     }
@@ -117,13 +117,13 @@ __device__ __forceinline__ float load_elem(const void *x, int64_t i)
 }
 
 // The map to codes of a [rows, cols] matrix: unit u = 16 consecutive codes of one row (one
-// 16-byte store); this thread takes units first, first + stride, ...
+// 16-byte store); this thread takes units first, first + stride, ... below `end` (at most rows * ldq / 16)
 template <bool BF16>
 __device__ __forceinline__ void quantize_row_units(const void *__restrict__ x, int64_t rows, int64_t cols, int64_t ldq,
-                                                   float inv, int8_t *__restrict__ q, int64_t first, int64_t stride)
+                                                   float inv, int8_t *__restrict__ q, int64_t first, int64_t end, int64_t stride)
 {
     const int64_t upr = (ldq + 15) >> 4;                     // 16-byte units per row
-    const int64_t units = rows * upr;
+    const int64_t units = end < rows * upr ? end : rows * upr;
     const bool narrow = units < (1LL << 32);
     const bool vec_ok = BF16 ? ((cols & 7) == 0) : ((cols & 3) == 0);
     int64_t u = first;
@@ -201,14 +201,41 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
     const uint32_t *__restrict__ slot, int n_slot, int slot_stride,
     const float *__restrict__ fixed_scale,
     int8_t *__restrict__ q, float *__restrict__ scale_out, float *__restrict__ scale_out2,
-    uint32_t *__restrict__ flag)
+    uint32_t *__restrict__ flag, int64_t per, bool flat)
 {
     float scale;
     bool bad;
+    const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * per;
+    if (!BF16 && flat) {
+        // fp32 rows without padding, whole units: one contiguous run.  A thread takes four 16-byte loads 256 units of four
+        // values apart, so that every load and store of a wave is contiguous; the first ones go out before the scale
+        // is waited for.
+        const int64_t n4 = rows * (cols >> 2), end = (beg + per) * 4 < n4 ? (beg + per) * 4 : n4;
+        const float4 *x4 = (const float4 *)x;
+        float4 v[4];
+        auto request = [&](int64_t i) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = x4[i + 256 * k < end ? i + 256 * k : end - 1];
+        };
+        int64_t i = beg * 4 + threadIdx.x;
+        request(i);
+        const float inv = scales_from(slot, n_slot, slot_stride, fixed_scale, &scale, &bad);
+        if (blockIdx.x == 0 && threadIdx.x == 0) publish(scale, bad, scale_out, scale_out2, flag);
+        for (;;) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i + 256 * k < end)
+                    ((uint32_t *)q)[i + 256 * k] = quant1(v[k].x, inv) | (quant1(v[k].y, inv) << 8) | (quant1(v[k].z, inv) << 16) |
+                                                   (quant1(v[k].w, inv) << 24);
+            i += 1024;
+            if (i - threadIdx.x >= end) break;
+            request(i);
+        }
+        return;
+    }
     const float inv = scales_from(slot, n_slot, slot_stride, fixed_scale, &scale, &bad);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(scale, bad, scale_out, scale_out2, flag);
-    quantize_row_units<BF16>(x, rows, cols, ldq, inv, q, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
-                             (int64_t)gridDim.x * blockDim.x);
+    quantize_row_units<BF16>(x, rows, cols, ldq, inv, q, beg + threadIdx.x, beg + per, 256);
 }
 
 hipError_t launch_quantize_rows(const void *x, egeria_dtype dt, int64_t rows, int64_t cols,
@@ -217,16 +244,14 @@ hipError_t launch_quantize_rows(const void *x, egeria_dtype dt, int64_t rows, in
                                 int8_t *q, float *scale_out, float *scale_out2, uint32_t *flag,
                                 hipStream_t st)
 {
-    const int64_t units = rows * ((ldq + 15) / 16);
-    int64_t blocks = (units + 255) / 256;
-    if (blocks < 1) blocks = 1;
-    if (blocks > 8192) blocks = 8192;
-    const dim3 grid((unsigned)blocks), block(256);
+    const UnitShare sh = share_units(rows * ((ldq + 15) / 16));
+    const dim3 grid(sh.blocks), block(256);
+    const bool flat = rows > 0 && cols > 0 && cols == ldq && (cols & 15) == 0 && (((uintptr_t)x | (uintptr_t)q) & 15) == 0;
     if (dt == EGERIA_F32)
         return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_rows_kernel<false>, grid, block, 0, st, x, rows, cols, ldq,
-                        slot, n_slot, slot_stride, fixed_scale, q, scale_out, scale_out2, flag);
+                        slot, n_slot, slot_stride, fixed_scale, q, scale_out, scale_out2, flag, sh.per, flat);
     return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_rows_kernel<true>, grid, block, 0, st, x, rows, cols, ldq, slot,
-                    n_slot, slot_stride, fixed_scale, q, scale_out, scale_out2, flag);
+                    n_slot, slot_stride, fixed_scale, q, scale_out, scale_out2, flag, sh.per, false);
 }
 
 // ---- quantise [n, c, hw] -> int8 [n, hw, cp] -------------------------------------------
@@ -270,13 +295,13 @@ __global__ __launch_bounds__(256) void quantize_nchw_kernel(
 // multiple of 4: a thread owns 4 consecutive pixels x 16 channels (sixteen
 // 16-byte loads, lanes along the pixel axis, all in flight together) and
 // writes four 16-byte channel groups.
-// (this thread takes units first, first + stride, ...)
+// (this thread takes units first, first + stride, ... below `end`, at most n * cp / 16 * hw / 4)
 __device__ __forceinline__ void quantize_nchw_vec_units(const float *__restrict__ x, int64_t n, int64_t c, int64_t hw,
                                                         int64_t cp, float inv, int8_t *__restrict__ q, int64_t first,
-                                                        int64_t stride)
+                                                        int64_t end, int64_t stride)
 {
     const int64_t pq = hw >> 2, cg = cp >> 4;
-    const int64_t units = n * cg * pq;
+    const int64_t units = end < n * cg * pq ? end : n * cg * pq;
     const bool narrow = units < (1LL << 32);
     for (int64_t u = first; u < units; u += stride) {
         const int64_t ig = div_u(u, pq, narrow);
@@ -313,14 +338,14 @@ __global__ __launch_bounds__(256) void quantize_nchw_vec_kernel(
     const uint32_t *__restrict__ slot, int n_slot, int slot_stride,
     const float *__restrict__ fixed_scale,
     int8_t *__restrict__ q, float *__restrict__ scale_out, float *__restrict__ scale_out2,
-    uint32_t *__restrict__ flag)
+    uint32_t *__restrict__ flag, int64_t per)
 {
     float scale;
     bool bad;
     const float inv = scales_from(slot, n_slot, slot_stride, fixed_scale, &scale, &bad);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(scale, bad, scale_out, scale_out2, flag);
-    quantize_nchw_vec_units(x, n, c, hw, cp, inv, q, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
-                            (int64_t)gridDim.x * blockDim.x);
+    const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * per;
+    quantize_nchw_vec_units(x, n, c, hw, cp, inv, q, beg + threadIdx.x, beg + per, 256);
 }
 
 hipError_t launch_quantize_nchw(const void *x, egeria_dtype dt, int64_t n, int64_t c, int64_t hw,
@@ -331,12 +356,10 @@ hipError_t launch_quantize_nchw(const void *x, egeria_dtype dt, int64_t n, int64
 {
     const dim3 grid((unsigned)((hw + 63) / 64), (unsigned)((cp + 63) / 64), (unsigned)n), block(256);
     if (dt == EGERIA_F32 && (hw & 3) == 0 && hw >= 4 && n > 0 && c > 0) {
-        const int64_t units = n * (cp >> 4) * (hw >> 2);
-        int64_t blocks = (units + 255) / 256;
-        if (blocks > 16384) blocks = 16384;
-        return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_nchw_vec_kernel, dim3((unsigned)blocks), block, 0, st,
+        const UnitShare sh = share_units(n * (cp >> 4) * (hw >> 2));
+        return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_nchw_vec_kernel, dim3(sh.blocks), block, 0, st,
                         (const float *)x, n, c, hw, cp, slot, n_slot, slot_stride, fixed_scale, q, scale_out, scale_out2,
-                        flag);
+                        flag, sh.per);
     }
     if (dt == EGERIA_F32)
         return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_nchw_kernel<false>, grid, block, 0, st, x, n, c, hw, cp, slot,
@@ -394,7 +417,7 @@ __device__ __forceinline__ void quantize_small_body(const void *__restrict__ x, 
     const float inv = scales_from(sm, 4, 1, nullptr, &scale, &bad);
     if (threadIdx.x == 0) publish(scale, bad, scale_out, nullptr, flag);
     if (hw == 1) {                                   // rows of a matrix: 16 codes per thread and store
-        quantize_row_units<BF16>(x, nimg, c, cp, inv, q, threadIdx.x, 256);
+        quantize_row_units<BF16>(x, nimg, c, cp, inv, q, threadIdx.x, (int64_t)nimg * ((cp + 15) >> 4), 256);
         return;
     }
     const int nout = nimg * hw * cp;
@@ -634,17 +657,19 @@ __global__ __launch_bounds__(256) void quantize_weights_kernel(const WeightBatch
                                                                const InputMaxJob extra, const InputQuantJob xq)
 {
     if ((int)blockIdx.x >= total_blocks) {
-        const int blk = (int)blockIdx.x - total_blocks;
+        // (the others start at an id that is a multiple of 8: pieces are dealt by XCD)
+        const int blk = (int)blockIdx.x - (total_blocks + 7) / 8 * 8;
+        if (blk < 0) return;
         if (PHASE == 2 && xq.kind != 0) {
             // second launch: the codes of the mini-batch whose maxima the first launch took
             float scale;
             bool bad;
             const float inv = scales_from(xq.slot, xq.n_slot, 1, nullptr, &scale, &bad);
             if (blk == 0 && threadIdx.x == 0) publish(scale, bad, xq.scale_out, nullptr, xq.flag);
-            const int64_t first = (int64_t)blk * 256 + threadIdx.x, stride = (int64_t)xq.nblk * 256;
-            if (xq.kind == 2) quantize_nchw_vec_units((const float *)xq.x, xq.rows, xq.cols, xq.hw, xq.ldq, inv, xq.q, first, stride);
-            else if (xq.bf16) quantize_row_units<true>(xq.x, xq.rows, xq.cols, xq.ldq, inv, xq.q, first, stride);
-            else quantize_row_units<false>(xq.x, xq.rows, xq.cols, xq.ldq, inv, xq.q, first, stride);
+            const int64_t beg = xcd_piece((uint32_t)blk, (uint32_t)xq.nblk) * xq.per, first = beg + threadIdx.x, end = beg + xq.per;
+            if (xq.kind == 2) quantize_nchw_vec_units((const float *)xq.x, xq.rows, xq.cols, xq.hw, xq.ldq, inv, xq.q, first, end, 256);
+            else if (xq.bf16) quantize_row_units<true>(xq.x, xq.rows, xq.cols, xq.ldq, inv, xq.q, first, end, 256);
+            else quantize_row_units<false>(xq.x, xq.rows, xq.cols, xq.ldq, inv, xq.q, first, end, 256);
             return;
         }
         if (PHASE != 2 && extra.q) {
@@ -871,7 +896,8 @@ hipError_t launch_quantize_weights(const WeightBatch &b, int total_blocks, bool 
     InputQuantJob qj{};
     if (extra) ex = *extra;
     if (extra && xq && !one_launch) qj = *xq;               // the codes need the maxima of an earlier launch
-    const dim3 first((unsigned)(total_blocks + ex.nblk)), second((unsigned)(total_blocks + qj.nblk)), block(256);
+    const int others = (total_blocks + 7) / 8 * 8;          // id of the first workgroup that is not the table's
+    const dim3 first((unsigned)(ex.nblk ? others + ex.nblk : total_blocks)), second((unsigned)(qj.nblk ? others + qj.nblk : total_blocks)), block(256);
     if (one_launch)
         return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_weights_kernel<0>, first, block, 0, st, b, partials, flag,
                         total_blocks, ex, InputQuantJob{});
@@ -965,7 +991,7 @@ __device__ __forceinline__ uint32_t quant_gelu_fast(float v, float inv, float er
 __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
     const float *__restrict__ v, int64_t rows, int64_t cols, int64_t ldq, const uint32_t *__restrict__ vmax,
     const uint32_t *__restrict__ exact_absmax, int8_t *__restrict__ q, float *__restrict__ scale_out,
-    uint32_t *__restrict__ flag)
+    uint32_t *__restrict__ flag, int64_t per)
 {
     // absolute maximum of gelu(v): gelu is increasing for v >= 0 and bounded by 0.17 for v < 0
     const float vm = __uint_as_float(reduce_ways(vmax));
@@ -982,13 +1008,14 @@ __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
     __syncthreads();
     const float err_abs_inv = kGeluErrAbs * inv;
     const int64_t upr = ldq >> 4;
-    const int64_t units = rows * upr;
-    const bool narrow = units < (1LL << 32);
+    const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * per;
+    const int64_t units = beg + per < rows * upr ? beg + per : rows * upr;
+    const bool narrow = rows * upr < (1LL << 32);
     const bool vec_ok = (cols & 3) == 0;
     // a thread's units are `stride` apart: row and unit within the row advance by stride / upr and stride % upr
     // (one division at the start instead of one per unit)
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = 256;
+    const int64_t first = beg + threadIdx.x;
     const int64_t step_rows = div_u(stride, upr, narrow), step_units = stride - step_rows * upr;
     auto run = [&](auto big_c) {
         constexpr bool BIG = decltype(big_c)::value;
@@ -1042,12 +1069,11 @@ hipError_t launch_quantize_gelu_rows(const float *v, int64_t rows, int64_t cols,
                                      const uint32_t *vmax, const uint32_t *exact_absmax, int8_t *q,
                                      float *scale_out, uint32_t *flag, hipStream_t st)
 {
-    const int64_t units = rows * (ldq / 16);
-    int64_t blocks = (units + 255) / 256;
-    if (blocks < 1) blocks = 1;
-    if (blocks > 8192) blocks = 8192;
-    return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_gelu_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, v,
-                    rows, cols, ldq, vmax, exact_absmax, q, scale_out, flag);
+    // (the table costs a workgroup a round trip: two units per thread rather than one where there are many; 16384 x 3072
+    // with one 67 us, with two 53)
+    const UnitShare sh = share_units(rows * (ldq / 16), 8192);
+    return launch_k(EGERIA_KERNEL_QUANTIZE, quantize_gelu_rows_kernel, dim3(sh.blocks), dim3(256), 0, st, v,
+                    rows, cols, ldq, vmax, exact_absmax, q, scale_out, flag, sh.per);
 }
 
 __global__ __launch_bounds__(256) void gelu_exact_kernel(const float *v, int64_t n, float *y)
@@ -1072,15 +1098,15 @@ hipError_t launch_gelu_exact(const float *v, int64_t n, float *y, hipStream_t st
 // where the interval straddles zero, so it takes the fp64 form too.  What bounds it is the table walk and the fp64 forms;
 // 4096 x 3072: 19.4 us, against 39.8 (fp64 erf for every value) + 26.5 (cast) before.
 __global__ __launch_bounds__(256) void gelu_f16_rows_kernel(const float *__restrict__ v, int64_t rows, int64_t cols, int64_t ldh,
-                                                            uint16_t *__restrict__ out)
+                                                            uint16_t *__restrict__ out, int64_t per)
 {
     __shared__ float4 tab[256];
     tab[threadIdx.x] = kGeluTable[threadIdx.x];
     __syncthreads();
-    const int64_t upr = ldh >> 3, total = rows * upr;
-    const bool narrow = total < (1LL << 32);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < total; u += stride) {
+    const int64_t upr = ldh >> 3, beg = xcd_piece(blockIdx.x, gridDim.x) * per;
+    const int64_t end = beg + per < rows * upr ? beg + per : rows * upr;
+    const bool narrow = rows * upr < (1LL << 32);
+    for (int64_t u = beg + threadIdx.x; u < end; u += 256) {
         const int64_t row = div_u(u, upr, narrow), c0 = (u - row * upr) * 8, base = row * cols + c0;
         float x[8];
         if ((cols & 3) == 0) {                             // (rows start on 16 bytes, units hold 4 or 8 values)
@@ -1119,12 +1145,10 @@ __global__ __launch_bounds__(256) void gelu_f16_rows_kernel(const float *__restr
 
 hipError_t launch_gelu_f16_rows(const float *v, int64_t rows, int64_t cols, int64_t ldh, void *out, hipStream_t st)
 {
-    const int64_t units = rows * (ldh >> 3);
-    if (units <= 0) return hipSuccess;
-    int64_t blocks = (units + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    return launch_k(EGERIA_KERNEL_QUANTIZE, gelu_f16_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, v, rows, cols, ldh,
-                    (uint16_t *)out);
+    if (rows * (ldh >> 3) <= 0) return hipSuccess;
+    const UnitShare sh = share_units(rows * (ldh >> 3), 8192);
+    return launch_k(EGERIA_KERNEL_QUANTIZE, gelu_f16_rows_kernel, dim3(sh.blocks), dim3(256), 0, st, v, rows, cols, ldh,
+                    (uint16_t *)out, sh.per);
 }
 
 // ---- dequantise ------------------------------------------------------------------------

@@ -376,3 +376,19 @@ def test_gelu_operand(eg, precision, ffn, spread):
     eg.ref_forward(ref, x, seen, ws, taps)
     eg.ref_forward(ref, x, plain, ws)
     assert torch.equal(plain, seen)
+
+
+# The work of a launch is dealt in pieces, an eighth of them to each XCD: fewer pieces than XCDs, a multiple of eight and its
+# neighbours, pieces of one and of several units per thread.  The largest value sits in the last place, then in the first.
+@pytest.mark.parametrize("rows,cols", [(1, 16), (3, 16), (7, 4096), (8, 4096), (9, 4096), (255, 16), (257, 16), (17, 4112), (1031, 48),
+                                       (5, 30), (700, 20), (4099, 16384)])
+def test_codes_of_rows_in_pieces(eg, rows, cols):
+    x = torch.randn(rows, cols, device="cuda", generator=torch.Generator(device="cuda").manual_seed(rows + cols)).clamp_(-4, 4)
+    for at in (-1, 0):
+        y = x.clone()
+        y.view(-1)[at] = 5.0
+        q, scale = eg.quantize_rows(y)
+        assert scale.item() == np.float32(5.0 / 127.0)
+        want = torch.clamp(torch.round(y * torch.tensor(127.0 / 5.0, dtype=torch.float64).float().item()), -127, 127).to(torch.int8)
+        assert torch.equal(q[:, :cols], want)
+        assert not q[:, cols:].any()
