@@ -40,6 +40,12 @@ PEAK_GRAM_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 6.0
 PEAK_ATTENTION_TFLOPS = PEAK_BF16_MFMA_TFLOPS / 3.0
 
 
+def gelu_in_gemm(wl):
+    """The library's rule for writing the codes of the GELU from the first feed-forward layer's launch (unobserved runs)."""
+    d = wl.dims
+    return "seq" in d and d["ffn"] > 32 and (d["hidden"] + 15) // 16 * 16 <= 1024
+
+
 def layernorm_in_gemm(wl):
     """The library's rule for taking the layer norm after the attention-output layer into that layer's launch
     (unobserved runs): at least three quarters of the compute units' worth of 64-row workgroups, rows of at
@@ -88,6 +94,8 @@ def algorithmic_work(wl, cls, eg):
         else:
             M, h, f = b * d["seq"], d["hidden"], d["ffn"]
             shapes = [(M, 3 * h, h, h, 0), (M, h, h, h, 0), (M, f, h, h, 0), (M, h, f, f, 0)]
+            if gelu_in_gemm(wl):
+                shapes[2:3] = [(M, f, h, h, "max"), (M, f, h, h, "codes")]
             if layernorm_in_gemm(wl):
                 del shapes[1]            # that launch is counted with the layer norms, whose work it also does
             shapes = shapes * d["n_layers"]
@@ -96,6 +104,11 @@ def algorithmic_work(wl, cls, eg):
             if narrow:
                 # the narrow convolutions quantise while loading: fp32 operand and fp32 skip input read once
                 out.append((2.0 * M * N * K, 4.0 * M * kin + N * K + 4.0 * M * N + (4.0 * M * N if res else 0)))
+                continue
+            if res in ("max", "codes"):
+                # the first feed-forward layer makes its sums twice, for their maximum and for the codes of their GELU: its
+                # operations count once
+                out.append((2.0 * M * N * K if res == "codes" else 0.0, M * kin + N * K + (M * N if res == "codes" else 0.0)))
                 continue
             # int8 activations read once (not the im2col expansion), weights, fp32 output, int8 residual
             out.append((2.0 * M * N * K, M * kin + N * K + 4.0 * M * N + (M * N if res else 0)))
@@ -128,7 +141,7 @@ def hbm_class_bytes(wl, cls, eg):
     n_w = float(sum(w.size for w in wl.weights))
     if wl.kind in (si.KIND_BERT_LAYER, si.KIND_BERT_STACK):
         M, h, f = b * d["seq"], d["hidden"], d["ffn"]
-        acts = d["n_layers"] * (3.0 * M * h + M * f)
+        acts = d["n_layers"] * (3.0 * M * h + (0.0 if gelu_in_gemm(wl) else M * f))
         first = M * h
     elif wl.kind == si.KIND_FC_RELU:
         acts, first = float(b * d["c_in"]), float(b * d["c_in"])
@@ -155,7 +168,7 @@ def source_digest(kernel):
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2201_06227_amd", "csrc")
-    for name in (KERNEL_SOURCES[kernel], "common.hpp"):
+    for name in (KERNEL_SOURCES[kernel], "common.hpp", "gelu.hpp"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -526,8 +526,27 @@ egeria_status forward_bert_layer(const Fwd &f, int l, const float *cur, float *o
                                 ws_flag(f.ws), f.st));
     EG_OK(f.copy_tap_q(s0 + 2, xq, (size_t)(M * hp), f.scale(s0 + 2)));
     // first feed-forward GEMM: pre-activations only, tracking their positive maximum;
-    // GELU is applied inside the next quantiser
+    // GELU is applied inside the next quantiser, or by the GEMM itself
     uint32_t *exact_word = f.slot(4 * f.p.n_layers + l);
+    if (!f.taps && gemm_gelu_codes(M, F, hp)) {
+        // the sums twice, first for the maximum, then for the codes, which take the place of the fp32 tensor
+        int8_t *codes = (int8_t *)ff;
+        for (int pass = 1; pass <= 2; ++pass) {
+            const egeria_qlinear &L = f.qw->linear[s0 + 2];
+            GemmArgs g{};
+            g.a = xq; g.w = L.w_q; g.M = M; g.N = F; g.kp = hp; g.lda = hp;
+            g.a_bytes = M * hp;
+            g.w_bytes = (int64_t)F * hp;
+            if (g.a_bytes >= (1LL << 31) || g.w_bytes >= (1LL << 31)) return EGERIA_ERR_UNSUPPORTED;
+            g.sx = f.scale(s0 + 2); g.sw = L.scale; g.sw_per_n = L.per_channel ? 1 : 0; g.bias = L.bias;
+            g.gelu_pass = pass; g.gelu_neg = exact_word;
+            if (pass == 1) g.absmax_out = f.slot(s0 + 3);
+            else { g.gelu_max = f.slot(s0 + 3); g.q_out = codes; g.q_ld = fp; g.gelu_scale = f.scale(s0 + 3); g.flag = ws_flag(f.ws); }
+            EG_HIP(launch_gemm_i8(g, f.st));
+        }
+        return run_gemm_layernorm(f, s0 + 3, codes, fp, M, Hd, fp, f.scale(s0 + 3), proj, y1, nm ? &nm[1] : nullptr, out,
+                                  last ? nullptr : f.slot(s0 + 4));
+    }
     EG_OK(run_gemm(f, s0 + 2, xq, hp, M, F, hp, false, 0, 0, 0, f.scale(s0 + 2), 0, nullptr, nullptr, 0, ff,
                    f.slot(s0 + 3), true, false));
     if (const egeria_tap *t = f.tap(s0 + 2))

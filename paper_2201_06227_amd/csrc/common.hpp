@@ -291,10 +291,22 @@ struct GemmArgs {
     const float *ln_gamma;
     const float *ln_beta;
     double ln_eps;
+    // optional: the GELU that follows a linear layer and its int8 codes without the fp32 tensor in between (int8 operands,
+    // gemm_gelu_codes(...); no residual, observation or zero points, y ignored).  Two launches, since the scale needs the
+    // tensor's maximum: gelu_pass 1 leaves max(y, 0) in absmax_out and, where that may be too small, candidates for the largest
+    // |gelu| of a negative value in the first two words of gelu_neg's ways; gelu_pass 2 makes the same sums again and
+    // writes the codes of gelu(y) to q_out [M, q_ld] (zero pad columns) and the scale to gelu_scale.
+    int32_t gelu_pass;
+    const uint32_t *gelu_max;
+    uint32_t *gelu_neg;
+    float *gelu_scale;
+    uint32_t *flag;
 };
 hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st);
 void gemm_tile(int64_t M, int32_t N, int64_t kp, bool conv3x3, int32_t *rows, int32_t *cols, int32_t *k_step);
 int gemm_stages(int64_t M, int32_t N, int64_t kp, bool conv3x3);
+// true if launch_gemm_i8 offers gelu_pass for a linear layer of these sizes and it is the faster way
+bool gemm_gelu_codes(int64_t M, int32_t N, int64_t kp);
 // true if launch_gemm_i8 can take the layer norm of an [M, N] output into the GEMM's launch
 bool gemm_layernorm_fusable(int32_t N, const void *ln_out, const void *ln_res, const void *gamma, const void *beta);
 

@@ -18,7 +18,8 @@
 // exact whatever the instruction's internal K order is.  Workgroup ids are
 // dealt so that each XCD works on a contiguous range of tiles (N fastest) and
 // its L2 serves the re-reads of A rows and of the weights.
-#include "common.hpp"
+#include "gelu.hpp"
+#include <climits>
 #include <type_traits>
 
 namespace egeria {
@@ -96,11 +97,24 @@ constexpr int resident_target(int bm, int bn)
     return bm * bn > 256 * 128 ? 1 : (bm * bn > 128 * 128 ? 2 : 3);
 }
 
-template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, bool LNF = false, int NST = stages_for(BK)>
-__global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g)
+// What a workgroup does with its sums (EPI)
+enum GemmEpilogue {
+    kStore = 0,          // y, int8 codes, maxima, observation points
+    kLayerNorm = 1,      // the layer norm of its rows (GemmArgs::ln_out)
+    kGeluMax = 2,        // nothing but their maximum (gelu_pass 1)
+    kGeluCodes = 3       // int8 codes of their GELU (gelu_pass 2)
+};
+constexpr int kGeluTableBytes = kGeluLines * 8;
+// values per wave whose code the table leaves open that one round settles; 8 bytes each in the stage memory
+constexpr int kGeluList = 512;
+
+template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, int EPI = kStore, int NST = stages_for(BK)>
+__global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 * 128 ? 2 : resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g)
 {
     typedef typename AccOf<ET>::type acc_t;
     typedef typename ResOf<ET>::type res_t;
+    constexpr bool LNF = EPI == kLayerNorm;
+    constexpr bool kTurned = EPI == kGeluCodes;      // the transposed product: a lane holds neighbouring columns of one row
     static_assert(BK == 64 || BK == 128, "K step of 64 or 128 bytes");
     constexpr int kBK = BK;
     constexpr int UPR = BK / 16;                 // 16-byte K units per row of a stage
@@ -281,7 +295,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = mma<ET>(fa[i], fb[j], acc[i][j]);
+                acc[i][j] = kTurned ? mma<ET>(fb[j], fa[i], acc[i][j]) : mma<ET>(fa[i], fb[j], acc[i][j]);
     };
 
     // Software pipeline over a ring of NST LDS stages.  During step kt the
@@ -295,10 +309,38 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     constexpr int kWaitNext = 0x0f70 | (((NST - 2) * NLD) & 0xf) | ((((NST - 2) * NLD) >> 4) << 14);   // vmcnt only
     const int nk = (g.kp + kBK - 1) / kBK;
     v4i fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+    if constexpr (EPI == kGeluCodes) {
+        // the maximum's words (a way's word per lane, into the stage that is filled last) and the wave's part of the GELU's lines
+        static_assert(STAGE >= NW * 1024 && kGeluTableBytes % (4 * 1024) == 0, "a kilobyte per wave, and per request");
+        load_to_lds_b128((const uint8_t *)(g.gelu_max + lane * kAmaxStride), lds0 + (NST - 1) * STAGE + wave_u * 1024);
+#pragma unroll
+        for (int c = 0; c < kGeluTableBytes / 1024 / 4; ++c) {
+            const int at = ((wave_u & 3) + 4 * c) * 1024;           // (of eight waves the second four ask for the same)
+            load_to_lds_b128((const uint8_t *)kGeluLine + at + lane * 16, lds0 + NST * STAGE + at);
+        }
+    }
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p) fetch(p, p);
+    // the scale of the codes, worked out while the first K steps are on their way
+    float gelu_vm = 0.0f, gelu_inv = 0.0f;
+    if constexpr (EPI == kGeluCodes) {
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (((NST - 1) * NLD) & 0xf) | ((((NST - 1) * NLD) >> 4) << 14));
+        wave_lds_turn();
+        gelu_vm = __uint_as_float(wave_max_u32(*(const uint32_t *)&lds[(NST - 1) * STAGE + wave_u * 1024 + lane * 16]));
+        float absmax = gelu_exact(gelu_vm);
+        if (gelu_vm < kGeluShortcutMin) {            // uniform, rare
+            const uint32_t *way = g.gelu_neg + lane * kAmaxStride;
+            const uint32_t below = wave_max_u32(way[0]), above = wave_max_u32(way[1]);
+            if (below) absmax = fmaxf(absmax, fabsf(gelu_exact(-__uint_as_float(0x7fffffffu - below))));
+            if (above) absmax = fmaxf(absmax, fabsf(gelu_exact(-__uint_as_float(above))));
+        }
+        float scale;
+        const bool bad = !(gelu_vm <= 3.402823466e+38f);
+        gelu_inv = gelu_code_scale(absmax, bad, &scale);
+        if (tile == 0 && tid == 0) publish(scale, bad, g.gelu_scale, nullptr, g.flag);
+    }
     // which form the epilogue takes: decided while the first K steps are on their way
-    int inside = m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
+    int inside = EPI == kStore && m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
                  (ET == 0 && BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q);
     inside = __builtin_amdgcn_readfirstlane(inside);
     asm volatile("" : "+s"(inside));
@@ -323,7 +365,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                acc[i][j] = mma<ET>(fa0[i], fb0[j], acc[i][j]);
+                acc[i][j] = kTurned ? mma<ET>(fb0[j], fa0[i], acc[i][j]) : mma<ET>(fa0[i], fb0[j], acc[i][j]);
                 constexpr int per = (NLD + NMF - 1) / NMF;               // requests after each MFMA
 #pragma unroll
                 for (int q = 0; q < per; ++q)
@@ -424,6 +466,177 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             }
         }
         amax = (int32_t)amax_u;
+    } else if constexpr (EPI == kGeluMax) {
+        // ---- nothing is stored.  y = fma(sum, s, b) grows (or falls) with the sum, so a column's largest y is that of its largest
+        // or its smallest sum.
+        float sj[TN], bj[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = n0 + (wn_u * TN + j) * 32 + lcol;
+            const bool ok = col < g.N;
+            sj[j] = !ok ? 0.0f : (g.sw_per_n ? sxv * g.sw[ok ? col : 0] : s);    // one fp32 multiply
+            bj[j] = g.bias && ok ? g.bias[ok ? col : 0] : 0.0f;
+        }
+        const int rows = (int)(g.M - m0 < BM ? g.M - m0 : BM);                   // valid rows of the tile
+        auto track = [&](float v) {
+            const int32_t bits = (int32_t)__float_as_uint(v);
+            amax = amax > bits ? amax : bits;
+        };
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            int hi = INT_MIN, lo = INT_MAX;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int left = rows - (wm_u * TM + i) * 32;                    // (uniform)
+                if (left >= 32) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        hi = hi > acc[i][j][r] ? hi : acc[i][j][r];
+                        lo = lo < acc[i][j][r] ? lo : acc[i][j][r];
+                    }
+                } else if (left > 0) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const bool ok = lrow + 8 * (r >> 2) + (r & 3) < left;
+                        const int up = ok ? acc[i][j][r] : INT_MIN, down = ok ? acc[i][j][r] : INT_MAX;
+                        hi = hi > up ? hi : up;
+                        lo = lo < down ? lo : down;
+                    }
+                }
+            }
+            if (lo <= hi) {                             // (a lane may have no row at all)
+                track(fmaf((float)hi, sj[j], bj[j]));
+                track(fmaf((float)lo, sj[j], bj[j]));
+            }
+        }
+        if (__uint_as_float(wave_max_u32((uint32_t)amax)) < kGeluShortcutMin) {
+            uint32_t below = 0, above = 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float v = (wm_u * TM + i) * 32 + lrow + 8 * (r >> 2) + (r & 3) < rows ? fmaf((float)acc[i][j][r], sj[j], bj[j]) : 0.0f;
+                        const uint32_t a = abs_bits(v);
+                        if (v <= kGeluArgMin) below = below > 0x7fffffffu - a ? below : 0x7fffffffu - a;
+                        if (v >= kGeluArgMin && v < 0.0f) above = above > a ? above : a;
+                    }
+            below = wave_max_u32(below);
+            above = wave_max_u32(above);
+            uint32_t *way = g.gelu_neg + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
+            if (lane == 0 && below) atomicMax(way, below);
+            if (lane == 0 && above) atomicMax(way + 1, above);
+        }
+    } else if constexpr (EPI == kGeluCodes) {
+        // ---- codes of gelu(y).  The product is the transposed one, so a lane holds, of every 32x32 block, 16 columns of one row: four
+        // times four neighbouring ones, the other half of the wave those between them.  A swap of halves makes 16 neighbours, one
+        // store.  Values whose code the lines leave open go on the wave's list (value, place) in the stage memory and
+        // are settled side by side afterwards.  Bound by the vector
+        // instructions, 13 a value (16384 x 3072 values: 20 us of the launch's 61; the sums alone 38).
+        static_assert((size_t)NST * STAGE >= (size_t)NW * (kGeluList * 8 + 4096), "the waves' lists must fit the stage memory");
+        float2 *lines = (float2 *)&lds[NST * STAGE];
+        uint2 *list = (uint2 *)&lds[wave_u * (kGeluList * 8 + 4096)];
+        const float room = 0.5f - kGeluLineErr * gelu_inv;
+        const int rows = (int)(g.M - m0 < BM ? g.M - m0 : BM);
+        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)(g.q_out + m0 * g.q_ld), 0, (int)(rows * g.q_ld), 0x00020000);
+        const uint32_t q_ld = (uint32_t)g.q_ld;
+        const int half = lane >> 5;
+#pragma unroll
+        for (int c = tid; c < kGeluLines; c += NT) lines[c] = make_float2(lines[c].x * gelu_inv, lines[c].y * gelu_inv);
+        __syncthreads();                                // every wave has read its last operands
+        // COLS: a scale or a bias per column (pad columns: gelu(0) = 0)
+        auto run = [&](auto cols_c) {
+            constexpr bool COLS = decltype(cols_c)::value;
+            int n = 0;
+            {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int col0 = n0 + (wn_u * TN + j) * 32;      // register r: column col0 + 8 (r / 4) + 4 half + r % 4
+                    float sr[COLS ? 16 : 1], br[COLS ? 16 : 1];
+                    sr[0] = s;
+                    br[0] = 0.0f;
+                    if constexpr (COLS) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int col = col0 + 8 * (r >> 2) + 4 * half + (r & 3), cc = col < g.N ? col : g.N - 1;
+                            const float sv = g.sw_per_n ? sxv * g.sw[cc] : s, bv = g.bias ? g.bias[cc] : 0.0f;   // one fp32 multiply
+                            sr[r] = col < g.N ? sv : 0.0f;
+                            br[r] = col < g.N ? bv : 0.0f;
+                        }
+                    }
+                    const uint32_t c16 = (uint32_t)(col0 + 16 * half) < q_ld ? (uint32_t)(col0 + 16 * half) : kOob;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const uint32_t row = (uint32_t)((wm_u * TM + i) * 32 + lcol);    // the lane's row of the tile
+                        uint32_t c[16];
+                        bool un[16], any = false;
+                        auto value = [&](int r) { return fmaf((float)acc[i][j][r], sr[COLS ? r : 0], br[COLS ? r : 0]); };
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            c[r] = quant_gelu_lines(value(r), room, lines, &un[r]);
+                            any = any || un[r];
+                            if (r == 7) __builtin_amdgcn_sched_barrier(0);               // (sixteen look-ups in flight would spill)
+                        }
+                        uint32_t w[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) w[q] = pack_bytes(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+                        const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+                        const v4u out = {(unsigned)a[0], (unsigned)a[1], (unsigned)b[0], (unsigned)b[1]};
+                        __builtin_amdgcn_raw_buffer_store_b128(out, rq, (int)(c16 == kOob ? kOob : row * q_ld + c16), 0, 0);
+                        if (__ballot(any)) {                                             // rare
+                            float *turn = (float *)(list + kGeluList);       // the block's values, by register and lane
+                            uint32_t open = 0;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                turn[r * 64 + lane] = value(r);
+                                open |= un[r] ? 1u << r : 0u;
+                            }
+                            if ((int)row >= rows) open = 0;
+                            wave_lds_turn();
+#pragma unroll 1
+                            while (__ballot(open != 0)) {
+                                const int r = __ffs((int)open) - 1, col = col0 + 8 * (r >> 2) + 4 * half + (r & 3);
+                                const bool mine = open != 0 && col < g.N;
+                                const uint64_t m = __ballot(mine);
+                                const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                                if (mine && at < kGeluList) list[at] = make_uint2(__float_as_uint(turn[r * 64 + lane]), row * q_ld + (uint32_t)col);
+                                n += __popcll(m);
+                                open &= open - 1;
+                            }
+                            wave_lds_turn();
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            if (n > 0) {                                // (uniform)
+                wave_lds_turn();
+                __builtin_amdgcn_s_waitcnt(0x0f70);     // the stores above have been performed
+                if (n <= kGeluList) {
+#pragma unroll 1
+                    for (int k = lane; k < n; k += 64) {
+                        const uint2 e = list[k];
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code_of(gelu_exact(__uint_as_float(e.x)) * gelu_inv), rq, (int)e.y, 0, 0);
+                    }
+                } else {
+                    // more than one value in twelve of a wave's: every one from its operands, value by value
+                    const int wrow0 = wm_u * TM * 32, wcol0 = n0 + wn_u * TN * 32;
+#pragma unroll 1
+                    for (int k = lane; k < TM * TN * 1024; k += 64) {
+                        const int tr = wrow0 + k / (TN * 32), col = wcol0 + k % (TN * 32);
+                        if (tr >= rows || col >= g.N) continue;
+                        const int *ar = (const int *)(g.a + (m0 + tr) * g.lda), *wr = (const int *)(g.w + (int64_t)col * g.kp);
+                        int sum = 0;
+#pragma unroll 1
+                        for (int u = 0; u < g.kp / 4; ++u) sum = __builtin_amdgcn_sdot4(ar[u], wr[u], sum, false);
+                        const float sv = g.sw_per_n ? sxv * g.sw[col] : s, v = fmaf((float)sum, sv, g.bias ? g.bias[col] : 0.0f);
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code_of(gelu_exact(v) * gelu_inv), rq, (int)((uint32_t)tr * q_ld + (uint32_t)col), 0, 0);
+                    }
+                }
+            }
+        };
+        if (g.sw_per_n || g.bias) run(std::true_type{}); else run(std::false_type{});
     } else if (inside) {
         // ---- a tile that lies inside the output: stored from the accumulators.  For a fixed register each half of the wave owns
         // 32 neighbouring columns of one row, so every store of y writes two whole 128-byte segments and nothing is tested.
@@ -719,7 +932,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
             if (track) fixed(F{}, T{}, F{}, F{}, F{}); else fixed(F{}, F{}, F{}, F{}, F{});
         }
     }
-    if (g.absmax_out) {
+    if (EPI != kGeluCodes && g.absmax_out) {
         __shared__ uint32_t smw[NW];
         if constexpr (NW == 4) {
             block_atomic_max((uint32_t)amax, g.absmax_out, smw);
@@ -738,7 +951,7 @@ __global__ __launch_bounds__(64 * WM * WN, resident_target(BM, BN)) void gemm_i8
     }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int ET = 0, bool LNF = false, int NST = stages_for(BK)>
+template <int BM, int BN, int WM, int WN, int BK, int ET = 0, int EPI = kStore, int NST = stages_for(BK)>
 static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
 {
     const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
@@ -748,33 +961,33 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     constexpr size_t stages = (size_t)NST * (BM + BN) * BK;
     // affine codes: weight-code sums and row classes behind the epilogue's block
     constexpr size_t affine = ((size_t)WM * 32 * (BN + 8 * WN) + 16 * BN) * 4 + BM, largest = stages > affine ? stages : affine;
-    const size_t smem = g.zp_in ? largest : stages;
+    const size_t smem = EPI == kGeluCodes ? stages + kGeluTableBytes : (g.zp_in ? largest : stages);
     hipError_t e;
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     if (g.conv3x3) {
-        if constexpr (LNF || WM * WN != 4) {
+        if constexpr (EPI != kStore || WM * WN != 4) {
             return hipErrorInvalidValue;                         // shapes for linear layers only
         } else {
             static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
             if (!set[dev]) {
-                e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>,
+                e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, EPI, NST>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
                 if (e != hipSuccess) return e;
                 set[dev] = true;
             }
-            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, false, NST>, grid, block, smem, st, g);
+            return launch_k(EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, true, BK, ET, EPI, NST>, grid, block, smem, st, g);
         }
     }
     static bool set[kMaxDevices] = {};
     if (!set[dev]) {
-        e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF, NST>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)largest);
+        e = hipFuncSetAttribute((const void *)gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, EPI, NST>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)(EPI == kGeluCodes ? stages + kGeluTableBytes : largest));
         if (e != hipSuccess) return e;
         set[dev] = true;
     }
     // (instrumentation: the launch that also normalises its rows is timed with the layer norms, whose bytes bound it)
-    return launch_k(LNF ? EGERIA_KERNEL_LAYERNORM : EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, LNF, NST>,
+    return launch_k(EPI == kLayerNorm ? EGERIA_KERNEL_LAYERNORM : EGERIA_KERNEL_GEMM, gemm_i8_kernel<BM, BN, WM, WN, false, BK, ET, EPI, NST>,
                     grid, block, smem, st, g);
 }
 
@@ -1167,10 +1380,42 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
     case 5: return launch_variant<128, 64, 2, 2, 128, ET>(g, st);
     case 6: return launch_variant<256, 256, 2, 4, 128, ET>(g, st);
     case 7: return launch_variant<256, 192, 4, 2, 128, ET>(g, st);
-    case kDeepSmall: return launch_variant<64, 64, 2, 2, 128, ET, false, 3>(g, st);
-    case kDeepMid: return launch_variant<128, 64, 2, 2, 128, ET, false, 3>(g, st);
-    case kDeepLarge: return launch_variant<128, 128, 2, 2, 128, ET, false, 3>(g, st);
+    case kDeepSmall: return launch_variant<64, 64, 2, 2, 128, ET, kStore, 3>(g, st);
+    case kDeepMid: return launch_variant<128, 64, 2, 2, 128, ET, kStore, 3>(g, st);
+    case kDeepLarge: return launch_variant<128, 128, 2, 2, 128, ET, kStore, 3>(g, st);
     default: return hipErrorInvalidValue;
+    }
+}
+
+// The two passes of a layer whose output only feeds a GELU (GemmArgs::gelu_pass): nothing or a byte a value is stored, so the
+// operands' way into LDS and, in the second pass, vector instructions are what they cost, and large tiles with whole-line K steps
+// and eight waves are the fast ones.  A round takes about 3.5 us and 1 us for every 4096 values of a compute unit's tiles (both
+// passes of 768 products, us: 256x256 11.4 + 19, 256x192 9.8 + 15.6, two 128x128 7.7 + 11.9, 128x192 10.9 for the second,
+// two 64x64 5.9): the shape whose rounds cost least.  us, 128x192 / 128x128 / 256x192 / 256x256: 4096 x 3072 x 768 42.6 / 43.4 / 33.3 /
+// 36.5, 4728 rows 54.7 / 46.9 / 55.7 / 42.9, 16384 rows 136 / 121 / 110 / 99, 1920 x 2304 x 576 19.4 / 20.3 / 28.9 / 32.7.
+template <int EPI>
+static hipError_t launch_gelu(const GemmArgs &g, hipStream_t st)
+{
+    constexpr struct { int bm, bn, resident; double penalty; } shapes[] = {
+        {256, 256, 1, 1.0}, {256, 192, 1, 1.0}, {128, 192, 1, 1.07}, {128, 128, 2, 1.07}, {128, 64, 2, 1.07}, {64, 64, 2, 1.07}};
+    int best = 0;
+    double best_cost = 0.0;
+    for (int i = 0; i < 6; ++i) {
+        const int64_t tiles = ((g.M + shapes[i].bm - 1) / shapes[i].bm) * ((g.N + shapes[i].bn - 1) / shapes[i].bn);
+        const int64_t slots = (int64_t)compute_units() * shapes[i].resident;
+        const double cost = (double)((tiles + slots - 1) / slots) * (shapes[i].bm * shapes[i].bn * shapes[i].resident + 14336) * shapes[i].penalty;
+        if (i == 0 || cost < best_cost) {
+            best_cost = cost;
+            best = i;
+        }
+    }
+    switch (best) {
+    case 0: return launch_variant<256, 256, 2, 4, 128, 0, EPI>(g, st);
+    case 1: return launch_variant<256, 192, 4, 2, 128, 0, EPI>(g, st);
+    case 2: return launch_variant<128, 192, 2, 2, 64, 0, EPI>(g, st);
+    case 3: return launch_variant<128, 128, 2, 2, 64, 0, EPI>(g, st);
+    case 4: return launch_variant<128, 64, 2, 2, 64, 0, EPI>(g, st);
+    default: return launch_variant<64, 64, 2, 2, 128, 0, EPI, 3>(g, st);
     }
 }
 
@@ -1266,13 +1511,25 @@ bool gemm_layernorm_fusable(int32_t N, const void *ln_out, const void *ln_res, c
     return N >= 4 && N <= 768 && (N & 3) == 0 && ln_out && ln_res && ok16(ln_out) && ok16(ln_res) && ok16(gamma) && ok16(beta);
 }
 
+// Which layers make their sums twice (GemmArgs::gelu_pass): a second set of sums instead of an fp32 tensor written and read back,
+// as long as they are short.
+bool gemm_gelu_codes(int64_t M, int32_t N, int64_t kp) { return M > 0 && N > 32 && N < (1 << 22) && kp <= 1024; }
+
 hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
 {
     if (g.ln_out) {
         // a linear layer and the layer norm of its rows in one launch: 64 whole rows per workgroup
         if (g.et != 0 || g.conv3x3 || g.act || g.res_q || g.q_out || g.acc_out || g.zp_in || g.zp_res) return hipErrorInvalidValue;
         if (!gemm_layernorm_fusable(g.N, g.ln_out, g.ln_res, g.ln_gamma, g.ln_beta)) return hipErrorInvalidValue;
-        return launch_variant<64, 768, 1, 8, 64, 0, true>(g, st);
+        return launch_variant<64, 768, 1, 8, 64, 0, kLayerNorm>(g, st);
+    }
+    if (g.gelu_pass) {
+        if (g.et != 0 || g.conv3x3 || g.act || g.res_q || g.acc_out || g.zp_in || g.zp_res || !gemm_gelu_codes(g.M, g.N, g.kp))
+            return hipErrorInvalidValue;
+        if (g.gelu_pass == 1) return g.absmax_out && g.gelu_neg ? launch_gelu<kGeluMax>(g, st) : hipErrorInvalidValue;
+        // (256 rows of codes are addressed with 31 bits)
+        if (!g.q_out || (g.q_ld & 15) || g.q_ld < g.N || g.q_ld >= (1 << 22) || !g.gelu_max || !g.gelu_neg || !g.gelu_scale) return hipErrorInvalidValue;
+        return launch_gelu<kGeluCodes>(g, st);
     }
     if (g.et == 1 || g.et == 2) {
         if (g.q_out || g.absmax_out) return hipErrorInvalidValue;

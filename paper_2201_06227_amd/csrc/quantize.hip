@@ -1,7 +1,7 @@
 // Per-tensor symmetric int8 quantisation (Section 4.1 of the paper: the
 // reference model is an int8 post-training-quantised snapshot).  Two coalesced
 // HBM passes per tensor: an absolute-maximum reduction, then the map to codes.
-#include "common.hpp"
+#include "gelu.hpp"
 #include <type_traits>
 
 namespace egeria {
@@ -24,8 +24,11 @@ __device__ __forceinline__ void absmax_share(const void *__restrict__ xv, int64_
                                              uint32_t *__restrict__ reset, int n_reset, int blk, int nblks)
 {
     if (blk == 0) {
-        for (int t = threadIdx.x; t < n_reset * kAmaxWays; t += blockDim.x)
-            reset[(size_t)(t / kAmaxWays) * kAmaxWays * kAmaxStride + (t % kAmaxWays) * kAmaxStride] = 0u;
+        for (int t = threadIdx.x; t < n_reset * kAmaxWays; t += blockDim.x) {
+            uint32_t *way = reset + (size_t)(t / kAmaxWays) * kAmaxWays * kAmaxStride + (t % kAmaxWays) * kAmaxStride;
+            way[0] = 0u;
+            way[1] = 0u;                     // (the second word of a GELU's slot, see GemmArgs::gelu_neg)
+        }
         // `reset` is the first atomic slot, kHeaderFixedWords words into the workspace: the header's
         // counter of re-evaluated attention values starts every chain at zero as well
         if (n_reset > 0 && threadIdx.x == 0) reset[kUnsureWord - kHeaderFixedWords] = 0u;
@@ -908,20 +911,12 @@ hipError_t launch_quantize_weights(const WeightBatch &b, int total_blocks, bool 
                     total_blocks, InputMaxJob{}, qj);
 }
 
-// ---- fused GELU + quantise ---------------------------------------------------------------
+// ---- fused GELU + quantise (gelu.hpp) ----------------------------------------------------
 // The GELU output of a Transformer layer's first feed-forward GEMM is consumed
 // only by the next quantiser, and its codes must equal those of the fp64
 // evaluation rounded to fp32.  GELU is evaluated in fp32 first (cubic pieces from a
 // table); a lane falls back to the fp64 form only when the error bound of that
 // evaluation leaves two candidate codes (a few elements per 100 000).
-__device__ __forceinline__ float gelu_exact(float v)
-{
-    const double d = (double)v;
-    return (float)(0.5 * d * (1.0 + erf(d * 0.70710678118654752440)));
-}
-
-constexpr float kGeluShortcutMin = 0.5f;   // gelu(0.5) = 0.346 exceeds max |gelu| over v < 0 (0.17)
-
 __global__ __launch_bounds__(256) void gelu_absmax_exact_kernel(const float *__restrict__ v, int64_t n,
                                                                 const uint32_t *__restrict__ vmax,
                                                                 uint32_t *__restrict__ exact_absmax)
@@ -946,67 +941,23 @@ hipError_t launch_gelu_absmax_exact(const float *v, int64_t n, const uint32_t *v
                     exact_absmax);
 }
 
-// fp32 GELU from a table of cubic pieces (gelu_table.inc: 256 pieces of width 1/16 on [-8, 8), generated
-// with the measured error of the fp32 evaluation; beyond 8 gelu(v) rounds to v, below -8 it lies within
-// 5e-15 of the table's first value).  |approximation - gelu| <= kGeluErrAbs + kGeluErrRel * |gelu|.
-#include "gelu_table.inc"
-
-// BIG: values of 8 and more may occur (the caller knows the tensor's maximum); otherwise the test is left out.
-template <bool BIG>
-__device__ __forceinline__ float gelu_table(float v, const float4 *__restrict__ tab)
-{
-    const float vc = fminf(fmaxf(v, -8.0f), 7.999999f);
-    const int i = (int)fmaf(vc, 16.0f, 128.0f);                  // piece, 0..255
-    const float t = vc - fmaf((float)i, 0.0625f, -8.0f);
-    const float4 c = tab[i];
-    const float g = fmaf(fmaf(fmaf(c.w, t, c.z), t, c.y), t, c.x);
-    return (BIG && v >= 8.0f) ? v : g;
-}
-
-__device__ __forceinline__ uint32_t code_of(float t)
-{
-    float r = rintf(t);
-    r = fminf(fmaxf(r, -127.0f), 127.0f);
-    return (uint32_t)((int)r) & 0xffu;
-}
-
-// Code of gelu(v) from the table.  The code clamp(rne(fp32(g * inv))) is monotone in g, so when both ends of
-// the interval that the error bound leaves for g * inv round to the same integer, that integer is the code
-// of the exact value; *unsure is set otherwise (a few values per 100 000) and the caller takes the fp64 form.
-// err_abs_inv = kGeluErrAbs * inv.  (The relative part also covers the rounding of the two products.)
-// (The interval [t - e, t + e] rounds to one integer if |t - rne(t)| + e < 1/2.  No clamp: the scale is the
-// tensor's exact maximum of |gelu| over 127, so |t| stays below 127.5 by the table's error bound; with a
-// non-finite maximum inv is 0 and every code is 0.)
-template <bool BIG>
-__device__ __forceinline__ uint32_t quant_gelu_fast(float v, float inv, float err_abs_inv, const float4 *__restrict__ tab,
-                                                    bool *unsure)
-{
-    const float t = gelu_table<BIG>(v, tab) * inv;
-    const float e = fmaf(kGeluErrRel + 3.0e-7f, fabsf(t), err_abs_inv);
-    const float rt = rintf(t);
-    *unsure = !(fabsf(t - rt) + e < 0.5f);
-    return (uint32_t)((int)rt) & 0xffu;
-}
-
 __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
     const float *__restrict__ v, int64_t rows, int64_t cols, int64_t ldq, const uint32_t *__restrict__ vmax,
     const uint32_t *__restrict__ exact_absmax, int8_t *__restrict__ q, float *__restrict__ scale_out,
     uint32_t *__restrict__ flag, int64_t per)
 {
+    const float4 entry = kGeluTable[threadIdx.x];
     // absolute maximum of gelu(v): gelu is increasing for v >= 0 and bounded by 0.17 for v < 0
     const float vm = __uint_as_float(reduce_ways(vmax));
     const bool bad = !(vm <= 3.402823466e+38f);
     const float exact = __uint_as_float(reduce_ways(exact_absmax));
-    float absmax = vm >= kGeluShortcutMin ? gelu_exact(vm) : exact;
-    if (bad) absmax = 0.0f;
-    float scale = (float)((double)absmax / 127.0);
-    float inv = (float)(127.0 / (double)absmax);
-    if (!(inv <= 3.402823466e+38f) || !(scale > 0.0f)) { scale = 1.0f; inv = 0.0f; }
+    float scale;
+    const float inv = gelu_code_scale(vm >= kGeluShortcutMin ? gelu_exact(vm) : exact, bad, &scale);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(scale, bad, scale_out, nullptr, flag);
     __shared__ float4 tab[256];                    // the table, once per workgroup (256 threads)
-    tab[threadIdx.x] = kGeluTable[threadIdx.x];
+    tab[threadIdx.x] = scale_gelu_entry(entry, inv);
     __syncthreads();
-    const float err_abs_inv = kGeluErrAbs * inv;
+    const float room = 0.5f - kGeluErrAbs * inv;
     const int64_t upr = ldq >> 4;
     const int64_t beg = xcd_piece(blockIdx.x, gridDim.x) * per;
     const int64_t units = beg + per < rows * upr ? beg + per : rows * upr;
@@ -1033,10 +984,8 @@ __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     bool u0, u1, u2, u3;
-                    w[j] = quant_gelu_fast<BIG>(x[j].x, inv, err_abs_inv, tab, &u0) |
-                           (quant_gelu_fast<BIG>(x[j].y, inv, err_abs_inv, tab, &u1) << 8) |
-                           (quant_gelu_fast<BIG>(x[j].z, inv, err_abs_inv, tab, &u2) << 16) |
-                           (quant_gelu_fast<BIG>(x[j].w, inv, err_abs_inv, tab, &u3) << 24);
+                    w[j] = pack_bytes(quant_gelu_fast<BIG>(x[j].x, inv, room, tab, &u0), quant_gelu_fast<BIG>(x[j].y, inv, room, tab, &u1),
+                                      quant_gelu_fast<BIG>(x[j].z, inv, room, tab, &u2), quant_gelu_fast<BIG>(x[j].w, inv, room, tab, &u3));
                     redo |= ((u0 ? 1u : 0u) | (u1 ? 2u : 0u) | (u2 ? 4u : 0u) | (u3 ? 8u : 0u)) << (4 * j);
                 }
             } else {
@@ -1061,8 +1010,8 @@ __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
             if (cu >= upr) { cu -= upr; ++row; }
         }
     };
-    // values of 8 and more (where gelu(v) rounds to v and the table ends) only if the tensor's maximum says so
-    if (vm >= 8.0f || bad) run(std::true_type{}); else run(std::false_type{});
+    // values of kGeluTop and more (where gelu(v) rounds to v and the table ends) only if the tensor's maximum says so
+    if (vm >= kGeluTop || bad) run(std::true_type{}); else run(std::false_type{});
 }
 
 hipError_t launch_quantize_gelu_rows(const float *v, int64_t rows, int64_t cols, int64_t ldq,
@@ -1120,7 +1069,7 @@ __global__ __launch_bounds__(256) void gelu_f16_rows_kernel(const float *__restr
         uint32_t w[4] = {0, 0, 0, 0}, redo = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float g = gelu_table<true>(x[e], tab);
+            const float g = gelu_table<true>(x[e], 1.0f, tab);
             const float err = fmaf(kGeluErrRel + 3.0e-7f, fabsf(g), kGeluErrAbs * 1.001f);
             const uint32_t lo = __builtin_bit_cast(uint16_t, (_Float16)(g - err)), hi = __builtin_bit_cast(uint16_t, (_Float16)(g + err));
             const bool in = c0 + e < cols;                 // pad columns: zero

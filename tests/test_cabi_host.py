@@ -232,3 +232,25 @@ def test_attention_threshold_is_in_flops_of_the_products(eg):
     finally:
         eg.attention_threshold(old)
     assert [eg.attention_certified(*k) for k in rule] == by_rule
+
+
+def test_gelu_lines_are_what_their_generator_writes():
+    """The straight lines of the GEMM that writes GELU codes: the committed generator's output, and within its bound on values
+    that the generator did not measure."""
+    import importlib.util
+    import math
+    import numpy as np
+    path = os.path.join(ROOT, "paper_2201_06227_amd", "csrc", "gen_gelu_table.py")
+    spec = importlib.util.spec_from_file_location("gen_gelu_table", path)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    text, worst = mod.lines_text()
+    assert text == open(os.path.join(ROOT, "paper_2201_06227_amd", "csrc", "gelu_lines.inc")).read()
+    assert worst < 8e-7
+    lines = np.array([[float(t.rstrip("f")) for t in row.strip().strip("{},").split(", ")] for row in text.splitlines() if row.startswith("    {")])
+    assert lines.shape == (mod.LINES, 2)
+    v = np.concatenate([np.random.default_rng(5).uniform(-7, 7, 20000), np.linspace(-6.01, 6.01, 4001)]).astype(np.float32)
+    j = np.rint((np.clip(v.astype(np.float64), -6.0, 5.99609375) + 6.0) * 256.0).astype(int)
+    got = (lines[j, 0] + lines[j, 1] * v.astype(np.float64)).astype(np.float32)
+    want = np.array([0.5 * float(t) * (1.0 + math.erf(float(t) / math.sqrt(2.0))) for t in v])
+    assert (np.abs(got - want) <= 1.25 * worst + 6e-8 * np.abs(want)).all()

@@ -392,3 +392,70 @@ def test_codes_of_rows_in_pieces(eg, rows, cols):
         want = torch.clamp(torch.round(y * torch.tensor(127.0 / 5.0, dtype=torch.float64).float().item()), -127, 127).to(torch.int8)
         assert torch.equal(q[:, :cols], want)
         assert not q[:, cols:].any()
+
+
+# The first feed-forward layer that writes the codes of its GELU itself (two passes over its sums), on each of its tiles with rows
+# and columns that end inside: the observed run keeps the fp32 tensor and the row quantiser, A_R has to be the same bit for bit.
+# spread: pre-activations so small that the largest |gelu| is a negative value's, ordinary ones, some beyond the table's ends.
+GELU_TILES = [((64, 64), 2, 37, 200), ((128, 64), 20, 65, 1540), ((128, 192), 32, 60, 2308), ((128, 128), 40, 65, 2308),
+              ((256, 192), 40, 65, 3083), ((256, 256), 100, 70, 2056)]
+
+
+def _gelu_tile(M, N, cu):
+    cost = {}
+    for bm, bn, resident, penalty in ((256, 256, 1, 1.0), (256, 192, 1, 1.0), (128, 192, 1, 1.07), (128, 128, 2, 1.07), (128, 64, 2, 1.07),
+                                      (64, 64, 2, 1.07)):
+        tiles = -(-M // bm) * -(-N // bn)
+        cost[(bm, bn)] = -(-tiles // (cu * resident)) * (bm * bn * resident + 14336) * penalty
+    return min(cost, key=cost.get)
+
+
+def _same_observed_and_not(eg, wl, per_channel=False, biases=True):
+    import gpu_common as gc
+    ref = eg.make_reference(wl.kind, wl.dims, [gc.to_dev(w) for w in wl.weights], [gc.to_dev(b) if biases else None for b in wl.biases],
+                            per_channel=per_channel)
+    x, ws = gc.to_dev(wl.x), eg.workspace(eg.workspace_bytes(ref.desc), "cuda")
+    got = [torch.empty(gc.a_ref_numel(wl), device="cuda") for _ in range(2)]
+    taps, bufs, _keep = eg.make_taps(ref, gc.tap_shapes(wl), "cuda")
+    eg.ref_forward(ref, x, got[0], ws, taps)
+    eg.ref_forward(ref, x, got[1], ws)
+    assert eg.check(ws) == eg.OK
+    assert torch.equal(got[0], got[1])
+    return bufs
+
+
+@pytest.mark.parametrize("spread,per_channel,biases", [(1.0, False, False), (0.03, False, False), (12.0, False, True), (0.03, True, True)])
+@pytest.mark.parametrize("tile,b,s,ffn", GELU_TILES, ids=["x".join(map(str, t[0])) for t in GELU_TILES])
+def test_gelu_codes_from_the_gemm(eg, tile, b, s, ffn, spread, per_channel, biases):
+    import synth_inputs as si
+    assert _gelu_tile(b * s, ffn, torch.cuda.get_device_properties(0).multi_processor_count) == tile
+    wl = si.make_bert(b=b, s=s, hidden=68, heads=2, ffn=ffn, seed=17, train_act_dtype="f32")
+    wl.weights[2] *= np.float32(spread)
+    wl.biases[2] = np.linspace(-0.3, 0.2 * spread, ffn).astype(np.float32)
+    bufs = _same_observed_and_not(eg, wl, per_channel, biases)
+    top = bufs[2]["y"].max().item()                                # of gelu(v): 0.35 at the shortcut's line
+    assert (top < 0.3) == (spread < 1.0) and (top > 9.0) == (spread > 1.0), top
+
+
+# Values that all sit on the border of two codes: a wave's list overflows and it works its values out from the operands.  Equal
+# tokens have equal sums, which the biases lift to the border (largest value 3, code 60.5).
+@pytest.mark.parametrize("b,s,ffn", [(3, 33, 100), (40, 65, 3083)])
+def test_gelu_codes_on_the_border(eg, b, s, ffn):
+    import math
+    import synth_inputs as si
+    wl = si.make_bert(b=b, s=s, hidden=64, heads=2, ffn=ffn, seed=19, train_act_dtype="f32")
+    wl.x[:] = wl.x[:1, :1]
+    bufs = _same_observed_and_not(eg, wl, biases=False)
+    acc = bufs[2]["acc"][0].cpu().numpy().astype(np.float64)
+    scale = np.float64(np.float32(bufs[2]["x_scale"].item()) * np.float32(np.abs(wl.weights[2]).max() / np.float64(127.0)))
+    gelu = lambda v: 0.5 * v * (1.0 + math.erf(v / math.sqrt(2.0)))  # noqa: E731
+    lo, hi = 0.0, 3.0
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if gelu(mid) / gelu(3.0) * 127.0 < 60.5 else (lo, mid)
+    v = np.full(ffn, lo)
+    v[0] = 3.0
+    wl.biases[2] = (v - acc * scale).astype(np.float32)
+    bufs = _same_observed_and_not(eg, wl)
+    codes = bufs[3]["x_q"][:, 1:ffn]
+    assert set(torch.unique(codes).tolist()) <= {60, 61}
