@@ -2,6 +2,7 @@
 exports every function include/egeria.h declares, sizes workspaces sanely and
 rejects bad arguments before anything would be launched."""
 import ctypes
+import math
 import os
 import re
 
@@ -254,3 +255,31 @@ def test_gelu_lines_are_what_their_generator_writes():
     got = (lines[j, 0] + lines[j, 1] * v.astype(np.float64)).astype(np.float32)
     want = np.array([0.5 * float(t) * (1.0 + math.erf(float(t) / math.sqrt(2.0))) for t in v])
     assert (np.abs(got - want) <= 1.25 * worst + 6e-8 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("per_channel", [False, True])
+def test_snapshot_plan_places_every_tensor(eg, per_channel):
+    """Codes and scales of a snapshot lie side by side in their two allocations, on 16-byte boundaries, and the views of a
+    group's rows start where the kernels write."""
+    shapes = [(40, 33), (16, 16, 3, 3), (7, 48), (5, 33), (0, 20), (16, 5, 3, 3), (9, 40), (3, 48, 1, 1), (11, 3, 3, 3)]
+    plan = eg._snapshot_plan(tuple(shapes), per_channel)
+    starts = {}
+    for shape, stride, at, outs in plan.groups:
+        assert stride[0] == math.prod(shape[1:]) and sum(outs) == shape[0]
+        for n in outs:
+            starts[len(starts)] = (at, n, shape[1:])
+            at += n * stride[0]
+    end_q, end_s = [], []
+    for i, s in enumerate(shapes):
+        o, c, kh, kw, q, sc = plan.rows[i]
+        cp = eg.padded(c)
+        assert (o, c, kh, kw) == (*s, 1, 1)[:4] and q % 16 == 0 and sc % 16 == 0
+        assert starts[plan.order[i]] == (q, o, (kh, kw, cp) if len(s) == 4 else (cp,))
+        end_q.append((q, q + o * kh * kw * cp))
+        end_s.append((sc, sc + 4 * (o if per_channel else 1)))
+        assert plan.cuts[i] == (o if per_channel else 1) and plan.room[i] % 4 == 0 and plan.room[i] >= plan.cuts[i]
+    for spans, total in ((end_q, plan.codes), (end_s, 4 * plan.scales)):
+        spans = sorted(spans)
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and spans[-1][1] <= total
+    with pytest.raises(ValueError):
+        eg._snapshot_plan(((4, 5, 6),), per_channel)
