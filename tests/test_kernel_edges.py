@@ -459,3 +459,19 @@ def test_gelu_codes_on_the_border(eg, b, s, ffn):
     bufs = _same_observed_and_not(eg, wl)
     codes = bufs[3]["x_q"][:, 1:ffn]
     assert set(torch.unique(codes).tolist()) <= {60, 61}
+
+
+# Images whose planes are no whole 16-byte units, through LDS by groups of 64, 32 and 16 channels with all their pixels: the borders
+# of the groups' rule, pad channels, planes shorter than a unit, the longest, and the sizes that stay with the tile of 64 pixels.
+@pytest.mark.parametrize("n,c,h,w", [(1, 4, 1, 2), (2, 20, 1, 3), (3, 64, 7, 7), (2, 68, 7, 9), (2, 132, 5, 13), (1, 36, 1, 127), (2, 40, 3, 43),
+                                     (1, 20, 31, 33), (1, 20, 25, 41), (2, 33, 7, 7), (50, 260, 7, 7)])
+@pytest.mark.parametrize("static", [False, True])
+def test_odd_planes(eg, n, c, h, w, static):
+    x = torch.randn(n, c, h, w, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n * c + h)).clamp_(-4, 4)
+    x.view(-1)[-1] = -5.0
+    q, scale = eg.quantize_nchw(x, torch.tensor([5.0 / 127.0], device="cuda") if static else None)
+    inv = torch.tensor(1.0 / np.float64(np.float32(5.0 / 127.0)) if static else 127.0 / 5.0, dtype=torch.float64).float().item()
+    want = torch.clamp(torch.round(x * inv), -127, 127).to(torch.int8).permute(0, 2, 3, 1)
+    assert scale.item() == np.float32(5.0 / 127.0)
+    assert torch.equal(q[..., :c], want)
+    assert not q[..., c:].any()
