@@ -300,9 +300,9 @@ egeria_status forward_fc(Fwd &f, const void *x, egeria_dtype dt, float *a_ref)
 {
     const egeria_block_desc *d = f.d;
     const int64_t kp = pad16(d->c_in);
-    if (!f.is_static() && fc_input_is_small(d)) {
+    if (!f.is_static() && fc_input_is_small(d) && (!f.input_max_done || f.input_codes_done)) {
         // a small mini-batch: maximum, scale and codes in one workgroup and one launch
-        if (!f.input_max_done)
+        if (!f.input_codes_done)
             EG_HIP(launch_quantize_small(x, dt, (int)d->batch, (int)d->c_in, 1, (int)kp, f.qbuf(0), f.scale(0),
                                          ws_flag(f.ws), f.st));
     } else {
@@ -1098,10 +1098,14 @@ egeria_status egeria_refresh_eval(const egeria_weight *w, int32_t n_w, void *ws_
     job.nblk = job.n > 0 ? absmax_blocks(job.n, x_dt) : 0;
     if (desc->kind == EGERIA_FC_RELU && !qw->act_scale && desc->ref_precision == EGERIA_REF_INT8 &&
         desc->act_scheme == EGERIA_ACT_SYMMETRIC && fc_input_is_small(desc)) {
-        // the whole quantisation of a small FC input is one workgroup's work
+        // The whole quantisation of a small FC input is one workgroup's work.  It takes that workgroup 3 us, twice as long as
+        // the others' share of a snapshot's first pass (32 x 512 values, 512 x 512 weights), so beside a snapshot of two
+        // launches the input goes the long way too: its maximum with the first, its codes with the second (the step 20.4 ->
+        // 19.1 us).
         job.n = (int64_t)desc->batch * desc->c_in;
-        job.nblk = 1;
-        job.q = (int8_t *)((char *)ws + p.off_q[0]);
+        const bool two = n_w == 1 && !w[0].per_channel && (int64_t)w[0].out * w[0].in > kSmallTensor;
+        job.nblk = two ? absmax_blocks(job.n, x_dt) : 1;
+        if (!two) job.q = (int8_t *)((char *)ws + p.off_q[0]);
         job.scale_out = ws_scale(ws, p.slots, 0);
         job.flag = ws_flag(ws);
         job.rows = desc->batch; job.cols = desc->c_in; job.cp = (int32_t)pad16(desc->c_in);
@@ -1135,6 +1139,7 @@ egeria_status egeria_refresh_eval(const egeria_weight *w, int32_t n_w, void *ws_
     bool carried = false, codes = false;
     EG_OK(quantize_weights_impl(w, n_w, ws_w, ws_w_bytes, stream, job.n > 0 ? &job : nullptr, &carried,
                                 qj.kind != 0 ? &qj : nullptr, &codes));
+    codes = codes || (carried && job.q);
     return forward_impl(desc, qw, x, x_dt, nullptr, nullptr, a_train, t_dt, p_out, ws, p, (hipStream_t)stream, carried,
                         codes);
 }

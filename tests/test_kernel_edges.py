@@ -475,3 +475,20 @@ def test_odd_planes(eg, n, c, h, w, static):
     assert scale.item() == np.float32(5.0 / 127.0)
     assert torch.equal(q[..., :c], want)
     assert not q[..., c:].any()
+
+
+# A small FC mini-batch beside a snapshot of one launch and of two, per tensor and per channel: the same as the two calls.
+@pytest.mark.parametrize("b,k,n,per_channel", [(5, 40, 30, False), (32, 512, 512, False), (32, 512, 512, True), (7, 100, 700, False), (64, 250, 66, False)])
+def test_fc_refresh_is_the_two_calls(eg, b, k, n, per_channel):
+    from paper_2201_06227_amd.evaluator import PlasticityEvaluator
+    gen = torch.Generator(device="cuda").manual_seed(b + k)
+    for dt in (torch.float32, torch.bfloat16):
+        x, wt = torch.randn(b, k, device="cuda", generator=gen).to(dt), torch.randn(n, k, device="cuda", generator=gen) * k ** -0.5
+        a_t = [torch.relu(x.float() @ (wt * 1.01).t())]
+        ev = PlasticityEvaluator(eg.FC_RELU, dict(batch=b, c_in=k, c_out=n), [wt], [None], per_channel=per_channel)
+        one = ev.step(x, a_t).clone()
+        codes, scales = ev.w_q[0].clone(), ev.scales[0].clone()
+        ev.w_q[0].zero_(); ev.scales[0].zero_()
+        two = ev.step_two_calls(x, a_t)
+        assert torch.equal(one, two) and torch.equal(codes, ev.w_q[0]) and torch.equal(scales, ev.scales[0])
+        assert eg.check(ev.ws) == eg.OK
