@@ -966,7 +966,7 @@ static hipError_t launch_variant(const GemmArgs &g, hipStream_t st)
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     if (g.conv3x3) {
-        if constexpr (EPI != kStore || WM * WN != 4) {
+        if constexpr (EPI != kStore || BM * BN > 256 * 128) {
             return hipErrorInvalidValue;                         // shapes for linear layers only
         } else {
             static bool set[kMaxDevices] = {};                   // the attribute belongs to one device's code object
@@ -1365,7 +1365,7 @@ static const TileShape kShapes[kNumShapes + 3] = {
     {256, 128, 64, 2, 4, 1.06},  {128, 192, 64, 2, 4, 1.10}, {128, 128, 64, 3, 4, 1.20},  {128, 128, 128, 2, 4, 1.22},
     {128, 64, 64, 4, 4, 1.40},   {128, 64, 128, 3, 4, 1.38}, {256, 256, 128, 1, 8, 1.00}, {256, 192, 128, 1, 8, 1.02},
     // three stages of whole lines, for layers that bring a compute unit one workgroup or two (chosen by rule, not by price)
-    {64, 64, 128, 3, 4, 0.0},    {128, 64, 128, 2, 4, 0.0},  {128, 128, 128, 1, 4, 0.0},
+    {64, 64, 128, 3, 4, 0.0},    {128, 64, 128, 2, 8, 0.0},  {128, 128, 128, 1, 8, 0.0},
 };
 
 template <int ET>
@@ -1381,8 +1381,8 @@ static hipError_t launch_shape(int i, const GemmArgs &g, hipStream_t st)
     case 6: return launch_variant<256, 256, 2, 4, 128, ET>(g, st);
     case 7: return launch_variant<256, 192, 4, 2, 128, ET>(g, st);
     case kDeepSmall: return launch_variant<64, 64, 2, 2, 128, ET, kStore, 3>(g, st);
-    case kDeepMid: return launch_variant<128, 64, 2, 2, 128, ET, kStore, 3>(g, st);
-    case kDeepLarge: return launch_variant<128, 128, 2, 2, 128, ET, kStore, 3>(g, st);
+    case kDeepMid: return launch_variant<128, 64, 4, 2, 128, ET, kStore, 3>(g, st);
+    case kDeepLarge: return launch_variant<128, 128, 2, 4, 128, ET, kStore, 3>(g, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1442,6 +1442,9 @@ static hipError_t launch_gelu(const GemmArgs &g, hipStream_t st)
 // 2304 (3x3) 18.2 / 21.2 / 17.8 / 16.7; 4096 x 768 x 768 8.5 with all of them; and up to a whole round of
 // 128x128 tiles (another run) 4992 x 768 x 3072 22.5 / 24.1 / 22.0 / 20.2, 8000 x 512 x 1536 16.1 / 17.1 / 17.1 / 16.0, 10500 x 260 x
 // 2448 (3x3) 21.9 / 26.1 / 21.1 / 19.9.
+//   The 128-row ones of these have eight waves: two on a SIMD, one at its operand reads while the other multiplies (four waves /
+// eight, us: 4096 x 768 x 3072 20.0 / 18.9, 3000 x 1024 x 4096 23.8 / 22.2, 12544 x 256 x 1024 11.8 / 11.4, 12544 x 256 x 2304 (3x3)
+// 18.9 / 17.8, 6468 x 256 x 2304 (3x3) 14.5 / 13.6, 21560 x 128 x 1152 (3x3) 12.8 / 12.0; a fourth stage changes nothing).
 static int choose_shape(int64_t M, int32_t N, int64_t kp, bool conv3x3)
 {
     const int64_t cu = compute_units(), t64 = ((M + 63) / 64) * ((N + 63) / 64), t128x64 = ((M + 127) / 128) * ((N + 63) / 64),
