@@ -1248,13 +1248,13 @@ __global__ __launch_bounds__(256) void attention_settle_kernel(const float *__re
 // the listed values in fp64 and overwrites their codes.  A re-evaluation needs all keys of its head (S x dh floats): read
 // from global memory per value, that traffic (and the sixteen-byte pieces of 256 different rows each load instruction asks
 // for) would bound the whole step.  The workgroup copies the head's keys into LDS, 256 at a
-// time, with coalesced loads, and each of its waves re-evaluates one listed value from there: lane l holds keys l,
-// l + 64, ..., a row of LDS each (rows padded by 16 bytes, so the lanes' 16-byte reads do not collide), the query row is
-// broadcast from LDS, and only the value column (one float per key) comes from global memory.  Up to 256 keys are copied
-// once; more are copied for every four values.  What bounds it: a workgroup's chain of round trips (its keys 4 us, codes 3,
-// four re-evaluations 4, of which it has one to three) and, for many heads, the value columns: a line per key and value
-// listed, four to twelve of them per head and 256 tokens.  64 x 256 tokens x 12 heads, us: attention 87, settling the
-// maximum 9, this kernel 64 (82 with the settling inside).  (Eight waves and 128 registers: spills, 30 % longer.)
+// time, with coalesced loads, and re-evaluates sixteen listed values together from there, on the fp64 matrix cores (rows padded by
+// 16 bytes against bank conflicts); only the value columns (one float per key and value) come from global memory.  Up to 256 keys are
+// copied once; more are copied for every sixteen values.  What bounds it: a workgroup's chain of round trips (its keys 4 us, codes
+// 3, sixteen re-evaluations 5, of which it has one as a rule) and, for many heads, the value columns: a line per key and value
+// listed, four to twelve of them per head and 256 tokens.  With a value per wave and its keys spread over the lanes (four values
+// in 4 us, two to six times over) it took, us: 24 x 197 tokens x 12 heads 42, now 25; in the stack of 64 x 256 tokens 64, now 47; 8 x
+// 384 x 12 49, now 27.  (Eight waves and 128 registers: spills, 30 % longer.)
 constexpr int kKeysLds = 256;            // keys a workgroup can hold
 constexpr int kKeyRow = kDh + 4;         // floats per key row in LDS (one 16-byte pad)
 
@@ -1283,7 +1283,7 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
     __shared__ uint32_t todo[kList];
     __shared__ uint32_t n_todo, more;
     __shared__ __attribute__((aligned(16))) float ks[kKeysLds * kKeyRow];
-    __shared__ __attribute__((aligned(16))) float qs[NW * kDh];
+    __shared__ double red[NW][16][3];                             // the waves' maximum and sums of sixteen values
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t piece = xcd_piece(blockIdx.x, gridDim.x), bh = piece / (uint32_t)splits, share = piece - bh * (uint32_t)splits;
     const uint32_t bi = bh / (uint32_t)heads, hd = bh - bi * (uint32_t)heads;
@@ -1417,75 +1417,101 @@ __global__ __launch_bounds__(kCertifyThreads, 2) void quantize_attention_certify
             const uint32_t n = n_todo < kList ? n_todo : kList;
             again = more != 0;
             met += n;
-            const int cpr = dh >> 2;                          // 16-byte pieces per row
-            for (uint32_t k0 = 0; k0 < n; k0 += NW) {         // a value per wave
-                const uint32_t k = k0 + (uint32_t)wave;
-                const bool active = k < n;
-                const uint32_t e = todo[active ? k : k0];
+            // Sixteen listed values at a time: S^T = K Q^T on v_mfma_f64_16x16x4f64 as in attention_kernel, lane (c, g) holding, of
+            // every 16-key tile, keys 4 r + g of value c's query.  A wave takes every fourth tile with a running maximum
+            // of its own; the waves' sums meet at the end.
+            const int c = lane & 15, g = lane >> 4;
+            for (uint32_t k0 = 0; k0 < n; k0 += 16) {
+                const uint32_t k = k0 + (uint32_t)c;
+                const uint32_t e = todo[k < n ? k : k0];
                 const uint32_t t = e / (uint32_t)dh, d = e - t * (uint32_t)dh;
-                qs[wave * kDh + lane] = lane < dh ? qb[(int64_t)t * ld + lane] : 0.0f;
-                double m = -INFINITY, l = 0.0, o = 0.0;       // l and o: this lane's share
-                for (int j0 = 0; j0 < S; j0 += kKeysLds) {    // one round up to 256 keys
-                    const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds, nk = (nj + 63) >> 6;   // keys; keys per lane
-                    float vj[4];
+                double q[16];                                 // dims 16 u + 4 g + i in q[4 u + i]
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) {
-                        const int j = lane + 64 * kk;
-                        vj[kk] = vb[(int64_t)(j0 + (j < nj ? j : nj - 1)) * ld + d];
-                    }
+                for (int u = 0; u < 4; ++u) {
+                    const int d0 = 16 * u + 4 * g;
+                    const float4 x = *(const float4 *)(qb + (int64_t)t * ld + (d0 < dh ? d0 : 0));
+                    q[4 * u] = d0 < dh ? (double)x.x : 0.0;
+                    q[4 * u + 1] = d0 < dh ? (double)x.y : 0.0;
+                    q[4 * u + 2] = d0 < dh ? (double)x.z : 0.0;
+                    q[4 * u + 3] = d0 < dh ? (double)x.w : 0.0;
+                }
+                double m = -INFINITY, l = 0.0, o = 0.0;       // the wave's maximum, this lane's share of its sums
+                for (int j0 = 0; j0 < S; j0 += kKeysLds) {    // one round up to 256 keys
+                    const int nj = S - j0 < kKeysLds ? S - j0 : kKeysLds;
+                    float vj[4][4];                           // the value column at the lane's keys
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int j = 16 * (wave + NW * kk) + 4 * r + g;
+                            vj[kk][r] = vb[(int64_t)(j0 + (j < nj ? j : nj - 1)) * ld + d];
+                        }
                     if (S > kKeysLds) {
                         __syncthreads();                      // the keys of the round before have been read
                         stage_keys(j0);
+                        __syncthreads();
                     }
-                    __syncthreads();
-                    if (active) {
-                        // a product of two fp32 values is exact in fp64, so each fma is the multiply and the
-                        // add of the plain definition, dims in ascending order
-                        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                    double sc[4][4], mx = -INFINITY;
 #pragma unroll
-                        for (int u4 = 0; u4 < kDh / 4; ++u4) {
-                            if (u4 < cpr) {
-                                const float4 qv = *(const float4 *)&qs[wave * kDh + 4 * u4];
+                    for (int kk = 0; kk < 4; ++kk) {
+                        const int tile = 16 * (wave + NW * kk);
+                        v4d acc = {0.0, 0.0, 0.0, 0.0};
+                        if (tile < nj) {                      // (uniform)
+                            const float *row = &ks[(tile + c < nj ? tile + c : nj - 1) * kKeyRow + 4 * g];
 #pragma unroll
-                                for (int kk = 0; kk < 4; ++kk) {
-                                    if (kk < nk) {
-                                        const int j = lane + 64 * kk;
-                                        const float4 kv = *(const float4 *)&ks[(j < nj ? j : nj - 1) * kKeyRow + 4 * u4];
-                                        acc[kk] = fma((double)qv.x, (double)kv.x, acc[kk]);
-                                        acc[kk] = fma((double)qv.y, (double)kv.y, acc[kk]);
-                                        acc[kk] = fma((double)qv.z, (double)kv.z, acc[kk]);
-                                        acc[kk] = fma((double)qv.w, (double)kv.w, acc[kk]);
-                                    }
-                                }
+                            for (int u = 0; u < 4; ++u) {
+                                const bool in = 16 * u + 4 * g < dh;
+                                const float4 kv = *(const float4 *)(row + (in ? 16 * u : -4 * g));
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)kv.x : 0.0, q[4 * u], acc, 0, 0, 0);
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)kv.y : 0.0, q[4 * u + 1], acc, 0, 0, 0);
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)kv.z : 0.0, q[4 * u + 2], acc, 0, 0, 0);
+                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)kv.w : 0.0, q[4 * u + 3], acc, 0, 0, 0);
                             }
                         }
-                        double sc[4], mx = -INFINITY;
 #pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            sc[kk] = lane + 64 * kk < nj ? acc[kk] * scale : -INFINITY;
-                            mx = fmax(mx, sc[kk]);
-                        }
-                        const double mnew = fmax(m, wave_max(mx));
-                        if (j0) {
-                            const double corr = exp(m - mnew);
-                            l *= corr;
-                            o *= corr;
-                        }
-                        m = mnew;
-#pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) {
-                            const double pr = exp(sc[kk] - m);   // exp(-inf) = 0 for the keys beyond S
-                            l += pr;
-                            o += pr * (double)vj[kk];
+                        for (int r = 0; r < 4; ++r) {
+                            sc[kk][r] = tile + 4 * r + g < nj ? acc[r] * scale : -INFINITY;
+                            mx = fmax(mx, sc[kk][r]);
                         }
                     }
+                    mx = fmax(mx, lane_xor<16>(mx));
+                    mx = fmax(mx, lane_xor<32>(mx));
+                    const double mnew = fmax(m, mx);
+                    if (mnew > -INFINITY) {                   // (a wave may have had no key yet)
+                        const double corr = exp(m - mnew);    // 0 in the first round
+                        l *= corr;
+                        o *= corr;
+                        m = mnew;
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const double pr = exp(sc[kk][r] - m);   // exp(-inf) = 0 for the keys beyond S
+                                l += pr;
+                                o += pr * (double)vj[kk][r];
+                            }
+                    }
                 }
-                if (active) {
-                    l = wave_sum(l);
-                    o = wave_sum(o);
-                    if (lane == 0) xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1((float)(o / l), inv);
+                l += lane_xor<16>(l);
+                l += lane_xor<32>(l);
+                o += lane_xor<16>(o);
+                o += lane_xor<32>(o);
+                if (g == 0) { red[wave][c][0] = m; red[wave][c][1] = l; red[wave][c][2] = o; }
+                __syncthreads();
+                if (tid < 16 && k < n) {
+                    double top = red[0][c][0];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) top = fmax(top, red[w][c][0]);
+                    double ls = 0.0, os = 0.0;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) {
+                        const double f = exp(red[w][c][0] - top);
+                        ls += red[w][c][1] * f;
+                        os += red[w][c][2] * f;
+                    }
+                    xq[(int64_t)(tok0 + t) * ldq + hd * dh + d] = (int8_t)quant1((float)(os / ls), inv);
                 }
-                __syncthreads();                              // qs is free
+                __syncthreads();                              // red is free
             }
         } while (again);
     }
