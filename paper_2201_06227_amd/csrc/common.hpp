@@ -386,6 +386,15 @@ __device__ __forceinline__ uint32_t xcd_piece(uint32_t blk, uint32_t n)
     return x * (n >> 3) + (x < rest ? x : rest) + (blk >> 3);
 }
 
+// Cache policy of stores that the next kernel reads (the auxiliary operand of a raw buffer store): written through the L2, which
+// keeps the line.  What a kernel leaves dirty in the L2s has to be written back before the next one may start; written through
+// it is on its way while the kernel runs.  Plain / this way, us: 48 MB 9.2 / 8.3, 15 MB 4.7 / 3.6 (alone); of the GEMMs' outputs,
+// whole passes: affine forward of 64 x 1024 x 14 x 14 83.0 / 80.4, bottleneck step 111.5 / 108.9, static block 67.6 / 66.0, two ragged
+// encoder layers 406.2 / 400.4, float16 layer 183.4 / 180.1, one encoder layer 186.2 / 183.9; nothing where the outputs
+// overflow the L2s many times (12-layer stack of 64 x 256 tokens).
+constexpr int kThrough = 16;         // sc1
+constexpr int kBufferWord = 0x00020000;
+
 // Between LDS writes of a wave and reads of what its other lanes have written (or the other way round): the wave's LDS
 // traffic is in order, so nothing is awaited; the compiler, which reasons about one lane, must not move either across.
 __device__ __forceinline__ void wave_lds_turn()

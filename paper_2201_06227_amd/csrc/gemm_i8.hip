@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
         if (tile == 0 && tid == 0) publish(scale, bad, g.gelu_scale, nullptr, g.flag);
     }
     // which form the epilogue takes: decided while the first K steps are on their way
-    int inside = EPI == kStore && m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in &&
+    int inside = EPI == kStore && m0 + BM <= g.M && n0 + BN <= g.N && !g.acc_out && !g.zp_in && g.ldy < (1 << 20) && g.q_ld < (1 << 20) &&
                  (ET == 0 && BM * BN <= 128 * 128 ? (g.q_out ? g.act == 1 && !g.res_q : g.y != nullptr) : g.y && !g.q_out && !g.res_q);
     inside = __builtin_amdgcn_readfirstlane(inside);
     asm volatile("" : "+s"(inside));
@@ -409,6 +409,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
         static_assert((size_t)NST * STAGE >= (size_t)32 * YS * 4, "a 32-row block must fit the stage memory");
         float *yt = (float *)lds;
         const int H = g.N, nv = H >> 2;
+        const __amdgpu_buffer_rsrc_t rln = __builtin_amdgcn_make_buffer_rsrc((void *)(g.ln_out + m0 * H), 0, BM * H * 4, kBufferWord);
         const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f), one4 = make_float4(1.f, 1.f, 1.f, 1.f);
         float4 gmv[NV], btv[NV];
 #pragma unroll
@@ -460,7 +461,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll
                     for (int u = 0; u < NV; ++u) {
                         const int c = lane + 64 * u;
-                        if (c < nv) reinterpret_cast<float4 *>(g.ln_out + row * H)[c] = o[u];
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o[u]), rln, (int)(c < nv ? (uint32_t)(i * 32 + lr) * (uint32_t)H * 4u + (uint32_t)c * 16u : kOob), 0, kThrough);
                     }
                 }
             }
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                         for (int q = 0; q < 4; ++q) w[q] = pack_bytes(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
                         const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
                         const v4u out = {(unsigned)a[0], (unsigned)a[1], (unsigned)b[0], (unsigned)b[1]};
-                        __builtin_amdgcn_raw_buffer_store_b128(out, rq, (int)(c16 == kOob ? kOob : row * q_ld + c16), 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(out, rq, (int)(c16 == kOob ? kOob : row * q_ld + c16), 0, kThrough);
                         if (__ballot(any)) {                                             // rare
                             float *turn = (float *)(list + kGeluList);       // the block's values, by register and lane
                             uint32_t open = 0;
@@ -669,7 +670,10 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
         auto direct = [&](auto relu_c, auto res_c, auto qout_c) {
             constexpr bool RELU = decltype(relu_c)::value, RES = decltype(res_c)::value, QOUT = decltype(qout_c)::value;
             const int32_t keep = RELU || g.amax_pos ? -1 : 0x7fffffff;
-            const uint32_t yoff = (uint32_t)(lrow * g.ldy + lcol), qoff = QOUT ? (uint32_t)(lrow * g.q_ld + lcol) : 0u;
+            // buffers of the tile's rows: a lane's place in a 32x32 block, and what the block and the register add, in scalars
+            const __amdgpu_buffer_rsrc_t ryd = __builtin_amdgcn_make_buffer_rsrc((void *)(g.y + m0 * g.ldy), 0, g.y ? (int)(BM * g.ldy * 4) : 0, kBufferWord);
+            const __amdgpu_buffer_rsrc_t rqd = __builtin_amdgcn_make_buffer_rsrc((void *)(g.q_out + m0 * g.q_ld), 0, QOUT ? (int)(BM * g.q_ld) : 0, kBufferWord);
+            const int yoff = (int)((uint32_t)(lrow * g.ldy + lcol) * 4u), qoff = QOUT ? (int)(lrow * g.q_ld + lcol) : 0;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int col0 = n0 + (wn_u * TN + j) * 32;
@@ -677,17 +681,15 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                 const float sj = g.sw_per_n ? sxv * g.sw[col0 + lcol] : s;     // one fp32 multiply
 #pragma unroll
                 for (int i = 0; i < TM; ++i) {
-                    const int64_t row0 = m0 + (wm_u * TM + i) * 32;
-                    float *yb = g.y + row0 * g.ldy + col0;
-                    int8_t *qb = g.q_out + row0 * g.q_ld + col0;
+                    const int row0 = (wm_u * TM + i) * 32;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int rr = 8 * (r >> 2) + (r & 3);
                         float v = fmaf((float)acc[i][j][r], sj, bj);
                         if constexpr (RES) v = v + (float)(int8_t)lds[((wm_u * TM + i) * 32 + lrow + rr) * BN + (wn_u * TN + j) * 32 + lcol] * rs;
                         if (RELU) v = v > 0.0f ? v : 0.0f;
-                        if (!QOUT || g.y) yb[(size_t)rr * g.ldy + yoff] = v;
-                        if (QOUT) qb[(size_t)rr * g.q_ld + qoff] = (int8_t)quant1(v, q_inv);
+                        if (!QOUT || g.y) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ryd, yoff, (int)((row0 + rr) * g.ldy + col0) * 4, kThrough);
+                        if (QOUT) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)quant1(v, q_inv), rqd, qoff, (int)((row0 + rr) * g.q_ld + col0), kThrough);
                         const int32_t bits = (int32_t)__float_as_uint(v) & keep;
                         amax = amax > bits ? amax : bits;
                     }
@@ -830,8 +832,8 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                             amax = amax > bits ? amax : bits;
                         }
                     }
-                    __builtin_amdgcn_raw_buffer_store_b128(w, ry, (int)(ycol + (uint32_t)(row0 + p * RPI) * ystep), 0, 0);
-                    if (QOUT) __builtin_amdgcn_raw_buffer_store_b32(codes, rq, (int)(qcol + (uint32_t)(row0 + p * RPI) * (uint32_t)g.q_ld), 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(w, ry, (int)(ycol + (uint32_t)(row0 + p * RPI) * ystep), 0, kThrough);
+                    if (QOUT) __builtin_amdgcn_raw_buffer_store_b32(codes, rq, (int)(qcol + (uint32_t)(row0 + p * RPI) * (uint32_t)g.q_ld), 0, kThrough);
                 }
             }
         };
