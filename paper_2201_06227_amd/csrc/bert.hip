@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
                                                             float *__restrict__ y,
                                                             uint32_t *__restrict__ absmax_out)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row = (int64_t)xcd_piece(blockIdx.x, gridDim.x) * 4 + wave;
     const int nv = H >> 2;
     uint32_t amax = 0;
@@ -89,11 +89,10 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
         }
         float4 o[NV];
         ln_row_vec<NV>(xv, rv, gmv, btv, lane, nv, H, eps, o, amax);
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)(y + row * H), 0, H * 4, kBufferWord);   // (a unit beyond the row is dropped)
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int c = lane + 64 * i;
-            if (c < nv) reinterpret_cast<float4 *>(y + row * H)[c] = o[i];
-        }
+        for (int i = 0; i < NV; ++i)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o[i]), ry, (lane + 64 * i) * 16, 0, kThrough);
     }
     if (absmax_out) {
         __shared__ uint32_t sm4[4];
@@ -651,7 +650,6 @@ __global__ __launch_bounds__(256) void attention_fast_kernel(const float *__rest
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
 typedef _Float16 v2hf __attribute__((ext_vector_type(2)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // (defined further down; the kernel below ends with the exact evaluation of its candidates for the maximum)
 __device__ __forceinline__ float context_exact(const float *__restrict__ qkv, int S, int Hd, int heads, int dh, double scale,
                                                uint32_t el, double *red);

@@ -47,6 +47,7 @@ __global__ __launch_bounds__(256) void cast_chlast_kernel(const void *__restrict
     const int64_t per = hw == 1 ? upr : (FORM == kPlanes ? hw >> 2 : hw);
     const int64_t total = n * upr * (hw == 1 ? 1 : per);
     const int64_t end = beg + share < total ? beg + share : total;
+    const __amdgpu_buffer_rsrc_t rows_out = __builtin_amdgcn_make_buffer_rsrc(out + beg * 16, 0, 0x7fffffff, kBufferWord);   // kRows: unit u is the u-th of the output
     const bool narrow = total < (1LL << 32);
     for (int64_t u = beg + threadIdx.x; u < end; u += 256) {
         const int64_t rest = narrow ? (int64_t)((uint32_t)u / (uint32_t)per) : u / per, at = u - rest * per;
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(256) void cast_chlast_kernel(const void *__restrict
                 f[4 * j + 2] = in ? v[j].z : 0.0f;
                 f[4 * j + 3] = in ? v[j].w : 0.0f;
             }
-            *dst = pack_unit<ET>(f);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, pack_unit<ET>(f)), rows_out, (int)(u - beg) * 16, 0, kThrough);
         } else {
             float f[EPU];
 #pragma unroll

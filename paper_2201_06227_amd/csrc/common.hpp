@@ -372,6 +372,7 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
 // ---- device helpers ------------------------------------------------------------
 #ifdef __HIPCC__
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
 // Which of the launch's n pieces workgroup blk takes.  Workgroup ids go round the 8 XCDs, and each XCD has an L2 of its own
@@ -391,7 +392,9 @@ __device__ __forceinline__ uint32_t xcd_piece(uint32_t blk, uint32_t n)
 // it is on its way while the kernel runs.  Plain / this way, us: 48 MB 9.2 / 8.3, 15 MB 4.7 / 3.6 (alone); of the GEMMs' outputs,
 // whole passes: affine forward of 64 x 1024 x 14 x 14 83.0 / 80.4, bottleneck step 111.5 / 108.9, static block 67.6 / 66.0, two ragged
 // encoder layers 406.2 / 400.4, float16 layer 183.4 / 180.1, one encoder layer 186.2 / 183.9; nothing where the outputs
-// overflow the L2s many times (12-layer stack of 64 x 256 tokens).
+// overflow the L2s many times (12-layer stack of 64 x 256 tokens).  Layer norms and row quantisers after that: the encoder layer
+// 178.0 / 174.2, the ragged ones 392.5 / 386.2.  Only for stores that fill their lines: the attention kernels' contexts, 4 or 16
+// bytes of a line at a time, cost more this way (the stack 5850 / 6040, the encoder layer 164.9 / 166.7).
 constexpr int kThrough = 16;         // sc1
 constexpr int kBufferWord = 0x00020000;
 

@@ -25,7 +25,6 @@
 namespace egeria {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 // K bytes per step, BK: 128 (one 128-byte cache line of every row per request)
 // or 64.  With 64-byte steps each line is fetched half now and half one step

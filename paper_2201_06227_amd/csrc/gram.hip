@@ -58,7 +58,6 @@ namespace egeria {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kSlab = 16;                // features of one matrix instruction
 constexpr int kGramWaves = 8;

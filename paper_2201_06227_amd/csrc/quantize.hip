@@ -216,6 +216,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
         const int64_t n4 = rows * (cols >> 2), end = (beg + per) * 4 < n4 ? (beg + per) * 4 : n4;
         const float4 *x4 = (const float4 *)x;
         float4 v[4];
+        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(q + beg * 16, 0, (int)((end - beg * 4) * 4), kBufferWord);
         auto request = [&](int64_t i) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = x4[i + 256 * k < end ? i + 256 * k : end - 1];
@@ -227,9 +228,9 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
         for (;;) {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                if (i + 256 * k < end)
-                    ((uint32_t *)q)[i + 256 * k] = quant1(v[k].x, inv) | (quant1(v[k].y, inv) << 8) | (quant1(v[k].z, inv) << 16) |
-                                                   (quant1(v[k].w, inv) << 24);
+                __builtin_amdgcn_raw_buffer_store_b32(quant1(v[k].x, inv) | (quant1(v[k].y, inv) << 8) | (quant1(v[k].z, inv) << 16) |
+                                                          (quant1(v[k].w, inv) << 24),
+                                                      rq, (int)(i - beg * 4 + 256 * k) * 4, 0, kThrough);   // (beyond the end: dropped)
             i += 1024;
             if (i - threadIdx.x >= end) break;
             request(i);
