@@ -13,7 +13,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
                                                         int H, const float *__restrict__ gamma,
                                                         const float *__restrict__ beta, double eps,
                                                         float *__restrict__ y,
-                                                        uint32_t *__restrict__ absmax_out)
+                                                        uint32_t *__restrict__ absmax_out, uint16_t *__restrict__ y_half)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t row = (int64_t)xcd_piece(blockIdx.x, gridDim.x) * 4 + wave;
@@ -36,6 +36,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
             const double gm = gamma ? (double)gamma[h] : 1.0, bt = beta ? (double)beta[h] : 0.0;
             const float o = (float)((v - mean) * rstd * gm + bt);
             y[row * H + h] = o;
+            if (y_half) y_half[row * H + h] = __builtin_bit_cast(uint16_t, (_Float16)o);
             const uint32_t ab = abs_bits(o);
             amax = amax > ab ? amax : ab;
         }
@@ -55,7 +56,8 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
                                                             int H, const float *__restrict__ gamma,
                                                             const float *__restrict__ beta, double eps,
                                                             float *__restrict__ y,
-                                                            uint32_t *__restrict__ absmax_out)
+                                                            uint32_t *__restrict__ absmax_out,
+                                                            uint16_t *__restrict__ y_half)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row = (int64_t)xcd_piece(blockIdx.x, gridDim.x) * 4 + wave;
@@ -93,6 +95,15 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, o[i]), ry, (lane + 64 * i) * 16, 0, kThrough);
+        if (y_half) {
+            const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void *)(y_half + row * H), 0, H * 2, kBufferWord);
+            typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const v4h half = {(_Float16)o[i].x, (_Float16)o[i].y, (_Float16)o[i].z, (_Float16)o[i].w};
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, half), rh, (lane + 64 * i) * 8, 0, kThrough);
+            }
+        }
     }
     if (absmax_out) {
         __shared__ uint32_t sm4[4];
@@ -104,23 +115,23 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 hipError_t launch_layernorm(const float *x, const float *res, int64_t rows, int32_t H,
                             const float *gamma, const float *beta, float eps, float *y,
-                            uint32_t *absmax_out, hipStream_t st)
+                            uint32_t *absmax_out, hipStream_t st, uint16_t *y_half)
 {
     if (rows <= 0) return hipSuccess;
     const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
     const bool vec = (H % 4) == 0 && H <= 1024 && aligned16(x) && aligned16(res) && aligned16(gamma) &&
-                     aligned16(beta) && aligned16(y);
+                     aligned16(beta) && aligned16(y) && (reinterpret_cast<uintptr_t>(y_half) & 7u) == 0;
     if (vec && H <= 256)
         return launch_k(EGERIA_KERNEL_LAYERNORM, layernorm_vec_kernel<1>, grid, block, 0, st, x, res, rows, (int)H,
-                        gamma, beta, (double)eps, y, absmax_out);
+                        gamma, beta, (double)eps, y, absmax_out, y_half);
     if (vec && H <= 768)
         return launch_k(EGERIA_KERNEL_LAYERNORM, layernorm_vec_kernel<3>, grid, block, 0, st, x, res, rows, (int)H,
-                        gamma, beta, (double)eps, y, absmax_out);
+                        gamma, beta, (double)eps, y, absmax_out, y_half);
     if (vec)
         return launch_k(EGERIA_KERNEL_LAYERNORM, layernorm_vec_kernel<4>, grid, block, 0, st, x, res, rows, (int)H,
-                        gamma, beta, (double)eps, y, absmax_out);
+                        gamma, beta, (double)eps, y, absmax_out, y_half);
     return launch_k(EGERIA_KERNEL_LAYERNORM, layernorm_kernel, grid, block, 0, st, x, res, rows, (int)H, gamma, beta,
-                    (double)eps, y, absmax_out);
+                    (double)eps, y, absmax_out, y_half);
 }
 
 // ---- multi-head self-attention -----------------------------------------------------------
@@ -146,7 +157,7 @@ template <int QB>
 __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict__ qkv, int B, int S,
                                                         int Hd, int heads, int dh, double scale,
                                                         float *__restrict__ ctx,
-                                                        uint32_t *__restrict__ absmax_out)
+                                                        uint32_t *__restrict__ absmax_out, uint16_t *__restrict__ ctx_half)
 {
     __shared__ __attribute__((aligned(16))) float sKb[2][kKeyTile][kKVPad];   // two stages
     __shared__ __attribute__((aligned(16))) float sVb[2][kKeyTile][kKVPad];
@@ -333,7 +344,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
     for (int qb = 0; qb < QB; ++qb) {
         const int q = qidx[qb];
         if (q >= S) continue;
-        float *dst = ctx + (tok0 + q) * Hd + hd * dh;
+        const int64_t dst = (tok0 + q) * Hd + hd * dh;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -341,7 +352,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
                 const int d = db * 16 + 4 * r + g;
                 if (d < dh) {
                     const float v = (float)(o[qb][db][r] / lrun[qb]);
-                    dst[d] = v;
+                    if (ctx_half) ctx_half[dst + d] = __builtin_bit_cast(uint16_t, (_Float16)v);
+                    else ctx[dst + d] = v;
                     const uint32_t ab = abs_bits(v);
                     amax = amax > ab ? amax : ab;
                 }
@@ -1627,7 +1639,7 @@ hipError_t launch_attention_certified(const float *qkv, int32_t B, int32_t S, in
 }
 
 hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads,
-                            float *ctx, uint32_t *absmax_out, hipStream_t st)
+                            float *ctx, uint32_t *absmax_out, hipStream_t st, uint16_t *ctx_half)
 {
     const int dh = Hd / heads;
     constexpr int QB = 1;               // one 16-query block per wave: ~120 VGPRs, several waves per SIMD
@@ -1636,7 +1648,7 @@ hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, 
     if (grid <= 0) return hipSuccess;
     if (dh > kDh || grid > 0x7ffffff0LL) return hipErrorInvalidValue;
     return launch_k(EGERIA_KERNEL_ATTENTION, attention_kernel<QB>, dim3((unsigned)grid), dim3(256), 0, st, qkv,
-                    (int)B, (int)S, (int)Hd, (int)heads, dh, 1.0 / sqrt((double)dh), ctx, absmax_out);
+                    (int)B, (int)S, (int)Hd, (int)heads, dh, 1.0 / sqrt((double)dh), ctx, absmax_out, ctx_half);
 }
 
 }  // namespace egeria

@@ -337,14 +337,16 @@ constexpr int kConvFuseMaxWidth = 256;      // image width up to which the halo 
 hipError_t launch_conv3x3_c16_fused(const GemmArgs &g, const ConvFuse &z, hipStream_t st);
 
 // y = LN(x + res) over rows of length H, optional atomicMax of |y|.
+// y_half: null, or float16 [rows, H] that receives the outputs rounded as well.
 hipError_t launch_layernorm(const float *x, const float *res, int64_t rows, int32_t H,
                             const float *gamma, const float *beta, float eps, float *y,
-                            uint32_t *absmax_out, hipStream_t st);
+                            uint32_t *absmax_out, hipStream_t st, uint16_t *y_half = nullptr);
 
 // Multi-head self-attention on packed qkv [B, S, 3*Hd] -> ctx [B, S, Hd];
 // optional atomicMax of |ctx|.
+// ctx_half: null, or float16 [B, S, Hd] that receives the context rounded in place of ctx.
 hipError_t launch_attention(const float *qkv, int32_t B, int32_t S, int32_t Hd, int32_t heads,
-                            float *ctx, uint32_t *absmax_out, hipStream_t st);
+                            float *ctx, uint32_t *absmax_out, hipStream_t st, uint16_t *ctx_half = nullptr);
 
 // The same attention for unobserved runs, head dims in whole units of 8 (attention_splits): approximate matrix-core
 // arithmetic, then the int8 codes [B*S, ldq] and the scale of the context as the fp64 evaluation defines them (values whose
@@ -373,6 +375,7 @@ hipError_t launch_plasticity(const void *a_t, egeria_dtype t_dt, const void *a_r
 #ifdef __HIPCC__
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
 
 // Which of the launch's n pieces workgroup blk takes.  Workgroup ids go round the 8 XCDs, and each XCD has an L2 of its own

@@ -378,6 +378,32 @@ def test_gelu_operand(eg, precision, ffn, spread):
     assert torch.equal(plain, seen)
 
 
+# Attention and the layer norms write the float16 operands of unobserved layers themselves: rows of one and of many 16-byte units,
+# past the width of the vector layer norm, with parameters off its alignment, and rows with pad columns (which are cast).
+@pytest.mark.parametrize("hidden,heads,off", [(8, 1, 0), (72, 3, 0), (72, 3, 1), (264, 11, 0), (768, 12, 0), (1032, 24, 0), (68, 2, 0)])
+def test_float16_operands_of_a_layer(eg, hidden, heads, off):
+    import gpu_common as gc
+    from paper_2201_06227_amd.binding import Norm
+    import synth_inputs as si
+    wl = si.make_bert(b=3, s=67, hidden=hidden, heads=heads, ffn=2 * hidden + 4, n_layers=3, seed=23, train_act_dtype="f32")
+    W, B = [gc.to_dev(w) for w in wl.weights], [None if t is None else gc.to_dev(t) for t in wl.biases]
+    gen = torch.Generator(device="cuda").manual_seed(hidden)
+    gamma, beta = (torch.randn(hidden + 4, device="cuda", generator=gen)[off:off + hidden] for _ in range(2))
+    ref = eg.make_float_reference(wl.kind, wl.dims, W, B, eg.REF_F16)
+    norms = (Norm * 6)(*[Norm(gamma.data_ptr(), beta.data_ptr())] * 6)
+    ref.qweights.n_norm, ref.qweights.norm = 6, norms
+    ws = eg.workspace(eg.workspace_bytes(ref.desc))
+    x = gc.to_dev(wl.x)
+    plain, seen = (torch.full((gc.a_ref_numel(wl),), 7.0, device="cuda") for _ in range(2))
+    shapes = gc.tap_shapes(wl)
+    for t in shapes:
+        t["kp"] = t["kp"] * 4
+    taps, _bufs, _keep = eg.make_taps(ref, shapes)
+    eg.ref_forward(ref, x, seen, ws, taps)
+    eg.ref_forward(ref, x, plain, ws)
+    assert torch.equal(plain, seen)
+
+
 # The work of a launch is dealt in pieces, an eighth of them to each XCD: fewer pieces than XCDs, a multiple of eight and its
 # neighbours, pieces of one and of several units per thread.  The largest value sits in the last place, then in the first.
 @pytest.mark.parametrize("rows,cols", [(1, 16), (3, 16), (7, 4096), (8, 4096), (9, 4096), (255, 16), (257, 16), (17, 4112), (1031, 48),
