@@ -145,7 +145,9 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
     const float s = g.sw_per_n ? 0.0f : sxv * (*g.sw);
     const float rs = g.res_q ? (ET == 0 ? *g.res_scale : 1.0f) : 0.0f;
     float q_inv = 0.0f;                          // multiplier of the optional int8 output
-    if (g.q_out) q_inv = (float)(1.0 / (double)*g.q_scale);
+    if constexpr (EPI == kStore) {               // (GELU passes have codes without a static scale)
+        if (g.q_out) q_inv = (float)(1.0 / (double)*g.q_scale);
+    }
     // affine activation codes: stored codes are q - 128, so 128 - zero point goes back in
     const int zmul = (ET == 0 && g.zp_in) ? 128 - *g.zp_in : 0;
     const int rmul = (ET == 0 && g.zp_res) ? 128 - *g.zp_res : 0;

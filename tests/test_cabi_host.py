@@ -283,3 +283,22 @@ def test_snapshot_plan_places_every_tensor(eg, per_channel):
         assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and spans[-1][1] <= total
     with pytest.raises(ValueError):
         eg._snapshot_plan(((4, 5, 6),), per_channel)
+
+
+def test_static_scale_is_read_by_storing_gemms_alone(tmp_path):
+    """GELU passes of the GEMM have int8 output but no static scale: their GemmArgs::q_scale is null.  The kernels as written,
+    before any optimiser could drop a load without use, have to leave it alone; those that store codes under it read it."""
+    import subprocess
+    from paper_2201_06227_amd import _build
+    out = tmp_path / "gemm.ll"
+    subprocess.run([_build.HIPCC, "-std=c++17", "--offload-arch=gfx950", "--offload-device-only", "-S", "-emit-llvm", "-O1", "-Xclang",
+                    "-disable-llvm-passes", "-fno-discard-value-names", os.path.join(_build.CSRC, "gemm_i8.hip"), "-o", str(out)], check=True)
+    reads = {}                                                     # epilogue -> kernels that form the address of the scale
+    for body in re.split(r"^define ", out.read_text(), flags=re.M)[1:]:
+        name = re.search(r"@_ZN6egeria14gemm_i8_kernelI(\w+?)EEvNS_8GemmArgsE\(", body)
+        if name:
+            epilogue = int(re.findall(r"Li(\d+)", name.group(1))[6])   # <BM, BN, WM, WN, CONV (a bool), BK, ET, EPI, NST>
+            reads.setdefault(epilogue, []).append("%q_scale" in body)
+    assert sorted(reads) == [0, 1, 2, 3]
+    assert all(reads[0])
+    assert not any(reads[1] + reads[2] + reads[3])
