@@ -56,13 +56,20 @@ __device__ __forceinline__ uint32_t code_of(float t)
     return (uint32_t)((int)r) & 0xffu;
 }
 
+// Code of a value that a table leaves open, in fp64: 0 for -infinity and NaN, whose gelu is a NaN here, as the cubic table has it
+// (it clamps v from below).  +infinity leaves inv = 0 and a NaN: code -127, and the tensor is flagged.
+__device__ __forceinline__ uint32_t settle_gelu(float v, float inv)
+{
+    return v >= -3.402823466e+38f ? code_of(gelu_exact(v) * inv) : 0u;
+}
+
 // Code of gelu(v) from the table scaled by inv, in the low byte of the result.  The code clamp(rne(fp32(g * inv))) is monotone in
 // g, so when both ends of the interval that the error bound leaves for g * inv round to the same integer, that integer is the
 // code of the exact value; *unsure is set otherwise (a few values per 100 000) and the caller takes the fp64 form.
 // room = 1/2 - kGeluErrAbs * inv.  (The relative part also covers the rounding of the scaled coefficients and of the product.)
 // (The interval [t - e, t + e] rounds to one integer if |t - rne(t)| + e < 1/2.  No clamp: the scale is the
 // tensor's exact maximum of |gelu| over 127, so |t| stays below 127.5 by the table's error bound; with a
-// non-finite maximum inv is 0 and every code is 0.)  25 vector instructions a value with the conversions spelt out (floor,
+// non-finite maximum inv is 0, and so is every code but that of +infinity, which is left unsure.)  25 vector instructions a value with the conversions spelt out (floor,
 // int and back, rint), 18 this way.
 template <bool BIG>
 __device__ __forceinline__ uint32_t quant_gelu_fast(float v, float inv, float room, const float4 *__restrict__ tab, bool *unsure)
@@ -76,7 +83,8 @@ __device__ __forceinline__ uint32_t quant_gelu_fast(float v, float inv, float ro
 // The same from straight lines (gelu_lines.inc), for the GEMM that writes the codes: half the bytes per look-up and 8 instructions
 // less than the cubic pieces; about one value in 20 000 is left open.  lines: gelu_lines.inc scaled by inv, room = 1/2 -
 // kGeluLineErr * inv.  Adding 1.5 * 2^15 + 6 rounds v to the multiple of 1/256 whose line is looked up and leaves its number in
-// the low bits.  (Relative part: the scaled coefficients, the sum, and the exact form's two steps, each 2^-24 |t|.)
+// the low bits.  (Relative part: the scaled coefficients, the sum, and the exact form's two steps, each 2^-24 |t|.)  A value
+// that is not finite makes t a NaN and stays unsure.
 #include "gelu_lines.inc"
 __device__ __forceinline__ uint32_t quant_gelu_lines(float v, float room, const float2 *__restrict__ lines, bool *unsure)
 {

@@ -334,6 +334,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
             const uint32_t below = wave_max_u32(way[0]), above = wave_max_u32(way[1]);
             if (below) absmax = fmaxf(absmax, fabsf(gelu_exact(-__uint_as_float(0x7fffffffu - below))));
             if (above) absmax = fmaxf(absmax, fabsf(gelu_exact(-__uint_as_float(above))));
+            if (above > 0x7f800000u) absmax = __uint_as_float(above);    // a NaN among them: no scale is left
         }
         float scale;
         const bool bad = !(gelu_vm <= 3.402823466e+38f);
@@ -523,6 +524,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                         const uint32_t a = abs_bits(v);
                         if (v <= kGeluArgMin) below = below > 0x7fffffffu - a ? below : 0x7fffffffu - a;
                         if (v >= kGeluArgMin && v < 0.0f) above = above > a ? above : a;
+                        if (!(v >= -3.402823466e+38f)) above = 0x7fc00000u;             // gelu of -infinity and of NaN
                     }
             below = wave_max_u32(below);
             above = wave_max_u32(above);
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll 1
                     for (int k = lane; k < n; k += 64) {
                         const uint2 e = list[k];
-                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code_of(gelu_exact(__uint_as_float(e.x)) * gelu_inv), rq, (int)e.y, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(__uint_as_float(e.x), gelu_inv), rq, (int)e.y, 0, 0);
                     }
                 } else {
                     // more than one value in twelve of a wave's: every one from its operands, value by value
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll 1
                         for (int u = 0; u < g.kp / 4; ++u) sum = __builtin_amdgcn_sdot4(ar[u], wr[u], sum, false);
                         const float sv = g.sw_per_n ? sxv * g.sw[col] : s, v = fmaf((float)sum, sv, g.bias ? g.bias[col] : 0.0f);
-                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code_of(gelu_exact(v) * gelu_inv), rq, (int)((uint32_t)tr * q_ld + (uint32_t)col), 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(v, gelu_inv), rq, (int)((uint32_t)tr * q_ld + (uint32_t)col), 0, 0);
                     }
                 }
             }

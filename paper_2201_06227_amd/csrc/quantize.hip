@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(256) void quantize_gelu_rows_kernel(
                 const int e = __ffs((int)redo) - 1;
                 redo &= redo - 1;
                 if (c0 + e >= cols) continue;
-                const uint32_t code = code_of(gelu_exact(v[base + e]) * inv);
+                const uint32_t code = settle_gelu(v[base + e], inv);
                 const uint32_t sh = (e & 3) * 8, keep = ~(0xffu << sh);
                 if ((e >> 2) == 0) w[0] = (w[0] & keep) | (code << sh);
                 if ((e >> 2) == 1) w[1] = (w[1] & keep) | (code << sh);

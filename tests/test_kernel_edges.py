@@ -436,7 +436,7 @@ def _gelu_tile(M, N, cu):
     return min(cost, key=cost.get)
 
 
-def _same_observed_and_not(eg, wl, per_channel=False, biases=True):
+def _same_observed_and_not(eg, wl, per_channel=False, biases=True, status=0):
     import gpu_common as gc
     ref = eg.make_reference(wl.kind, wl.dims, [gc.to_dev(w) for w in wl.weights], [gc.to_dev(b) if biases else None for b in wl.biases],
                             per_channel=per_channel)
@@ -445,7 +445,7 @@ def _same_observed_and_not(eg, wl, per_channel=False, biases=True):
     taps, bufs, _keep = eg.make_taps(ref, gc.tap_shapes(wl), "cuda")
     eg.ref_forward(ref, x, got[0], ws, taps)
     eg.ref_forward(ref, x, got[1], ws)
-    assert eg.check(ws) == eg.OK
+    assert eg.check(ws) == status
     assert torch.equal(got[0], got[1])
     return bufs
 
@@ -518,3 +518,25 @@ def test_fc_refresh_is_the_two_calls(eg, b, k, n, per_channel):
         two = ev.step_two_calls(x, a_t)
         assert torch.equal(one, two) and torch.equal(codes, ev.w_q[0]) and torch.equal(scales, ev.scales[0])
         assert eg.check(ev.ws) == eg.OK
+
+
+# Pre-activations that are no numbers: units whose bias is -infinity (masked out) or a NaN with its sign set, neither of which the
+# maximum tracks.  Their code is 0 where the largest value sets the scale; below the shortcut the fp64 maximum takes them in and no
+# scale is left (1, every code 0).  Infinity and NaN leave no scale either, and the run is flagged.
+@pytest.mark.parametrize("bits", [0xff800000, 0xffc00000, 0x7f800000, 0x7fc00000], ids=["-inf", "-nan", "inf", "nan"])
+@pytest.mark.parametrize("spread", [1.0, 0.03])
+@pytest.mark.parametrize("b,s,ffn", [(2, 37, 200), (100, 70, 2056)])
+def test_gelu_codes_of_masked_units(eg, b, s, ffn, spread, bits):
+    import synth_inputs as si
+    wl = si.make_bert(b=b, s=s, hidden=68, heads=2, ffn=ffn, seed=29, train_act_dtype="f32")
+    wl.weights[2] *= np.float32(spread)
+    masked = [0, 5, 37, ffn // 2, ffn - 1]
+    wl.biases[2] = np.linspace(-0.3, 0.2 * spread, ffn).astype(np.float32)
+    wl.biases[2][masked] = np.array([bits], np.uint32).view(np.float32)
+    bufs = _same_observed_and_not(eg, wl, status=eg.OK if bits >> 31 else eg.ERR_NONFINITE)
+    codes = bufs[3]["x_q"]
+    if bits != 0x7f800000:
+        assert not codes[:, masked].any()
+    codes[:, masked] = 0
+    scaled = spread == 1.0 and bits >> 31 == 1
+    assert (bufs[3]["x_scale"].item() == 1.0) != scaled and bool(codes.any()) == scaled
