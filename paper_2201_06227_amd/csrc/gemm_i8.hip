@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll
         for (int c = tid; c < kGeluLines; c += NT) lines[c] = make_float2(lines[c].x * gelu_inv, lines[c].y * gelu_inv);
         __syncthreads();                                // every wave has read its last operands
-        // COLS: a scale or a bias per column (pad columns: gelu(0) = 0)
+        // COLS: a scale or a bias per column.  Pad columns are values of 0, settled like the others: the line around 0 is not 0 there.
         auto run = [&](auto cols_c) {
             constexpr bool COLS = decltype(cols_c)::value;
             int n = 0;
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll 1
                             while (__ballot(open != 0)) {
                                 const int r = __ffs((int)open) - 1, col = col0 + 8 * (r >> 2) + 4 * half + (r & 3);
-                                const bool mine = open != 0 && col < g.N;
+                                const bool mine = open != 0 && (uint32_t)col < q_ld;
                                 const uint64_t m = __ballot(mine);
                                 const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
                                 if (mine && at < kGeluList) list[at] = make_uint2(__float_as_uint(turn[r * 64 + lane]), row * q_ld + (uint32_t)col);
@@ -629,12 +629,13 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
 #pragma unroll 1
                     for (int k = lane; k < TM * TN * 1024; k += 64) {
                         const int tr = wrow0 + k / (TN * 32), col = wcol0 + k % (TN * 32);
-                        if (tr >= rows || col >= g.N) continue;
+                        if (tr >= rows || (uint32_t)col >= q_ld) continue;
                         const int *ar = (const int *)(g.a + (m0 + tr) * g.lda), *wr = (const int *)(g.w + (int64_t)col * g.kp);
                         int sum = 0;
 #pragma unroll 1
-                        for (int u = 0; u < g.kp / 4; ++u) sum = __builtin_amdgcn_sdot4(ar[u], wr[u], sum, false);
-                        const float sv = g.sw_per_n ? sxv * g.sw[col] : s, v = fmaf((float)sum, sv, g.bias ? g.bias[col] : 0.0f);
+                        for (int u = 0; u < (col < g.N ? g.kp / 4 : 0); ++u) sum = __builtin_amdgcn_sdot4(ar[u], wr[u], sum, false);
+                        const bool in = col < g.N;
+                        const float sv = g.sw_per_n && in ? sxv * g.sw[col] : s, v = in ? fmaf((float)sum, sv, g.bias ? g.bias[col] : 0.0f) : 0.0f;
                         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(v, gelu_inv), rq, (int)((uint32_t)tr * q_ld + (uint32_t)col), 0, 0);
                     }
                 }

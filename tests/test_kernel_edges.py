@@ -436,10 +436,11 @@ def _gelu_tile(M, N, cu):
     return min(cost, key=cost.get)
 
 
-def _same_observed_and_not(eg, wl, per_channel=False, biases=True, status=0):
+def _same_observed_and_not(eg, wl, per_channel=False, biases=True, prepare=lambda ref: None, status=0):
     import gpu_common as gc
     ref = eg.make_reference(wl.kind, wl.dims, [gc.to_dev(w) for w in wl.weights], [gc.to_dev(b) if biases else None for b in wl.biases],
                             per_channel=per_channel)
+    prepare(ref)
     x, ws = gc.to_dev(wl.x), eg.workspace(eg.workspace_bytes(ref.desc), "cuda")
     got = [torch.empty(gc.a_ref_numel(wl), device="cuda") for _ in range(2)]
     taps, bufs, _keep = eg.make_taps(ref, gc.tap_shapes(wl), "cuda")
@@ -540,3 +541,20 @@ def test_gelu_codes_of_masked_units(eg, b, s, ffn, spread, bits):
     codes[:, masked] = 0
     scaled = spread == 1.0 and bits >> 31 == 1
     assert (bufs[3]["x_scale"].item() == 1.0) != scaled and bool(codes.any()) == scaled
+
+
+# Pad columns of the codes are zero, however small the tensor's largest value: the next layer's weights get codes in their pad
+# columns here, which any other code would multiply.
+@pytest.mark.parametrize("spread", [1.0, 1e-3, 1e-4, 1e-5])
+@pytest.mark.parametrize("b,s,ffn", [(2, 37, 200), (100, 70, 2056)])
+def test_gelu_codes_leave_the_pad_zero(eg, b, s, ffn, spread):
+    import gpu_common as gc
+    import synth_inputs as si
+    wl = si.make_bert(b=b, s=s, hidden=68, heads=2, ffn=ffn, seed=31, train_act_dtype="f32")
+    wl.weights[2] *= np.float32(spread)
+
+    def mark(ref):
+        assert ref.w_q[3].shape[1] == eg.padded(ffn) > ffn
+        ref.w_q[3][:, ffn:] = 127
+    bufs = _same_observed_and_not(eg, wl, prepare=mark)
+    assert not bufs[3]["x_q"][:, ffn:].any()
