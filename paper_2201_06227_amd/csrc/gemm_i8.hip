@@ -104,8 +104,13 @@ enum GemmEpilogue {
     kGeluCodes = 3       // int8 codes of their GELU (gelu_pass 2)
 };
 constexpr int kGeluTableBytes = kGeluLines * 8;
-// values per wave whose code the table leaves open that one round settles; 8 bytes each in the stage memory
+// Values of a wave (1024 to 8192 by the tile) that the lines may leave open: a list of 8 bytes each in the stage memory.
 constexpr int kGeluList = 512;
+// The lines' error in codes from which on the epilogue takes the cubic pieces instead (largest |gelu| below 6 x 10^-3).  The lines
+// leave twice that share of the values open, 4 %: the list still holds them, of the largest tile one value in sixteen.  An
+// encoder layer, us, lines / pieces, largest |gelu| 8.5 x 10^-3: 165 / 169 (32 x 128 x 768), 498 / 499 (64 x 256), 196 / 203 (24 x 197);
+// 3.4 x 10^-3, 7 % left open and lists that overflow: 168 / 169, 541 / 501, 215 / 203.
+constexpr float kGeluLinesOpen = 0.02f;
 
 template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, int EPI = kStore, int NST = stages_for(BK)>
 __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 * 128 ? 2 : resident_target(BM, BN)) void gemm_i8_kernel(const GemmArgs g)
@@ -512,7 +517,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                 track(fmaf((float)lo, sj[j], bj[j]));
             }
         }
-        if (__uint_as_float(wave_max_u32((uint32_t)amax)) < kGeluShortcutMin) {
+        if (__builtin_expect(__uint_as_float(wave_max_u32((uint32_t)amax)) < kGeluShortcutMin, 0)) {
             uint32_t below = 0, above = 0;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -536,11 +541,14 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
         // ---- codes of gelu(y).  The product is the transposed one, so a lane holds, of every 32x32 block, 16 columns of one row: four
         // times four neighbouring ones, the other half of the wave those between them.  A swap of halves makes 16 neighbours, one
         // store.  Values whose code the lines leave open go on the wave's list (value, place) in the stage memory and
-        // are settled side by side afterwards.  Bound by the vector
-        // instructions, 13 a value (16384 x 3072 values: 20 us of the launch's 61; the sums alone 38).
+        // are settled side by side afterwards; where they are too many, the cubic pieces leave a thirteenth of them open.  Bound by
+        // the vector instructions, 13 a value (16384 x 3072 values: 72 us the launch, 40 the sums alone), about 30 with the
+        // pieces.  An encoder layer with its first feed-forward weights times 1 / 10^-3 / 10^-6, us: 64 x 256 x 768 457 / 504 / 615 (fp32
+        // tensor and row quantiser 526 / 619 / 717), 32 x 128 x 768 156 / 170 / 197 (173 / 191 / 215).  (The rare branches are out of
+        // line: 72.4 us with them in their places.)
         static_assert((size_t)NST * STAGE >= (size_t)NW * (kGeluList * 8 + 4096), "the waves' lists must fit the stage memory");
         float2 *lines = (float2 *)&lds[NST * STAGE];
-        uint2 *list = (uint2 *)&lds[wave_u * (kGeluList * 8 + 4096)];
+        uint2 *list = (uint2 *)&lds[(uint32_t)wave_u * (uint32_t)((size_t)NST * STAGE / NW)];
         const float room = 0.5f - kGeluLineErr * gelu_inv;
         const int rows = (int)(g.M - m0 < BM ? g.M - m0 : BM);
         const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)(g.q_out + m0 * g.q_ld), 0, (int)(rows * g.q_ld), 0x00020000);
@@ -588,7 +596,7 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                         const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
                         const v4u out = {(unsigned)a[0], (unsigned)a[1], (unsigned)b[0], (unsigned)b[1]};
                         __builtin_amdgcn_raw_buffer_store_b128(out, rq, (int)(c16 == kOob ? kOob : row * q_ld + c16), 0, kThrough);
-                        if (__ballot(any)) {                                             // rare
+                        if (__builtin_expect(__ballot(any) != 0, 0)) {
                             float *turn = (float *)(list + kGeluList);       // the block's values, by register and lane
                             uint32_t open = 0;
 #pragma unroll
@@ -614,34 +622,80 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                     }
                 }
             }
-            if (n > 0) {                                // (uniform)
-                wave_lds_turn();
-                __builtin_amdgcn_s_waitcnt(0x0f70);     // the stores above have been performed
-                if (n <= kGeluList) {
-#pragma unroll 1
-                    for (int k = lane; k < n; k += 64) {
-                        const uint2 e = list[k];
-                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(__uint_as_float(e.x), gelu_inv), rq, (int)e.y, 0, 0);
-                    }
-                } else {
-                    // more than one value in twelve of a wave's: every one from its operands, value by value
-                    const int wrow0 = wm_u * TM * 32, wcol0 = n0 + wn_u * TN * 32;
-#pragma unroll 1
-                    for (int k = lane; k < TM * TN * 1024; k += 64) {
-                        const int tr = wrow0 + k / (TN * 32), col = wcol0 + k % (TN * 32);
-                        if (tr >= rows || (uint32_t)col >= q_ld) continue;
-                        const int *ar = (const int *)(g.a + (m0 + tr) * g.lda), *wr = (const int *)(g.w + (int64_t)col * g.kp);
-                        int sum = 0;
-#pragma unroll 1
-                        for (int u = 0; u < (col < g.N ? g.kp / 4 : 0); ++u) sum = __builtin_amdgcn_sdot4(ar[u], wr[u], sum, false);
-                        const bool in = col < g.N;
-                        const float sv = g.sw_per_n && in ? sxv * g.sw[col] : s, v = in ? fmaf((float)sum, sv, g.bias ? g.bias[col] : 0.0f) : 0.0f;
-                        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(v, gelu_inv), rq, (int)((uint32_t)tr * q_ld + (uint32_t)col), 0, 0);
-                    }
-                }
-            }
+            return n;
         };
-        if (g.sw_per_n || g.bias) run(std::true_type{}); else run(std::false_type{});
+        int n = __builtin_amdgcn_readfirstlane(kGeluLineErr * gelu_inv < kGeluLinesOpen ? 0 : kGeluList + 1);
+        if (__builtin_expect(n == 0, 1)) n = g.sw_per_n || g.bias ? run(std::true_type{}) : run(std::false_type{});
+        if (n == 0) return;                             // (uniform)
+        wave_lds_turn();
+        __builtin_amdgcn_s_waitcnt(0x0f70);             // the stores above have been performed
+        if (__builtin_expect(n <= kGeluList, 1)) {
+#pragma unroll 1
+            for (int k = lane; k < n; k += 64) {
+                const uint2 e = list[k];
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)settle_gelu(__uint_as_float(e.x), gelu_inv), rq, (int)e.y, 0, 0);
+            }
+            return;
+        }
+        // Too many for the list (values on the border of two codes), or lines too coarse for the tensor's scale: every block from
+        // its sums with the cubic pieces.  As many blocks at a time as the wave's stage memory holds beside the pieces go there first, so that one
+        // loop can take them in turn (the fp64 form's registers beside all of the sums would spill).
+        constexpr int kSpan = (int)((size_t)NST * STAGE / NW), kGroup = (kSpan - 4096) / 4096 < TM * TN ? (kSpan - 4096) / 4096 : TM * TN;
+        static_assert(kGroup >= 1, "a block's sums and the cubic pieces must fit a wave's share of the stage memory");
+        float4 *tab = (float4 *)list;
+        int *turn = (int *)(list + kGeluList);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tab[lane + 64 * k] = scale_gelu_entry(kGeluTable[lane + 64 * k], gelu_inv);
+        const float room3 = 0.5f - kGeluErrAbs * gelu_inv;
+        const __amdgpu_buffer_rsrc_t rsw = __builtin_amdgcn_make_buffer_rsrc((void *)g.sw, 0, g.sw_per_n ? g.N * 4 : 0, kBufferWord);
+        const __amdgpu_buffer_rsrc_t rbias = __builtin_amdgcn_make_buffer_rsrc((void *)g.bias, 0, g.bias ? g.N * 4 : 0, kBufferWord);
+#pragma unroll
+        for (int b0 = 0; b0 < TM * TN; b0 += kGroup) {
+            wave_lds_turn();
+#pragma unroll
+            for (int k = 0; k < kGroup; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (b0 + k < TM * TN) turn[k * 1024 + r * 64 + lane] = acc[(b0 + k) % TM][(b0 + k) / TM][r];
+            wave_lds_turn();
+#pragma unroll 1
+            for (int b = b0; b < b0 + kGroup && b < TM * TN; ++b) {
+                int *mine = turn + (b - b0) * 1024 + lane;
+                const int col0 = n0 + (wn_u * TN + b / TM) * 32;
+                const uint32_t row = (uint32_t)((wm_u * TM + b % TM) * 32 + lcol);
+                const uint32_t c16 = (uint32_t)(col0 + 16 * half) < q_ld ? (uint32_t)(col0 + 16 * half) : kOob;
+                uint32_t w[4], open = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t c[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = 4 * q + e, at = (col0 + 4 * half) * 4;       // (beyond N the loads are 0)
+                        const float sw = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsw, at, (8 * q + e) * 4, 0));
+                        const float bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbias, at, (8 * q + e) * 4, 0));
+                        const float v = fmaf((float)mine[r * 64], g.sw_per_n ? sxv * sw : s, bv);    // one fp32 multiply
+                        bool un;
+                        c[e] = quant_gelu_fast<true>(v, gelu_inv, room3, tab, &un);
+                        open |= un ? 1u << r : 0u;
+                        mine[r * 64] = (int)__float_as_uint(v);
+                    }
+                    w[q] = pack_bytes(c[0], c[1], c[2], c[3]);
+                }
+                if ((int)row >= rows) open = 0;
+#pragma unroll 1
+                while (__ballot(open != 0)) {
+                    const int r = open ? __ffs((int)open) - 1 : 0;
+                    const uint32_t code = settle_gelu(__uint_as_float((uint32_t)mine[r * 64]), gelu_inv);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (open && (r >> 2) == q) w[q] = (w[q] & ~(0xffu << (8 * (r & 3)))) | code << (8 * (r & 3));
+                    open &= open - 1;
+                }
+                const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), c = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+                const v4u out = {(unsigned)a[0], (unsigned)a[1], (unsigned)c[0], (unsigned)c[1]};
+                __builtin_amdgcn_raw_buffer_store_b128(out, rq, (int)(c16 == kOob ? kOob : row * q_ld + c16), 0, kThrough);
+            }
+        }
     } else if (inside) {
         // ---- a tile that lies inside the output: stored from the accumulators.  For a fixed register each half of the wave owns
         // 32 neighbouring columns of one row, so every store of y writes two whole 128-byte segments and nothing is tested.

@@ -464,7 +464,7 @@ def test_gelu_codes_from_the_gemm(eg, tile, b, s, ffn, spread, per_channel, bias
     assert (top < 0.3) == (spread < 1.0) and (top > 9.0) == (spread > 1.0), top
 
 
-# Values that all sit on the border of two codes: a wave's list overflows and it works its values out from the operands.  Equal
+# Values that all sit on the border of two codes: a wave's list overflows and it takes its sums through the cubic pieces.  Equal
 # tokens have equal sums, which the biases lift to the border (largest value 3, code 60.5).
 @pytest.mark.parametrize("b,s,ffn", [(3, 33, 100), (40, 65, 3083)])
 def test_gelu_codes_on_the_border(eg, b, s, ffn):
@@ -558,3 +558,44 @@ def test_gelu_codes_leave_the_pad_zero(eg, b, s, ffn, spread):
         ref.w_q[3][:, ffn:] = 127
     bufs = _same_observed_and_not(eg, wl, prepare=mark)
     assert not bufs[3]["x_q"][:, ffn:].any()
+
+
+# Small pre-activations, for which the straight lines leave more and more codes open, then the cubic pieces, at last all of them: the
+# same codes on every tile, with one scale and with one per column and a bias, and a pass takes no more than twice what one of
+# ordinary values does (with the fp32 tensor and the row quantiser it took up to 1.4 times as long; waves that worked out again
+# what their lists could not hold, 40 times).
+SMALL_SPREADS = (1.0, 1e-2, 5e-3, 2e-3, 1e-3, 1e-4, 1e-6, 1e-20)
+
+
+@pytest.mark.parametrize("per_channel", [False, True])
+@pytest.mark.parametrize("tile,b,s,ffn", GELU_TILES, ids=["x".join(map(str, t[0])) for t in GELU_TILES])
+def test_gelu_codes_of_small_values(eg, tile, b, s, ffn, per_channel):
+    import synth_inputs as si
+    wl = si.make_bert(b=b, s=s, hidden=68, heads=2, ffn=ffn, seed=37, train_act_dtype="f32")
+    plain = wl.weights[2].copy()
+    for spread in SMALL_SPREADS[1:]:
+        wl.weights[2] = plain * np.float32(spread)
+        wl.biases[2] = np.linspace(-0.5, 0.5, ffn).astype(np.float32) * np.float32(spread)
+        bufs = _same_observed_and_not(eg, wl, per_channel, biases=per_channel)
+        assert bufs[3]["x_q"].abs().max().item() == 127
+
+
+def test_gelu_codes_of_small_values_take_no_longer(eg):
+    import gpu_common as gc
+    import synth_inputs as si
+    wl = si.make_bert(b=64, s=128, seed=37, train_act_dtype="f32")
+    W = [gc.to_dev(w) for w in wl.weights]
+    x, out = gc.to_dev(wl.x), torch.empty(gc.a_ref_numel(wl), device="cuda")
+    times = {}
+    for spread in SMALL_SPREADS:
+        ref = eg.make_reference(wl.kind, wl.dims, [W[0], W[1], W[2] * spread, W[3]], [None] * 4)
+        ws = eg.workspace(eg.workspace_bytes(ref.desc), "cuda")
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        times[spread] = float("inf")
+        for _ in range(5):
+            ev[0].record()
+            eg.ref_forward(ref, x, out, ws)
+            ev[1].record()
+            ev[1].synchronize()
+            times[spread] = min(times[spread], ev[0].elapsed_time(ev[1]))
+    assert max(times.values()) < 2.0 * times[1.0], times
