@@ -517,7 +517,8 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                 track(fmaf((float)lo, sj[j], bj[j]));
             }
         }
-        if (__builtin_expect(__uint_as_float(wave_max_u32((uint32_t)amax)) < kGeluShortcutMin, 0)) {
+        // (a wave beyond the last row or column has no values)
+        if (__builtin_expect(__uint_as_float(wave_max_u32((uint32_t)amax)) < kGeluShortcutMin && wm_u * TM * 32 < rows && n0 + wn_u * TN * 32 < g.N, 0)) {
             uint32_t below = 0, above = 0;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
