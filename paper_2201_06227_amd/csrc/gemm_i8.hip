@@ -1576,8 +1576,8 @@ bool gemm_layernorm_fusable(int32_t N, const void *ln_out, const void *ln_res, c
 }
 
 // Which layers make their sums twice (GemmArgs::gelu_pass): a second set of sums instead of an fp32 tensor written and read back,
-// as long as they are short.
-bool gemm_gelu_codes(int64_t M, int32_t N, int64_t kp) { return M > 0 && N > 32 && N < (1 << 22) && kp <= 1024; }
+// as long as they are short.  (Rows of codes, padded to 16, stay below 2^22 bytes: launch_gemm_i8 addresses 256 of them with 31 bits.)
+bool gemm_gelu_codes(int64_t M, int32_t N, int64_t kp) { return M > 0 && N > 32 && N <= (1 << 22) - 16 && kp <= 1024; }
 
 hipError_t launch_gemm_i8(const GemmArgs &g, hipStream_t st)
 {

@@ -599,3 +599,23 @@ def test_gelu_codes_of_small_values_take_no_longer(eg):
             ev[1].synchronize()
             times[spread] = min(times[spread], ev[0].elapsed_time(ev[1]))
     assert max(times.values()) < 2.0 * times[1.0], times
+
+
+# Layers whose padded output is too wide for the GEMM that writes the codes, and the widest that is not.
+@pytest.mark.parametrize("ffn", [4194288, 4194289, 4194300])
+def test_gelu_codes_of_the_widest_layers(eg, ffn):
+    import gpu_common as gc
+    import synth_inputs as si
+    gen = torch.Generator(device="cuda").manual_seed(ffn)
+    W = [torch.randn(o, i, device="cuda", generator=gen) * (2.0 / (o + i)) ** 0.5 for o, i in ((48, 16), (16, 16), (ffn, 16), (16, ffn))]
+    W[2] *= 500.0
+    dims = dict(batch=1, seq=3, hidden=16, heads=1, ffn=ffn, n_layers=1, ln_eps=1e-12)
+    ref = eg.make_reference(si.KIND_BERT_LAYER, dims, W, [None] * 4)
+    x, ws = torch.randn(1, 3, 16, device="cuda", generator=gen), eg.workspace(eg.workspace_bytes(ref.desc), "cuda")
+    plain, seen = (torch.empty(48, device="cuda") for _ in range(2))
+    shapes = [dict(M=3, kp=eg.padded(k), N=n) for k, n in ((16, 48), (16, 16), (16, ffn), (ffn, 16))]
+    taps, _bufs, _keep = eg.make_taps(ref, shapes, "cuda")
+    eg.ref_forward(ref, x, seen, ws, taps)
+    eg.ref_forward(ref, x, plain, ws)
+    assert eg.check(ws) == eg.OK
+    assert torch.equal(plain, seen)
