@@ -468,13 +468,14 @@ constexpr double kAttentionRule = 5.0e9;
 double g_attention_min_flops = kAttentionRule;
 // The measure is the work of the fp64 kernel in whole tiles (64 queries x 32 keys, heads padded to 64 dims, 29 us per 1e9
 // flops); heads of 32 dims and less cost the certified kernels half as much.  Up to 64 tokens, one tile of that kernel, they do
-// not pay at any batch; up to 256 from 1.75e9 on, and for every 256 tokens more (a listed value reads all keys of its head,
-// and the more there are the more values are listed) from twice as much; beyond 1024 fp64 is faster at any batch that was
-// tried.  One layer, us, fp64 / certified: 12 x 128 x 768 90 / 93, 32 x 128 x 768 (1.6e9) 127 / 127, 24 x 128 x 384 (heads of 32,
-// 2.4e9) 98 / 94, 64 x 80 x 768 (2.4e9) 150 / 141, 12 x 197 x 768 (2.1e9) 138 / 124, 24 x 197 x 768 193 / 161, 12 x 256 x 768 150 /
-// 128, 64 x 256 x 768 468 / 345; 8 x 300 x 768 (2.5e9) 134 / 149, 8 x 384 x 768 (3.6e9) 184 / 173, 4 x 512 x 768 (3.2e9) 163 / 167, 8 x
-// 512 x 768 (6.4e9) 226 / 203; 4 x 768 x 768 (7.2e9) 286 / 238; 4 x 1024 x 512 (8.6e9) 260 / 292, 8 x 1024 x 768 (26e9) 684 / 529;
-// 2 x 2048 x 512 443 / 634, 16 x 2048 x 768 4578 / 5002.
+// not pay at any batch; up to 256 from 1.75e9 on, for every 256 tokens more (a listed value reads all keys of its head,
+// and the more there are the more values are listed) from twice as much, and not beyond 1024.  The line was drawn where the two
+// were level while the certification evaluated a listed value per wave; sixteen at a time it takes 0.55 to 0.75 of that, so the
+// line now lies above where they are level.  One layer, us, fp64 / certified, beyond the line: 40 x 128 x 768 167 / 155, 24 x 128 x 384
+// (heads of 32) 98 / 90, 64 x 80 x 768 176 / 165, 12 x 197 x 768 144 / 122, 24 x 197 x 768 219 / 175, 12 x 256 x 768 165 / 137, 64 x 256 x
+// 768 585 / 433, 8 x 384 x 768 198 / 155, 8 x 512 x 768 244 / 182, 4 x 768 x 768 299 / 213, 8 x 1024 x 768 706 / 420; below it: 32 x 80 x
+// 768 112 / 112, 12 x 128 x 768 100 / 98, 32 x 128 x 768 143 / 137, 6 x 256 x 768 121 / 106, 8 x 300 x 768 140 / 136, 2 x 512 x 768 114 /
+// 111, 4 x 512 x 768 171 / 134, 2 x 1024 x 512 162 / 166, 4 x 1024 x 512 260 / 203; 2 x 2048 x 512 445 / 370, 16 x 2048 x 768 4863 / 3051.
 bool attention_certified(int32_t batch, int32_t seq, int32_t hidden, int32_t heads)
 {
     // (the certified kernels index the context's values in 32 bits)
@@ -1106,8 +1107,8 @@ egeria_status egeria_refresh_eval(const egeria_weight *w, int32_t n_w, void *ws_
         desc->act_scheme == EGERIA_ACT_SYMMETRIC && fc_input_is_small(desc)) {
         // The whole quantisation of a small FC input is one workgroup's work.  It takes that workgroup 3 us, twice as long as
         // the others' share of a snapshot's first pass (32 x 512 values, 512 x 512 weights), so beside a snapshot of two
-        // launches the input goes the long way too: its maximum with the first, its codes with the second (the step 20.4 ->
-        // 19.1 us).
+        // launches the input goes the long way too: its maximum with the first, its codes with the second (the step 20.7 ->
+        // 19.0 us).
         job.n = (int64_t)desc->batch * desc->c_in;
         const bool two = n_w == 1 && !w[0].per_channel && (int64_t)w[0].out * w[0].in > kSmallTensor;
         job.nblk = two ? absmax_blocks(job.n, x_dt) : 1;

@@ -396,8 +396,10 @@ __device__ __forceinline__ uint32_t xcd_piece(uint32_t blk, uint32_t n)
 // whole passes: affine forward of 64 x 1024 x 14 x 14 83.0 / 80.4, bottleneck step 111.5 / 108.9, static block 67.6 / 66.0, two ragged
 // encoder layers 406.2 / 400.4, float16 layer 183.4 / 180.1, one encoder layer 186.2 / 183.9; nothing where the outputs
 // overflow the L2s many times (12-layer stack of 64 x 256 tokens).  Layer norms and row quantisers after that: the encoder layer
-// 178.0 / 174.2, the ragged ones 392.5 / 386.2.  Only for stores that fill their lines: the attention kernels' contexts, 4 or 16
-// bytes of a line at a time, cost more this way (the stack 5850 / 6040, the encoder layer 164.9 / 166.7).
+// 178.0 / 174.2, the ragged ones 392.5 / 386.2.  Not for stores of small pieces of a line: the attention kernels' contexts, 4 or 16
+// bytes at a time, cost more this way (the stack 5850 / 6040, the encoder layer 164.9 / 166.7).  The int8 outputs of static
+// layers, single bytes that are 32 neighbouring ones of a wave, are the same either way (forward of 50 x 2048 x 7 x 7 43.6 / 43.7, of
+// 64 x 1024 x 14 x 14 51.7 / 51.5).
 constexpr int kThrough = 16;         // sc1
 constexpr int kBufferWord = 0x00020000;
 

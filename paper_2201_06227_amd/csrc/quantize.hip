@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void quantize_nchw_vec_kernel(
 
 // fp32 planes of an odd number of pixels (7x7, 13x13): `group` channels of an image with all their pixels, which lie side by side in
 // memory, pass through LDS and come back as pixels x channels.  The loads are whole 16-byte units along memory, whatever the
-// length of a plane (a load per value, 49 of 64 lanes at work, took 9.7 us for 50 x 2048 x 49; 6.5 this way).  Rows of the LDS
+// length of a plane (a load per value, 49 of 64 lanes at work, took 9.0 us for 50 x 2048 x 49; 6.2 this way).  Rows of the LDS
 // tile are padded by a word: lanes hold values four pixels apart, at most four of them fall on one bank.
 constexpr int64_t kPlaneMax = 1024;          // pixels of such a plane
 __global__ __launch_bounds__(256) void quantize_planes_kernel(

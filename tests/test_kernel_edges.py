@@ -601,6 +601,14 @@ def test_gelu_codes_of_small_values_take_no_longer(eg):
     assert max(times.values()) < 2.0 * times[1.0], times
 
 
+# The longest rows whose sums are made twice, and the next longer ones, which are not.
+@pytest.mark.parametrize("hidden,heads", [(1008, 16), (1024, 16), (1040, 20)])
+@pytest.mark.parametrize("b,s,ffn", [(3, 45, 300), (40, 65, 3083)])
+def test_gelu_codes_of_the_longest_rows(eg, b, s, ffn, hidden, heads):
+    import synth_inputs as si
+    _same_observed_and_not(eg, si.make_bert(b=b, s=s, hidden=hidden, heads=heads, ffn=ffn, seed=41, train_act_dtype="f32"))
+
+
 # Layers whose padded output is too wide for the GEMM that writes the codes, and the widest that is not.
 @pytest.mark.parametrize("ffn", [4194288, 4194289, 4194300])
 def test_gelu_codes_of_the_widest_layers(eg, ffn):
