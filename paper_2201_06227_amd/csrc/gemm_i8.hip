@@ -108,8 +108,8 @@ constexpr int kGeluTableBytes = kGeluLines * 8;
 constexpr int kGeluList = 512;
 // The lines' error in codes from which on the epilogue takes the cubic pieces instead (largest |gelu| below 6 x 10^-3).  The lines
 // leave twice that share of the values open, 4 %: the list still holds them, of the largest tile one value in sixteen.  An
-// encoder layer, us, lines / pieces, largest |gelu| 8.5 x 10^-3: 165 / 169 (32 x 128 x 768), 498 / 499 (64 x 256), 196 / 203 (24 x 197);
-// 3.4 x 10^-3, 7 % left open and lists that overflow: 168 / 169, 541 / 501, 215 / 203.
+// encoder layer, us, lines / pieces, largest |gelu| 8.5 x 10^-3: 151 / 159 (32 x 128 x 768), 475 / 476 (64 x 256), 186 / 195 (24 x 197);
+// 3.4 x 10^-3, 7 % left open and, but for the first, lists that overflow: 154 / 159, 524 / 482, 208 / 197.
 constexpr float kGeluLinesOpen = 0.02f;
 
 template <int BM, int BN, int WM, int WN, bool CONV, int BK, int ET, int EPI = kStore, int NST = stages_for(BK)>
@@ -486,9 +486,11 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
             bj[j] = g.bias && ok ? g.bias[ok ? col : 0] : 0.0f;
         }
         const int rows = (int)(g.M - m0 < BM ? g.M - m0 : BM);                   // valid rows of the tile
+        uint32_t worst = 0;                                                      // largest |y| of the two: not finite if any y is not
         auto track = [&](float v) {
             const int32_t bits = (int32_t)__float_as_uint(v);
             amax = amax > bits ? amax : bits;
+            worst = worst > abs_bits(v) ? worst : abs_bits(v);
         };
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -530,8 +532,8 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                         const uint32_t a = abs_bits(v);
                         if (v <= kGeluArgMin) below = below > 0x7fffffffu - a ? below : 0x7fffffffu - a;
                         if (v >= kGeluArgMin && v < 0.0f) above = above > a ? above : a;
-                        if (!(v >= -3.402823466e+38f)) above = 0x7fc00000u;             // gelu of -infinity and of NaN
                     }
+            if (worst >= 0x7f800000u) above = 0x7fc00000u;                              // -infinity, NaN: a NaN
             below = wave_max_u32(below);
             above = wave_max_u32(above);
             uint32_t *way = g.gelu_neg + (blockIdx.x & (kAmaxWays - 1)) * kAmaxStride;
@@ -543,10 +545,11 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
         // times four neighbouring ones, the other half of the wave those between them.  A swap of halves makes 16 neighbours, one
         // store.  Values whose code the lines leave open go on the wave's list (value, place) in the stage memory and
         // are settled side by side afterwards; where they are too many, the cubic pieces leave a thirteenth of them open.  Bound by
-        // the vector instructions, 13 a value (16384 x 3072 values: 72 us the launch, 40 the sums alone), about 30 with the
-        // pieces.  An encoder layer with its first feed-forward weights times 1 / 10^-3 / 10^-6, us: 64 x 256 x 768 457 / 504 / 615 (fp32
-        // tensor and row quantiser 526 / 619 / 717), 32 x 128 x 768 156 / 170 / 197 (173 / 191 / 215).  (The rare branches are out of
-        // line: 72.4 us with them in their places.)
+        // the vector instructions, 13 a value (16384 x 3072 values: 69 us the launch, 38 the sums alone), about 30 with the
+        // pieces.  An encoder layer with its first feed-forward weights times 1 / 10^-3 / 10^-6, us: 64 x 256 x 768 429 / 484 / 550 (fp32
+        // tensor and row quantiser 496 / 589 / 676), 32 x 128 x 768 153 / 161 / 177 (171 / 181 / 203).  What is rare is out of line and
+        // short (a loop over quarters of a block): cold instructions count, 32 x 128 x 768 178.4 us a step with sixteen values of the
+        // pieces unrolled, 177.7 this way.
         static_assert((size_t)NST * STAGE >= (size_t)NW * (kGeluList * 8 + 4096), "the waves' lists must fit the stage memory");
         float2 *lines = (float2 *)&lds[NST * STAGE];
         uint2 *list = (uint2 *)&lds[(uint32_t)wave_u * (uint32_t)((size_t)NST * STAGE / NW)];
@@ -665,32 +668,31 @@ __global__ __launch_bounds__(64 * WM * WN, EPI == kGeluCodes && BM * BN <= 128 *
                 const int col0 = n0 + (wn_u * TN + b / TM) * 32;
                 const uint32_t row = (uint32_t)((wm_u * TM + b % TM) * 32 + lcol);
                 const uint32_t c16 = (uint32_t)(col0 + 16 * half) < q_ld ? (uint32_t)(col0 + 16 * half) : kOob;
-                uint32_t w[4], open = 0;
-#pragma unroll
+                uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll 1
                 for (int q = 0; q < 4; ++q) {
-                    uint32_t c[4];
+                    const int at = (col0 + 8 * q + 4 * half) * 4;              // (beyond N the loads are 0)
+                    uint32_t code[4], open = 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const int r = 4 * q + e, at = (col0 + 4 * half) * 4;       // (beyond N the loads are 0)
-                        const float sw = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsw, at, (8 * q + e) * 4, 0));
-                        const float bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbias, at, (8 * q + e) * 4, 0));
-                        const float v = fmaf((float)mine[r * 64], g.sw_per_n ? sxv * sw : s, bv);    // one fp32 multiply
+                        const float sw = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsw, at, 4 * e, 0));
+                        const float bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbias, at, 4 * e, 0));
+                        const float v = fmaf((float)mine[(4 * q + e) * 64], g.sw_per_n ? sxv * sw : s, bv);    // one fp32 multiply
                         bool un;
-                        c[e] = quant_gelu_fast<true>(v, gelu_inv, room3, tab, &un);
-                        open |= un ? 1u << r : 0u;
-                        mine[r * 64] = (int)__float_as_uint(v);
+                        code[e] = quant_gelu_fast<true>(v, gelu_inv, room3, tab, &un);
+                        open |= un ? 1u << e : 0u;
+                        mine[(4 * q + e) * 64] = (int)__float_as_uint(v);
                     }
-                    w[q] = pack_bytes(c[0], c[1], c[2], c[3]);
-                }
-                if ((int)row >= rows) open = 0;
+                    uint32_t word = pack_bytes(code[0], code[1], code[2], code[3]);
+                    if ((int)row >= rows) open = 0;
 #pragma unroll 1
-                while (__ballot(open != 0)) {
-                    const int r = open ? __ffs((int)open) - 1 : 0;
-                    const uint32_t code = settle_gelu(__uint_as_float((uint32_t)mine[r * 64]), gelu_inv);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        if (open && (r >> 2) == q) w[q] = (w[q] & ~(0xffu << (8 * (r & 3)))) | code << (8 * (r & 3));
-                    open &= open - 1;
+                    while (__ballot(open != 0)) {
+                        const int e = open ? __ffs((int)open) - 1 : 0;
+                        const uint32_t exact = settle_gelu(__uint_as_float((uint32_t)mine[(4 * q + e) * 64]), gelu_inv);
+                        if (open) word = (word & ~(0xffu << (8 * e))) | exact << (8 * e);
+                        open &= open - 1;
+                    }
+                    w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = word;
                 }
                 const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), c = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
                 const v4u out = {(unsigned)a[0], (unsigned)a[1], (unsigned)c[0], (unsigned)c[1]};
